@@ -34,7 +34,7 @@ struct Offsets {
   size_t x, z, g, v_ring, sigma_ring, rho_tilde;
   size_t r_ptr, r_src, r_dst, r_w, r_self, c_ptr, c_src, c_dst, c_w, c_self, co_ptr, co_eid, co_w, ro_ptr, ro_eid;
   size_t t, t_hist, tau_r, tau_c, deliv_r, deliv_c, round_no, err;
-  size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_head;
+  size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_head, t_next, hist_next, ticket;
   size_t gen_active, gen_delay_r, gen_delay_c, gen_drop_r, gen_drop_c, gen_batch, gen_cdf;
   int32_t gen_depth;
   size_t xbar, resid, gscratch, diag;
@@ -88,20 +88,24 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
   o.deliv_r = L.take(eR * 8);
   o.deliv_c = L.take(eC * 8);
   o.round_no = L.take(4);
-  o.err = L.take(16);
+  o.err = L.take(24);
   o.n_active = L.take(8);
   o.active_plan = L.take(((size_t)n + 8) * 8);
   o.plan_t = L.take(n * 4);
   o.slot_r = L.take(eR * 4);
   o.slot_c = L.take(eC * 4);
   o.plan_c = L.take(eC * 4);
-  o.node_spill = L.take(n);
+  o.node_spill = L.take(n * 4);
   // the seven arrays above are the plan of one round; kResolveAhead - 1 more such sets follow, so that the
   // resolver can run that many rounds ahead of the kernels that read the plans
   o.plan_set_bytes = L.total - o.n_active;
   (void)L.take((size_t)(kResolveAhead - 1) * o.plan_set_bytes);
   o.blk_plan = L.take((size_t)kBlockRounds * ((size_t)n + eR + eC + 1) * 4);
+  o.blk_spill = L.take((size_t)kBlockRounds * n * 4);
   o.blk_head = L.take((kHeadWords * (size_t)n + eC) * 4);
+  o.t_next = L.take(n * 4);
+  o.hist_next = L.take(n * H * 4);
+  o.ticket = L.take(4);
   // the generator draws the schedule of up to gen_depth rounds per launch (as many as fit 64 MB, at most kBlockRounds)
   const size_t gen_rows = (size_t)n * (size_t)(prob->kind == RFAST_OBJ_DIAG_QUADRATIC ? 0 : prob->batch);
   const size_t gen_round = (size_t)n + 5 * (eR + eC) + 4 * gen_rows;
@@ -474,8 +478,10 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   d.round_no = (int32_t*)(b + o.round_no); d.err = (int32_t*)(b + o.err);
   d.n_active = (int32_t*)(b + o.n_active); d.active_plan = (int2*)(b + o.active_plan);
   d.plan_t = (int32_t*)(b + o.plan_t); d.slot_r = (int32_t*)(b + o.slot_r); d.slot_c = (int32_t*)(b + o.slot_c);
-  d.plan_c = (int32_t*)(b + o.plan_c); d.node_spill = (uint8_t*)(b + o.node_spill);
+  d.plan_c = (int32_t*)(b + o.plan_c); d.node_spill = (int32_t*)(b + o.node_spill);
   d.blk_plan = nullptr;
+  d.blk_spill = (int32_t*)(b + o.blk_spill);
+  d.t_next = (int32_t*)(b + o.t_next); d.hist_next = (int32_t*)(b + o.hist_next); d.ticket = (int32_t*)(b + o.ticket);
   d.blk_head = nullptr;
   c->blk_plan_base = (int32_t*)(b + o.blk_plan);
   c->blk_head_base = (int32_t*)(b + o.blk_head);
@@ -502,6 +508,7 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   chk(upload(c, b, o.ro_ptr, gr.out_ptr)); chk(upload(c, b, o.ro_eid, gr.out_eid));
   for (int i = 0; i < n; ++i)
     c->max_degree = std::max({c->max_degree, gr.ptr[i + 1] - gr.ptr[i], gc.ptr[i + 1] - gc.ptr[i], gc.out_ptr[i + 1] - gc.out_ptr[i]});
+  chk(hipMemsetAsync(d.ticket, 0, 4, c->stream));
   chk(rfast_wave_prime(c));
   chk(hipStreamSynchronize(c->stream));  // the host vectors die with this scope
   if (e != hipSuccess) {
@@ -548,6 +555,8 @@ int rfast_init(rfast_ctx* c, const float* d_x0, const int32_t* d_batch_idx0) {
   chk(hipMemsetAsync(d.plan_t, 0, (size_t)d.n * 4, c->stream));
   chk(hipMemsetAsync(d.round_no, 0, 4, c->stream));
   chk(hipMemsetAsync(d.err, 0, 16, c->stream));
+  chk(hipMemsetAsync(d.err + 4, 0xff, 8, c->stream));
+  chk(hipMemsetAsync(d.ticket, 0, 4, c->stream));
   chk(hipMemsetAsync(d.n_active, 0, 8, c->stream));
   if (e != hipSuccess) return hipfail(c, e, "rfast_init clears");
   e = rfast_launch_init_grad(c, d_batch_idx0);
@@ -1005,9 +1014,16 @@ int rfast_check(rfast_ctx* c) {
   if (!c) return RFAST_EINVAL;
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hipfail(c, e, "stream synchronize");
-  int32_t err[4];
-  e = hipMemcpy(err, c->d.err, 16, hipMemcpyDeviceToHost);
+  int32_t err[6];
+  e = hipMemcpy(err, c->d.err, 24, hipMemcpyDeviceToHost);
   if (e != hipSuccess) return hipfail(c, e, "reading device status");
+  const uint64_t edge = (uint64_t)(uint32_t)err[5] << 32 | (uint32_t)err[4];  // the earliest delay out of range
+  if (edge != ~0ull && (err[0] == 0 || (int32_t)(edge >> 32) <= err[1])) {
+    err[0] = RFAST_ERANGE;
+    err[1] = (int32_t)(edge >> 32);
+    err[2] = (int32_t)(edge >> 31 & 1);
+    err[3] = (int32_t)(edge & 0x7fffffff);
+  }
   if (err[0] == 0) return RFAST_OK;
   static const char* kinds[] = {"delay on R edge", "delay on C edge", "sample row of node", "class label of a sample of node"};
   const char* what = err[2] >= 0 && err[2] <= 3 ? kinds[err[2]] : "value";

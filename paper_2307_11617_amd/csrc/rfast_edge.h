@@ -33,6 +33,12 @@ __device__ inline void record_error(int32_t* err, int code, int round, int kind,
   }
 }
 
+// a delay out of range, from a resolver whose lanes go through the rounds on their own: the earliest round is kept
+__device__ inline void record_edge_error(const RfastDev& s, int round, int kind, int e) {
+  atomicMin(reinterpret_cast<unsigned long long*>(s.err + 4),
+            (unsigned long long)(unsigned)round << 32 | (unsigned long long)(unsigned)kind << 31 | (unsigned)e);
+}
+
 // What one lane knows about its edge before it decides anything.  The loads come in two levels of
 // dependency (by edge number; by the node numbers and the delay found there), and both are issued
 // ahead of the node pass of the kernel, so that the whole resolver costs about two memory round

@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(kThreads) rfast_cols_track_mix_kernel(RfastDev
   *reinterpret_cast<float4*>(s.z + node_off) = z_new;
   if (pushes) {
     *reinterpret_cast<float4*>(s.sigma_ring + ((size_t)i * M + slot_new) * p + k) = add(sig_cur, z_half);
-    if (s.node_spill[i] != 0) {  // S4 for receivers that do not do it themselves in this round
+    if (s.node_spill[i] == t_old + 1) {  // S4 for receivers that do not do it themselves in this round
       const float4 leaving = *reinterpret_cast<const float4*>(s.sigma_ring + ((size_t)i * M + (t_old - (M - 2)) % M) * p + k);
       for (int o = s.co_ptr[i]; o < s.co_ptr[i + 1]; ++o)
         if (s.plan_c[s.co_eid[o]] & (1 << 18))

@@ -61,7 +61,8 @@ struct RfastDev {
   unsigned long long* deliv_r;  // [eR] bit s set: the version in slot s was delivered on this edge
   unsigned long long* deliv_c;  // [eC]
   int32_t* round_no;      // [1]
-  int32_t* err;           // [4] code, round, kind, edge (first error wins)
+  int32_t* err;           // [4] code, round, kind, edge (first error wins), then [1] 64-bit word: the earliest edge with a
+                          // delay out of range as round << 32 | kind << 31 | edge (all ones: none)
   // per-round plan written by the resolver, read by the state kernels
   int32_t* n_active;      // [2]: active nodes of the round, round counter after it
   // [n + 8] work slots of the round: {node, t_node at the start of the round}, the active nodes in
@@ -80,11 +81,17 @@ struct RfastDev {
   //   bit 30     live, bits 8-15 are a slot and bit 17 is clear (the usual live edge)
   //   bit 31     live otherwise
   int32_t* plan_c;        // [eC]
-  uint8_t* node_spill;    // [n]   some out-edge of this node has bit 18 set
+  int32_t* node_spill;    // [n]   the node's counter after the last round in which some out-edge of it had bit 18 set
   // The plan of one round once more, as one record for the kernel that keeps a tile of coordinates
   // in LDS over several rounds (NULL: not wanted): [n] node words (bit 31 active, low 30 bits the
   // counter at the start of the round), [eR] ring slot per R edge, [eC] plan word per C edge.
   int32_t* blk_plan;
+  int32_t* blk_spill;     // [rounds][n] beside the records: round number + 1 if some in-edge of C of the node has bit 18 set (other
+                          // values: no such edge)
+  // graphs of more than one resolver workgroup: counters and history after the launch, workgroups that are through
+  int32_t* t_next;        // [n]
+  int32_t* hist_next;     // [n][H]
+  int32_t* ticket;        // [1]
   // What a multi-round launch needs to know about the state before its first round and after its last,
   // written by the resolver around the rounds it resolves (NULL: not wanted).  [n][kHeadWords] per node j:
   //   0, 1    its counter before and after

@@ -1,4 +1,4 @@
-// Integer schedule resolver: turns one round's masks into ring-slot indices.
+// Integer schedule resolver: turns the masks of a stretch of rounds into ring-slot indices.
 //
 // For an active receiver i and in-edge e = (j -> i) the stamp picked up is the
 // newest one that has arrived on the edge (Algorithm 1, S2a / S2b), i.e. the
@@ -14,350 +14,367 @@
 // tau_ij >= t_j - D; only a version about to leave the ring is copied to the rho~ array
 // (by the receiver if it consumes exactly that version in this round, else by the sender).
 //
-// One workgroup, one lane per edge; every step is integer and deterministic.
+// An edge needs nothing of any other edge: its stamp and its delivery bits are its own, and the counter of its
+// sender, now and at the start of earlier rounds, is a count of the sender's activity flags.  So one lane takes one
+// edge through all rounds of the launch, with its stamp, the sender's counter, the sender's last 64 activity flags and
+// the delivery bits in registers (the bits as a shift register, newest version first, so that no remainder by the ring
+// length is left in the loop), and a round has no barrier and no LDS.  What bounds it is the dependent instructions of
+// one wavefront per edge (0.35 us per round on small graphs), while the inputs of the next eight rounds are on their
+// way.  Measured, us per launch of 25 to 32 rounds, against one workgroup in step with three barriers per round: 31
+// nodes and 60 edges 51 -> 14, 32 nodes and 320 edges 61 -> 17, 128 nodes and 1792 edges 132 -> 19; a single round
+// 6.1 -> 4.1.
 #include "rfast_edge.h"
 #include "rfast_internal.h"
 
 namespace {
 
-// kind 0: graph R (v packets), kind 1: graph C (rho packets); e counts within its graph
-__device__ inline void edge_level1(const RfastDev& s, int kind, int e, const int32_t* delay, const uint8_t* drop, EdgeIn* q) {
-  q->i = (kind ? s.c_dst : s.r_dst)[e];
-  q->j = (kind ? s.c_src : s.r_src)[e];
-  q->bits = (kind ? s.deliv_c : s.deliv_r)[e];
-  q->d = delay[e];
-  q->old = (kind ? s.tau_c : s.tau_r)[e];
-  q->dropped = drop[e] != 0;
+constexpr int kGroupLanes = 1024;  // nodes and edges (each rounded up to wavefronts) one workgroup looks after
+constexpr int kChunk = 8;          // rounds whose inputs are fetched ahead together
+
+typedef unsigned long long u64;
+
+// The delivery bits as they are kept between launches, bit s for the version in ring slot s, against the bits the loop
+// works with, bit k for version t - k, where t sits in slot st: s and k are each other's mirror, k = (st - s) mod M, so
+// that one function goes both ways.
+__device__ inline u64 mirror_bits(u64 bits, int st, int M) {
+  const u64 rev = __brevll(bits);
+  const u64 low = rev >> (63 - st);                                        // slots st .. 0 as k = 0 .. st
+  const u64 high = st + 1 < M ? (rev >> (64 - M)) << (st + 1) : 0ull;      // slots M-1 .. st+1 as k = st+1 .. M-1
+  return (low | high) & (M == 64 ? ~0ull : (1ull << M) - 1);
 }
 
-__device__ inline void edge_level2(const RfastDev& s, int r, const uint8_t* active, EdgeIn* q) {
-  q->act_i = active[q->i] != 0;
-  q->act_j = active[q->j] != 0;
-  q->tj = s.t[q->j];  // the counters are advanced only after the last barrier of the kernel
-  const int d = q->d < 0 ? 0 : (q->d > s.d_max ? s.d_max : q->d);
-  const int at = r - d;
-  // the sender's counter at the start of round `at`; round r itself is the current counter (its
-  // history slot is being written by the node pass)
-  q->u = at <= 0 ? 0 : (at >= r ? q->tj : s.t_hist[(size_t)q->j * s.H + (at % s.H)]);
+template <class P> __device__ inline P* shifted(P* ptr, size_t bytes) {
+  return reinterpret_cast<P*>(reinterpret_cast<char*>(ptr) + bytes);
 }
 
-// Decides edge e for round r, leaves the new stamp and delivery bits in q as well (a lane that keeps its edges
-// over several rounds goes on from them) and writes the round's plan; what an idle receiver does not change is
-// stored again unchanged.  KIND 0: graph R, 1: graph C.
+struct Sched {
+  const uint8_t* active;
+  const int32_t* delay_R;
+  const int32_t* delay_C;
+  const uint8_t* drop_R;
+  const uint8_t* drop_C;
+};
+
+// Where a lane's edge starts from.
+struct EdgeState {
+  int i, j, old, tj, st;  // receiver, sender, stamp held, the sender's counter and the ring slot of that version
+  u64 dl, hist;           // delivery bits (bit k: version tj - k), activity of the sender (bit k: k+1 rounds ago)
+};
+
 template <int KIND>
-__device__ inline void edge_decide_t(const RfastDev& s, const FastMod& modM, int e, int r, EdgeIn& q) {
-  const EdgeOut o = edge_compute<KIND>(s, modM, e, r, q);
-  (KIND ? s.tau_c : s.tau_r)[e] = q.old;
-  (KIND ? s.slot_c : s.slot_r)[e] = o.slot;
-  if (KIND == 0) {
-    if (s.blk_plan) s.blk_plan[s.n + e] = o.word;
+__device__ inline void edge_begin(const RfastDev& s, int e, int r0, int rounds, const int32_t* delay, EdgeState* q) {
+  q->i = (KIND ? s.c_dst : s.r_dst)[e];
+  q->j = (KIND ? s.c_src : s.r_src)[e];
+  const u64 bits = (KIND ? s.deliv_c : s.deliv_r)[e];
+  q->old = (KIND ? s.tau_c : s.tau_r)[e];
+  q->tj = s.t[q->j];
+  q->st = FastMod(s.M)(q->tj);
+  q->dl = mirror_bits(bits, q->st, s.M);
+  // activity of the sender before this launch, from the counters at the start of the last H rounds (no delay is
+  // longer); a launch of one round looks its one counter up instead, and the bits are any that give that count
+  q->hist = 0;
+  if (rounds == 1) {
+    const int d0 = delay[0], d = d0 < 0 ? 0 : (d0 > s.d_max ? s.d_max : d0);
+    if (d > 0) q->hist = (1ull << (q->tj - (d < r0 ? s.t_hist[(size_t)q->j * s.H + FastMod(s.H)(r0 - d)] : 0))) - 1;
   } else {
-    s.plan_c[e] = o.word;
-    if (s.blk_plan) s.blk_plan[s.n + s.eR + e] = o.word;
-    if (o.spill) s.node_spill[q.j] = 1;
-  }
-  (KIND ? s.deliv_c : s.deliv_r)[e] = q.bits;
-}
-
-__device__ inline void edge_decide(const RfastDev& s, const FastMod& modM, int kind, int e, int r, EdgeIn& q) {
-  if (kind) edge_decide_t<1>(s, modM, e, r, q);
-  else edge_decide_t<0>(s, modM, e, r, q);
-}
-
-// What the kernel that moves the rings of a multi-round launch needs to know about the state before
-// the first round (when = 0, called ahead of the rounds) and after the last (when = 1), see
-// RfastDev::blk_head.  Called by every lane of the one workgroup.
-__device__ inline void block_head(const RfastDev& s, int when) {
-  int32_t* H = s.blk_head;
-  constexpr int K = kHeadWords;
-  __syncthreads();  // when = 1: the last round's counters and stamps are written
-  for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
-    H[K * j + when] = s.t[j];
-    H[K * j + 2 + 2 * when] = 0x7fffffff;
-    H[K * j + 3 + 2 * when] = 0x7fffffff;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < s.eR; e += blockDim.x) atomicMin(&H[K * s.r_src[e] + 2 + 2 * when], s.tau_r[e]);
-  for (int e = threadIdx.x; e < s.eC; e += blockDim.x) {
-    const int j = s.c_src[e], tau = s.tau_c[e];
-    atomicMin(&H[K * j + 3 + 2 * when], tau);
-    const int outside = tau < s.t[j] - (s.M - 2) ? 1 : 0;  // the S4 buffer of the edge is in the rho_tilde array
-    if (when == 0) H[K * s.n + e] = outside;
-    else H[K * s.n + e] |= outside << 1;
-  }
-  __syncthreads();  // when = 0: the rounds below move the stamps and the counters
-  if (when == 0) return;
-  // the same facts per ring slot, so that the lanes of the launch test a bit where they would compute a version
-  for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
-    const int M = s.M, t0 = H[K * j], te = H[K * j + 1];
-    const int s0 = t0 % M, se = te % M;
-    unsigned in_v = 0, in_s = 0, written = 0, out_v = 0, out_s = 0;
-    for (int m = 0; m < M && m < 32; ++m) {
-      // version held by slot m when the latest version t is in slot t mod M (negative: never written)
-      const int v0 = t0 - (s0 - m < 0 ? s0 - m + M : s0 - m), v1 = te - (se - m < 0 ? se - m + M : se - m);
-      const unsigned bit = 1u << m;
-      if (v0 >= H[K * j + 2]) in_v |= bit;
-      if (v0 >= H[K * j + 3]) in_s |= bit;
-      if (v1 > t0) written |= bit;
-      if (v1 >= H[K * j + 4]) out_v |= bit;
-      if (v1 >= H[K * j + 5]) out_s |= bit;
+    const int32_t* h = s.t_hist + (size_t)q->j * s.H;
+    int later = q->tj, at = FastMod(s.H)(r0);
+    const int back = r0 < s.H - 1 ? r0 : s.H - 1;
+    for (int k0 = 0; k0 < back; k0 += kChunk) {
+      int t[kChunk];
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) {  // all of them before the first use (past the last: one that is not used)
+        at = at == 0 ? s.H - 1 : at - 1;
+        t[u] = h[at];
+      }
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u)
+        if (k0 + u < back) {
+          q->hist |= (u64)(later - t[u]) << (k0 + u);
+          later = t[u];
+        }
     }
-    H[K * j + 8] = s0;
-    H[K * j + 9] = se;
-    H[K * j + 10] = (int)in_v;
-    H[K * j + 11] = (int)in_s;
-    H[K * j + 12] = (int)written;
-    H[K * j + 13] = (int)out_v;
-    H[K * j + 14] = (int)out_s;
   }
 }
 
-constexpr int kResolveThreads = 1024;
-constexpr int kAhead = 2;  // edges per lane whose loads are issued before the node pass
+// Decides the edge for round r: delay d0 and loss flag as the schedule has them.  Returns the slot read (-1: the
+// receiver is idle) and the plan word.
+template <int KIND>
+__device__ inline int edge_round(const RfastDev& s, int e, int r, int d0, bool dropped, bool act_i, bool act_j, EdgeState& q, int* word, bool* spilled) {
+  const int M = s.M, tj = q.tj, lo = tj - (M - 2);  // oldest version that stays readable in j's ring during this round
+  const int d = d0 < 0 ? 0 : (d0 > s.d_max ? s.d_max : d0);
+  if (act_i && d != d0) record_edge_error(s, r, KIND, e);  // resolved with the clamped delay
+  const int seen = tj - __popcll(q.hist & ((1ull << d) - 1));  // the sender's counter at the start of round r - d
+  // S2a / S2b: the newest delivered version that is not newer than that: at most burst-1 steps back (a version is
+  // delivered by force once the burst-1 before it were all lost; version 0 always counts as delivered)
+  const u64 from = q.dl >> (tj - seen);
+  int back = from ? __ffsll((long long)from) - 1 : 64;
+  back = back < s.burst - 1 ? back : s.burst - 1;
+  const int u = seen - back > 0 ? seen - back : 0;
+  const int old = q.old;
+  const int now = act_i && u > old ? u : old;
+  const int sn = q.st - (tj - now), now_slot = sn < 0 ? sn + M : sn;  // wherever it is used, now lies within the ring
+  q.old = now;
+  *spilled = false;
+  if (KIND == 0) {
+    *word = act_i ? now_slot : 0;
+  } else {
+    const bool live = now != old;                // never with an idle receiver
+    const bool leaves = act_j && now == lo;      // after this round the ring of an active sender no longer covers version lo
+    const bool spill = !live && leaves;          // the receiver does not consume, and the version its buffer holds leaves
+    const bool held = old >= lo;                 // what was consumed last time is still in the ring
+    const int so = q.st - (tj - old), old_slot = held ? (so < 0 ? so + M : so) : 0xFF;
+    // bits 30 and 31 sort the live edges for a consumer that wants one compare per case: the usual one (what was
+    // consumed last time is still in the ring, what is consumed now stays there) and the rest;
+    // bits 0-7 of a spill word: the slot of the version that leaves (now == lo then)
+    const bool usual = live && !leaves && held;
+    const int on = now_slot | old_slot << 8 | (live ? 1 << 16 : 0) | (live && leaves ? 1 << 17 : 0) | (spill ? 1 << 18 : 0) |
+                   (usual ? 1 << 30 : 0) | (live && !usual ? (int)0x80000000 : 0);
+    *word = act_i ? on : (spill ? now_slot | 1 << 18 : 0);
+    *spilled = spill;
+  }
+  // the sender publishes version t_j + 1 this round (if it is active): lost only if the schedule says so and not all
+  // of the burst-1 versions before it were lost too (versions up to 0 count as delivered)
+  const bool all_lost = (q.dl & ((1ull << (s.burst - 1)) - 1)) == 0 && (s.burst == 1 || tj + 2 - s.burst > 0);
+  if (act_j) {
+    q.dl = (q.dl << 1) | ((!dropped || all_lost) ? 1u : 0u);
+    q.tj = tj + 1;
+    q.st = q.st + 1 == M ? 0 : q.st + 1;
+  }
+  q.hist = (q.hist << 1) | (act_j ? 1u : 0u);
+  return act_i ? now_slot : -1;
+}
 
-template <class P> __device__ inline void advance(P*& ptr, size_t bytes) {
-  ptr = reinterpret_cast<P*>(reinterpret_cast<char*>(ptr) + bytes);
+// One edge through all rounds.  barrier: called once everything read from the state arrays is in registers.
+// RECORDS: plan records (s.blk_plan) instead of per-round plan arrays.  The body of the loop is straight-line but for
+// the rare spill, and loads nothing but the inputs of the next chunk: memory operations complete in order, so a load
+// inside a round would wait for the stores of the rounds before it (0.5 us per round instead of 0.35).
+template <int KIND, bool RECORDS, class Barrier>
+__device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds, size_t plan_stride, const Sched& sc, bool mine,
+                                   Barrier barrier) {
+  EdgeState q;
+  const int32_t* delay = (KIND ? sc.delay_C : sc.delay_R) + e;
+  if (mine) edge_begin<KIND>(s, e, r0, rounds, delay, &q);
+  barrier();
+  if (!mine) return;
+  const int E = KIND ? s.eC : s.eR;
+  const uint8_t* drop = (KIND ? sc.drop_C : sc.drop_R) + e;
+  const int W1 = s.n + s.eR + s.eC + 1;
+  const int lo0 = q.old, t0 = q.tj;
+  int d[kChunk];
+  uint8_t x[kChunk], ai[kChunk], aj[kChunk];
+  auto fetch = [&](int base) {  // (past the last round: the last one again, which is not used)
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const size_t rq = base + u < rounds ? base + u : rounds - 1;
+      d[u] = delay[rq * E];
+      x[u] = drop[rq * E];
+      ai[u] = sc.active[rq * s.n + q.i];
+      aj[u] = sc.active[rq * s.n + q.j];
+    }
+  };
+  fetch(0);
+  int32_t* rec = RECORDS ? s.blk_plan + s.n + (KIND ? s.eR : 0) + e : nullptr;
+  int32_t* slot_out = (KIND ? s.slot_c : s.slot_r) + e;
+  int32_t* plan_out = s.plan_c + e;
+  int slot = -1, word = 0;
+  for (int base = 0; base < rounds; base += kChunk) {
+    int dn[kChunk];
+    unsigned fl[kChunk];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      dn[u] = d[u];
+      fl[u] = (x[u] ? 1u : 0u) | (ai[u] ? 2u : 0u) | (aj[u] ? 4u : 0u);
+    }
+    fetch(base + kChunk);
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const int rq = base + u;
+      if (rq >= rounds) break;
+      bool spilled;
+      slot = edge_round<KIND>(s, e, r0 + rq, dn[u], fl[u] & 1u, fl[u] & 2u, fl[u] & 4u, q, &word, &spilled);
+      if (RECORDS) {
+        *rec = word;
+        rec += W1;
+        if (KIND && spilled) s.blk_spill[(size_t)rq * s.n + q.i] = r0 + rq + 1;
+      } else {
+        *slot_out = slot;
+        slot_out = shifted(slot_out, plan_stride);
+        if (KIND) {
+          *plan_out = word;
+          plan_out = shifted(plan_out, plan_stride);
+          if (spilled) shifted(s.node_spill, (size_t)rq * plan_stride)[q.j] = q.tj;  // the counter the sender has after this round
+        }
+      }
+    }
+  }
+  if (RECORDS) {  // of the per-round arrays only the last round's slots are looked at (reads of the slot fields)
+    *slot_out = slot;
+    if (KIND) *plan_out = word;
+  }
+  (KIND ? s.tau_c : s.tau_r)[e] = q.old;
+  (KIND ? s.deliv_c : s.deliv_r)[e] = mirror_bits(q.dl, q.st, s.M);
+  if (s.blk_head) {
+    // oldest version held on an out-edge of j before and after the rounds; where the S4 buffer lives before and after
+    int32_t* H = s.blk_head;
+    atomicMin(&H[kHeadWords * q.j + (KIND ? 3 : 2)], lo0);
+    atomicMin(&H[kHeadWords * q.j + (KIND ? 5 : 4)], q.old);
+    if (KIND) H[kHeadWords * s.n + e] = (lo0 < t0 - (s.M - 2) ? 1 : 0) | (q.old < q.tj - (s.M - 2) ? 2 : 0);
+  }
+}
+
+// The node side: counters, their history, the list of active nodes of every round (or the node words of its record).
+// Lane = node; every wavefront counts the active nodes of the others by itself.  Returns the lane's counter at the end.
+__device__ inline int node_rounds(const RfastDev& s, int node, int wave, int lane, int r0, int rounds, size_t plan_stride,
+                                  const uint8_t* active, int t, int32_t* hist) {
+  const int n = s.n, waves = (n + 63) / 64, W1 = n + s.eR + s.eC + 1;
+  const bool mine = node < n;
+  const FastMod modH(s.H);
+  int at = modH(r0);
+  uint8_t a[kChunk];
+  auto fetch = [&](int base) {
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u)  // (past the last round or node: some other flag, which is not used)
+      a[u] = active[(size_t)(base + u < rounds ? base + u : rounds - 1) * n + (mine ? node : 0)];
+  };
+  fetch(0);
+  for (int base = 0; base < rounds; base += kChunk) {
+    uint8_t an[kChunk];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) an[u] = mine && a[u] != 0;
+    fetch(base + kChunk);
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const int rq = base + u;
+      if (rq >= rounds) break;
+      const bool on = an[u] != 0;
+      if (s.blk_plan) {
+        int32_t* rec = s.blk_plan + (size_t)rq * W1;
+        if (mine) rec[node] = (t & 0x3FFFFFFF) | (on ? (int)0x80000000 : 0);
+        if (node == 0) rec[W1 - 1] = 0;  // a record ends with a word that is always zero
+      }
+      if (!s.blk_plan || rq + 1 == rounds) {
+        const size_t off_set = s.blk_plan ? 0 : (size_t)rq * plan_stride;
+        const u64 mask = __ballot(on);
+        int before = 0, total = __popcll(mask);
+        for (int w = 0; w < waves; ++w)  // activity of the nodes of the other wavefronts
+          if (w != wave) {
+            const int m = w * 64 + lane;
+            const int c = __popcll(__ballot(m < n && active[(size_t)rq * n + m] != 0));
+            total += c;
+            before += w < wave ? c : 0;
+          }
+        if (mine) shifted(s.plan_t, off_set)[node] = t;
+        int2* list = shifted(s.active_plan, off_set);
+        if (on) list[before + __popcll(mask & ((1ull << lane) - 1))] = make_int2(node, t);
+        // what is left of the n + 8 work slots, shared out among the wavefronts
+        for (int q = total + wave * 64 + lane; q < n + 8; q += waves * 64) list[q] = make_int2(-1, 0);
+        if (node == 0) {
+          int32_t* cnt = shifted(s.n_active, off_set);
+          cnt[0] = total;
+          cnt[1] = r0 + rq + 1;
+        }
+      }
+      if (mine && rq + s.H >= rounds) hist[(size_t)node * s.H + at] = t;
+      at = at + 1 == s.H ? 0 : at + 1;
+      t += on ? 1 : 0;
+    }
+  }
+  return t;
 }
 
 // rounds > 1: consecutive rounds in one launch, the schedule arrays of round q at offset q of each
-// pointer, its plan record (multi-round kernels) behind the previous one and its per-round plan
-// arrays plan_stride bytes behind those of the previous round (0: every round overwrites the same
-// arrays, which then hold the last round only).  The rounds are sequential -- each reads the
-// counters, stamps and delivery bits the one before wrote -- with the workgroup's barrier between
-// them.
-__global__ void __launch_bounds__(kResolveThreads) rfast_resolve_kernel(RfastDev s, int rounds, size_t plan_stride, const uint8_t* active,
-                                                                         const int32_t* delay_R, const int32_t* delay_C,
-                                                                         const uint8_t* drop_R, const uint8_t* drop_C) {
-  __shared__ int wave_cnt[kResolveThreads / 64];
-  __shared__ int base;
+// pointer, its plan record (multi-round kernels) behind the previous one, or, without records, its per-round plan
+// arrays plan_stride bytes behind those of the previous round.
+// lanes_*: lanes (whole wavefronts) of the nodes, the edges of R and those of C, in this order.
+// A graph whose lanes fit one workgroup has one barrier, between the last read of the state arrays and the first
+// write to them.  Larger graphs take several workgroups, which leave the counters and the history in a second set of
+// arrays; the last workgroup to finish copies them over (only there does anybody write what another workgroup reads).
+__global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, int rounds, size_t plan_stride, Sched sc, int lanes_n,
+                                                                    int lanes_R, int lanes_C) {
   const int r0 = *s.round_no;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int E = s.eR + s.eC;
-  const FastMod modM(s.M);
-  if (s.blk_head) block_head(s, 0);
-  for (int rq = 0; rq < rounds; ++rq) {
-    const int r = r0 + rq;
-    EdgeIn ahead[kAhead];
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) {
-      const int e = threadIdx.x + a * kResolveThreads;
-      if (e < s.eR) edge_level1(s, 0, e, delay_R, drop_R, &ahead[a]);
-      else if (e < E) edge_level1(s, 1, e - s.eR, delay_C, drop_C, &ahead[a]);
+  const bool single = gridDim.x == 1;
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  auto barrier = [&] {
+    if (single) __syncthreads();
+  };
+  if (s.blk_head)  // (graphs of one workgroup only)
+    for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
+      s.blk_head[kHeadWords * j + 2] = s.blk_head[kHeadWords * j + 3] = 0x7fffffff;
+      s.blk_head[kHeadWords * j + 4] = s.blk_head[kHeadWords * j + 5] = 0x7fffffff;
     }
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a)
-      if (threadIdx.x + a * kResolveThreads < E) edge_level2(s, r, active, &ahead[a]);
-    if (threadIdx.x == 0) base = 0;
-    if (threadIdx.x == 0 && s.blk_plan) s.blk_plan[s.n + E] = 0;  // a record ends with a word that is always zero
-    // node pass: snapshot of the counters, and the ordered list of active nodes (ballot + prefix per chunk)
-    for (int i0 = 0; i0 < s.n; i0 += kResolveThreads) {
-      const int i = i0 + threadIdx.x;
-      bool act = false;
-      int ti = 0;
-      if (i < s.n) {
-        ti = s.t[i];
-        s.plan_t[i] = ti;
-        s.node_spill[i] = 0;
-        s.t_hist[(size_t)i * s.H + (r % s.H)] = ti;
-        act = active[i] != 0;
-        if (s.blk_plan) s.blk_plan[i] = (ti & 0x3FFFFFFF) | (act ? (int)0x80000000 : 0);
+  // (the kind of a lane is the same throughout a wavefront)
+  if (id < lanes_n) {
+    const int t0 = id < s.n ? s.t[id] : 0;
+    barrier();
+    const int t = node_rounds(s, id, id >> 6, lane, r0, rounds, plan_stride, sc.active, t0, single ? s.t_hist : s.hist_next);
+    if (id < s.n) {
+      (single ? s.t : s.t_next)[id] = t;
+      if (s.blk_head) {
+        s.blk_head[kHeadWords * id] = t0;
+        s.blk_head[kHeadWords * id + 1] = t;
       }
-      const unsigned long long m = __ballot(act);
-      if (lane == 0) wave_cnt[wave] = __popcll(m);
-      __syncthreads();
-      int off = base;
-      for (int w = 0; w < wave; ++w) off += wave_cnt[w];
-      if (act) s.active_plan[off + __popcll(m & ((1ull << lane) - 1ull))] = make_int2(i, ti);
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        int tot = 0;
-        for (int w = 0; w < kResolveThreads / 64; ++w) tot += wave_cnt[w];
-        base += tot;
-      }
-      __syncthreads();
     }
-    if (threadIdx.x == 0) {
-      s.n_active[0] = base;
-      s.n_active[1] = r + 1;
-    }
-    for (int q = base + threadIdx.x; q < s.n + 8; q += kResolveThreads) s.active_plan[q] = make_int2(-1, 0);
-    // edge pass (node_spill was cleared above, before the barriers); nothing in it depends on the node pass
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) {
-      const int e = threadIdx.x + a * kResolveThreads;
-      if (e < E) edge_decide(s, modM, e >= s.eR, e >= s.eR ? e - s.eR : e, r, ahead[a]);
-    }
-    for (int e = threadIdx.x + kAhead * kResolveThreads; e < E; e += kResolveThreads) {  // more than 2048 edges
-      const int kind = e >= s.eR, el = kind ? e - s.eR : e;
-      EdgeIn q;
-      edge_level1(s, kind, el, kind ? delay_C : delay_R, kind ? drop_C : drop_R, &q);
-      edge_level2(s, r, active, &q);
-      edge_decide(s, modM, kind, el, r, q);
-    }
-    __syncthreads();  // every read of the counters is done
-    for (int i = threadIdx.x; i < s.n; i += kResolveThreads)
-      if (active[i] != 0) s.t[i] = s.plan_t[i] + 1;
-    if (rq + 1 < rounds) {
-      __syncthreads();  // the next round reads what this one wrote
-      active += s.n;
-      delay_R += s.eR;
-      drop_R += s.eR;
-      delay_C += s.eC;
-      drop_C += s.eC;
-      if (s.blk_plan) s.blk_plan += s.n + E + 1;
-      advance(s.n_active, plan_stride);
-      advance(s.active_plan, plan_stride);
-      advance(s.plan_t, plan_stride);
-      advance(s.slot_r, plan_stride);
-      advance(s.slot_c, plan_stride);
-      advance(s.plan_c, plan_stride);
-      advance(s.node_spill, plan_stride);
-    }
-  }
-  if (s.blk_head) block_head(s, 1);
-  if (threadIdx.x == 0) *s.round_no = r0 + rounds;
-}
-
-// ---------------------------------------------------------------------------
-// The same rounds with everything a round reads held on chip: the schedule of all rounds of the
-// launch (delay and loss of every edge as 16-bit words, the activity masks) is copied to LDS first,
-// the counters t and their history live in LDS, and every lane keeps the stamp and the delivery bits
-// of its (at most two) edges in registers.  A round then costs LDS gathers and barriers; what it
-// writes to global memory (plans, stamps, bits, counters, history) nobody waits for.  For graphs of
-// up to 1024 nodes and about 2048 edges whose schedule fits into LDS; bit for bit the plans of the
-// kernel above.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kResolveThreads) rfast_resolve_cached_kernel(RfastDev s, int rounds, size_t plan_stride,
-                                                                                const uint8_t* active, const int32_t* delay_R,
-                                                                                const int32_t* delay_C, const uint8_t* drop_R,
-                                                                                const uint8_t* drop_C, int lanes_R, int lanes_C) {
-  extern __shared__ int lds_i[];
-  __shared__ int wave_cnt[kResolveThreads / 64];
-  const int n = s.n, E = s.eR + s.eC, H = s.H;
-  const int T = blockDim.x;  // a multiple of 64, n <= T: barriers among few wavefronts are cheap
-  // The first lanes_R lanes (whole wavefronts) look after the edges of R, the next lanes_C after those of C, up to
-  // kAhead edges each: the kind of an edge is the same for all lanes of a wavefront, and small graphs have their
-  // edges decided side by side in different wavefronts rather than one after the other in one.
-  const bool kind = (int)threadIdx.x >= lanes_R;
-  const int lane_k = kind ? (int)threadIdx.x - lanes_R : (int)threadIdx.x, lanes_k = kind ? lanes_C : lanes_R;
-  const int edges_k = (int)threadIdx.x < lanes_R + lanes_C ? (kind ? s.eC : s.eR) : 0;
-  const FastMod modM(s.M), modH(H);
-  int* t_l = lds_i;                                                      // [n]
-  int* hist_l = t_l + n;                                                 // [n][H]
-  unsigned short* sched_l = reinterpret_cast<unsigned short*>(hist_l + n * H);  // [rounds][E]: delay | loss << 8 | out of range << 15
-  uint8_t* act_l = reinterpret_cast<uint8_t*>(sched_l + (size_t)rounds * E + ((size_t)rounds * E & 1));  // [rounds][n]
-  const int r0 = *s.round_no;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (s.blk_head) block_head(s, 0);
-  for (int w = threadIdx.x; w < rounds * E; w += T) {
-    const int q = w / E, e = w - q * E;
-    const bool kind = e >= s.eR;
-    const int d = kind ? delay_C[(size_t)q * s.eC + (e - s.eR)] : delay_R[(size_t)q * s.eR + e];
-    const bool lost = (kind ? drop_C[(size_t)q * s.eC + (e - s.eR)] : drop_R[(size_t)q * s.eR + e]) != 0;
-    const bool bad = d < 0 || d > s.d_max;
-    sched_l[w] = (unsigned short)((d < 0 ? 0 : (d > s.d_max ? s.d_max : d)) | (lost ? 1 << 8 : 0) | (bad ? 1 << 15 : 0));
-  }
-  for (int w = threadIdx.x; w < rounds * n; w += T) act_l[w] = active[w];
-  for (int i = threadIdx.x; i < n; i += T) t_l[i] = s.t[i];
-  for (int w = threadIdx.x; w < n * H; w += T) hist_l[w] = s.t_hist[w];
-  EdgeIn mine[kAhead];
-#pragma unroll
-  for (int a = 0; a < kAhead; ++a) {
-    const int el = lane_k + a * lanes_k;
-    if (el < edges_k) {
-      mine[a].i = (kind ? s.c_dst : s.r_dst)[el];
-      mine[a].j = (kind ? s.c_src : s.r_src)[el];
-      mine[a].bits = (kind ? s.deliv_c : s.deliv_r)[el];
-      mine[a].old = (kind ? s.tau_c : s.tau_r)[el];
-    }
-  }
-  // The loads above must have landed before the round loop starts: the compiler puts the wait for a loaded register at
-  // its first use, which is inside the loop, and a wait on the memory counter there also waits for every store of the
-  // round before (a microsecond per round that nothing needs).  An empty asm that takes the registers is a use.
-#pragma unroll
-  for (int a = 0; a < kAhead; ++a) {
-    unsigned lo = (unsigned)mine[a].bits, hi = (unsigned)(mine[a].bits >> 32);
-    asm volatile("" : "+v"(mine[a].i), "+v"(mine[a].j), "+v"(mine[a].old), "+v"(lo), "+v"(hi));
-    mine[a].bits = ((unsigned long long)hi << 32) | lo;
+  } else if (id < lanes_n + lanes_R) {
+    const int e = id - lanes_n;
+    if (s.blk_plan) edge_rounds<0, true>(s, e, r0, rounds, plan_stride, sc, e < s.eR, barrier);
+    else edge_rounds<0, false>(s, e, r0, rounds, plan_stride, sc, e < s.eR, barrier);
+  } else {
+    const int e = id - lanes_n - lanes_R;
+    if (s.blk_plan) edge_rounds<1, true>(s, e, r0, rounds, plan_stride, sc, e < s.eC, barrier);
+    else edge_rounds<1, false>(s, e, r0, rounds, plan_stride, sc, e < s.eC, barrier);
   }
   __syncthreads();
-  const int i = threadIdx.x;  // the node this lane looks after (n <= T)
-  for (int rq = 0; rq < rounds; ++rq) {
-    const int r = r0 + rq, r_slot = modH(r);
-    const uint8_t* act = act_l + (size_t)rq * n;
-    // what the lane's edges see: schedule, activity and the sender's counters, all from LDS
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) {
-      const int el = lane_k + a * lanes_k;
-      const int e = kind ? s.eR + el : el;  // position in a round's schedule words: R's edges, then C's
-      if (el < edges_k) {
-        EdgeIn& q = mine[a];
-        const unsigned sw = sched_l[(size_t)rq * E + e];
-        const int d = sw & 0xFF;
-        q.d = (sw >> 15) ? -1 : d;  // out of range: reported by edge_decide, resolved with the clamped value
-        q.dropped = (sw >> 8) & 1;
-        q.act_i = act[q.i] != 0;
-        q.act_j = act[q.j] != 0;
-        q.tj = t_l[q.j];
-        const int at = r - d;
-        q.u = at <= 0 ? 0 : (at >= r ? q.tj : hist_l[q.j * H + modH(at)]);
+  if (!single) {
+    __shared__ bool last;
+    if (threadIdx.x == 0) {
+      __threadfence();
+      last = atomicAdd(s.ticket, 1) == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    const FastMod modH(s.H);
+    for (int i = threadIdx.x; i < s.n; i += blockDim.x) {
+      s.t[i] = s.t_next[i];
+      for (int k = rounds < s.H ? rounds : s.H; k > 0; --k) {
+        const int at = modH(r0 + rounds - k);
+        s.t_hist[(size_t)i * s.H + at] = s.hist_next[(size_t)i * s.H + at];
       }
     }
-    if (threadIdx.x == 0 && s.blk_plan) s.blk_plan[n + E] = 0;  // a record ends with a word that is always zero
-    // node pass: snapshot of the counters, and the ordered list of active nodes (ballot + prefix)
-    bool on = false;
-    int ti = 0;
-    if (i < n) {
-      ti = t_l[i];
-      s.plan_t[i] = ti;
-      s.node_spill[i] = 0;
-      s.t_hist[(size_t)i * H + r_slot] = ti;
-      on = act[i] != 0;
-      if (s.blk_plan) s.blk_plan[i] = (ti & 0x3FFFFFFF) | (on ? (int)0x80000000 : 0);
-    }
-    const unsigned long long m = __ballot(on);
-    if (lane == 0) wave_cnt[wave] = __popcll(m);
-    __syncthreads();  // also: every lane has read the history of this round's delays
-    if (i < n) hist_l[i * H + r_slot] = ti;
-    int off = 0, total = 0;
-    for (int w = 0; w < T / 64; ++w) {
-      if (w < wave) off += wave_cnt[w];
-      total += wave_cnt[w];
-    }
-    if (on) s.active_plan[off + __popcll(m & ((1ull << lane) - 1ull))] = make_int2(i, ti);
-    if (threadIdx.x == 0) {
-      s.n_active[0] = total;
-      s.n_active[1] = r + 1;
-    }
-    for (int q = total + threadIdx.x; q < n + 8; q += T) s.active_plan[q] = make_int2(-1, 0);
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) {
-      const int el = lane_k + a * lanes_k;
-      if (el < edges_k) edge_decide(s, modM, kind, el, r, mine[a]);
-    }
-    __syncthreads();  // every read of the counters is done (and wave_cnt may be reused)
-    if (on) {
-      t_l[i] = ti + 1;
-      s.t[i] = ti + 1;
-    }
-    __syncthreads();  // the next round reads what this one wrote
-    if (s.blk_plan) s.blk_plan += n + E + 1;
-    advance(s.n_active, plan_stride);
-    advance(s.active_plan, plan_stride);
-    advance(s.plan_t, plan_stride);
-    advance(s.slot_r, plan_stride);
-    advance(s.slot_c, plan_stride);
-    advance(s.plan_c, plan_stride);
-    advance(s.node_spill, plan_stride);
+    if (threadIdx.x == 0) *s.ticket = 0;
   }
-  if (s.blk_head) block_head(s, 1);
+  // what the lanes of a multi-round launch test per ring slot (RfastDev::blk_head), from the counters and stamps
+  if (s.blk_head)
+    for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
+      int32_t* H = s.blk_head + kHeadWords * j;
+      const int M = s.M, t0 = H[0], te = H[1];
+      const int lo_v0 = __hip_atomic_load(&H[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int lo_s0 = __hip_atomic_load(&H[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int lo_v1 = __hip_atomic_load(&H[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int lo_s1 = __hip_atomic_load(&H[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int s0 = t0 % M, se = te % M;
+      unsigned in_v = 0, in_s = 0, written = 0, out_v = 0, out_s = 0;
+      for (int m = 0; m < M && m < 32; ++m) {
+        // version held by slot m when the latest version t is in slot t mod M (negative: never written)
+        const int v0 = t0 - (s0 - m < 0 ? s0 - m + M : s0 - m), v1 = te - (se - m < 0 ? se - m + M : se - m);
+        const unsigned bit = 1u << m;
+        if (v0 >= lo_v0) in_v |= bit;
+        if (v0 >= lo_s0) in_s |= bit;
+        if (v1 > t0) written |= bit;
+        if (v1 >= lo_v1) out_v |= bit;
+        if (v1 >= lo_s1) out_s |= bit;
+      }
+      H[8] = s0;
+      H[9] = se;
+      H[10] = (int)in_v;
+      H[11] = (int)in_s;
+      H[12] = (int)written;
+      H[13] = (int)out_v;
+      H[14] = (int)out_s;
+    }
   if (threadIdx.x == 0) *s.round_no = r0 + rounds;
-}
-
-size_t cached_lds_bytes(const RfastDev& d, int rounds) {
-  const size_t E = (size_t)d.eR + d.eC;
-  return ((size_t)d.n + (size_t)d.n * d.H) * sizeof(int) + (((size_t)rounds * E + 1) & ~(size_t)1) * sizeof(unsigned short) +
-         (size_t)rounds * d.n;
 }
 
 }  // namespace
@@ -366,30 +383,17 @@ hipError_t rfast_launch_resolve(rfast_ctx* c, const uint8_t* active, const int32
                                 const int32_t* delay_C, const uint8_t* drop_R, const uint8_t* drop_C, int rounds,
                                 size_t plan_stride) {
   const RfastDev& d = c->d;
-  const size_t lds = cached_lds_bytes(d, rounds);
-  if (rounds > 1 && d.n <= kResolveThreads && (d.eR + 127) / 128 + (d.eC + 127) / 128 <= kResolveThreads / 64 && lds <= 150 * 1024) {
-    static bool raised = false;
-    if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once (the kernel has 64 B of static LDS too)
-      const hipError_t e = hipFuncSetAttribute((const void*)rfast_resolve_cached_kernel,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
-      if (e != hipSuccess) return e;
-      raised = true;
-    }
-    // whole wavefronts for the edges of R, then for those of C: one edge per lane if that fits 1024 lanes, else two;
-    // as many lanes as the graph has nodes, at least four wavefronts for the copy of the schedule
-    auto whole = [](int v) { return (v + 63) / 64 * 64; };
-    int lanes_R = whole(d.eR), lanes_C = whole(d.eC);
-    if (lanes_R + lanes_C > kResolveThreads) {
-      lanes_R = whole((d.eR + 1) / 2);
-      lanes_C = whole((d.eC + 1) / 2);
-    }
-    int threads = lanes_R + lanes_C > whole(d.n) ? lanes_R + lanes_C : whole(d.n);
-    threads = threads < 256 ? 256 : threads;
-    hipLaunchKernelGGL(rfast_resolve_cached_kernel, dim3(1), dim3(threads), lds, c->stream, c->d, rounds, plan_stride,
-                       active, delay_R, delay_C, drop_R, drop_C, lanes_R, lanes_C);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(rfast_resolve_kernel, dim3(1), dim3(kResolveThreads), 0, c->stream, c->d, rounds, plan_stride, active,
-                     delay_R, delay_C, drop_R, drop_C);
+  auto whole = [](int v) { return (v + 63) / 64 * 64; };
+  const int lanes_n = whole(d.n), lanes_R = whole(d.eR), lanes_C = whole(d.eC);
+  const int64_t lanes = (int64_t)lanes_n + lanes_R + lanes_C;
+  // One workgroup as long as it holds every lane; beyond, workgroups of two wavefronts, which spread over the chip.
+  const bool single = lanes <= kGroupLanes;
+  if (!single && d.blk_head) return hipErrorInvalidValue;  // the kernels that read it take graphs of at most 64 nodes
+  const int threads = single ? (int)lanes : 128;
+  const int64_t groups = (lanes + threads - 1) / threads;
+  if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
+  const Sched sc = {active, delay_R, delay_C, drop_R, drop_C};
+  hipLaunchKernelGGL(rfast_resolve_kernel, dim3((unsigned)groups), dim3(threads), 0, c->stream, d, rounds, plan_stride, sc, lanes_n,
+                     lanes_R, lanes_C);
   return hipGetLastError();
 }

@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
   T vb[KB], sg[KB], rt[KB];
   float vw[KB], ca[KB];
   int pl[KB];  // plan words of the C in-edges of the current batch (0: nothing to do)
-  const bool spills = pushes && s.node_spill[i] != 0;
+  const bool spills = pushes && s.node_spill[i] == t_old + 1;
   z_i = V<VEC>::ld(s.z + node_off);
   if (kMix) {
     x_i = V<VEC>::ld(s.x + node_off);
