@@ -248,13 +248,20 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * memory), at most 4096 sampled rows per round and n + eR + eC < 1024; same bits as the chain of
  * four kernels per round.  With at most 64 nodes and 64 edges of a kind that workgroup also resolves
  * the stamps of its rounds itself (no resolver kernel runs ahead of it).
- * Where these objectives do not fit one workgroup (and p is a multiple of 4, no heavy-ball buffer), rfast_run and
- * rfast_run_generated run a round as two kernels instead of four: the sampled rows' residuals, then one kernel
- * that forms the gradient, does the tracker update and mixes the same coordinates for the next round; same bits.
+ * Where these objectives do not fit one workgroup, every node gets a team of workgroups that keep its state in
+ * registers and its sampled rows in LDS over the same stretches of rounds and meet through memory (rounds of any
+ * number, also single ones, event-driven iterations and synchronous steps; with or without the heavy-ball buffer, any
+ * p >= 4): at most 256 workgroups of up to 2048 coordinates each, one per compute unit, at most 64 edges of a kind at
+ * a node.  All of them wait for each other, so launches on different streams of a process are ordered by the library
+ * (by an event); a wait that cannot end (the device is kept busy by another process) gives up after some seconds and
+ * rfast_check reports RFAST_EHIP.  While kernels are timed (rfast_profile_enable) or a stream is being captured, and
+ * where a team does not fit, a round is two kernels instead of four (p a multiple of 4, no heavy-ball buffer;
+ * consecutive rounds): the sampled rows' residuals, then one kernel that forms the gradient, does the tracker update
+ * and mixes the same coordinates for the next round; same bits.
  * on == 0: always one kernel pass per round (four kernels for these objectives).  on == 2: as the default, but
  * 2 rounds are enough at any size (for measurements). */
 int rfast_use_blocks(rfast_ctx* ctx, int32_t on);
-/* *lanes_per_node = 0 if a call of rfast_run for several rounds would now run one pass per round,
+/* *lanes_per_node = 0 if a call of rfast_run for several rounds would now run without tiles in LDS,
  * else the number of lanes per node of the multi-round kernel (its tile is 4 * lanes coordinates;
  * 1024 / n, at least 1, for the single workgroup of the non-separable objectives);
  * *tile_per_wavefront (may be NULL) = 1 if a tile belongs to one wavefront, 0 if to a workgroup. */

@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -37,7 +38,7 @@ struct Offsets {
   size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_head, t_next, hist_next, ticket;
   size_t gen_active, gen_delay_r, gen_delay_c, gen_drop_r, gen_drop_c, gen_batch, gen_cdf;
   int32_t gen_depth;
-  size_t xbar, resid, gscratch, diag;
+  size_t xbar, resid, gscratch, diag, team_packets, team_flags;
   size_t total;
 };
 
@@ -122,6 +123,13 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
   o.resid = L.take(rfast_gemv_scratch_floats(n, prob) * 4);
   o.gscratch = L.take(rfast_softmax_scratch_bytes(n, prob));
   o.diag = L.take(64 * sizeof(double));
+  // the team kernel's packets and progress words: which team a problem gets depends on the graph and the device, so
+  // room for the largest one (at most kTeamMost workgroups)
+  const bool gemv = prob->kind == RFAST_OBJ_LEAST_SQUARES || prob->kind == RFAST_OBJ_LOGISTIC;
+  RfastTeam most;
+  if (gemv && n <= kTeamMost) most.W = std::min(32, kTeamMost / n);
+  o.team_packets = L.take(rfast_team_packet_bytes(most, n, prob));
+  o.team_flags = L.take(rfast_team_flag_bytes(most, n));
   o.total = L.total;
   return o;
 }
@@ -309,6 +317,69 @@ int fold_sync(rfast_ctx* c) {
 
 constexpr int32_t kGraphRounds = 16;
 
+// Which team of workgroups a node gets for the several-rounds-per-launch form of least squares and logistic regression,
+// and the chunks in which every kernel sums a row's dot product.  A problem that fits the LDS of one compute unit keeps
+// its rows in one chunk (the one-workgroup kernel sums them so).
+void choose_team(rfast_ctx* c, int max_out_r) {
+  RfastDev& d = c->d;
+  int units = 0;
+  d.row_chunk = (int32_t)std::min<int64_t>(d.p, 0x7fffffff);
+  if (hipGetDevice(&c->device) != hipSuccess ||
+      hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
+    return;
+  units = std::min(units, kTeamMost);
+  if (rfast_tiny_eligible(c)) units = std::min(units, d.n);  // one workgroup per node at most
+  c->team = rfast_team_shape(d, c->max_degree, max_out_r, units);
+  if (c->team.W > 1) d.row_chunk = c->team.C;
+}
+
+// The workgroups of a team launch wait for each other, so they must all become resident: two such launches that each
+// hold a part of the chip would wait forever.  Launches on one stream follow each other; a launch on another stream
+// than the last one first waits for what that stream holds.
+struct TeamOrder {
+  bool used = false;
+  hipStream_t stream = nullptr;
+  hipEvent_t event = nullptr;
+};
+std::mutex g_team_mutex;
+TeamOrder g_team_order[64];
+
+template <class Launch> hipError_t in_team_order(rfast_ctx* c, Launch launch) {
+  if (c->device < 0 || c->device >= 64) return hipErrorInvalidDevice;
+  const std::lock_guard<std::mutex> lock(g_team_mutex);
+  TeamOrder& o = g_team_order[c->device];
+  if (o.used && o.stream != c->stream) {
+    hipError_t e = hipSuccess;
+    if (!o.event) e = hipEventCreateWithFlags(&o.event, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(o.event, o.stream);
+    if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, o.event, 0);
+    if (e != hipSuccess) return e;
+  }
+  const hipError_t e = launch();
+  o.used = true;
+  o.stream = c->stream;
+  return e;
+}
+
+// the context's stream has been waited for and is about to be given up
+void leave_team_order(rfast_ctx* c) {
+  if (c->device < 0 || c->device >= 64) return;
+  const std::lock_guard<std::mutex> lock(g_team_mutex);
+  TeamOrder& o = g_team_order[c->device];
+  if (o.used && o.stream == c->stream) o.used = false;
+}
+
+// A captured launch would be replayed with the progress words of its capture, so captured rounds take the chain; so do
+// profiled ones, whose state and gradient kernels are to be timed apart.
+bool team_usable(const rfast_ctx* c) {
+  if (!c->use_blocks || c->team.W <= 0 || c->capturing || c->profiling) return false;
+  if (c->stream != nullptr) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
+  }
+  return true;
+}
+
 // step size of round `round`: gamma * factor^(round div step_rounds)
 float gamma_at(const rfast_ctx* c, float gamma, int64_t round) {
   if (c->gamma_step <= 0) return gamma;
@@ -353,6 +424,7 @@ int build_graph(rfast_ctx* c, uint64_t seed, const float* d_p_active, int32_t ma
   hipError_t e = hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return hipfail(c, e, "hipStreamBeginCapture");
   c->stream = c->capture_stream;
+  c->capturing = true;
   const int64_t round_before = c->host_round;  // capture enqueues nothing: the counter moves when the graph is launched
   int rc = RFAST_OK;
   for (int32_t r = 0; r < kGraphRounds && rc == RFAST_OK; ++r) {
@@ -361,6 +433,7 @@ int build_graph(rfast_ctx* c, uint64_t seed, const float* d_p_active, int32_t ma
     else rc = rfast_round(c, d.gen_active, d.gen_delay_r, d.gen_delay_c, d.gen_drop_r, d.gen_drop_c, gamma, d.gen_batch);
   }
   c->stream = user;
+  c->capturing = false;
   c->host_round = round_before;
   hipGraph_t graph = nullptr;
   e = hipStreamEndCapture(c->capture_stream, &graph);
@@ -494,6 +567,7 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   d.gen_cdf = (uint32_t*)(b + o.gen_cdf);
   c->gen_depth = o.gen_depth;
   d.xbar = (float*)(b + o.xbar);
+  c->team_packets = (void*)(b + o.team_packets); c->team_flags = (unsigned*)(b + o.team_flags);
   d.mom = nullptr; d.beta = 0.f; d.wd = 0.f;
   d.resid = (float*)(b + o.resid); d.gscratch = (void*)(b + o.gscratch);
   c->d_diag = (double*)(b + o.diag);
@@ -508,7 +582,14 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   chk(upload(c, b, o.ro_ptr, gr.out_ptr)); chk(upload(c, b, o.ro_eid, gr.out_eid));
   for (int i = 0; i < n; ++i)
     c->max_degree = std::max({c->max_degree, gr.ptr[i + 1] - gr.ptr[i], gc.ptr[i + 1] - gc.ptr[i], gc.out_ptr[i + 1] - gc.out_ptr[i]});
+  int max_out_r = 0;
+  for (int i = 0; i < n; ++i) max_out_r = std::max(max_out_r, gr.out_ptr[i + 1] - gr.out_ptr[i]);
   chk(hipMemsetAsync(d.ticket, 0, 4, c->stream));
+  choose_team(c, max_out_r);
+  if (c->team.W > 0) {
+    chk(hipMemsetAsync(c->team_packets, 0, rfast_team_packet_bytes(c->team, n, prob), c->stream));
+    chk(hipMemsetAsync(c->team_flags, 0, rfast_team_flag_bytes(c->team, n), c->stream));
+  }
   chk(rfast_wave_prime(c));
   chk(hipStreamSynchronize(c->stream));  // the host vectors die with this scope
   if (e != hipSuccess) {
@@ -587,12 +668,17 @@ static int check_round_args(rfast_ctx* c, const uint8_t* d_active, const int32_t
 }
 
 static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx);
+static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round = -1);
+static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const int32_t* d_delay_R, const int32_t* d_delay_C,
+                     const uint8_t* d_drop_R, const uint8_t* d_drop_C, float gamma, const int32_t* d_batch_idx);
 
 int rfast_round(rfast_ctx* c, const uint8_t* d_active, const int32_t* d_delay_R, const int32_t* d_delay_C,
                 const uint8_t* d_drop_R, const uint8_t* d_drop_C, float gamma, const int32_t* d_batch_idx) {
   if (!c) return RFAST_EINVAL;
   const int rc = check_round_args(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C, gamma, d_batch_idx);
   if (rc != RFAST_OK) return rc;
+  if (c->d.prob.kind != RFAST_OBJ_DIAG_QUADRATIC && block_length(c, 1) > 0)
+    return run_block(c, 1, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C, gamma, d_batch_idx);
   if (fold_sync(c) != RFAST_OK) return RFAST_EHIP;
   time_begin(c, 2);
   const hipError_t e = rfast_launch_resolve(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C);
@@ -664,8 +750,11 @@ static int chained_rounds(rfast_ctx* c, int32_t count, float gamma, const uint8_
 // multiple of the rebase interval, and it runs with one step size, so it must end with the current
 // step of the step-size schedule; and it reads and writes every ring slot once, which a large
 // state earns back only over enough rounds.
-static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round = -1) {
-  if (!c->use_blocks || !(rfast_wave_eligible(c) || rfast_block_eligible(c) || rfast_tiny_eligible(c))) return 0;
+static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round) {
+  if (!c->use_blocks || c->capturing) return 0;
+  const bool gemv = rfast_tiny_eligible(c) || c->team.W > 0;  // (every round of these takes the multi-round kernels)
+  if (!gemv && (c->no_tiles || !(rfast_wave_eligible(c) || rfast_block_eligible(c)))) return 0;
+  if (gemv && !rfast_tiny_eligible(c) && !team_usable(c)) return 0;
   const int64_t now = at_round >= 0 ? at_round : c->host_round;  // the round the launch would start with
   int32_t len = rounds < kBlockRounds ? rounds : kBlockRounds;
   if (c->rebase_interval > 0) {
@@ -676,6 +765,7 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
     const int64_t to_decay = c->gamma_step - now % c->gamma_step;
     if (to_decay < len) len = (int32_t)to_decay;
   }
+  if (gemv) return len;
   const bool large = (double)c->d.n * (double)c->d.p * 4.0 > 8.0e6;
   return len >= (large && c->use_blocks != 2 ? kBlockMinRoundsLarge : 2) ? len : 0;
 }
@@ -693,11 +783,12 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   // running sums while it writes its tiles back (the other kernel is followed by the rebase kernel)
   const bool rebase_due = c->rebase_interval > 0 && (c->host_round + len) % c->rebase_interval == 0;
   blk.rebase = rebase_due && rfast_wave_eligible(c) ? 1 : 0;
+  const bool tiny = rfast_tiny_eligible(c), team = !tiny && c->team.W > 0;
   blk.gamma = gamma_now(c, gamma);  // of the first round: a launch does not straddle a decay step
   const bool own_resolver = rfast_tiny_resolves(c);  // the one-workgroup kernel resolves its rounds itself
   hipError_t e = hipSuccess;
   d.blk_plan = c->blk_plan_base;
-  d.blk_head = c->blk_head_base;
+  d.blk_head = tiny || team ? nullptr : c->blk_head_base;
   if (!own_resolver) {
     time_begin(c, 2);
     e = rfast_launch_resolve(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C, len);
@@ -706,7 +797,9 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   c->host_round += len;
   if (e == hipSuccess) {
     time_begin(c, 0);
-    if (rfast_tiny_eligible(c))
+    if (team)
+      e = in_team_order(c, [&] { return rfast_launch_team(c, false, len, blk.gamma, (int)(c->host_round - len), d_batch_idx, d_delay_R, d_delay_C); });
+    else if (tiny)
       e = rfast_launch_tiny(c, blk, d_batch_idx, (int)(c->host_round - len), d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C);
     else e = rfast_wave_eligible(c) ? rfast_launch_wave(c, blk) : rfast_launch_block(c, blk);
     time_end(c, 0);
@@ -723,7 +816,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
 
 int rfast_block_info(rfast_ctx* c, int32_t* lanes_per_node, int32_t* tile_per_wavefront) {
   if (!c || !lanes_per_node) return RFAST_EINVAL;
-  const bool taken = block_length(c, kBlockRounds) > 0, wave = rfast_wave_eligible(c);
+  const bool taken = block_length(c, kBlockRounds) > 0 && (rfast_tiny_eligible(c) || c->team.W <= 0), wave = rfast_wave_eligible(c);
   if (taken && rfast_tiny_eligible(c)) {  // one workgroup holds the whole problem
     *lanes_per_node = 1024 / c->d.n > 0 ? 1024 / c->d.n : 1;
     if (tile_per_wavefront) *tile_per_wavefront = 0;
@@ -890,10 +983,10 @@ int rfast_run_events(rfast_ctx* c, int32_t iterations, uint64_t seed, const floa
   hipError_t e = hipMemcpyAsync(d.gen_cdf, cdf.data(), (size_t)d.n * 4, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the host vector dies with this scope
   if (e != hipSuccess) return hipfail(c, e, "uploading selection thresholds");
-  // A stretch of iterations drawn by one launch, then one pass per iteration with the resolver ahead (a
-  // multi-round launch, where one lane in n would work, is not what a single activation wants).
-  const int32_t blocks = c->use_blocks;
-  c->use_blocks = 0;
+  // A stretch of iterations drawn by one launch, then, for the separable objective, one pass per iteration with the
+  // resolver ahead (a multi-round launch on tiles, where one lane in n would work, is not what a single activation
+  // wants); the kernels of least squares and logistic regression skip the rounds of nodes that are not active.
+  c->no_tiles = true;
   int rc = RFAST_OK;
   for (int32_t k = 0; k < iterations && rc == RFAST_OK;) {
     const int32_t len = iterations - k < c->gen_depth ? iterations - k : c->gen_depth;
@@ -906,7 +999,7 @@ int rfast_run_events(rfast_ctx* c, int32_t iterations, uint64_t seed, const floa
     c->gen_last = len - 1;
     k += len;
   }
-  c->use_blocks = blocks;
+  c->no_tiles = false;
   return rc;
 }
 
@@ -917,6 +1010,7 @@ int rfast_sync_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx) {
   if (!separable && d.prob.batch > 0 && !d_batch_idx) return fail(c, RFAST_EINVAL, "sample rows are required when batch > 0");
   if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
   if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
+  if (team_usable(c)) return rfast_sync_run(c, 1, gamma, d_batch_idx);
   gamma = gamma_now(c, gamma);
   hipError_t e;
   time_begin(c, 0);
@@ -945,7 +1039,26 @@ int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_b
   const size_t B = d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC ? 0 : (size_t)d.prob.batch;
   const bool multi = c->use_blocks && rfast_sync_wave_eligible(c);
   const bool large = (double)d.n * (double)d.p * 4.0 > 8.0e6;
+  const bool team = team_usable(c);
   for (int32_t r = 0; r < rounds;) {
+    if (team) {  // least squares / logistic regression: the steps up to the next decay of the step size in one launch
+      int32_t len = std::min(rounds - r, 1 << 20);
+      if (c->gamma_step > 0) len = (int32_t)std::min<int64_t>(len, c->gamma_step - c->host_round % c->gamma_step);
+      if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
+      if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
+      if (B > 0 && !d_batch_idx) return fail(c, RFAST_EINVAL, "sample rows are required when batch > 0");
+      if (fold_sync(c) != RFAST_OK) return RFAST_EHIP;
+      time_begin(c, 0);
+      hipError_t e = in_team_order(c, [&] {
+        return rfast_launch_team(c, true, len, gamma_now(c, gamma), (int)c->host_round, d_batch_idx ? d_batch_idx + (size_t)r * d.n * B : nullptr, nullptr, nullptr);
+      });
+      time_end(c, 0);
+      if (e == hipSuccess) e = rfast_launch_sync_plan(c, len);
+      if (e != hipSuccess) return hipfail(c, e, "multi-step synchronous launch");
+      c->host_round += len;
+      r += len;
+      continue;
+    }
     // several steps per launch for the separable objective on a small graph, with one step size
     int32_t len = multi ? rounds - r : 0;
     if (len > 0 && c->gamma_step > 0) {
@@ -1026,6 +1139,7 @@ int rfast_check(rfast_ctx* c) {
   }
   if (err[0] == 0) return RFAST_OK;
   static const char* kinds[] = {"delay on R edge", "delay on C edge", "sample row of node", "class label of a sample of node"};
+  if (err[0] == RFAST_EHIP) return fail(c, RFAST_EHIP, "a workgroup waited in vain for another one in the rounds from " + std::to_string(err[1]) + " on: the state is not valid");
   const char* what = err[2] >= 0 && err[2] <= 3 ? kinds[err[2]] : "value";
   return fail(c, err[0], std::string(what) + " " + std::to_string(err[3]) + " out of range in round " + std::to_string(err[1]) +
                              " (clamped on the device)");
@@ -1237,6 +1351,7 @@ const char* rfast_last_error(const rfast_ctx* c) { return c ? c->err.c_str() : g
 void rfast_destroy(rfast_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
+  leave_team_order(c);
   drop_graph(c);
   if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
   for (int w = 0; w < 3; ++w)

@@ -25,6 +25,24 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
+// coordinates k .. k+3 of a vector that ends at `end`, zeros past it (at any float's address)
+__device__ inline float4 ld_quad(const float* v, int64_t k, int64_t end) {
+  if (k + 4 <= end) return V<4>::ldu(v + k);
+  float4 t = make_float4(v[k], 0.f, 0.f, 0.f);
+  if (k + 1 < end) t.y = v[k + 1];
+  if (k + 2 < end) t.z = v[k + 2];
+  return t;
+}
+__device__ inline void st_quad(float* v, int64_t k, int64_t end, float4 t) {
+  if (k + 4 <= end) {
+    V<4>::stu(v + k, t);
+    return;
+  }
+  v[k] = t.x;
+  if (k + 1 < end) v[k + 1] = t.y;
+  if (k + 2 < end) v[k + 2] = t.z;
+}
+
 // a sampled row number as read from the caller's array: clamped into the node's samples, and reported, if outside
 __device__ inline int checked_row(const RfastDev& s, int i, int row) {
   if (row < 0 || row >= s.prob.samples) {
@@ -89,47 +107,50 @@ __global__ void __launch_bounds__(kThreads) rfast_rows_kernel(RfastDev s, const 
   const float* x = s.x + (size_t)i * p;
   // the target goes out with the row, not after the dot product (one round trip to memory less at the end)
   const float y = ((const float*)s.prob.data1)[(size_t)i * s.prob.samples + row];
-  float acc = 0.f;
-  if ((p & 3) == 0) {
+  // Lane c sums the products of coordinates 4c .. 4c+3 (+ 256 m) of a chunk, the lanes' sums are added as a butterfly,
+  // and the chunks (one, unless the team kernel splits the coordinates of a node) in order.
+  float total = 0.f;
+  const int64_t chunk = s.row_chunk;
+  for (int64_t c0 = 0; c0 < p; c0 += chunk) {
+    const int64_t end = c0 + chunk < p ? c0 + chunk : p;
+    float acc = 0.f;
     // sixteen 1 KiB pieces of the row (4096 coordinates) per step, all thirty-two loads issued before the first
     // use: one wavefront per row has nothing else to hide the memory latency with, and a step costs a round trip
     constexpr int kPieces = 16;
-    for (int64_t k0 = (int64_t)lane * 4; k0 < p; k0 += 256 * kPieces) {
+    for (int64_t k0 = c0 + (int64_t)lane * 4; k0 < end; k0 += 256 * kPieces) {
       float4 av[kPieces], xv[kPieces];
 #pragma unroll
       for (int u = 0; u < kPieces; ++u)
-        if (k0 + 256 * u < p) {
-          av[u] = *reinterpret_cast<const float4*>(a + k0 + 256 * u);
-          xv[u] = *reinterpret_cast<const float4*>(x + k0 + 256 * u);
+        if (k0 + 256 * u < end) {
+          av[u] = ld_quad(a, k0 + 256 * u, end);
+          xv[u] = ld_quad(x, k0 + 256 * u, end);
         }
 #pragma unroll
       for (int u = 0; u < kPieces; ++u)
-        if (k0 + 256 * u < p) {
+        if (k0 + 256 * u < end) {
           acc = fmaf(av[u].x, xv[u].x, acc);
           acc = fmaf(av[u].y, xv[u].y, acc);
           acc = fmaf(av[u].z, xv[u].z, acc);
           acc = fmaf(av[u].w, xv[u].w, acc);
         }
     }
-  } else {
-    for (int64_t k = lane; k < p; k += 64) acc = fmaf(a[k], x[k], acc);
+    acc = wave_sum(acc);
+    total = c0 == 0 ? acc : total + acc;
   }
-  acc = wave_sum(acc);
+  const float acc = total;
   if (lane == 0) {
     const float r = s.prob.kind == RFAST_OBJ_LOGISTIC ? 1.0f / (1.0f + expf(-acc)) - y : acc - y;
     s.resid[(size_t)i * B + b] = r;
   }
 }
 
-// VEC = 4: a workgroup owns 256 coordinates (one float4 per lane); its four wavefronts each take
+// A workgroup owns 256 coordinates (one float4 per lane); its four wavefronts each take
 // every fourth sampled row (a row is then one coalesced 1 KiB read per wavefront and the row
 // number is wavefront-uniform) and the four partial sums meet in LDS.  That gives p/256
 // workgroups per node instead of p/1024 and a quarter of the loop per lane: with a few dozen
-// rows per node there is not enough work to hide the latency otherwise.  VEC = 1: one coordinate
-// per lane, every lane walks over all rows.
-template <int VEC>
+// rows per node there is not enough work to hide the latency otherwise.
 __global__ void __launch_bounds__(kThreads) rfast_cols_kernel(RfastDev s, const int32_t* batch_idx, int B, bool init) {
-  extern __shared__ float sh[];  // [B] residuals, [B] row numbers, then (VEC = 4) [4][64] float4 partial sums
+  extern __shared__ float sh[];  // [B] residuals, [B] row numbers, then [4][64] float4 partial sums
   int t_old;
   const int i = pick_node(s, init, &t_old);
   if (i < 0) return;
@@ -145,42 +166,33 @@ __global__ void __launch_bounds__(kThreads) rfast_cols_kernel(RfastDev s, const 
   const float inv = 1.0f / (float)B;
   // l2 term of the logistic objective plus the weight decay of the optimizer variant
   const float lam = (s.prob.kind == RFAST_OBJ_LOGISTIC ? s.prob.lambda : 0.f) + s.wd;
-  if (VEC == 4) {
-    const int lane = threadIdx.x & 63, rg = threadIdx.x >> 6;
-    const int64_t k = ((int64_t)blockIdx.x * 64 + lane) * 4;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (k < p) {
-      const float* base = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p + k;
+  const int lane = threadIdx.x & 63, rg = threadIdx.x >> 6;
+  const int64_t k = ((int64_t)blockIdx.x * 64 + lane) * 4;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (k < p) {
+    const float* base = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p;
 #pragma unroll 4
-      for (int b = rg; b < B; b += kWaves) {
-        const float4 av = *reinterpret_cast<const float4*>(base + (size_t)row_sh[b] * p);
-        const float r = r_sh[b];
-        acc.x = fmaf(r, av.x, acc.x);
-        acc.y = fmaf(r, av.y, acc.y);
-        acc.z = fmaf(r, av.z, acc.z);
-        acc.w = fmaf(r, av.w, acc.w);
-      }
+    for (int b = rg; b < B; b += kWaves) {
+      const float4 av = ld_quad(base + (size_t)row_sh[b] * p, k, p);
+      const float r = r_sh[b];
+      acc.x = fmaf(r, av.x, acc.x);
+      acc.y = fmaf(r, av.y, acc.y);
+      acc.z = fmaf(r, av.z, acc.z);
+      acc.w = fmaf(r, av.w, acc.w);
     }
-    float4* part = reinterpret_cast<float4*>(sh + ((2 * B + 3) & ~3));
-    part[rg * 64 + lane] = acc;
-    __syncthreads();
-    if (rg == 0 && k < p) {
+  }
+  float4* part = reinterpret_cast<float4*>(sh + ((2 * B + 3) & ~3));
+  part[rg * 64 + lane] = acc;
+  __syncthreads();
+  if (rg == 0 && k < p) {
 #pragma unroll
-      for (int q = 1; q < kWaves; ++q) {
-        const float4 o = part[q * 64 + lane];
-        acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
-      }
-      const float4 xv = *reinterpret_cast<const float4*>(s.x + (size_t)i * p + k);
-      *reinterpret_cast<float4*>(g_new + k) = make_float4(fmaf(lam, xv.x, acc.x * inv), fmaf(lam, xv.y, acc.y * inv),
-                                                          fmaf(lam, xv.z, acc.z * inv), fmaf(lam, xv.w, acc.w * inv));
+    for (int q = 1; q < kWaves; ++q) {
+      const float4 o = part[q * 64 + lane];
+      acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
     }
-  } else {
-    const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (k >= p) return;
-    const float* base = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p + k;
-    float acc = 0.f;
-    for (int b = 0; b < B; ++b) acc = fmaf(r_sh[b], base[(size_t)row_sh[b] * p], acc);
-    g_new[k] = fmaf(lam, s.x[(size_t)i * p + k], acc * inv);
+    const float4 xv = ld_quad(s.x + (size_t)i * p, k, p);
+    st_quad(g_new, k, p, make_float4(fmaf(lam, xv.x, acc.x * inv), fmaf(lam, xv.y, acc.y * inv), fmaf(lam, xv.z, acc.z * inv),
+                                     fmaf(lam, xv.w, acc.w * inv)));
   }
 }
 
@@ -194,7 +206,7 @@ __global__ void __launch_bounds__(kThreads) rfast_cols_kernel(RfastDev s, const 
 //   rfast_cols_track_mix_kernel    g' of round r from the residuals, the tracker update with it, and then x', v
 //                                  of round r+1 for the nodes that round activates
 // (a node active in round r+1 but not in round r is mixed by the same workgroups, from z in memory).  Every
-// step computes what rfast_cols_kernel<4>, rfast_state_kernel<TRACK> and rfast_state_kernel<MIX> compute, in the
+// step computes what rfast_cols_kernel, rfast_state_kernel<TRACK> and rfast_state_kernel<MIX> compute, in the
 // same order: same bits.  What a round reads of other nodes was written by an earlier launch: the versions of v
 // that round r+1 mixes were published by round r's mixing at the latest, the running sums that round r tracks by
 // round r-1's tracking at the latest.  The loads of the tracker update and of the mixing go out before the
@@ -319,7 +331,7 @@ __global__ void __launch_bounds__(kThreads) rfast_cols_track_mix_kernel(RfastDev
   if (mine && t_next >= 0) chain_mix_loads(s, next_slot_r, i, k, vb, vw);
   __syncthreads();  // residuals and row numbers are in LDS
 
-  // ---- as rfast_cols_kernel<4>: wavefront rg sums rows rg, rg + 4, ...; sixteen rows in flight
+  // ---- as rfast_cols_kernel: wavefront rg sums rows rg, rg + 4, ...; sixteen rows in flight
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (k < p) {
     const float* base = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p + k;
@@ -421,14 +433,9 @@ hipError_t gemv_pair(rfast_ctx* c, const int32_t* batch_idx, bool init) {
   hipLaunchKernelGGL(rfast_rows_kernel, dim3((B + kWaves - 1) / kWaves, d.n), dim3(kThreads), 0, c->stream, d, bi, B, init, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool vec4 = (d.p % 4) == 0;
-  const int64_t per_block = vec4 ? 256 : kThreads;  // coordinates per workgroup
-  const unsigned gx = (unsigned)((d.p + per_block - 1) / per_block);
-  const size_t shm = (size_t)((2 * B + 3) & ~3) * 4 + (vec4 ? (size_t)kWaves * 64 * 16 : 0);
-  if (vec4)
-    hipLaunchKernelGGL(rfast_cols_kernel<4>, dim3(gx, d.n), dim3(kThreads), shm, c->stream, d, bi, B, init);
-  else
-    hipLaunchKernelGGL(rfast_cols_kernel<1>, dim3(gx, d.n), dim3(kThreads), shm, c->stream, d, bi, B, init);
+  const unsigned gx = (unsigned)((d.p + 255) / 256);
+  const size_t shm = (size_t)((2 * B + 3) & ~3) * 4 + (size_t)kWaves * 64 * 16;
+  hipLaunchKernelGGL(rfast_cols_kernel, dim3(gx, d.n), dim3(kThreads), shm, c->stream, d, bi, B, init);
   return hipGetLastError();
 }
 

@@ -116,6 +116,7 @@ struct RfastDev {
   int32_t* gen_batch;     // [n][batch]
   uint32_t* gen_cdf;      // [n] selection thresholds of the event-driven mode (one node per iteration)
   float* xbar;            // [p] node average, written by the diagnostics kernel
+  int32_t row_chunk;      // least squares / logistic: a row's dot product is summed by chunks of this many coordinates
   // optimizer variant: heavy-ball buffers m_i [n][p] (caller's memory, NULL when beta == 0)
   float* mom;
   float beta, wd;
@@ -123,6 +124,12 @@ struct RfastDev {
   float* resid;           // [n][rows] residuals of the GEMV pair / unused
   void* gscratch;         // softmax: bf16 W copy and E matrix
   rfast_problem prob;
+};
+
+// Workgroups per node of the team kernel (rfast_team.hip), their chunk of the coordinates (a multiple of 256 if there
+// are several), coordinates per owning lane, tiles of sampled rows in LDS (0: the rows are read from memory twice).  W = 0: not for this problem.
+struct RfastTeam {
+  int W = 0, C = 0, per_lane = 0, tiles = 0;
 };
 
 struct rfast_ctx {
@@ -153,6 +160,13 @@ struct rfast_ctx {
   int32_t* blk_plan_base = nullptr;  // kBlockRounds plan records
   int32_t* blk_head_base = nullptr;  // kHeadWords n + eC words, see RfastDev::blk_head
   int32_t max_degree = 0;       // most in-edges of R, in-edges of C or out-edges of C at any node
+  RfastTeam team;
+  unsigned team_base = 0;       // rounds handed to the team kernel so far (its progress words and packet tags never repeat)
+  void* team_packets = nullptr;
+  unsigned* team_flags = nullptr;
+  int device = 0;
+  bool no_tiles = false;        // event-driven iterations: no multi-round launch on coordinate tiles
+  bool capturing = false;       // rounds are being captured into the context's own graph
   // the per-round plan arrays of RfastDev exist kResolveAhead times; `plan_set` is the set d points at
   char* plan_set0 = nullptr;
   size_t plan_set_bytes = 0;
@@ -169,6 +183,7 @@ enum { RFAST_MODE_FUSED = 0, RFAST_MODE_MIX = 1, RFAST_MODE_TRACK = 2 };
 // plus 0.33 ms per round against 1.53 ms per round of the streaming kernel: even from 6 rounds on)
 constexpr int kHeadWords = 16;  // words per node in RfastDev::blk_head
 constexpr int kBlockRounds = 512;
+constexpr int kTeamMost = 256;  // workgroups of a team launch at most
 constexpr int kPlanChunk = 16;
 constexpr int kBlockMinRoundsLarge = 8;
 // rounds the resolver may run ahead of the kernels that read its plans (rfast_run, one pass per round)
@@ -198,6 +213,12 @@ bool rfast_chain_eligible(const rfast_ctx* c);
 hipError_t rfast_launch_rows(rfast_ctx* c, const int32_t* d_batch_idx, const uint8_t* d_active);
 hipError_t rfast_launch_cols_track_mix(rfast_ctx* c, const int32_t* d_batch_idx, const uint8_t* d_active, const uint8_t* d_active_next,
                                        size_t next_set_bytes, float gamma_next);
+// least squares / logistic regression: several rounds per launch with a team of workgroups per node
+RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree_r, int compute_units);
+size_t rfast_team_packet_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob);
+size_t rfast_team_flag_bytes(const RfastTeam& t, int32_t n);
+hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int round0, const int32_t* d_batch_idx,
+                             const int32_t* d_delay_R, const int32_t* d_delay_C);
 bool rfast_tiny_eligible(const rfast_ctx* c);   // the multi-round kernel for least squares / logistic problems that fit one CU's LDS
 bool rfast_tiny_resolves(const rfast_ctx* c);   // ... and it resolves its rounds itself (no resolver launch ahead of it)
 hipError_t rfast_launch_tiny(rfast_ctx* c, const RfastBlock& blk, const int32_t* d_batch_idx, int round0, const uint8_t* d_active,

@@ -1,0 +1,727 @@
+// Several rounds per launch for least squares and logistic regression beyond one compute unit: a TEAM of workgroups
+// per node, all of them resident for the whole launch.
+//
+// As a chain of kernels a round of these objectives is 12 to 25 us however little it moves: every kernel of the chain
+// starts with a launch and three or four dependent round trips to memory.  Here workgroup (i, w) keeps chunk w of the
+// coordinates of node i: x, z, the stored sample, the latest running sum and the heavy-ball buffer stay in registers
+// and, where they fit, the sampled rows in LDS; it goes through the rounds in which its node does something and talks
+// to the other workgroups through memory:
+//   rings   v and the running sums are published by stores and read by loads of agent scope (the L2 caches of the
+//           accelerator dies are not coherent with each other; such accesses meet behind them).  The part of a ring
+//           that wavefront y of workgroup (j, w) writes is read by wavefronts y of the workgroups (i, w) only, so the
+//           two progress words of a wavefront, "v of every round before this one is out", "the sums are", are all the
+//           synchronisation there is between nodes: no barrier over the chip, a node waits for the versions it reads.
+//   dots    a row's product a_s . x' is the sum of one term per workgroup of the team, exchanged as 8-byte packets of
+//           value and round number: the packet is its own flag, one trip through memory (0.8-1.3 us, measured)
+//           instead of data, acknowledgement, flag, poll and read.
+// What a wavefront may wait for belongs to rounds before the one it is in, or (packets) to the same round of its own
+// team, whose members wait for earlier rounds only: by induction over the rounds every wait ends, as long as all
+// workgroups of the launch are resident, one per compute unit (rfast_team_shape).  The waits are bounded all the
+// same: a wait that runs out reports an error (rfast_check) and no later wait of the workgroup waits at all.
+//   A ring slot is overwritten only when every receiver is past the rounds in which its version could be read: the
+// slot of version t + 1 held version t - D - 1, which left the readable window with the sender's previous activation,
+// so the receivers must have finished the round of that activation.
+//
+// Four wavefronts own the coordinates (kOwn lanes, kE each); four more fetch the sampled rows of the next active round
+// while the others update and mix.  (Loads return in order: a wavefront that polls and fetches rows would poll behind
+// the rows.)  All eight form dot products and column sums.
+//
+// The arithmetic is, operation for operation, that of rfast_state_kernel<MIX>, rfast_rows_kernel, rfast_cols_kernel and
+// rfast_state_kernel<TRACK> (same bits); rfast_rows_kernel adds a row's terms by the chunks of RfastDev::row_chunk, the
+// chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step.
+//
+// Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
+// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.8; 32 nodes, p = 4096,
+// batch 64: 21.2 -> 9.2; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 8.8; one agent of 55 per
+// iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
+// products out and in, sums out).
+#include <type_traits>
+
+#include "rfast_vec.h"
+
+namespace {
+
+constexpr int kThreads = 512;
+constexpr int kOwn = 256;                  // lanes that own coordinates
+constexpr int kOwnWaves = kOwn / 64;
+constexpr int kLoad = kThreads - kOwn;     // lanes that fetch rows
+constexpr int kLoadWaves = kLoad / 64;
+constexpr int kTileRows = 64 * kLoadWaves; // most sampled rows of a tile: a fetching wavefront holds their numbers, one per lane
+constexpr int kFlagWords = 16;             // 32-bit words per progress entry (64 bytes): [0] v, [1] sums
+constexpr int kSpin = 1 << 24;             // polls before a wait gives up (some ten seconds)
+constexpr size_t kLds = 156 * 1024;
+
+typedef unsigned long long u64;
+
+__device__ inline void put32(unsigned* p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline unsigned get32(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void put64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u64 get64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void put_f(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float get_f(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+__device__ inline int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ inline float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+
+struct TeamArgs {
+  int rounds, W, C, B, buffers;  // buffers: tiles of rows in LDS (two: the next round's rows arrive during this one)
+  float gamma;
+  unsigned base;              // progress words and packet tags count rounds from here on (they never repeat)
+  int round0;                 // number of the first round, for error reports
+  const int32_t* batch_idx;   // [rounds][n][B], NULL: all rows, in order
+  const int32_t* delay_R;     // [rounds][eR] (not SYNC)
+  const int32_t* delay_C;     // [rounds][eC]
+  u64* packets;               // [2][n][W][B]
+  unsigned* flags;            // [n][W][kOwnWaves][kFlagWords]
+};
+
+// first set bit at or after `from` of a mask of kBlockRounds bits, kBlockRounds if there is none
+__device__ inline int next_bit(const u64* mask, int from) {
+  int w = from >> 6;
+  if (w >= kBlockRounds / 64) return kBlockRounds;
+  u64 m = mask[w] & (~0ull << (from & 63));
+  while (m == 0) {
+    if (++w == kBlockRounds / 64) return kBlockRounds;
+    m = mask[w];
+  }
+  return w * 64 + __ffsll((long long)m) - 1;
+}
+
+template <int kE, bool TILE, bool SYNC>
+__global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamArgs a) {
+  constexpr int KB = kE <= 2 ? 8 : (kE == 4 ? 4 : 2);  // in-edges whose ring values are in flight together
+  extern __shared__ float4 lds4[];
+  const int n = s.n, M = s.M, W = a.W, B = a.B, S = s.prob.samples;
+  const int64_t p = s.p;
+  const int i = blockIdx.x / W, w = blockIdx.x - i * W;
+  const int first = w * a.C;                                        // first coordinate of the chunk
+  const int Cw = (int)p - first < a.C ? (int)p - first : a.C;       // its coordinates
+  const int Q = (Cw + 3) >> 2, Qm = (a.C + 3) >> 2;                 // its groups of four; those of the widest chunk
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool owner = tid < kOwn;
+  const bool sampled = a.batch_idx != nullptr;
+  // ---- LDS
+  float4* const tiles = lds4;                                       // TILE: [a.buffers][B][Q]
+  float4* xs4 = tiles + (TILE ? (size_t)a.buffers * B * Qm : 0);    // [Q] the mixed x of this round
+  float4* cp4 = xs4 + Qm;                                           // [4][Q] column sums of the four groups of rows
+  float* rs = reinterpret_cast<float*>(cp4 + 4 * Qm);               // [B] residuals
+  int* rowi = reinterpret_cast<int*>(rs + B);                       // [2][B] sampled rows of this active round and the next
+  int* nodew = rowi + (sampled ? 2 * B : 0);                        // [kBlockRounds] node words
+  __shared__ u64 act_mask[kBlockRounds / 64], ev_mask[kBlockRounds / 64];
+  float* xs = reinterpret_cast<float*>(xs4);
+  const float* rows_g = (const float*)s.prob.data0 + (size_t)i * S * p + first;   // + row p + coordinate in the chunk
+  const float* targets = (const float*)s.prob.data1 + (size_t)i * S;
+
+  // ---- the rounds in which the node does something: it is active, or an S4 buffer of it has to be saved
+  const int W1 = n + s.eR + s.eC + 1;
+  if (!SYNC) {
+    int word = 0;
+    bool spill = false;
+    if (tid < a.rounds) {
+      word = s.blk_plan[(size_t)tid * W1 + i];
+      spill = s.blk_spill[(size_t)tid * n + i] == a.round0 + tid + 1;
+    }
+    nodew[tid] = word;
+    const u64 am = __ballot(word < 0), em = __ballot(word < 0 || spill);
+    if (lane == 0) {
+      act_mask[wave] = am;
+      ev_mask[wave] = em;
+    }
+  }
+  static_assert(kThreads == kBlockRounds, "one lane per round above");
+
+  // ---- graph of the node, one edge per lane; state of the owned coordinates
+  const int re0 = s.r_ptr[i], dR = s.r_ptr[i + 1] - re0, ce0 = s.c_ptr[i], dI = s.c_ptr[i + 1] - ce0;
+  const int ro0 = s.ro_ptr[i], dRo = s.ro_ptr[i + 1] - ro0, co0 = s.co_ptr[i], dCo = s.co_ptr[i + 1] - co0;
+  const float r_self = s.r_self[i], c_self = s.c_self[i];
+  int r_src = 0, c_src = 0, r_dst = 0, c_dst = 0;
+  float r_w = 0.f, c_w = 0.f;
+  if (lane < dR) { r_src = s.r_src[re0 + lane]; r_w = s.r_w[re0 + lane]; }
+  if (lane < dI) { c_src = s.c_src[ce0 + lane]; c_w = s.c_w[ce0 + lane]; }
+  if (lane < dRo) r_dst = s.r_dst[s.ro_eid[ro0 + lane]];
+  if (lane < dCo) c_dst = s.c_dst[s.co_eid[co0 + lane]];
+  auto flag_of = [&](int node, int word) { return a.flags + ((size_t)(node * W + w) * kOwnWaves + wave) * kFlagWords + word; };
+  const bool momentum = s.mom != nullptr;
+  const float inv = 1.0f / (float)B;
+  const bool logistic = s.prob.kind == RFAST_OBJ_LOGISTIC;
+  const float lam = (logistic ? s.prob.lambda : 0.f) + s.wd;  // l2 term plus the weight decay of the optimizer variant
+  __syncthreads();
+  const int t0 = SYNC ? s.t[i] : nodew[0] & 0x3FFFFFFF;
+  float x[kE], z[kE], g[kE], sc[kE], m[kE];
+  bool has[kE];
+#pragma unroll
+  for (int e = 0; e < kE; ++e) {
+    const int k = tid + kOwn * e;
+    has[e] = owner && k < Cw;
+    x[e] = z[e] = g[e] = sc[e] = m[e] = 0.f;
+    if (has[e]) {
+      const size_t off = (size_t)i * p + first + k;
+      x[e] = s.x[off];
+      z[e] = s.z[off];
+      g[e] = s.g[(size_t)(t0 & 1) * n * p + off];
+      if (!SYNC) sc[e] = s.sigma_ring[((size_t)i * M + t0 % M) * p + first + k];
+      if (momentum) m[e] = s.mom[off];
+    }
+  }
+  if (tid < 4 * Q - Cw) xs[Cw + tid] = 0.f;  // the unused end of the last group of four stays zero
+  if (TILE)
+    for (int f = tid; f < a.buffers * B * (4 * Q - Cw); f += kThreads) {
+      const int r = f / (4 * Q - Cw);
+      reinterpret_cast<float*>(tiles + (size_t)r * Q)[Cw + (f - r * (4 * Q - Cw))] = 0.f;
+    }
+
+  bool dead = false;  // a wait has run out
+  auto give_up = [&] {
+    dead = true;
+    if (atomicCAS(&s.err[0], 0, RFAST_EHIP) == 0) {
+      s.err[1] = a.round0;
+      s.err[2] = 4;
+      s.err[3] = i;
+    }
+  };
+  // waits until the progress words of the lanes that have one are at least round `need` of this launch
+  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2) {
+    if (need1 <= 0) f1 = nullptr;
+    if (need2 <= 0) f2 = nullptr;
+    if (!__any(f1 != nullptr || f2 != nullptr) || dead) return;
+    for (int spin = 0;; ++spin) {
+      const unsigned v1 = f1 ? get32(f1) : 0, v2 = f2 ? get32(f2) : 0;
+      const bool ok = (!f1 || (int)(v1 - a.base) >= need1) && (!f2 || (int)(v2 - a.base) >= need2);
+      if (__all(ok)) break;
+      if (spin > kSpin) {
+        give_up();
+        break;
+      }
+    }
+    // what the words stand for was stored before them; nothing below may be loaded before they were seen
+    asm volatile("" ::: "memory");
+  };
+
+  // ---- rows.  A row number as the caller gave it, clamped into the node's samples and reported if outside.
+  auto row_of = [&](int q, int b) {
+    int row = a.batch_idx[((size_t)q * n + i) * B + b];
+    if (row < 0 || row >= S) {
+      if (w == 0 && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
+        s.err[1] = a.round0 + q;
+        s.err[2] = 2;
+        s.err[3] = i;
+      }
+      row = row < 0 ? 0 : S - 1;
+    }
+    return row;
+  };
+  auto fetch_rows = [&](int q, int* to) {
+    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = row_of(q, b);
+  };
+  // Four coordinates of a row (unaligned where p is no multiple of four).  At the chunk's ragged end the load starts up
+  // to three coordinates early, still inside the row, and whole_quad moves them into place and clears the rest.
+  const bool ragged = (Cw & 3) != 0;
+  auto row_quad = [&](int row, int quad) {
+    const int at = ragged && 4 * quad > Cw - 4 ? Cw - 4 : 4 * quad;
+    return V<4>::ldu(rows_g + (size_t)row * p + at);
+  };
+  auto whole_quad = [&](float4 v, int quad) {
+    const int by = 4 * quad + 4 - Cw;  // coordinates the load started early
+    if (ragged && by > 0) {
+      v.x = by == 1 ? v.y : by == 2 ? v.z : v.w;
+      v.y = by == 1 ? v.z : by == 2 ? v.w : 0.f;
+      v.z = by == 1 ? v.w : 0.f;
+      v.w = 0.f;
+    }
+    return v;
+  };
+  const unsigned q_magic = 0xFFFFFFFFu / (unsigned)Q;
+  auto split = [&](int f, int* b, int* quad) {  // f / Q and f mod Q
+    int d = (int)__umulhi((unsigned)f, q_magic);
+    int r = f - d * Q;
+    if (r >= Q) { r -= Q; ++d; }
+    *b = d;
+    *quad = r;
+  };
+  // Rows into LDS, straight from memory: no registers, so that everything is in flight at once.  A wavefront takes every
+  // kLoadWaves-th row; the destination of such a load is contiguous over the lanes.
+  const bool wide = (p & 3) == 0;  // 16-byte pieces need 16-byte addresses
+  auto load_tile = [&](const int* rows, float4* dst) {
+    const int lw = wave - kOwnWaves;
+    const int mine = sampled && lw + kLoadWaves * lane < B ? rows[lw + kLoadWaves * lane] : 0;
+    int r = 0;
+    for (int b = lw; b < B; b += kLoadWaves, ++r) {
+      const float* src = rows_g + (size_t)(sampled ? lane_value(mine, r) : b) * p;
+      float4* to = dst + b * Q;
+      if (wide) {
+        for (int quad = lane; quad < Q; quad += 64)
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + 4 * quad),
+                                           (__attribute__((address_space(3))) void*)(to + (quad - lane)), 16, 0, 0);
+      } else {
+        for (int k = lane; k < Cw; k += 64)
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + k),
+                                           (__attribute__((address_space(3))) void*)(reinterpret_cast<float*>(to) + (k - lane)), 4, 0, 0);
+      }
+    }
+  };
+  const int rounds = a.rounds;
+  auto next_active = [&](int from) { return SYNC ? from : next_bit(act_mask, from); };
+  auto next_event = [&](int from) { return SYNC ? from : next_bit(ev_mask, from); };
+  int parity = 0;  // of the active rounds of this launch: packets and row numbers alternate
+  {
+    const int qa = next_active(0);
+    if (!owner && sampled && qa < rounds) fetch_rows(qa, rowi);
+    if (sampled) __syncthreads();
+    if (TILE && !owner && qa < rounds) load_tile(rowi, tiles);
+  }
+
+  int q = next_event(0), q_prev = -1;  // this event, and the last round in which the node was active
+  // plan words and delays of the event, an edge per lane (of the next event: fetched while this one is computed)
+  int rw_n = 0, cw_n = 0, rd_n = 0, cd_n = 0;
+  auto fetch_plan = [&](int at) {
+    if (SYNC || at >= rounds) return;
+    const int32_t* rec = s.blk_plan + (size_t)at * W1;
+    if (lane < dR) { rw_n = rec[n + re0 + lane]; rd_n = a.delay_R[(size_t)at * s.eR + re0 + lane]; }
+    if (lane < dI) { cw_n = rec[n + s.eR + ce0 + lane]; cd_n = a.delay_C[(size_t)at * s.eC + ce0 + lane]; }
+  };
+  auto clamped = [&](int d) { return d < 0 ? 0 : (d > s.d_max ? s.d_max : d); };
+  if (owner) {
+    fetch_plan(q);
+    if (!SYNC && lane == 0) {  // rounds before the first event: nothing to wait for
+      put32(flag_of(i, 0), a.base + (unsigned)(q < rounds ? q : rounds));
+      put32(flag_of(i, 1), a.base + (unsigned)(q < rounds ? q : rounds));
+    }
+  }
+
+  while (q < rounds) {
+    const int q_next = next_event(q + 1);
+    const unsigned done_word = a.base + (unsigned)(q_next < rounds ? q_next : rounds);
+    const int word = SYNC ? (int)0x80000000 : nodew[q];
+    const bool active = word < 0;
+    const int t_old = SYNC ? t0 + q : word & 0x3FFFFFFF;
+    const int rword = rw_n, cword = cw_n, rneed = q - clamped(rd_n), cneed = q - clamped(cd_n);
+    const int slot_new = SYNC ? q & 1 : (t_old + 1) % M;
+    dead = __any(dead);
+    if (owner && active) {
+      // ---- S1, S2a, S3 (v half)
+      if (!SYNC) wait2(lane < dR ? flag_of(r_src, 0) : nullptr, rneed, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1);
+      else wait2(lane < dRo ? flag_of(r_dst, 0) : nullptr, q, lane < dCo ? flag_of(c_dst, 0) : nullptr, q);
+      float v[kE], xn[kE];
+#pragma unroll
+      for (int e = 0; e < kE; ++e) {
+        float dir = z[e];
+        if (momentum) dir = m[e] = fmaf(s.beta, m[e], z[e]);
+        v[e] = fmaf(-a.gamma, dir, x[e]);
+        xn[e] = r_self * v[e];
+      }
+      float* own_v = s.v_ring + ((size_t)i * M + slot_new) * p + first + tid;
+      if (SYNC) {  // everybody's v and z of this step go out before anybody's are read
+        float* own_z = s.sigma_ring + ((size_t)i * M + slot_new) * p + first + tid;
+#pragma unroll
+        for (int e = 0; e < kE; ++e)
+          if (has[e]) {
+            put_f(own_v + kOwn * e, v[e]);
+            put_f(own_z + kOwn * e, z[e]);
+          }
+        __builtin_amdgcn_s_waitcnt(0);
+        if (lane == 0) put32(flag_of(i, 0), a.base + (unsigned)(q + 1));
+        wait2(lane < dR ? flag_of(r_src, 0) : nullptr, q + 1, lane < dI ? flag_of(c_src, 0) : nullptr, q + 1);
+      }
+      for (int e0 = 0; e0 < dR; e0 += KB) {
+        float vb[KB][kE];
+#pragma unroll
+        for (int u = 0; u < KB; ++u)
+          if (e0 + u < dR) {
+            const int slot = SYNC ? slot_new : lane_value(rword, e0 + u);
+            const float* src = s.v_ring + ((size_t)lane_value(r_src, e0 + u) * M + slot) * p + first + tid;
+#pragma unroll
+            for (int e = 0; e < kE; ++e)
+              if (has[e]) vb[u][e] = get_f(src + kOwn * e);
+          }
+#pragma unroll
+        for (int u = 0; u < KB; ++u)
+          if (e0 + u < dR) {
+            const float wt = lane_value(r_w, e0 + u);
+#pragma unroll
+            for (int e = 0; e < kE; ++e) xn[e] = fmaf(wt, vb[u][e], xn[e]);
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < kE; ++e)
+        if (has[e]) {
+          if (!SYNC) put_f(own_v + kOwn * e, v[e]);
+          x[e] = xn[e];
+          xs[tid + kOwn * e] = xn[e];
+        }
+    }
+    if (active) {
+      float4* const tile = tiles + (a.buffers > 1 && parity ? B * Q : 0);        // TILE: the rows of this round
+      float4* const tile_next = tiles + (a.buffers > 1 && !parity ? B * Q : 0);  // ... and of the next active one
+      if (TILE && !owner) __builtin_amdgcn_s_waitcnt(0);  // the rows on their way into LDS have arrived
+      __syncthreads();  // the mixed x and the sampled rows are in LDS
+      // ---- gradient, rows: eight (four) rows per wavefront at a time; lane c sums coordinates 4c .. 4c+3 (+ 256 m) of the
+      // chunk, and the lanes' sums are added as a butterfly from distance 32 down to 1 whose first steps halve the rows
+      const int* rows = rowi + (parity ? B : 0);
+      auto dots = [&](auto rb) {
+        constexpr int RB = decltype(rb)::value;
+        for (int b0 = wave * RB; b0 < B; b0 += RB * (kThreads / 64)) {
+          float acc[RB];
+          const float4* trow[RB];
+          int grow[RB];
+#pragma unroll
+          for (int r = 0; r < RB; ++r) {
+            acc[r] = 0.f;
+            const int b = b0 + r < B ? b0 + r : B - 1;
+            if (TILE) trow[r] = tile + b * Q;
+            else grow[r] = sampled ? rows[b] : b;
+          }
+          for (int quad = lane; quad < Q; quad += 64) {
+            const float4 xv = xs4[quad];
+            float4 av[RB];
+#pragma unroll
+            for (int r = 0; r < RB; ++r) av[r] = TILE ? trow[r][quad] : row_quad(grow[r], quad);
+            if (!TILE && ragged) {
+#pragma unroll
+              for (int r = 0; r < RB; ++r) av[r] = whole_quad(av[r], quad);
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+              acc[r] = fmaf(av[r].x, xv.x, acc[r]);
+              acc[r] = fmaf(av[r].y, xv.y, acc[r]);
+              acc[r] = fmaf(av[r].z, xv.z, acc[r]);
+              acc[r] = fmaf(av[r].w, xv.w, acc[r]);
+            }
+          }
+          int row = 0, dist = 32;
+#pragma unroll
+          for (int h = RB / 2; h > 0; h >>= 1) {
+            const bool up = lane & dist;
+#pragma unroll
+            for (int r = 0; r < h; ++r) {
+              const float keep = up ? acc[r + h] : acc[r], send = up ? acc[r] : acc[r + h];
+              acc[r] = keep + __shfl_xor(send, dist, 64);
+            }
+            row += up ? h : 0;
+            dist >>= 1;
+          }
+          float sum = acc[0];
+#pragma unroll
+          for (int d2 = 32 / RB; d2 > 0; d2 >>= 1) sum += __shfl_xor(sum, d2, 64);
+          const int b = b0 + row;
+          if ((lane & (64 / RB - 1)) == 0 && b < B) {
+            if (W == 1) rs[b] = sum;
+            else
+              put64(a.packets + (((size_t)parity * n + i) * W + w) * B + b,
+                    (u64)(a.base + (unsigned)q + 1u) << 32 | __float_as_uint(sum));
+          }
+        }
+      };
+      if (B >= 64) dots(std::integral_constant<int, 8>());
+      else dots(std::integral_constant<int, 4>());
+      // ---- the owners ask for the ring values of the tracker update; the others look up the rows of the next round
+      float sg[KB][kE], rt[KB][kE];
+      const int qa = next_active(q + 1);
+      if (owner) {
+        if (!SYNC) {
+          wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+#pragma unroll
+          for (int u = 0; u < KB; ++u)
+            if (u < dI) {
+              const int pl = lane_value(cword, u);
+              if (pl & (1 << 16)) {
+                const float* ring = s.sigma_ring + (size_t)lane_value(c_src, u) * M * p + first + tid;
+                const int prev = (pl >> 8) & 0xFF;
+                const float* saved = s.rho_tilde + (size_t)(ce0 + u) * p + first + tid;
+#pragma unroll
+                for (int e = 0; e < kE; ++e)
+                  if (has[e]) {
+                    sg[u][e] = get_f(ring + (size_t)(pl & 0xFF) * p + kOwn * e);
+                    rt[u][e] = prev != 0xFF ? get_f(ring + (size_t)prev * p + kOwn * e) : saved[kOwn * e];
+                  }
+              }
+            }
+        } else {
+#pragma unroll
+          for (int u = 0; u < KB; ++u)
+            if (u < dI) {
+              const float* src = s.sigma_ring + ((size_t)lane_value(c_src, u) * M + slot_new) * p + first + tid;
+#pragma unroll
+              for (int e = 0; e < kE; ++e)
+                if (has[e]) sg[u][e] = get_f(src + kOwn * e);
+            }
+        }
+        fetch_plan(q_next);
+      } else if (sampled && qa < rounds) {
+        fetch_rows(qa, rowi + (parity ? 0 : B));
+      }
+      // ---- residuals: the terms of the team in order
+      if (W == 1) __syncthreads();
+      for (int b = tid; b < B && (W == 1 || owner); b += W == 1 ? kThreads : kOwn) {
+        float dot;
+        if (W == 1) {
+          dot = rs[b];
+        } else {
+          dot = 0.f;
+          const u64* src = a.packets + ((size_t)parity * n + i) * W * B + b;
+          const unsigned tag = a.base + (unsigned)q + 1u;
+          for (int w0 = 0; w0 < W; w0 += 8) {
+            u64 got[8];
+            for (int spin = 0;; ++spin) {
+              bool ok = true;
+#pragma unroll
+              for (int u = 0; u < 8; ++u)
+                if (w0 + u < W) got[u] = get64(src + (size_t)(w0 + u) * B);
+#pragma unroll
+              for (int u = 0; u < 8; ++u)
+                if (w0 + u < W) ok = ok && (unsigned)(got[u] >> 32) == tag;
+              if (ok || dead) break;
+              if (spin > kSpin) {
+                give_up();
+                break;
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (w0 + u < W) dot = w0 + u == 0 ? __uint_as_float((unsigned)got[u]) : dot + __uint_as_float((unsigned)got[u]);
+          }
+        }
+        const float y = targets[sampled ? rows[b] : b];
+        rs[b] = logistic ? 1.0f / (1.0f + expf(-dot)) - y : dot - y;
+      }
+      // the loads above were issued after the stores of v and have returned: v is out
+      if (owner && !SYNC) {
+        __builtin_amdgcn_s_waitcnt(0);
+        if (lane == 0) put32(flag_of(i, 0), done_word);
+      }
+      __syncthreads();  // residuals, and the row numbers of the next active round
+      if (TILE && !owner && sampled && qa < rounds && a.buffers > 1) load_tile(rowi + (parity ? 0 : B), tile_next);
+      // ---- gradient, columns: group rg sums rows rg, rg + 4, ... for four coordinates
+      for (int f = tid; f < 4 * Q; f += kThreads) {
+        int rg, quad;
+        split(f, &rg, &quad);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+        for (int b = rg; b < B; b += 4) {
+          const float r = rs[b];
+          const float4 av = TILE ? tile[b * Q + quad] : whole_quad(row_quad(sampled ? rows[b] : b, quad), quad);
+          acc.x = fmaf(r, av.x, acc.x);
+          acc.y = fmaf(r, av.y, acc.y);
+          acc.z = fmaf(r, av.z, acc.z);
+          acc.w = fmaf(r, av.w, acc.w);
+        }
+        cp4[f] = acc;
+      }
+      __syncthreads();  // column sums; the tile may be overwritten
+      if (!owner) {
+        if (TILE && sampled && qa < rounds && a.buffers == 1) load_tile(rowi + (parity ? 0 : B), tile_next);
+      } else {
+        // ---- S2b, S2c, S3 (rho half), S4; or eq. (2)
+        float g_new[kE], z_half[kE];
+        const float* cp = reinterpret_cast<const float*>(cp4);
+#pragma unroll
+        for (int e = 0; e < kE; ++e)
+          if (has[e]) {
+            const int k = tid + kOwn * e;
+            const float acc = ((cp[k] + cp[4 * Q + k]) + cp[8 * Q + k]) + cp[12 * Q + k];
+            g_new[e] = fmaf(lam, x[e], acc * inv);
+            z_half[e] = SYNC ? c_self * z[e] : z[e];
+          }
+        for (int e0 = 0; e0 < dI; e0 += KB) {
+          if (e0 > 0) {  // in-degree above one batch
+#pragma unroll
+            for (int u = 0; u < KB; ++u)
+              if (e0 + u < dI) {
+                const int pl = SYNC ? 0 : lane_value(cword, e0 + u);
+                if (SYNC || (pl & (1 << 16))) {
+                  const float* ring = s.sigma_ring + (size_t)lane_value(c_src, e0 + u) * M * p + first + tid;
+                  const int prev = (pl >> 8) & 0xFF;
+                  const float* saved = s.rho_tilde + (size_t)(ce0 + e0 + u) * p + first + tid;
+#pragma unroll
+                  for (int e = 0; e < kE; ++e)
+                    if (has[e]) {
+                      sg[u][e] = get_f(ring + (size_t)(SYNC ? slot_new : pl & 0xFF) * p + kOwn * e);
+                      if (!SYNC) rt[u][e] = prev != 0xFF ? get_f(ring + (size_t)prev * p + kOwn * e) : saved[kOwn * e];
+                    }
+                }
+              }
+          }
+#pragma unroll
+          for (int u = 0; u < KB; ++u)
+            if (e0 + u < dI) {
+              const float wt = lane_value(c_w, e0 + u);
+              if (SYNC) {
+#pragma unroll
+                for (int e = 0; e < kE; ++e)
+                  if (has[e]) z_half[e] = fmaf(wt, sg[u][e], z_half[e]);
+              } else {
+                const int pl = lane_value(cword, e0 + u);
+                if (pl & (1 << 16)) {
+                  const bool in_ring = ((pl >> 8) & 0xFF) != 0xFF;
+                  float* saved = s.rho_tilde + (size_t)(ce0 + e0 + u) * p + first + tid;
+#pragma unroll
+                  for (int e = 0; e < kE; ++e)
+                    if (has[e]) {
+                      z_half[e] = track_edge(z_half[e], wt, sg[u][e], rt[u][e], in_ring);
+                      if (pl & (1 << 17)) saved[kOwn * e] = wt * sg[u][e];
+                    }
+                }
+              }
+            }
+        }
+        float* own_s = s.sigma_ring + ((size_t)i * M + slot_new) * p + first + tid;
+#pragma unroll
+        for (int e = 0; e < kE; ++e)
+          if (has[e]) {
+            const float zh = (z_half[e] + g_new[e]) - g[e];
+            g[e] = g_new[e];
+            if (SYNC) {
+              z[e] = zh;
+            } else {
+              z[e] = c_self * zh;
+              if (dCo > 0) {
+                sc[e] += zh;
+                put_f(own_s + kOwn * e, sc[e]);
+              }
+            }
+          }
+      }
+      parity ^= 1;
+      q_prev = q;
+    } else if (owner) {
+      // an S4 buffer is about to lose its version: its sender must have published it (long ago) and may overwrite it
+      // only after this
+      fetch_plan(q_next);
+    }
+    if (owner && !SYNC) {
+      // S4 for buffers whose version leaves the sender's ring in this round without being consumed
+      u64 leaving = __ballot(lane < dI && (cword & (1 << 18)));
+      if (!active && leaving) wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, nullptr, 0);
+      while (leaving) {
+        const int u = __ffsll((long long)leaving) - 1;
+        leaving &= leaving - 1;
+        const float* ring = s.sigma_ring + ((size_t)lane_value(c_src, u) * M + (lane_value(cword, u) & 0xFF)) * p + first + tid;
+        float* saved = s.rho_tilde + (size_t)(ce0 + u) * p + first + tid;
+        const float wt = lane_value(c_w, u);
+#pragma unroll
+        for (int e = 0; e < kE; ++e)
+          if (has[e]) saved[kOwn * e] = wt * get_f(ring + kOwn * e);
+      }
+      __builtin_amdgcn_s_waitcnt(0);
+      if (lane == 0) {
+        if (!active) put32(flag_of(i, 0), done_word);
+        put32(flag_of(i, 1), done_word);
+      }
+    }
+    q = q_next;
+  }
+
+  // ---- write-back
+  const int t_end = SYNC ? t0 + rounds : s.t[i];
+  if (owner && (SYNC ? rounds > 0 : q_prev >= 0)) {
+#pragma unroll
+    for (int e = 0; e < kE; ++e)
+      if (has[e]) {
+        const size_t off = (size_t)i * p + first + tid + kOwn * e;
+        s.x[off] = x[e];
+        s.z[off] = z[e];
+        s.g[(size_t)(t_end & 1) * n * p + off] = g[e];
+        if (momentum) s.mom[off] = m[e];
+      }
+  }
+}
+
+size_t team_lds(const RfastDev& d, int C, int B, int tiles) {
+  const size_t Qm = (size_t)(C + 3) / 4;
+  return ((size_t)tiles * B * Qm + 5 * Qm) * 16 + (size_t)B * 4 + (d.prob.batch > 0 ? 2 * (size_t)B * 4 : 0) + kBlockRounds * 4;
+}
+
+template <int kE, bool TILE, bool SYNC>
+hipError_t launch_team(rfast_ctx* c, const TeamArgs& a) {
+  static bool raised = false;
+  if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_team_kernel<kE, TILE, SYNC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (e != hipSuccess) return e;
+    raised = true;
+  }
+  hipLaunchKernelGGL((rfast_team_kernel<kE, TILE, SYNC>), dim3((unsigned)(c->d.n * a.W)), dim3(kThreads), team_lds(c->d, a.C, a.B, TILE ? a.buffers : 0),
+                     c->stream, c->d, a);
+  return hipGetLastError();
+}
+
+template <bool SYNC>
+hipError_t launch_team(rfast_ctx* c, const TeamArgs& a) {
+  const RfastTeam& t = c->team;
+  if (t.tiles > 0) {
+    switch (t.per_lane) {
+      case 1: return launch_team<1, true, SYNC>(c, a);
+      case 2: return launch_team<2, true, SYNC>(c, a);
+      case 4: return launch_team<4, true, SYNC>(c, a);
+      default: return launch_team<8, true, SYNC>(c, a);
+    }
+  }
+  switch (t.per_lane) {
+    case 1: return launch_team<1, false, SYNC>(c, a);
+    case 2: return launch_team<2, false, SYNC>(c, a);
+    case 4: return launch_team<4, false, SYNC>(c, a);
+    default: return launch_team<8, false, SYNC>(c, a);
+  }
+}
+
+int rows_per_gradient(const rfast_problem* prob) { return prob->batch > 0 ? prob->batch : prob->samples; }
+
+}  // namespace
+
+// The team of a problem: workgroups per node, and their chunk of the coordinates.  `compute_units` workgroups can be
+// resident at once, one each.  More workgroups mean fewer rows' bytes for each and one more trip through memory for the
+// dot products; the estimate is that of a round in which every node is active.
+RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree_r, int compute_units) {
+  RfastTeam best;
+  if ((d.prob.kind != RFAST_OBJ_LEAST_SQUARES && d.prob.kind != RFAST_OBJ_LOGISTIC) || d.p < 4 || d.p > (1 << 22)) return best;
+  if (max_degree > 64 || max_out_degree_r > 64 || d.n > compute_units || d.M > 254) return best;  // one edge per lane
+  const int B = rows_per_gradient(&d.prob), p = (int)d.p;
+  double best_us = 1e30;
+  for (int W = 1; W <= compute_units / d.n && W <= 32; ++W) {
+    const int C = W == 1 ? p : ((p + W - 1) / W + 255) / 256 * 256;
+    if ((p + C - 1) / C != W || C > 8 * kOwn) continue;
+    const int64_t quads = (int64_t)B * ((C + 3) / 4);
+    const bool fits = d.prob.batch == 0 || B <= kTileRows;
+    const int tiles = !fits || team_lds(d, C, B, 1) > kLds ? 0 : d.prob.batch > 0 && team_lds(d, C, B, 2) <= kLds ? 2 : 1;
+    if (!tiles && (quads * 16 > 512 * 1024 || team_lds(d, C, B, 0) > kLds)) continue;
+    const double kb = quads * 16 / 1024.0;
+    double us = 3.0 + (W > 1 ? 1.0 + 0.05 * W : 0.0) + 0.15 * C / kOwn;
+    if (!tiles) us += kb / 20.0;  // read twice, through the L2
+    else us += kb / 120.0 + (d.prob.batch > 0 && tiles == 1 && kb > 64 ? (kb - 64) / 40.0 : 0.0);  // the next rows arrive beside the update
+    if (us < best_us) {
+      best_us = us;
+      best.W = W;
+      best.C = C;
+      best.tiles = tiles;
+      const int per = (C + kOwn - 1) / kOwn;
+      best.per_lane = per <= 1 ? 1 : per <= 2 ? 2 : per <= 4 ? 4 : 8;
+    }
+  }
+  return best;
+}
+
+size_t rfast_team_packet_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob) {
+  return t.W > 0 ? (size_t)2 * n * t.W * rows_per_gradient(prob) * sizeof(u64) : 0;
+}
+size_t rfast_team_flag_bytes(const RfastTeam& t, int32_t n) { return (size_t)n * t.W * kOwnWaves * kFlagWords * 4; }
+
+// rounds: at most kBlockRounds with sync = false (their plan records are in c->d.blk_plan)
+hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int round0, const int32_t* d_batch_idx,
+                             const int32_t* d_delay_R, const int32_t* d_delay_C) {
+  const RfastTeam& t = c->team;
+  if (t.W <= 0 || rounds < 1 || (!sync && (rounds > kBlockRounds || !c->d.blk_plan))) return hipErrorInvalidValue;
+  TeamArgs a;
+  a.rounds = rounds;
+  a.W = t.W;
+  a.C = t.C;
+  a.B = rows_per_gradient(&c->d.prob);
+  a.buffers = t.tiles;
+  a.gamma = gamma;
+  a.base = c->team_base;
+  a.round0 = round0;
+  a.batch_idx = c->d.prob.batch > 0 ? d_batch_idx : nullptr;
+  a.delay_R = d_delay_R;
+  a.delay_C = d_delay_C;
+  a.packets = (u64*)c->team_packets;
+  a.flags = c->team_flags;
+  c->team_base += (unsigned)rounds + 1;
+  return sync ? launch_team<true>(c, a) : launch_team<false>(c, a);
+}

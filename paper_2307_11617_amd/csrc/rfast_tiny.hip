@@ -22,7 +22,7 @@
 // numbers of the round after next, which travel in registers for a whole round before they are parked).
 //
 // The arithmetic is, operation for operation and in the same order, that of rfast_state_kernel<MIX>,
-// rfast_rows_kernel, rfast_cols_kernel<4> and rfast_state_kernel<TRACK>: the two paths give the same
+// rfast_rows_kernel, rfast_cols_kernel and rfast_state_kernel<TRACK>: the two paths give the same
 // bits.  The rows kernel has lane c of a wavefront sum the products of coordinates 4c .. 4c+3 (+ 256 m)
 // and adds the 64 lanes' sums as a butterfly from distance 32 down to 1; here lane j of a quad holds
 // the sixteen sums c = j, j+4, ..., adds them in that butterfly's order (distances 32 .. 4 stay inside
@@ -420,7 +420,7 @@ __global__ void __launch_bounds__(RES ? kTinyResThreads : kTinyThreads)
     }
     __syncthreads();
 
-    // ---- gradient, columns (as rfast_cols_kernel<4>): lane j of a quad sums rows j, j + 4, ... for the quad's four
+    // ---- gradient, columns (as rfast_cols_kernel): lane j of a quad sums rows j, j + 4, ... for the quad's four
     // coordinates; every lane then adds the four sums of its own coordinate in order;
     // then S2b, S2c, S3 (rho half), S4 (as rfast_state_kernel<TRACK>)
     // the resolver goes on to the round after next while the others finish this one

@@ -9,12 +9,22 @@
 // loads and stores, used when the state is far larger than the caches, so
 // that lines with no reuse do not displace anything.  VEC = 1: scalar, p % 4 != 0.
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
+typedef float u_f4 __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC> struct V;
 template <> struct V<4> {
   using T = float4;
   static constexpr int W = 4;
   static __device__ inline T ld(const float* p) { return *reinterpret_cast<const float4*>(p); }
   static __device__ inline void st(float* p, T v) { *reinterpret_cast<float4*>(p) = v; }
+  // the same at any float's address (the memory system takes 16-byte accesses at 4-byte addresses)
+  static __device__ inline T ldu(const float* p) {
+    const u_f4 t = *reinterpret_cast<const u_f4*>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+  }
+  static __device__ inline void stu(float* p, T v) {
+    const u_f4 t = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<u_f4*>(p) = t;
+  }
 };
 template <> struct V<-4> {
   using T = float4;

@@ -1,0 +1,114 @@
+"""Least squares and logistic regression with a team of workgroups per node (several rounds per launch): the same bits
+as one chain of kernels per round, at the edges of its chunks, tiles and batches, in every way rounds are asked for."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2307_11617_amd import rfast_set_rebase_interval, rfast_use_blocks
+from rfast_workloads import configs, graphs, problems
+
+import harness
+
+pytestmark = pytest.mark.gpu
+FIELDS = ("X", "Z", "G", "V_RING", "SIGMA_RING", "RHO_TILDE", "T_NODE", "TAU_R", "TAU_C", "SLOT_R", "SLOT_C", "ROUND",
+          "DELIV_R", "DELIV_C", "T_HIST")
+
+# graph, n, p, samples, batch (0: all), objective, momentum
+CASES = {
+    "chunk_of_one_row_piece": ("exponential", 16, 1001, 96, 0, "least_squares", 0.0),
+    "several_chunks_ragged": ("exponential", 32, 4099, 64, 22, "logistic", 0.0),
+    "several_chunks_aligned": ("exponential", 32, 4096, 96, 64, "logistic", 0.9),
+    "two_tiles_in_turn": ("binary_tree", 31, 784, 80, 32, "logistic", 0.0),
+    "rows_from_memory": ("directed_ring", 40, 1030, 310, 300, "logistic", 0.0),
+    "rows_from_memory_full_batch": ("mesh", 9, 2050, 261, 0, "least_squares", 0.0),
+    "eight_coordinates_per_lane": ("directed_ring", 130, 1795, 40, 7, "least_squares", 0.9),
+    "many_in_edges": ("tree_star", 40, 300, 30, 5, "logistic", 0.0),
+    "fewer_coordinates_than_a_quad_pair": ("bidirectional_ring", 50, 7, 20, 3, "least_squares", 0.0),
+}
+BUILD = {"exponential": graphs.exponential, "binary_tree": graphs.binary_tree, "directed_ring": graphs.directed_ring,
+         "mesh": graphs.mesh, "tree_star": graphs.tree_pull_star_push, "bidirectional_ring": graphs.bidirectional_ring}
+
+
+def _workload(case):
+    graph, n, p, samples, batch, objective, _ = CASES[case]
+    r, c = BUILD[graph](n)
+    data = problems.least_squares(n, p, samples, 5) if objective == "least_squares" else problems.logistic(n, p, samples, 5)
+    gamma = (0.5 / p if objective == "least_squares" else 0.02) * (1.0 if graph in ("exponential", "mesh", "bidirectional_ring") else 0.1)
+    return configs._mk(case, n, p, r, c, 3, gamma, 0, objective, data, 0.6, 0.3, 5, batch=batch, samples=samples, burst=3)
+
+
+def _pair(case):
+    w = _workload(case)
+    a, b = harness.make_gpu(w), harness.make_gpu(w)
+    rfast_use_blocks(b.ctx, False)
+    x0 = (0.1 * np.random.default_rng(3).standard_normal((w.n, w.p))).astype(np.float32)
+    for g in (a, b):
+        rfast_set_rebase_interval(g.ctx, 31)
+        if CASES[case][6]:
+            g.set_optimizer(CASES[case][6], 0.01)
+        g.set_gamma_schedule(20, 0.8)
+        g.init(x0, w.sched.initial_batch())
+    return w, a, b, x0
+
+
+def _same(a, b, where, fields=FIELDS):
+    for f in fields:
+        assert np.array_equal(a.read(f), b.read(f)), (where, f)
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_rounds(case):
+    w, a, b, x0 = _pair(case)
+    st, dev = harness.upload_chunk(a, w, 0, 50)
+    names = ("active", "delay_R", "delay_C", "drop_R", "drop_C")
+    for lo, hi in ((0, 27), (27, 28), (28, 50)):
+        for g in (a, b):
+            bi = None if dev["batch_idx"] is None else dev["batch_idx"][lo:hi].contiguous()
+            if hi - lo == 1:
+                g.round(*[dev[k][lo].contiguous() for k in names], w.gamma, None if bi is None else bi[0].contiguous())
+            else:
+                g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in names], w.gamma, bi)
+            g.check()
+        _same(a, b, (case, hi))
+    p_act = torch.full((w.n,), 0.5, dtype=torch.float32)
+    for g in (a, b):
+        g.run_generated(33, 5, p_act.to(g.device), w.sched.d_max, 0.1, w.gamma)
+        g.run_events(40, 6, None, w.sched.d_max, 0.2, w.gamma)
+        g.check()
+    _same(a, b, (case, "generated and events"))
+    if CASES[case][6]:
+        _same(a, b, case, ("MOMENTUM",))
+    assert np.abs(a.read("X") - x0).max() > 1e-4 and np.isfinite(a.read("X")).all() and np.isfinite(a.read("Z")).all()
+
+
+@pytest.mark.parametrize("case", ["chunk_of_one_row_piece", "several_chunks_ragged", "several_chunks_aligned", "rows_from_memory",
+                                  "many_in_edges", "eight_coordinates_per_lane"])
+def test_synchronous_steps(case):
+    w, a, b, _ = _pair(case)
+    st, dev = harness.upload_chunk(a, w, 0, 45)
+    for lo, hi in ((0, 30), (30, 31), (31, 45)):
+        for g in (a, b):
+            g.sync_run(hi - lo, w.gamma, None if dev["batch_idx"] is None else dev["batch_idx"][lo:hi].contiguous())
+            g.check()
+        _same(a, b, (case, hi), ("X", "Z", "G", "T_NODE", "ROUND"))
+
+
+def test_two_streams():
+    """Contexts on two streams whose launches overlap: the workgroups of a team wait for each other, so the library
+    orders the launches of different streams."""
+    w = _workload("several_chunks_ragged")
+    st, dev = None, None
+    gpus, streams = [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for s in streams:
+        with torch.cuda.stream(s):
+            g = harness.make_gpu(w)
+            g.init(None, w.sched.initial_batch())
+            gpus.append(g)
+    st, dev = harness.upload_chunk(gpus[0], w, 0, 40)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for g in gpus:
+            g.run(40, *[dev[k] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma, dev["batch_idx"])
+    for g in gpus:
+        g.check()
+    _same(gpus[0], gpus[1], "streams")
