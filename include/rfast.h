@@ -230,7 +230,7 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
 
 /* on != 0 (the default): rfast_run and rfast_run_generated advance up to 512 rounds with one
  * launch where that is possible and pays -- the separable objective (diagonal quadratic, with or
- * without the optimizer variant), p a multiple of 4, at most 64 nodes, no node with more than 6
+ * without the optimizer variant), at most 64 nodes, no node with more than 6
  * (33 to 64 nodes: 4) in-edges of R, in-edges of C or out-edges of C, a tile of coordinates of every node's two rings
  * fitting into the 160 KB of LDS of a CU (up to 32 nodes: 64 / n lanes of one wavefront per node, 4
  * coordinates per lane, n * (D+2) * (64 / n) * 32 B; beyond: at least 16 lanes of one workgroup per
@@ -261,8 +261,8 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * on == 0: always one kernel pass per round (four kernels for these objectives).  on == 2: as the default, but
  * 2 rounds are enough at any size (for measurements). */
 int rfast_use_blocks(rfast_ctx* ctx, int32_t on);
-/* *lanes_per_node = 0 if a call of rfast_run for several rounds would now run without tiles in LDS,
- * else the number of lanes per node of the multi-round kernel (its tile is 4 * lanes coordinates;
+/* *lanes_per_node = 0 if a call of rfast_run for several rounds would now run without tiles in LDS, or
+ * with tiles that start at any float's address (p no multiple of 4), else the number of lanes per node of the multi-round kernel (its tile is 4 * lanes coordinates;
  * 1024 / n, at least 1, for the single workgroup of the non-separable objectives);
  * *tile_per_wavefront (may be NULL) = 1 if a tile belongs to one wavefront, 0 if to a workgroup. */
 int rfast_block_info(rfast_ctx* ctx, int32_t* lanes_per_node, int32_t* tile_per_wavefront);
@@ -281,7 +281,7 @@ int rfast_set_tile_group(rfast_ctx* ctx, int32_t wavefronts);
  * rfast_round on the same context without an rfast_init in between.
  * d_batch_idx: device int32 [n][batch] (objectives with batch > 0), else NULL.
  * rfast_sync_run: `rounds` steps from sample rows stacked [rounds][n][batch].  Where rfast_use_blocks
- * allows it (separable objective, p a multiple of 4, at most 32 nodes with at most 6 edges of a kind)
+ * allows it (separable objective, at most 32 nodes with at most 6 edges of a kind)
  * the steps between two decay steps of the step-size schedule are taken by one launch that keeps
  * x, z and the samples in registers and exchanges x - gamma z and z through LDS: same bits. */
 int rfast_sync_round(rfast_ctx* ctx, float gamma, const int32_t* d_batch_idx);

@@ -816,7 +816,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
 
 int rfast_block_info(rfast_ctx* c, int32_t* lanes_per_node, int32_t* tile_per_wavefront) {
   if (!c || !lanes_per_node) return RFAST_EINVAL;
-  const bool taken = block_length(c, kBlockRounds) > 0 && (rfast_tiny_eligible(c) || c->team.W <= 0), wave = rfast_wave_eligible(c);
+  const bool taken = block_length(c, kBlockRounds) > 0 && c->d.p % 4 == 0 && (rfast_tiny_eligible(c) || c->team.W <= 0), wave = rfast_wave_eligible(c);
   if (taken && rfast_tiny_eligible(c)) {  // one workgroup holds the whole problem
     *lanes_per_node = 1024 / c->d.n > 0 ? 1024 / c->d.n : 1;
     if (tile_per_wavefront) *tile_per_wavefront = 0;

@@ -38,7 +38,7 @@ constexpr int kPlanPerLane = 10;
 // spills some 55 to scratch.  The alternative without spills, 8 lanes per node in workgroups of 512 with 186
 // registers, was measured and is slower, because it halves the wavefronts per CU: 0.201 against 0.192 ms per
 // round on a 6 x 6 mesh at p = 1 M, 0.149 against 0.088 ms on a ring of 36 nodes.
-template <int kLanes, int TPB, int kDeg>
+template <int kLanes, int TPB, int kDeg, bool ANY>
 __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock blk) {
   constexpr int VEC = 4;
   constexpr int kRingBatch = TPB > 512 ? 4 : 8;  // ring slots (of both rings) in flight while the tile is moved
@@ -52,6 +52,7 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
   const int i = threadIdx.x / kLanes, ln = threadIdx.x % kLanes;
   const int64_t k = (int64_t)blockIdx.x * (4 * kLanes) + ln * 4;
   const bool mine = i < n && k < p;
+  const int left = p - k < 4 ? (int)(p - k) : 4;  // ANY: coordinates of the row from the lane's first one on
   // The S4 buffers stay in global memory: they are touched only when a version leaves a ring before
   // its receiver has consumed a newer one (a store by one lane; a load by another lane of this
   // workgroup in a later round, with the barrier of every round in between).
@@ -79,11 +80,11 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
   unsigned put_v = 0, put_s = 0;        // one bit per slot of the node's rings: the slot is stored when the launch ends
   if (mine) {
     const size_t off = (size_t)i * p + k;
-    x = V<VEC>::ld(s.x + off);
-    z = V<VEC>::ld(s.z + off);
-    h = V<VEC>::ld((const float*)s.prob.data0 + off);
-    c = V<VEC>::ld((const float*)s.prob.data1 + off);
-    if (momentum) m = V<VEC>::ld(s.mom + off);
+    x = ld_group<ANY>(s.x + off, left);
+    z = ld_group<ANY>(s.z + off, left);
+    h = ld_group<ANY>((const float*)s.prob.data0 + off, left);
+    c = ld_group<ANY>((const float*)s.prob.data1 + off, left);
+    if (momentum) m = ld_group<ANY>(s.mom + off, left);
     re0 = s.r_ptr[i]; dR = s.r_ptr[i + 1] - re0;
     ce0 = s.c_ptr[i]; dI = s.c_ptr[i + 1] - ce0;
     o0 = s.co_ptr[i]; dO = s.co_ptr[i + 1] - o0;
@@ -120,8 +121,8 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
 #pragma unroll
       for (int u = 0; u < kRingBatch; ++u) {
         tv[u] = ts[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (get_v & (1u << u)) tv[u] = V<VEC>::ld(vg + (size_t)(m0 + u) * p);
-        if (get_s & (1u << u)) ts[u] = V<VEC>::ld(sgg + (size_t)(m0 + u) * p);
+        if (get_v & (1u << u)) tv[u] = ld_group<ANY>(vg + (size_t)(m0 + u) * p, left);
+        if (get_s & (1u << u)) ts[u] = ld_group<ANY>(sgg + (size_t)(m0 + u) * p, left);
       }
 #pragma unroll
       for (int u = 0; u < kRingBatch; ++u)
@@ -188,7 +189,7 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
       }
 #pragma unroll
       for (int u = 0; u < kDeg; ++u)  // rare: the version consumed last time has left the sender's ring
-        if ((c_pl[u] & (1 << 16)) && ((c_pl[u] >> 8) & 0xFF) == 0xFF) last[u] = V<VEC>::ld(rt_g + (size_t)(ce0 + u) * p);
+        if ((c_pl[u] & (1 << 16)) && ((c_pl[u] >> 8) & 0xFF) == 0xFF) last[u] = ld_group<ANY>(rt_g + (size_t)(ce0 + u) * p, left);
       const float4 sig_cur = sg_l[own + slot_cur * kLanes];
       const float4 sig_leaving = sg_l[own + leaving * kLanes];
       // S1: local descent; with the optimizer variant along the heavy-ball buffer m <- beta m + z
@@ -206,7 +207,7 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
       for (int u = 0; u < kDeg; ++u)
         if (c_pl[u] & (1 << 16)) {
           z_half = track_edge(z_half, c_w[u], cur[u], last[u], ((c_pl[u] >> 8) & 0xFF) != 0xFF);
-          if (c_pl[u] & (1 << 17)) V<VEC>::st(rt_g + (size_t)(ce0 + u) * p, mul_s(c_w[u], cur[u]));
+          if (c_pl[u] & (1 << 17)) st_group<ANY>(rt_g + (size_t)(ce0 + u) * p, left, mul_s(c_w[u], cur[u]));
         }
       z_half = sub(add(z_half, g_new), g);
       // S3: publish version t+1 (slots nobody reads in this round); S2c: keep a_ii, push
@@ -217,7 +218,7 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
         // slots ahead of the current one
 #pragma unroll
         for (int u = 0; u < kDeg; ++u)
-          if (o_pl[u] & (1 << 18)) V<VEC>::st(rt_g + (size_t)o_eid[u] * p, mul_s(o_w[u], sig_leaving));
+          if (o_pl[u] & (1 << 18)) st_group<ANY>(rt_g + (size_t)o_eid[u] * p, left, mul_s(o_w[u], sig_leaving));
       }
       x = x_new;
       z = mul_s(c_self, z_half);
@@ -237,9 +238,9 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
 
   if (mine) {
     const size_t off = (size_t)i * p + k;
-    V<VEC>::st(s.x + off, x);
-    V<VEC>::st(s.z + off, z);
-    if (momentum) V<VEC>::st(s.mom + off, m);
+    st_group<ANY>(s.x + off, left, x);
+    st_group<ANY>(s.z + off, left, z);
+    if (momentum) st_group<ANY>(s.mom + off, left, m);
     float* vg = s.v_ring + (size_t)i * M * p + k;
     float* sgg = s.sigma_ring + (size_t)i * M * p + k;
     for (int m0 = 0; m0 < M; m0 += kRingBatch) {
@@ -252,8 +253,8 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
       }
 #pragma unroll
       for (int u = 0; u < kRingBatch; ++u) {
-        if (back_v & (1u << u)) V<VEC>::st(vg + (size_t)(m0 + u) * p, tv[u]);
-        if (back_s & (1u << u)) V<VEC>::st(sgg + (size_t)(m0 + u) * p, ts[u]);
+        if (back_v & (1u << u)) st_group<ANY>(vg + (size_t)(m0 + u) * p, left, tv[u]);
+        if (back_s & (1u << u)) st_group<ANY>(sgg + (size_t)(m0 + u) * p, left, ts[u]);
       }
     }
   }
@@ -286,26 +287,31 @@ int block_lanes(const RfastDev& d) {
 // separable objective (the heavy-ball buffer of the optimizer variant is one more register set).
 bool rfast_block_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && (d.p % 4) == 0 && c->max_degree <= kMaxDeg && d.M <= 32 &&
+  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kMaxDeg && d.M <= 32 &&
          block_lanes(d) != 0;  // (rings of at most 32 slots: one bit per slot in the records of the resolver)
 }
 
 int rfast_block_lanes(const rfast_ctx* c) { return block_lanes(c->d); }
 
-template <int kLanes, int TPB, int kDeg>
-static hipError_t launch_block(rfast_ctx* c, const RfastBlock& blk, unsigned threads) {
+template <int kLanes, int TPB, int kDeg, bool ANY>
+static hipError_t launch_block_any(rfast_ctx* c, const RfastBlock& blk, unsigned threads) {
   static bool raised = false;
   if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    const hipError_t e = hipFuncSetAttribute((const void*)rfast_block_kernel<kLanes, TPB, kDeg>,
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_block_kernel<kLanes, TPB, kDeg, ANY>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
   }
   const int64_t tiles = (c->d.p + 4 * kLanes - 1) / (4 * kLanes);
   if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rfast_block_kernel<kLanes, TPB, kDeg>), dim3((unsigned)tiles), dim3(threads), block_lds_bytes(c->d, kLanes),
+  hipLaunchKernelGGL((rfast_block_kernel<kLanes, TPB, kDeg, ANY>), dim3((unsigned)tiles), dim3(threads), block_lds_bytes(c->d, kLanes),
                      c->stream, c->d, blk);
   return hipGetLastError();
+}
+
+template <int kLanes, int TPB, int kDeg>
+static hipError_t launch_block(rfast_ctx* c, const RfastBlock& blk, unsigned threads) {
+  return c->d.p % 4 == 0 ? launch_block_any<kLanes, TPB, kDeg, false>(c, blk, threads) : launch_block_any<kLanes, TPB, kDeg, true>(c, blk, threads);
 }
 
 template <int kLanes>

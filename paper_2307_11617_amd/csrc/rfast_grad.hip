@@ -26,22 +26,8 @@ __device__ inline float wave_sum(float v) {
 }
 
 // coordinates k .. k+3 of a vector that ends at `end`, zeros past it (at any float's address)
-__device__ inline float4 ld_quad(const float* v, int64_t k, int64_t end) {
-  if (k + 4 <= end) return V<4>::ldu(v + k);
-  float4 t = make_float4(v[k], 0.f, 0.f, 0.f);
-  if (k + 1 < end) t.y = v[k + 1];
-  if (k + 2 < end) t.z = v[k + 2];
-  return t;
-}
-__device__ inline void st_quad(float* v, int64_t k, int64_t end, float4 t) {
-  if (k + 4 <= end) {
-    V<4>::stu(v + k, t);
-    return;
-  }
-  v[k] = t.x;
-  if (k + 1 < end) v[k + 1] = t.y;
-  if (k + 2 < end) v[k + 2] = t.z;
-}
+__device__ inline float4 ld_quad(const float* v, int64_t k, int64_t end) { return ld_group<true>(v + k, (int)(end - k < 4 ? end - k : 4)); }
+__device__ inline void st_quad(float* v, int64_t k, int64_t end, float4 t) { st_group<true>(v + k, (int)(end - k < 4 ? end - k : 4), t); }
 
 // a sampled row number as read from the caller's array: clamped into the node's samples, and reported, if outside
 __device__ inline int checked_row(const RfastDev& s, int i, int row) {

@@ -23,12 +23,16 @@ namespace {
 constexpr int kThreads = 256;
 
 // ------------------------------------------------------------------- kernel
+// A value that is the same in all lanes, as the compiler should know (it takes what is read after a store through a
+// vector load, and would form every address and branch per lane).
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Loads of one live in-edge of C (plan word pl): the running sum being consumed and the one
 // consumed last time (rho~ of S4), which is read from the sender's ring while it is still there.
 template <int VEC>
-__device__ inline void load_edge(const RfastDev& s, int e, int pl, int M, int64_t p, int64_t k, typename V<VEC>::T* sg,
+__device__ inline void load_edge(const RfastDev& s, int e, int src, int pl, int M, int64_t p, int64_t k, typename V<VEC>::T* sg,
                                  typename V<VEC>::T* rt) {
-  const float* ring = s.sigma_ring + (size_t)s.c_src[e] * M * p + k;
+  const float* ring = s.sigma_ring + (size_t)src * M * p + k;
   const int prev = (pl >> 8) & 0xFF;
   const float* last = prev != 0xFF ? ring + (size_t)prev * p : s.rho_tilde + (size_t)e * p + k;
   *sg = V<VEC>::ld(ring + (size_t)(pl & 0xFF) * p);
@@ -61,15 +65,8 @@ __device__ inline void emit_bf16_blocked(const RfastDev& s, int i, int tile, typ
 // 91 (5 wavefronts): graphs with many in-edges per node want the deeper batch, graphs with few want
 // the wavefronts (measured: bidirectional ring 1.53 vs 1.59 ms with 8 vs 4, tree/star 0.293 vs 0.274).
 template <int MODE, int VEC, bool MOM, int KB>
-__global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float gamma, int tiles_per_node) {
+__device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, int tile, int64_t k) {
   using T = typename V<VEC>::T;
-  const int a = blockIdx.x / tiles_per_node;
-  const int2 slot = s.active_plan[a];  // {node, its counter at the start of the round}, node < 0: no work
-  if (slot.x < 0) return;
-  const int tile = blockIdx.x - a * tiles_per_node;
-  const int64_t k = ((int64_t)tile * kThreads + threadIdx.x) * V<VEC>::W;
-  if (k >= s.p) return;
-
   constexpr bool kMix = MODE != RFAST_MODE_TRACK, kTrack = MODE != RFAST_MODE_MIX;
   const int i = slot.x;
   const int64_t p = s.p;
@@ -118,7 +115,7 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
       const int e = ce0 + q;
       pl[q] = e < ce1 ? s.plan_c[e] : 0;
       if (pl[q] & (1 << 16)) {
-        load_edge<VEC>(s, e, pl[q], M, p, k, &sg[q], &rt[q]);
+        load_edge<VEC>(s, e, s.c_src[e], pl[q], M, p, k, &sg[q], &rt[q]);
         ca[q] = s.c_w[e];
       }
     }
@@ -138,22 +135,36 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
 #pragma unroll
     for (int q = 0; q < KB; ++q)
       if (re0 + q < re1) x_new = fma_s(vw[q], vb[q], x_new);
-    for (int eb = re0 + KB; eb < re1; eb += KB) {  // in-degree above one batch
+    if (re0 + KB < re1) {  // in-degree above one batch: what the loads of a batch need is read during the batch before
+      int src[KB], at[KB];
+      auto look = [&](int eb) {  // (past the last edge: the last one, which is not used)
 #pragma unroll
-      for (int q = 0; q < KB; ++q)
-        if (eb + q < re1) {
-          vb[q] = V<VEC>::ld(s.v_ring + ((size_t)s.r_src[eb + q] * M + s.slot_r[eb + q]) * p + k);
-          vw[q] = s.r_w[eb + q];
+        for (int q = 0; q < KB; ++q) {
+          const int e = eb + q < re1 ? eb + q : re1 - 1;
+          src[q] = s.r_src[e];
+          at[q] = s.slot_r[e];
+          vw[q] = s.r_w[e];
         }
+      };
+      look(re0 + KB);
+      for (int eb = re0 + KB; eb < re1; eb += KB) {
+        float w_now[KB];
 #pragma unroll
-      for (int q = 0; q < KB; ++q)
-        if (eb + q < re1) x_new = fma_s(vw[q], vb[q], x_new);
+        for (int q = 0; q < KB; ++q) {
+          if (eb + q < re1) vb[q] = V<VEC>::ld(s.v_ring + ((size_t)uniform(src[q]) * M + uniform(at[q])) * p + k);
+          w_now[q] = vw[q];
+        }
+        look(eb + KB);
+#pragma unroll
+        for (int q = 0; q < KB; ++q)
+          if (eb + q < re1) x_new = fma_s(w_now[q], vb[q], x_new);
+      }
     }
     // S3 (v half): publish version t+1
     V<VEC>::st(s.v_ring + ((size_t)i * M + slot_new) * p + k, v);
     V<VEC>::st(s.x + node_off, x_new);
     if (MODE == RFAST_MODE_MIX) {
-      if constexpr (VEC != 1) {  // p is a multiple of 2048 for this objective: every tile is full
+      if constexpr (VEC == 4 || VEC == -4) {  // p is a multiple of 2048 for this objective: every tile is full
         if (s.prob.kind == RFAST_OBJ_SOFTMAX_BF16 && (1024 % s.prob.K) == 0) emit_bf16_blocked<VEC>(s, i, tile, x_new);
       }
       return;
@@ -176,22 +187,35 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
       z_half = track_edge(z_half, ca[q], sg[q], rt[q], ((pl[q] >> 8) & 0xFF) != 0xFF);
       if (pl[q] & (1 << 17)) V<VEC>::st(s.rho_tilde + (size_t)(ce0 + q) * p + k, mul_s(ca[q], sg[q]));
     }
-  for (int eb = ce0 + KB; eb < ce1; eb += KB) {  // in-degree above one batch
+  if (ce0 + KB < ce1) {  // in-degree above one batch, in the same way
+    int src[KB];
+    auto look = [&](int eb) {
 #pragma unroll
-    for (int q = 0; q < KB; ++q) {
-      const int e = eb + q;
-      pl[q] = e < ce1 ? s.plan_c[e] : 0;
-      if (pl[q] & (1 << 16)) {
-        load_edge<VEC>(s, e, pl[q], M, p, k, &sg[q], &rt[q]);
+      for (int q = 0; q < KB; ++q) {
+        const int e = eb + q < ce1 ? eb + q : ce1 - 1;
+        src[q] = s.c_src[e];
+        pl[q] = eb + q < ce1 ? s.plan_c[e] : 0;
         ca[q] = s.c_w[e];
       }
-    }
+    };
+    look(ce0 + KB);
+    for (int eb = ce0 + KB; eb < ce1; eb += KB) {
+      int now[KB];
+      float a_now[KB];
 #pragma unroll
-    for (int q = 0; q < KB; ++q)
-      if (pl[q] & (1 << 16)) {
-        z_half = track_edge(z_half, ca[q], sg[q], rt[q], ((pl[q] >> 8) & 0xFF) != 0xFF);
-        if (pl[q] & (1 << 17)) V<VEC>::st(s.rho_tilde + (size_t)(eb + q) * p + k, mul_s(ca[q], sg[q]));
+      for (int q = 0; q < KB; ++q) {
+        now[q] = uniform(pl[q]);
+        a_now[q] = ca[q];
+        if (now[q] & (1 << 16)) load_edge<VEC>(s, eb + q, uniform(src[q]), now[q], M, p, k, &sg[q], &rt[q]);
       }
+      look(eb + KB);
+#pragma unroll
+      for (int q = 0; q < KB; ++q)
+        if (now[q] & (1 << 16)) {
+          z_half = track_edge(z_half, a_now[q], sg[q], rt[q], ((now[q] >> 8) & 0xFF) != 0xFF);
+          if (now[q] & (1 << 17)) V<VEC>::st(s.rho_tilde + (size_t)(eb + q) * p + k, mul_s(a_now[q], sg[q]));
+        }
+    }
   }
   z_half = sub(add(z_half, g_new), g_old);
 
@@ -210,20 +234,29 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
   }
 }
 
+template <int MODE, int VEC, bool MOM, int KB>
+__global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float gamma, int tiles_per_node) {
+  const int a = blockIdx.x / tiles_per_node;
+  const int2 slot = s.active_plan[a];  // {node, its counter at the start of the round}, node < 0: no work
+  if (slot.x < 0) return;
+  const int tile = blockIdx.x - a * tiles_per_node;
+  each_group<VEC>(tile, s.p, [&](auto vec, int64_t k) { state_update<MODE, decltype(vec)::value, MOM, KB>(s, gamma, slot, tile, k); });
+}
+
 // Writes the current sample of every node, g_i = sample(x_i, t_i), into g[t_i & 1][i]: the
 // initial gradient g^0 (t = 0, initialisation of Algorithm 1) and the copy that reads of
 // the G field return.
 template <int VEC>
 __global__ void __launch_bounds__(kThreads) rfast_diag_sample_kernel(RfastDev s) {
   const int i = blockIdx.y;
-  const int64_t k = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC;
-  if (k >= s.p) return;
-  const size_t off = (size_t)i * s.p + k;
-  using T = typename V<VEC>::T;
   const int t = s.t[i];
-  const T h = V<VEC>::ld((const float*)s.prob.data0 + off);
-  const T c = V<VEC>::ld((const float*)s.prob.data1 + off);
-  V<VEC>::st(s.g + (size_t)(t & 1) * s.n * s.p + off, diag_sample<VEC>(s, h, c, V<VEC>::ld(s.x + off), i, t, k));
+  each_group<VEC>(blockIdx.x, s.p, [&](auto vec, int64_t k) {
+    using Vk = V<decltype(vec)::value>;
+    const size_t off = (size_t)i * s.p + k;
+    const auto h = Vk::ld((const float*)s.prob.data0 + off);
+    const auto c = Vk::ld((const float*)s.prob.data1 + off);
+    Vk::st(s.g + (size_t)(t & 1) * s.n * s.p + off, diag_sample<decltype(vec)::value>(s, h, c, Vk::ld(s.x + off), i, t, k));
+  });
 }
 
 // Rebase of the running sums.  sigma_j only ever enters as a_ij*sigma_j - rho~_ij, so
@@ -232,19 +265,20 @@ __global__ void __launch_bounds__(kThreads) rfast_diag_sample_kernel(RfastDev s)
 // removes the ever-growing common offset that the difference otherwise has to cancel.
 template <int VEC>
 __global__ void __launch_bounds__(kThreads) rfast_rebase_kernel(RfastDev s) {
-  using T = typename V<VEC>::T;
   const int j = blockIdx.y;
-  const int64_t k = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * V<VEC>::W;
-  if (k >= s.p) return;
   const int o0 = s.co_ptr[j], o1 = s.co_ptr[j + 1];
   if (o0 == o1) return;  // nobody reads this sender's sums
-  float* ring = s.sigma_ring + (size_t)j * s.M * s.p + k;
-  const T c = V<VEC>::ld(ring + (size_t)(s.t[j] % s.M) * s.p);
-  for (int m = 0; m < s.M; ++m) V<VEC>::st(ring + (size_t)m * s.p, sub(V<VEC>::ld(ring + (size_t)m * s.p), c));
-  for (int o = o0; o < o1; ++o) {
-    float* rt = s.rho_tilde + (size_t)s.co_eid[o] * s.p + k;
-    V<VEC>::st(rt, sub(V<VEC>::ld(rt), mul_s(s.co_w[o], c)));
-  }
+  const int slot = s.t[j] % s.M;
+  each_group<VEC>(blockIdx.x, s.p, [&](auto vec, int64_t k) {
+    using Vk = V<decltype(vec)::value>;
+    float* ring = s.sigma_ring + (size_t)j * s.M * s.p + k;
+    const auto c = Vk::ld(ring + (size_t)slot * s.p);
+    for (int m = 0; m < s.M; ++m) Vk::st(ring + (size_t)m * s.p, sub(Vk::ld(ring + (size_t)m * s.p), c));
+    for (int o = o0; o < o1; ++o) {
+      float* rt = s.rho_tilde + (size_t)s.co_eid[o] * s.p + k;
+      Vk::st(rt, sub(Vk::ld(rt), mul_s(s.co_w[o], c)));
+    }
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -277,27 +311,56 @@ __global__ void __launch_bounds__(256) rfast_sync_plan_kernel(RfastDev s, int ro
 template <int VEC>
 __global__ void __launch_bounds__(kThreads) rfast_sync_descent_kernel(RfastDev s, float gamma, int parity) {
   const int i = blockIdx.y;
-  const int64_t k = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * V<VEC>::W;
-  if (k >= s.p) return;
-  const auto x = V<VEC>::ld(s.x + (size_t)i * s.p + k);
-  auto dir = V<VEC>::ld(sync_z(s, parity, i) + k);
-  if (s.mom) {
-    dir = fma_s(s.beta, V<VEC>::ld(s.mom + (size_t)i * s.p + k), dir);
-    V<VEC>::st(s.mom + (size_t)i * s.p + k, dir);
+  each_group<VEC>(blockIdx.x, s.p, [&](auto vec, int64_t k) {
+    using Vk = V<decltype(vec)::value>;
+    const auto x = Vk::ld(s.x + (size_t)i * s.p + k);
+    auto dir = Vk::ld(sync_z(s, parity, i) + k);
+    if (s.mom) {
+      dir = fma_s(s.beta, Vk::ld(s.mom + (size_t)i * s.p + k), dir);
+      Vk::st(s.mom + (size_t)i * s.p + k, dir);
+    }
+    Vk::st(s.v_ring + (size_t)i * s.M * s.p + k, fma_s(-gamma, dir, x));
+  });
+}
+
+// acc += sum of w_e row(src_e) over the edges e0 .. e1-1, in order: eight loads in flight, and what the next eight need
+// is read meanwhile (edge by edge, the root of a star of 44 nodes took 61 us a step).
+template <int VEC, class Row>
+__device__ inline void sum_edges(const int32_t* src, const float* w, int e0, int e1, Row row, typename V<VEC>::T* acc) {
+  constexpr int KB = 8;
+  typename V<VEC>::T vb[KB];
+  int from[KB];
+  float wt[KB];
+  if (e0 >= e1) return;
+  auto look = [&](int eb) {  // (past the last edge: the last one, which is not used)
+#pragma unroll
+    for (int q = 0; q < KB; ++q) {
+      const int e = eb + q < e1 ? eb + q : e1 - 1;
+      from[q] = src[e];
+      wt[q] = w[e];
+    }
+  };
+  look(e0);
+  for (int eb = e0; eb < e1; eb += KB) {
+    float w_now[KB];
+#pragma unroll
+    for (int q = 0; q < KB; ++q) {
+      if (eb + q < e1) vb[q] = V<VEC>::ld(row(uniform(from[q])));
+      w_now[q] = wt[q];
+    }
+    look(eb + KB);
+#pragma unroll
+    for (int q = 0; q < KB; ++q)
+      if (eb + q < e1) *acc = fma_s(w_now[q], vb[q], *acc);
   }
-  V<VEC>::st(s.v_ring + (size_t)i * s.M * s.p + k, fma_s(-gamma, dir, x));
 }
 
 // PHASE 0: mix only (x').  PHASE 1: tracker only (reads g' written by the gradient
 // kernels).  PHASE 2: mix + diagonal-quadratic gradient + tracker in one pass.
 template <int VEC, int PHASE>
-__global__ void __launch_bounds__(kThreads) rfast_sync_step_kernel(RfastDev s, int parity) {
+__device__ inline void sync_step(const RfastDev& s, int parity, int i, int t_old, int64_t k) {
   using T = typename V<VEC>::T;
-  const int i = blockIdx.y;
-  const int64_t k = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * V<VEC>::W;
-  if (k >= s.p) return;
   const int64_t p = s.p;
-  const int t_old = s.plan_t[i];
   const size_t off = (size_t)i * p + k;
   float* g_old_p = s.g + (size_t)(t_old & 1) * s.n * p + off;
   float* g_new_p = s.g + (size_t)((t_old + 1) & 1) * s.n * p + off;
@@ -305,8 +368,7 @@ __global__ void __launch_bounds__(kThreads) rfast_sync_step_kernel(RfastDev s, i
   if (PHASE != 1) {
     const T x_old = V<VEC>::ld(s.x + off);
     x_new = mul_s(s.r_self[i], V<VEC>::ld(s.v_ring + (size_t)i * s.M * p + k));
-    for (int e = s.r_ptr[i]; e < s.r_ptr[i + 1]; ++e)
-      x_new = fma_s(s.r_w[e], V<VEC>::ld(s.v_ring + (size_t)s.r_src[e] * s.M * p + k), x_new);
+    sum_edges<VEC>(s.r_src, s.r_w, s.r_ptr[i], s.r_ptr[i + 1], [&](int j) { return s.v_ring + (size_t)j * s.M * p + k; }, &x_new);
     V<VEC>::st(s.x + off, x_new);
     if (PHASE == 0) return;
     const T h = V<VEC>::ld((const float*)s.prob.data0 + off);
@@ -318,26 +380,31 @@ __global__ void __launch_bounds__(kThreads) rfast_sync_step_kernel(RfastDev s, i
     g_old = V<VEC>::ld(g_old_p);
   }
   T z_new = mul_s(s.c_self[i], V<VEC>::ld(sync_z(s, parity, i) + k));
-  for (int e = s.c_ptr[i]; e < s.c_ptr[i + 1]; ++e)
-    z_new = fma_s(s.c_w[e], V<VEC>::ld(sync_z(s, parity, s.c_src[e]) + k), z_new);
+  sum_edges<VEC>(s.c_src, s.c_w, s.c_ptr[i], s.c_ptr[i + 1], [&](int j) { return sync_z(s, parity, j) + k; }, &z_new);
   z_new = sub(add(z_new, g_new), g_old);
   V<VEC>::st(sync_z(s, parity ^ 1, i) + k, z_new);
+}
+
+template <int VEC, int PHASE>
+__global__ void __launch_bounds__(kThreads) rfast_sync_step_kernel(RfastDev s, int parity) {
+  const int i = blockIdx.y, t_old = s.plan_t[i];
+  each_group<VEC>(blockIdx.x, s.p, [&](auto vec, int64_t k) { sync_step<decltype(vec)::value, PHASE>(s, parity, i, t_old, k); });
 }
 
 template <int VEC>
 __global__ void __launch_bounds__(kThreads) rfast_sync_fold_kernel(RfastDev s) {
   const int i = blockIdx.y;
-  const int64_t k = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * V<VEC>::W;
-  if (k >= s.p) return;
-  V<VEC>::st(s.z + (size_t)i * s.p + k, V<VEC>::ld(sync_z(s, 1, i) + k));
+  each_group<VEC>(blockIdx.x, s.p, [&](auto vec, int64_t k) {
+    using Vk = V<decltype(vec)::value>;
+    Vk::st(s.z + (size_t)i * s.p + k, Vk::ld(sync_z(s, 1, i) + k));
+  });
 }
 
 template <int MODE, bool MOM, int KB>
 hipError_t launch(rfast_ctx* c, float gamma) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  const int64_t per_block = (int64_t)kThreads * (vec4 ? 4 : 1);
-  const int64_t tiles = (d.p + per_block - 1) / per_block;
+  const int64_t tiles = group_tiles(d.p);
   const int64_t blocks = tiles * d.n;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   // Stream past the caches once the state dwarfs them (256 MB of last-level cache).  Wavefronts per
@@ -348,8 +415,10 @@ hipError_t launch(rfast_ctx* c, float gamma) {
     hipLaunchKernelGGL((rfast_state_kernel<MODE, -4, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else if (vec4)
     hipLaunchKernelGGL((rfast_state_kernel<MODE, 4, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
+  else if (streaming)
+    hipLaunchKernelGGL((rfast_state_kernel<MODE, -5, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else
-    hipLaunchKernelGGL((rfast_state_kernel<MODE, 1, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
+    hipLaunchKernelGGL((rfast_state_kernel<MODE, 5, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   return hipGetLastError();
 }
 
@@ -358,12 +427,11 @@ hipError_t launch(rfast_ctx* c, float gamma) {
 hipError_t rfast_diag_init_gradient(rfast_ctx* c) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  const int64_t per_block = (int64_t)kThreads * (vec4 ? 4 : 1);
-  const unsigned gx = (unsigned)((d.p + per_block - 1) / per_block);
+  const unsigned gx = (unsigned)group_tiles(d.p);
   if (vec4)
     hipLaunchKernelGGL(rfast_diag_sample_kernel<4>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
   else
-    hipLaunchKernelGGL(rfast_diag_sample_kernel<1>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
+    hipLaunchKernelGGL(rfast_diag_sample_kernel<5>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
   return hipGetLastError();
 }
 
@@ -371,14 +439,13 @@ hipError_t rfast_diag_init_gradient(rfast_ctx* c) {
 hipError_t rfast_launch_sync(rfast_ctx* c, int phase, float gamma, int parity) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  const int64_t per_block = (int64_t)kThreads * (vec4 ? 4 : 1);
-  const dim3 grid((unsigned)((d.p + per_block - 1) / per_block), d.n), blk(kThreads);
+  const dim3 grid((unsigned)group_tiles(d.p), d.n), blk(kThreads);
   const bool streaming = vec4 && (double)d.n * (double)d.p * 4.0 >= 32.0e6;
   if (phase == 0 || phase == 2) {
     hipLaunchKernelGGL(rfast_sync_plan_kernel, dim3(1), dim3(256), 0, c->stream, d, 1);
     if (streaming) hipLaunchKernelGGL(rfast_sync_descent_kernel<-4>, grid, blk, 0, c->stream, d, gamma, parity);
     else if (vec4) hipLaunchKernelGGL(rfast_sync_descent_kernel<4>, grid, blk, 0, c->stream, d, gamma, parity);
-    else hipLaunchKernelGGL(rfast_sync_descent_kernel<1>, grid, blk, 0, c->stream, d, gamma, parity);
+    else hipLaunchKernelGGL(rfast_sync_descent_kernel<5>, grid, blk, 0, c->stream, d, gamma, parity);
   }
   if (streaming) {
     if (phase == 0) hipLaunchKernelGGL((rfast_sync_step_kernel<-4, 0>), grid, blk, 0, c->stream, d, parity);
@@ -391,10 +458,10 @@ hipError_t rfast_launch_sync(rfast_ctx* c, int phase, float gamma, int parity) {
     if (phase == 2) hipLaunchKernelGGL((rfast_sync_step_kernel<4, 2>), grid, blk, 0, c->stream, d, parity);
     if (phase == 3) hipLaunchKernelGGL(rfast_sync_fold_kernel<4>, grid, blk, 0, c->stream, d);
   } else {
-    if (phase == 0) hipLaunchKernelGGL((rfast_sync_step_kernel<1, 0>), grid, blk, 0, c->stream, d, parity);
-    if (phase == 1) hipLaunchKernelGGL((rfast_sync_step_kernel<1, 1>), grid, blk, 0, c->stream, d, parity);
-    if (phase == 2) hipLaunchKernelGGL((rfast_sync_step_kernel<1, 2>), grid, blk, 0, c->stream, d, parity);
-    if (phase == 3) hipLaunchKernelGGL(rfast_sync_fold_kernel<1>, grid, blk, 0, c->stream, d);
+    if (phase == 0) hipLaunchKernelGGL((rfast_sync_step_kernel<5, 0>), grid, blk, 0, c->stream, d, parity);
+    if (phase == 1) hipLaunchKernelGGL((rfast_sync_step_kernel<5, 1>), grid, blk, 0, c->stream, d, parity);
+    if (phase == 2) hipLaunchKernelGGL((rfast_sync_step_kernel<5, 2>), grid, blk, 0, c->stream, d, parity);
+    if (phase == 3) hipLaunchKernelGGL(rfast_sync_fold_kernel<5>, grid, blk, 0, c->stream, d);
   }
   return hipGetLastError();
 }
@@ -408,19 +475,19 @@ hipError_t rfast_launch_sync_plan(rfast_ctx* c, int rounds) {
 hipError_t rfast_launch_rebase(rfast_ctx* c) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  const int64_t per_block = (int64_t)kThreads * (vec4 ? 4 : 1);
-  const unsigned gx = (unsigned)((d.p + per_block - 1) / per_block);
+  const unsigned gx = (unsigned)group_tiles(d.p);
   if (vec4)
     hipLaunchKernelGGL(rfast_rebase_kernel<4>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
   else
-    hipLaunchKernelGGL(rfast_rebase_kernel<1>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
+    hipLaunchKernelGGL(rfast_rebase_kernel<5>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
   return hipGetLastError();
 }
 
 hipError_t rfast_launch_state(rfast_ctx* c, int mode, float gamma) {
   const bool mom = c->d.mom != nullptr;
-  // three or more in-edges per node on average (both graphs together): the deeper load batch
-  const bool deep = (int64_t)c->d.eR + c->d.eC >= 3 * (int64_t)c->d.n;
+  // three or more in-edges per node on average (both graphs together), or a state so small that wavefronts are few
+  // anyway and only the trips through memory count: the deeper load batch
+  const bool deep = (int64_t)c->d.eR + c->d.eC >= 3 * (int64_t)c->d.n || (double)c->d.n * (double)c->d.p < 4.0e6;
   switch (mode) {
     case RFAST_MODE_FUSED:
       if (deep) return mom ? launch<RFAST_MODE_FUSED, true, 8>(c, gamma) : launch<RFAST_MODE_FUSED, false, 8>(c, gamma);

@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const bool ragged = (Cw & 3) != 0;
   auto row_quad = [&](int row, int quad) {
     const int at = ragged && 4 * quad > Cw - 4 ? Cw - 4 : 4 * quad;
-    return V<4>::ldu(rows_g + (size_t)row * p + at);
+    return V<5>::ld(rows_g + (size_t)row * p + at);
   };
   auto whole_quad = [&](float4 v, int quad) {
     const int by = 4 * quad + 4 - Cw;  // coordinates the load started early

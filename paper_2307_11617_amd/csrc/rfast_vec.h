@@ -1,13 +1,18 @@
 // Vector access helpers and the counter-based Gaussian noise of the separable
 // objective, shared by the state-update and the diagnostics kernels (gfx950 only).
 #pragma once
+#include <type_traits>
+
 #include "rfast_internal.h"
 #include "rfast_philox.h"
 
 // ------------------------------------------------------------ vector helpers
 // VEC = 4: float4 per lane.  VEC = -4: the same with non-temporal (streaming)
 // loads and stores, used when the state is far larger than the caches, so
-// that lines with no reuse do not displace anything.  VEC = 1: scalar, p % 4 != 0.
+// that lines with no reuse do not displace anything.  VEC = 5, -5: the same at any float's address, for
+// p % 4 != 0, where the rows of a node-major array start anywhere (the memory system takes 16-byte
+// accesses at 4-byte addresses; a row then straddles one more cache line, and nothing else changes).
+// VEC = 1: scalar, the up to three coordinates at the end of such a row.
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 typedef float u_f4 __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC> struct V;
@@ -16,15 +21,6 @@ template <> struct V<4> {
   static constexpr int W = 4;
   static __device__ inline T ld(const float* p) { return *reinterpret_cast<const float4*>(p); }
   static __device__ inline void st(float* p, T v) { *reinterpret_cast<float4*>(p) = v; }
-  // the same at any float's address (the memory system takes 16-byte accesses at 4-byte addresses)
-  static __device__ inline T ldu(const float* p) {
-    const u_f4 t = *reinterpret_cast<const u_f4*>(p);
-    return make_float4(t.x, t.y, t.z, t.w);
-  }
-  static __device__ inline void stu(float* p, T v) {
-    const u_f4 t = {v.x, v.y, v.z, v.w};
-    *reinterpret_cast<u_f4*>(p) = t;
-  }
 };
 template <> struct V<-4> {
   using T = float4;
@@ -38,12 +34,79 @@ template <> struct V<-4> {
     __builtin_nontemporal_store(t, reinterpret_cast<nt_f4*>(p));
   }
 };
+template <> struct V<5> {
+  using T = float4;
+  static constexpr int W = 4;
+  static __device__ inline T ld(const float* p) {
+    const u_f4 t = *reinterpret_cast<const u_f4*>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+  }
+  static __device__ inline void st(float* p, T v) {
+    const u_f4 t = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<u_f4*>(p) = t;
+  }
+};
+template <> struct V<-5> {
+  using T = float4;
+  static constexpr int W = 4;
+  static __device__ inline T ld(const float* p) {
+    const u_f4 t = __builtin_nontemporal_load(reinterpret_cast<const u_f4*>(p));
+    return make_float4(t.x, t.y, t.z, t.w);
+  }
+  static __device__ inline void st(float* p, T v) {
+    const u_f4 t = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(t, reinterpret_cast<u_f4*>(p));
+  }
+};
 template <> struct V<1> {
   using T = float;
   static constexpr int W = 1;
   static __device__ inline T ld(const float* p) { return *p; }
   static __device__ inline void st(float* p, T v) { *p = v; }
 };
+// Runs f(vec, k) for the coordinates of one lane of tile `tile` (256 lanes): a group of four from coordinate k on
+// (vec = VEC), or, in one more tile that VEC = 5, -5 has for the ragged end of a row, a single coordinate (vec = 1).
+// (A tile of its own: lanes that went through the last coordinates one after the other would make the last wavefront of
+// every row three times as long.)
+__host__ __device__ inline int64_t group_tiles(int64_t p) { return (p / 4 + 255) / 256 + (p % 4 != 0 ? 1 : 0); }
+template <int VEC, class F> __device__ inline void each_group(int64_t tile, int64_t p, F f) {
+  if constexpr (VEC == 5 || VEC == -5) {
+    const int64_t full = p / 4;
+    if (tile * 256 < full) {
+      const int64_t q = tile * 256 + threadIdx.x;
+      if (q < full) f(std::integral_constant<int, VEC>(), 4 * q);
+    } else {
+      const int64_t k = 4 * full + threadIdx.x;
+      if (k < p) f(std::integral_constant<int, 1>(), k);
+    }
+  } else {
+    const int64_t k = (tile * 256 + threadIdx.x) * V<VEC>::W;
+    if (k < p) f(std::integral_constant<int, VEC>(), k);
+  }
+}
+// Coordinates of a row of which `left` (1 or more) remain: the group of four at an aligned address (ANY = false, left
+// is 4 or more then), or at any float's address and perhaps cut short by the end of the row, zeros past it.
+template <bool ANY> __device__ inline float4 ld_group(const float* p, int left) {
+  if constexpr (!ANY) return V<4>::ld(p);
+  if (left >= 4) return V<5>::ld(p);
+  float4 t = make_float4(p[0], 0.f, 0.f, 0.f);
+  if (left > 1) t.y = p[1];
+  if (left > 2) t.z = p[2];
+  return t;
+}
+template <bool ANY> __device__ inline void st_group(float* p, int left, float4 t) {
+  if constexpr (!ANY) {
+    V<4>::st(p, t);
+    return;
+  }
+  if (left >= 4) {
+    V<5>::st(p, t);
+    return;
+  }
+  p[0] = t.x;
+  if (left > 1) p[1] = t.y;
+  if (left > 2) p[2] = t.z;
+}
 __device__ inline float4 fma_s(float a, float4 b, float4 c) {
   return make_float4(fmaf(a, b.x, c.x), fmaf(a, b.y, c.y), fmaf(a, b.z, c.z), fmaf(a, b.w, c.w));
 }
@@ -107,6 +170,12 @@ template <> __device__ inline float4 add_noise<4>(float4 g, float scale, uint64_
   return add_noise4(g, scale, seed, node, ver, (uint64_t)k >> 2);
 }
 template <> __device__ inline float4 add_noise<-4>(float4 g, float scale, uint64_t seed, uint32_t node, uint32_t ver, int64_t k) {
+  return add_noise4(g, scale, seed, node, ver, (uint64_t)k >> 2);
+}
+template <> __device__ inline float4 add_noise<5>(float4 g, float scale, uint64_t seed, uint32_t node, uint32_t ver, int64_t k) {
+  return add_noise4(g, scale, seed, node, ver, (uint64_t)k >> 2);
+}
+template <> __device__ inline float4 add_noise<-5>(float4 g, float scale, uint64_t seed, uint32_t node, uint32_t ver, int64_t k) {
   return add_noise4(g, scale, seed, node, ver, (uint64_t)k >> 2);
 }
 // one coordinate: the same instructions on its group of four, so that it gets the very bits the vector form gives it

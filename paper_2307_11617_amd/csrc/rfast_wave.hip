@@ -45,6 +45,8 @@ __device__ inline void wave_sync() {
 // lw: lanes per node (64 / n, rounded down); kDeg: edge slots per node and kind; MOM: the optimizer
 // variant is in use, heavy-ball buffer, weight decay or both (a template flag, so that the plain method
 // carries neither the registers and the copies at the join nor the tests).
+// ANY: p is not a multiple of four: rows start at any float's address, and the last group of a row may be short (its
+// missing coordinates are zeros on chip and are not stored).
 // W: wavefronts per workgroup.  Every wavefront still owns a tile of 4 lw coordinates and runs its
 // rounds without looking at the others; the W tiles of a workgroup are neighbours, and the workgroup
 // moves their rings between HBM and LDS together, so that a row segment is W times as wide (16 nodes,
@@ -82,7 +84,7 @@ static WaveDiv wave_div(int lw, int W) {
   return dv;
 }
 
-template <int kDeg, bool MOM, int W>
+template <int kDeg, bool MOM, int W, bool ANY>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) rfast_wave_kernel(RfastDev s, RfastBlock blk, int lw, WaveDiv dv) {
   constexpr int VEC = 4;
   extern __shared__ float4 lds4[];
@@ -104,6 +106,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   const int64_t k = k_wg + (wave * lw + ln) * 4;
   const bool wave_has = k_wg + (int64_t)wave * lw * 4 < p;  // this wavefront has a tile (the last workgroup may be ragged)
   const bool mine = i < n && k < p;
+  const int left = p - k < 4 ? (int)(p - k) : 4;  // ANY: coordinates of the row from the lane's first one on
   const size_t ring_f4 = (size_t)n * M * lw;   // float4 of one ring of one wavefront's tile
   float4* v_l = lds4 + (size_t)wave * 2 * ring_f4;  // [n][M][lw], the tile of this wavefront
   float4* sg_l = v_l + ring_f4;                     // [n][M][lw]
@@ -120,6 +123,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   const int wT = W == 1 ? 0 : (int)(((unsigned)cT * dv.lanes) >> 16), lT = cT - wT * lw;                  // cT / lw
   const int64_t kT = k_wg + 4 * cT;
   const bool moves = iT < n && kT < p;
+  const int leftT = p - kT < 4 ? (int)(p - kT) : 4;
   float4* mv_l = lds4 + (size_t)wT * 2 * ring_f4 + (size_t)iT * M * lw + lT;  // + slot * lw (+ ring_f4 for the sums)
   // What the resolver, which has been through all rounds of the launch already, left about the moved node: the slot
   // of its latest version after the launch and, one bit per ring slot, which slots hold versions that a receiver
@@ -211,18 +215,18 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   fetch(0, plan_a);
   if (mine) {
     const size_t off = (size_t)i * p + k;
-    x = V<VEC>::ld(s.x + off);
-    z = V<VEC>::ld(s.z + off);
-    h = V<VEC>::ld((const float*)s.prob.data0 + off);
-    c = V<VEC>::ld((const float*)s.prob.data1 + off);
-    if (momentum) m = V<VEC>::ld(s.mom + off);
+    x = ld_group<ANY>(s.x + off, left);
+    z = ld_group<ANY>(s.z + off, left);
+    h = ld_group<ANY>((const float*)s.prob.data0 + off, left);
+    c = ld_group<ANY>((const float*)s.prob.data1 + off, left);
+    if (momentum) m = ld_group<ANY>(s.mom + off, left);
     // an S4 buffer is in the rho_tilde array only while its version is outside its sender's ring (rare)
 #pragma unroll
     for (int u = 0; u < kDeg; ++u)
       if (u < dI) {
         rt_where[u] = s.blk_head[kHeadWords * n + ce0 + u];
         end_slot[u] = s.blk_head[kHeadWords * c_from[u] + 9];  // of the sender's latest version after the launch
-        if (rt_where[u] & 1) rt[u] = V<VEC>::ld(s.rho_tilde + (size_t)(ce0 + u) * p + k);
+        if (rt_where[u] & 1) rt[u] = ld_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left);
       }
   }
   // rings: kBatch slots of both rings in flight at a time (rings of up to twelve slots in one round trip to
@@ -237,8 +241,8 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         tv[u] = ts[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (get_v & (1u << u)) tv[u] = V<VEC>::ld(vg);
-        if (get_s & (1u << u)) ts[u] = V<VEC>::ld(sgg);
+        if (get_v & (1u << u)) tv[u] = ld_group<ANY>(vg, leftT);
+        if (get_s & (1u << u)) ts[u] = ld_group<ANY>(sgg, leftT);
         vg += p;
         sgg += p;
       }
@@ -370,16 +374,16 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   if (mine) {
     const size_t off = (size_t)i * p + k;
     if (ver_next != ver_first) {  // x and z of a node that was not activated are what they were
-      V<VEC>::st(s.x + off, x);
-      V<VEC>::st(s.z + off, z);
-      if (momentum) V<VEC>::st(s.mom + off, m);
+      st_group<ANY>(s.x + off, left, x);
+      st_group<ANY>(s.z + off, left, z);
+      if (momentum) st_group<ANY>(s.mom + off, left, m);
     }
 #pragma unroll
     for (int u = 0; u < kDeg; ++u)
       // the buffer lives in the array only if its version is outside the sender's ring now
       if (u < dI && (rt_where[u] & 2)) {
         if (blk.rebase) rt[u] = sub(rt[u], mul_s(c_w[u], at(sg_l, c_col[u], end_slot[u])));
-        V<VEC>::st(s.rho_tilde + (size_t)(ce0 + u) * p + k, rt[u]);
+        st_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left, rt[u]);
       }
   }
   if (W > 1) __syncthreads();  // every wavefront of the workgroup is through with its rounds
@@ -403,8 +407,8 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
-        if (back_v & (1u << u)) V<VEC>::st(vg, tv[u]);
-        if (back_s & (1u << u)) V<VEC>::st(sgg, ts[u]);
+        if (back_v & (1u << u)) st_group<ANY>(vg, leftT, tv[u]);
+        if (back_s & (1u << u)) st_group<ANY>(sgg, leftT, ts[u]);
         vg += p;
         sgg += p;
       }
@@ -421,7 +425,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 // arguments that the one-step kernels recompute).  On return z is in its own array and slot 0 of
 // the v ring holds the last x - gamma z, as after the one-step kernels.
 // ---------------------------------------------------------------------------
-template <int kDeg, bool MOM>
+template <int kDeg, bool MOM, bool ANY>
 __global__ void __launch_bounds__(64) rfast_sync_wave_kernel(RfastDev s, float gamma, int rounds, int lw) {
   constexpr int VEC = 4;
   extern __shared__ float4 lds4[];
@@ -436,12 +440,13 @@ __global__ void __launch_bounds__(64) rfast_sync_wave_kernel(RfastDev s, float g
   float4* v_l = lds4;                   // [n][lw]
   float4* z_l = v_l + (size_t)n * lw;   // [n][lw]
   if (!mine) return;  // no barrier below: the lanes of a wavefront without coordinates may leave
+  const int left = p - k < 4 ? (int)(p - k) : 4;  // ANY: coordinates of the row from the lane's first one on
   const int own = i * lw + ln;
   const size_t off = (size_t)i * p + k;
-  float4 x = V<VEC>::ld(s.x + off), z = V<VEC>::ld(s.z + off);
-  const float4 h = V<VEC>::ld((const float*)s.prob.data0 + off), c = V<VEC>::ld((const float*)s.prob.data1 + off);
+  float4 x = ld_group<ANY>(s.x + off, left), z = ld_group<ANY>(s.z + off, left);
+  const float4 h = ld_group<ANY>((const float*)s.prob.data0 + off, left), c = ld_group<ANY>((const float*)s.prob.data1 + off, left);
   float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (MOM) m = V<VEC>::ld(s.mom + off);
+  if (MOM) m = ld_group<ANY>(s.mom + off, left);
   const int re0 = s.r_ptr[i], ce0 = s.c_ptr[i];
   const int dR = s.r_ptr[i + 1] - re0, dI = s.c_ptr[i + 1] - ce0;
   const float r_self = s.r_self[i], c_self = s.c_self[i];
@@ -482,22 +487,22 @@ __global__ void __launch_bounds__(64) rfast_sync_wave_kernel(RfastDev s, float g
     g = g_new;
     ++t;
   }
-  V<VEC>::st(s.x + off, x);
-  V<VEC>::st(s.z + off, z);
-  if (MOM) V<VEC>::st(s.mom + off, m);
-  V<VEC>::st(s.v_ring + (size_t)i * s.M * p + k, v);
+  st_group<ANY>(s.x + off, left, x);
+  st_group<ANY>(s.z + off, left, z);
+  if (MOM) st_group<ANY>(s.mom + off, left, m);
+  st_group<ANY>(s.v_ring + (size_t)i * s.M * p + k, left, v);
 }
 
 size_t wave_lds_bytes(const RfastDev& d, int lw) { return (size_t)2 * d.n * d.M * lw * sizeof(float4); }
 
 }  // namespace
 
-// The separable objective, p a multiple of 4, at most 32 nodes with at most kWaveMaxDeg edges of a
+// The separable objective, at most 32 nodes with at most kWaveMaxDeg edges of a
 // kind each, rings of at most 32 slots (one bit per slot in the records of the resolver), and the rings of one
 // wavefront's tile fitting into LDS.
 bool rfast_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && (d.p % 4) == 0 && c->max_degree <= kWaveMaxDeg &&
+  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg &&
          d.n <= kWaveMaxNodes && d.M <= 32 && wave_lds_bytes(d, 64 / d.n) <= 156 * 1024;
 }
 
@@ -521,11 +526,11 @@ static int wave_group(const rfast_ctx* c, int rounds) {
   return w;
 }
 
-template <int kDeg, bool MOM, int W>
+template <int kDeg, bool MOM, int W, bool ANY>
 static hipError_t launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   static bool raised = false;
   if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W>,
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
@@ -536,16 +541,16 @@ static hipError_t launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   const int64_t run = (int64_t)kXcds * (kTileRun / W), per = (int64_t)4 * lw * W;
   const int64_t groups = ((d.p + per - 1) / per + run - 1) / run * run;  // whole runs: a workgroup past the end leaves at once
   if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W>), dim3((unsigned)groups), dim3(64 * W), (size_t)W * wave_lds_bytes(d, lw),
+  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY>), dim3((unsigned)groups), dim3(64 * W), (size_t)W * wave_lds_bytes(d, lw),
                      c->stream, c->d, blk, lw, wave_div(lw, W));
   return hipGetLastError();
 }
 
 // A launch that does nothing (one workgroup that finds no coordinates and leaves): the first launch of a kernel
 // pays for loading its code, about 0.7 ms, which belongs to setting a context up and not to its first run.
-template <int kDeg, bool MOM, int W>
+template <int kDeg, bool MOM, int W, bool ANY>
 static hipError_t prime_wave(rfast_ctx* c) {
-  const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e != hipSuccess) return e;
   RfastDev none = c->d;
   none.p = 0;
@@ -553,16 +558,17 @@ static hipError_t prime_wave(rfast_ctx* c) {
   blk.gamma = 0.f;
   blk.rounds = 0;
   blk.rebase = 0;
-  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W>), dim3(1), dim3(64 * W), 0, c->stream, none, blk, 64 / c->d.n, wave_div(64 / c->d.n, W));
+  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY>), dim3(1), dim3(64 * W), 0, c->stream, none, blk, 64 / c->d.n, wave_div(64 / c->d.n, W));
   return hipGetLastError();
 }
 
 template <int kDeg, bool MOM>
 static hipError_t prime_wave_w(rfast_ctx* c) {
   const size_t one = wave_lds_bytes(c->d, 64 / c->d.n), cu = 160 * 1024;
-  hipError_t e = prime_wave<kDeg, MOM, 1>(c);
-  if (e == hipSuccess && 2 * one <= cu) e = prime_wave<kDeg, MOM, 2>(c);
-  if (e == hipSuccess && 4 * one <= cu) e = prime_wave<kDeg, MOM, 4>(c);
+  if (c->d.p % 4 != 0) return prime_wave<kDeg, MOM, 1, true>(c);
+  hipError_t e = prime_wave<kDeg, MOM, 1, false>(c);
+  if (e == hipSuccess && 2 * one <= cu) e = prime_wave<kDeg, MOM, 2, false>(c);
+  if (e == hipSuccess && 4 * one <= cu) e = prime_wave<kDeg, MOM, 4, false>(c);
   return e;
 }
 
@@ -578,10 +584,12 @@ hipError_t rfast_wave_prime(rfast_ctx* c) {
 
 template <int kDeg, bool MOM>
 static hipError_t launch_wave_w(rfast_ctx* c, const RfastBlock& blk) {
+  // rows that start at any address: a segment is never a whole cache line, one wavefront per workgroup
+  if (c->d.p % 4 != 0) return launch_wave<kDeg, MOM, 1, true>(c, blk);
   switch (wave_group(c, blk.rounds)) {
-    case 4: return launch_wave<kDeg, MOM, 4>(c, blk);
-    case 2: return launch_wave<kDeg, MOM, 2>(c, blk);
-    default: return launch_wave<kDeg, MOM, 1>(c, blk);
+    case 4: return launch_wave<kDeg, MOM, 4, false>(c, blk);
+    case 2: return launch_wave<kDeg, MOM, 2, false>(c, blk);
+    default: return launch_wave<kDeg, MOM, 1, false>(c, blk);
   }
 }
 
@@ -592,11 +600,11 @@ hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   return deg <= 2 ? launch_wave_w<2, false>(c, blk) : (deg <= 4 ? launch_wave_w<4, false>(c, blk) : launch_wave_w<kWaveMaxDeg, false>(c, blk));
 }
 
-// The synchronous mode through the multi-step kernel: the separable objective, p a multiple of 4,
+// The synchronous mode through the multi-step kernel: the separable objective,
 // at most 32 nodes with at most kWaveMaxDeg in-edges of a kind each.
 bool rfast_sync_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && (d.p % 4) == 0 && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes;
+  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes;
 }
 
 template <int kDeg, bool MOM>
@@ -606,8 +614,12 @@ static hipError_t launch_sync_wave(rfast_ctx* c, float gamma, int rounds) {
   const int64_t run = (int64_t)kXcds * kSyncTileRun;
   const int64_t tiles = ((d.p + 4 * lw - 1) / (4 * lw) + run - 1) / run * run;
   if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rfast_sync_wave_kernel<kDeg, MOM>), dim3((unsigned)tiles), dim3(64),
-                     (size_t)2 * d.n * lw * sizeof(float4), c->stream, c->d, gamma, rounds, lw);
+  if (d.p % 4 != 0)
+    hipLaunchKernelGGL((rfast_sync_wave_kernel<kDeg, MOM, true>), dim3((unsigned)tiles), dim3(64),
+                       (size_t)2 * d.n * lw * sizeof(float4), c->stream, c->d, gamma, rounds, lw);
+  else
+    hipLaunchKernelGGL((rfast_sync_wave_kernel<kDeg, MOM, false>), dim3((unsigned)tiles), dim3(64),
+                       (size_t)2 * d.n * lw * sizeof(float4), c->stream, c->d, gamma, rounds, lw);
   return hipGetLastError();
 }
 
