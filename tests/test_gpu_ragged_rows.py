@@ -75,3 +75,19 @@ def test_one_pass_against_the_oracle(n, p):
     d = b.diagnostics()
     xbar = orc.x.mean(0)
     assert abs(d["consensus_sq"] - ((orc.x - xbar) ** 2).sum()) <= 1e-3 * d["consensus_sq"]
+
+
+@pytest.mark.parametrize("floats", [1, 262_143, 262_144, 262_145, 524_289, 5_000_001])
+def test_reading_a_field_back(floats):
+    """Fields below, at and above one piece of the staged copy, read while rounds are still under way."""
+    import torch
+    w = _workload(2, floats)
+    gpu = harness.make_gpu(w)
+    x0 = np.random.default_rng(7).standard_normal((2, floats)).astype(np.float32)
+    gpu.init(x0, None)
+    assert np.array_equal(gpu.read("X"), x0)
+    st, dev = harness.upload_chunk(gpu, w, 0, 5)
+    gpu.run(5, *[dev[k] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma)
+    got = gpu.read("X")
+    torch.cuda.synchronize()
+    assert np.array_equal(gpu.read("X"), got) and np.abs(got - x0).max() > 1e-3
