@@ -125,13 +125,23 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
   o.resid = L.take(rfast_gemv_scratch_floats(n, prob) * 4);
   o.gscratch = L.take(rfast_softmax_scratch_bytes(n, prob));
   o.diag = L.take(64 * sizeof(double));
-  // the team kernel's packets and progress words: which team a problem gets depends on the graph and the device, so
+  // the team kernels' packets and progress words: which team a problem gets depends on the graph and the device, so
   // room for the largest one (at most kTeamMost workgroups)
-  const bool gemv = prob->kind == RFAST_OBJ_LEAST_SQUARES || prob->kind == RFAST_OBJ_LOGISTIC;
   RfastTeam most;
-  if (gemv && n <= kTeamMost) most.W = std::min(32, kTeamMost / n);
-  o.team_packets = L.take(rfast_team_packet_bytes(most, n, prob));
-  o.team_flags = L.take(rfast_team_flag_bytes(most, n));
+  if (prob->kind == RFAST_OBJ_SOFTMAX_BF16) {
+    RfastDev shape{};
+    shape.n = n;
+    shape.p = p;
+    shape.M = D + 2;
+    shape.prob = *prob;
+    most = rfast_team_softmax_shape(shape, 0, 0, kTeamMost);
+    o.team_packets = L.take(rfast_team_softmax_packet_bytes(most, n, prob));
+    o.team_flags = L.take(rfast_team_softmax_flag_bytes(most, n, prob));
+  } else {
+    if (prob->kind != RFAST_OBJ_DIAG_QUADRATIC && n <= kTeamMost) most.W = std::min(32, kTeamMost / n);
+    o.team_packets = L.take(rfast_team_packet_bytes(most, n, prob));
+    o.team_flags = L.take(rfast_team_flag_bytes(most, n));
+  }
   o.total = L.total;
   return o;
 }
@@ -319,7 +329,7 @@ int fold_sync(rfast_ctx* c) {
 
 constexpr int32_t kGraphRounds = 16;
 
-// Which team of workgroups a node gets for the several-rounds-per-launch form of least squares and logistic regression,
+// Which team of workgroups a node gets for the several-rounds-per-launch form of the objectives that are not separable,
 // and the chunks in which every kernel sums a row's dot product.  A problem that fits the LDS of one compute unit keeps
 // its rows in one chunk (the one-workgroup kernel sums them so).
 void choose_team(rfast_ctx* c, int max_out_r) {
@@ -331,8 +341,19 @@ void choose_team(rfast_ctx* c, int max_out_r) {
     return;
   units = std::min(units, kTeamMost);
   if (rfast_tiny_eligible(c)) units = std::min(units, d.n);  // one workgroup per node at most
+  if (d.prob.kind == RFAST_OBJ_SOFTMAX_BF16) {
+    c->team = rfast_team_softmax_shape(d, c->max_degree, max_out_r, units);
+    return;
+  }
   c->team = rfast_team_shape(d, c->max_degree, max_out_r, units);
   if (c->team.W > 1) d.row_chunk = c->team.C;
+}
+
+hipError_t launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int round0, const int32_t* d_batch_idx, const int32_t* d_delay_R,
+                       const int32_t* d_delay_C) {
+  return c->d.prob.kind == RFAST_OBJ_SOFTMAX_BF16
+             ? rfast_launch_team_softmax(c, rounds, gamma, round0, d_batch_idx, d_delay_R, d_delay_C)
+             : rfast_launch_team(c, sync, rounds, gamma, round0, d_batch_idx, d_delay_R, d_delay_C);
 }
 
 // The workgroups of a team launch wait for each other, so they must all become resident: two such launches that each
@@ -683,8 +704,9 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   chk(hipMemsetAsync(d.ticket, 0, 4, c->stream));
   choose_team(c, max_out_r);
   if (c->team.W > 0) {
-    chk(hipMemsetAsync(c->team_packets, 0, rfast_team_packet_bytes(c->team, n, prob), c->stream));
-    chk(hipMemsetAsync(c->team_flags, 0, rfast_team_flag_bytes(c->team, n), c->stream));
+    const bool softmax = prob->kind == RFAST_OBJ_SOFTMAX_BF16;
+    chk(hipMemsetAsync(c->team_packets, 0, softmax ? rfast_team_softmax_packet_bytes(c->team, n, prob) : rfast_team_packet_bytes(c->team, n, prob), c->stream));
+    chk(hipMemsetAsync(c->team_flags, 0, softmax ? rfast_team_softmax_flag_bytes(c->team, n, prob) : rfast_team_flag_bytes(c->team, n), c->stream));
   }
   chk(rfast_wave_prime(c));
   chk(hipStreamSynchronize(c->stream));  // the host vectors die with this scope
@@ -895,7 +917,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   if (e == hipSuccess) {
     time_begin(c, 0);
     if (team)
-      e = in_team_order(c, [&] { return rfast_launch_team(c, false, len, blk.gamma, (int)(c->host_round - len), d_batch_idx, d_delay_R, d_delay_C); });
+      e = in_team_order(c, [&] { return launch_team(c, false, len, blk.gamma, (int)(c->host_round - len), d_batch_idx, d_delay_R, d_delay_C); });
     else if (tiny)
       e = rfast_launch_tiny(c, blk, d_batch_idx, (int)(c->host_round - len), d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C);
     else e = rfast_wave_eligible(c) ? rfast_launch_wave(c, blk) : rfast_launch_block(c, blk);
@@ -1107,7 +1129,7 @@ int rfast_sync_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx) {
   if (!separable && d.prob.batch > 0 && !d_batch_idx) return fail(c, RFAST_EINVAL, "sample rows are required when batch > 0");
   if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
   if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
-  if (team_usable(c)) return rfast_sync_run(c, 1, gamma, d_batch_idx);
+  if (d.prob.kind != RFAST_OBJ_SOFTMAX_BF16 && team_usable(c)) return rfast_sync_run(c, 1, gamma, d_batch_idx);
   gamma = gamma_now(c, gamma);
   hipError_t e;
   time_begin(c, 0);
@@ -1136,7 +1158,7 @@ int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_b
   const size_t B = d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC ? 0 : (size_t)d.prob.batch;
   const bool multi = c->use_blocks && rfast_sync_wave_eligible(c);
   const bool large = (double)d.n * (double)d.p * 4.0 > 8.0e6;
-  const bool team = team_usable(c);
+  const bool team = d.prob.kind != RFAST_OBJ_SOFTMAX_BF16 && team_usable(c);
   for (int32_t r = 0; r < rounds;) {
     if (team) {  // least squares / logistic regression: the steps up to the next decay of the step size in one launch
       int32_t len = std::min(rounds - r, 1 << 20);
@@ -1147,7 +1169,7 @@ int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_b
       if (fold_sync(c) != RFAST_OK) return RFAST_EHIP;
       time_begin(c, 0);
       hipError_t e = in_team_order(c, [&] {
-        return rfast_launch_team(c, true, len, gamma_now(c, gamma), (int)c->host_round, d_batch_idx ? d_batch_idx + (size_t)r * d.n * B : nullptr, nullptr, nullptr);
+        return launch_team(c, true, len, gamma_now(c, gamma), (int)c->host_round, d_batch_idx ? d_batch_idx + (size_t)r * d.n * B : nullptr, nullptr, nullptr);
       });
       time_end(c, 0);
       if (e == hipSuccess) e = rfast_launch_sync_plan(c, len);

@@ -37,55 +37,17 @@
 // products out and in, sums out).
 #include <type_traits>
 
-#include "rfast_vec.h"
+#include "rfast_team.h"
 
 namespace {
 
-constexpr int kThreads = 512;
+constexpr int kThreads = kTeamThreads;
 constexpr int kOwn = 256;                  // lanes that own coordinates
 constexpr int kOwnWaves = kOwn / 64;
 constexpr int kLoad = kThreads - kOwn;     // lanes that fetch rows
 constexpr int kLoadWaves = kLoad / 64;
 constexpr int kTileRows = 64 * kLoadWaves; // most sampled rows of a tile: a fetching wavefront holds their numbers, one per lane
-constexpr int kFlagWords = 16;             // 32-bit words per progress entry (64 bytes): [0] v, [1] sums
-constexpr int kSpin = 1 << 24;             // polls before a wait gives up (some ten seconds)
-constexpr size_t kLds = 156 * 1024;
-
-typedef unsigned long long u64;
-
-__device__ inline void put32(unsigned* p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline unsigned get32(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void put64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline u64 get64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void put_f(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float get_f(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-__device__ inline int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ inline float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
-
-struct TeamArgs {
-  int rounds, W, C, B, buffers;  // buffers: tiles of rows in LDS (two: the next round's rows arrive during this one)
-  float gamma;
-  unsigned base;              // progress words and packet tags count rounds from here on (they never repeat)
-  int round0;                 // number of the first round, for error reports
-  const int32_t* batch_idx;   // [rounds][n][B], NULL: all rows, in order
-  const int32_t* delay_R;     // [rounds][eR] (not SYNC)
-  const int32_t* delay_C;     // [rounds][eC]
-  u64* packets;               // [2][n][W][B]
-  unsigned* flags;            // [n][W][kOwnWaves][kFlagWords]
-};
-
-// first set bit at or after `from` of a mask of kBlockRounds bits, kBlockRounds if there is none
-__device__ inline int next_bit(const u64* mask, int from) {
-  int w = from >> 6;
-  if (w >= kBlockRounds / 64) return kBlockRounds;
-  u64 m = mask[w] & (~0ull << (from & 63));
-  while (m == 0) {
-    if (++w == kBlockRounds / 64) return kBlockRounds;
-    m = mask[w];
-  }
-  return w * 64 + __ffsll((long long)m) - 1;
-}
+// packets: [2][n][W][B]; progress entries: [n][W][kOwnWaves]
 
 template <int kE, bool TILE, bool SYNC>
 __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamArgs a) {
@@ -171,47 +133,11 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     }
 
   bool dead = false;  // a wait has run out
-  auto give_up = [&] {
-    dead = true;
-    if (atomicCAS(&s.err[0], 0, RFAST_EHIP) == 0) {
-      s.err[1] = a.round0;
-      s.err[2] = 4;
-      s.err[3] = i;
-    }
-  };
-  // waits until the progress words of the lanes that have one are at least round `need` of this launch
-  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2) {
-    if (need1 <= 0) f1 = nullptr;
-    if (need2 <= 0) f2 = nullptr;
-    if (!__any(f1 != nullptr || f2 != nullptr) || dead) return;
-    for (int spin = 0;; ++spin) {
-      const unsigned v1 = f1 ? get32(f1) : 0, v2 = f2 ? get32(f2) : 0;
-      const bool ok = (!f1 || (int)(v1 - a.base) >= need1) && (!f2 || (int)(v2 - a.base) >= need2);
-      if (__all(ok)) break;
-      if (spin > kSpin) {
-        give_up();
-        break;
-      }
-    }
-    // what the words stand for was stored before them; nothing below may be loaded before they were seen
-    asm volatile("" ::: "memory");
-  };
+  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2) { wait_progress(s, a, i, f1, need1, f2, need2, &dead); };
 
-  // ---- rows.  A row number as the caller gave it, clamped into the node's samples and reported if outside.
-  auto row_of = [&](int q, int b) {
-    int row = a.batch_idx[((size_t)q * n + i) * B + b];
-    if (row < 0 || row >= S) {
-      if (w == 0 && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
-        s.err[1] = a.round0 + q;
-        s.err[2] = 2;
-        s.err[3] = i;
-      }
-      row = row < 0 ? 0 : S - 1;
-    }
-    return row;
-  };
+  // ---- rows
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = row_of(q, b);
+    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = team_row(s, a, i, q, b, w == 0);
   };
   // Four coordinates of a row (unaligned where p is no multiple of four).  At the chunk's ragged end the load starts up
   // to three coordinates early, still inside the row, and whole_quad moves them into place and clears the rest.
@@ -471,7 +397,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
                 if (w0 + u < W) ok = ok && (unsigned)(got[u] >> 32) == tag;
               if (ok || dead) break;
               if (spin > kSpin) {
-                give_up();
+                dead = true;
+                report_wait(s, a.round0, i);
                 break;
               }
             }
@@ -634,7 +561,7 @@ template <int kE, bool TILE, bool SYNC>
 hipError_t launch_team(rfast_ctx* c, const TeamArgs& a) {
   static bool raised = false;
   if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    const hipError_t e = hipFuncSetAttribute((const void*)rfast_team_kernel<kE, TILE, SYNC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_team_kernel<kE, TILE, SYNC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTeamLds);
     if (e != hipSuccess) return e;
     raised = true;
   }
@@ -680,8 +607,8 @@ RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree
     if ((p + C - 1) / C != W || C > 8 * kOwn) continue;
     const int64_t quads = (int64_t)B * ((C + 3) / 4);
     const bool fits = d.prob.batch == 0 || B <= kTileRows;
-    const int tiles = !fits || team_lds(d, C, B, 1) > kLds ? 0 : d.prob.batch > 0 && team_lds(d, C, B, 2) <= kLds ? 2 : 1;
-    if (!tiles && (quads * 16 > 512 * 1024 || team_lds(d, C, B, 0) > kLds)) continue;
+    const int tiles = !fits || team_lds(d, C, B, 1) > kTeamLds ? 0 : d.prob.batch > 0 && team_lds(d, C, B, 2) <= kTeamLds ? 2 : 1;
+    if (!tiles && (quads * 16 > 512 * 1024 || team_lds(d, C, B, 0) > kTeamLds)) continue;
     const double kb = quads * 16 / 1024.0;
     double us = 3.0 + (W > 1 ? 1.0 + 0.05 * W : 0.0) + 0.15 * C / kOwn;
     if (!tiles) us += kb / 20.0;  // read twice, through the L2

@@ -112,3 +112,61 @@ def test_two_streams():
     for g in gpus:
         g.check()
     _same(gpus[0], gpus[1], "streams")
+
+
+# graph, n, d, K, samples, batch, momentum: feature tiles per chunk, ragged last chunk, class counts, rows per workgroup
+SOFTMAX = {
+    "one_tile_chunks": ("exponential", 12, 512, 32, 256, 64, 0.9),
+    "ragged_last_chunk": ("mesh", 30, 320, 96, 200, 128, 0.0),
+    "two_chunks_all_classes": ("directed_ring", 90, 128, 128, 130, 64, 0.0),
+    "many_rows": ("binary_tree", 7, 192, 64, 300, 256, 0.0),
+    "eight_feature_tiles": ("bidirectional_ring", 128, 448, 32, 100, 64, 0.9),
+    "many_in_edges": ("tree_star", 20, 64, 96, 80, 64, 0.0),
+}
+
+
+def _softmax(case):
+    graph, n, d, K, samples, batch, momentum = SOFTMAX[case]
+    r, c = BUILD[graph](n)
+    gamma = 0.05 if graph in ("exponential", "mesh", "bidirectional_ring") else 0.002
+    w = configs._mk(case, n, d * K, r, c, 3, gamma, 0, "softmax_bf16", problems.softmax_pool(n, d, K, samples, 4), 0.6, 0.3, 6,
+                    batch=batch, samples=samples, burst=3, tol=2e-3, extra={"d": d, "K": K})
+    a, b = harness.make_gpu(w), harness.make_gpu(w)
+    rfast_use_blocks(b.ctx, False)
+    x0 = (0.05 * np.random.default_rng(3).standard_normal((w.n, w.p))).astype(np.float32)
+    for g in (a, b):
+        rfast_set_rebase_interval(g.ctx, 17)
+        if momentum:
+            g.set_optimizer(momentum, 0.01)
+        g.init(x0, w.sched.initial_batch())
+    return w, a, b
+
+
+def _close(a, b, where, tol=2e-3):
+    for f in ("T_NODE", "TAU_R", "TAU_C", "ROUND"):
+        assert np.array_equal(a.read(f), b.read(f)), (where, f)
+    for f in ("X", "Z", "G"):
+        x, y = a.read(f), b.read(f)
+        assert np.isfinite(x).all() and np.linalg.norm(x - y) <= tol * np.linalg.norm(y), (where, f, np.linalg.norm(x - y) / np.linalg.norm(y))
+        print(where, f, np.linalg.norm(x - y) / np.linalg.norm(y))
+
+
+@pytest.mark.parametrize("case", list(SOFTMAX))
+def test_softmax_rounds(case):
+    """The partial logits of a chunk are rounded to fp32 before they are added, so the two forms agree to the rounding of
+    a sum (and the bf16 roundings it tips), not bit for bit."""
+    w, a, b = _softmax(case)
+    st, dev = harness.upload_chunk(a, w, 0, 30)
+    for lo, hi in ((0, 20), (20, 21), (21, 30)):
+        for g in (a, b):
+            g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma,
+                  dev["batch_idx"][lo:hi].contiguous())
+            g.check()
+        _close(a, b, (case, hi))
+    p_act = torch.full((w.n,), 0.5, dtype=torch.float32)
+    for g in (a, b):
+        g.run_generated(15, 5, p_act.to(g.device), w.sched.d_max, 0.1, w.gamma)
+        g.run_events(20, 6, None, w.sched.d_max, 0.2, w.gamma)
+        g.check()
+    _close(a, b, (case, "generated and events"))
+
