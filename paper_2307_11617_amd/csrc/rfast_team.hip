@@ -49,6 +49,24 @@ constexpr int kLoadWaves = kLoad / 64;
 constexpr int kTileRows = 64 * kLoadWaves; // most sampled rows of a tile: a fetching wavefront holds their numbers, one per lane
 // packets: [2][n][W][B]; progress entries: [n][W][kOwnWaves]
 
+// value of lane ^ 1, ^ 2 (quad permutes), ^ 4 (half rows reversed, then quads), ^ 8 (rows of 16 rotated by 8)
+template <int CTRL> __device__ inline float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ inline float xor1(float v) { return dpp<0xB1>(v); }
+__device__ inline float xor2(float v) { return dpp<0x4E>(v); }
+__device__ inline float xor4(float v) { return dpp<0x1B>(dpp<0x141>(v)); }
+__device__ inline float xor8(float v) { return dpp<0x128>(v); }
+// a[l] + a[l ^ 32] in the lower half of the wavefront, b[l] + b[l ^ 32] in the upper; the same with rows of 16 lanes
+__device__ inline float fold32(float a, float b) {
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+  return __int_as_float(t[0]) + __int_as_float(t[1]);
+}
+__device__ inline float fold16(float a, float b) {
+  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+  return __int_as_float(t[0]) + __int_as_float(t[1]);
+}
+
 template <int kE, bool TILE, bool SYNC>
 __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamArgs a) {
   constexpr int KB = kE <= 2 ? 8 : (kE == 4 ? 4 : 2);  // in-edges whose ring values are in flight together
@@ -66,8 +84,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   float4* const tiles = lds4;                                       // TILE: [a.buffers][B][Q]
   float4* xs4 = tiles + (TILE ? (size_t)a.buffers * B * Qm : 0);    // [Q] the mixed x of this round
   float4* cp4 = xs4 + Qm;                                           // [4][Q] column sums of the four groups of rows
-  float* rs = reinterpret_cast<float*>(cp4 + 4 * Qm);               // [B] residuals
-  int* rowi = reinterpret_cast<int*>(rs + B);                       // [2][B] sampled rows of this active round and the next
+  float* rs = reinterpret_cast<float*>(cp4 + 4 * Qm);               // [4][Bq] residuals, row b at [b mod 4][b / 4]
+  const int Bq = (B + 15) / 16 * 4;
+  int* rowi = reinterpret_cast<int*>(rs + 4 * Bq);                       // [2][B] sampled rows of this active round and the next
   int* nodew = rowi + (sampled ? 2 * B : 0);                        // [kBlockRounds] node words
   __shared__ u64 act_mask[kBlockRounds / 64], ev_mask[kBlockRounds / 64];
   float* xs = reinterpret_cast<float*>(xs4);
@@ -283,6 +302,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       // ---- gradient, rows: eight (four) rows per wavefront at a time; lane c sums coordinates 4c .. 4c+3 (+ 256 m) of the
       // chunk, and the lanes' sums are added as a butterfly from distance 32 down to 1 whose first steps halve the rows
       const int* rows = rowi + (parity ? B : 0);
+      const float target = tid < B ? targets[sampled ? rows[tid] : tid] : 0.f;  // of the lane's first row
       auto dots = [&](auto rb) {
         constexpr int RB = decltype(rb)::value;
         for (int b0 = wave * RB; b0 < B; b0 += RB * (kThreads / 64)) {
@@ -313,24 +333,35 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
               acc[r] = fmaf(av[r].w, xv.w, acc[r]);
             }
           }
-          int row = 0, dist = 32;
+          // distances 32 and 16 halve the rows: one swap of half-wavefronts (rows of 16 lanes) brings both terms of two
+          // rows' sums together, the lower lanes going on with the first row; 8 .. 1 through the data-parallel moves
+          int row = 0;
+          if constexpr (RB == 8) {
 #pragma unroll
-          for (int h = RB / 2; h > 0; h >>= 1) {
-            const bool up = lane & dist;
+            for (int r = 0; r < 4; ++r) acc[r] = fold32(acc[r], acc[r + 4]);
+            row += lane & 32 ? 4 : 0;
 #pragma unroll
-            for (int r = 0; r < h; ++r) {
-              const float keep = up ? acc[r + h] : acc[r], send = up ? acc[r] : acc[r + h];
-              acc[r] = keep + __shfl_xor(send, dist, 64);
-            }
-            row += up ? h : 0;
-            dist >>= 1;
+            for (int r = 0; r < 2; ++r) acc[r] = fold16(acc[r], acc[r + 2]);
+            row += lane & 16 ? 2 : 0;
+            const bool up = lane & 8;
+            const float keep = up ? acc[1] : acc[0], send = up ? acc[0] : acc[1];
+            acc[0] = keep + xor8(send);
+            row += up ? 1 : 0;
+          } else {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) acc[r] = fold32(acc[r], acc[r + 2]);
+            row += lane & 32 ? 2 : 0;
+            acc[0] = fold16(acc[0], acc[1]);
+            row += lane & 16 ? 1 : 0;
+            acc[0] += xor8(acc[0]);
           }
           float sum = acc[0];
-#pragma unroll
-          for (int d2 = 32 / RB; d2 > 0; d2 >>= 1) sum += __shfl_xor(sum, d2, 64);
+          sum += xor4(sum);
+          sum += xor2(sum);
+          sum += xor1(sum);
           const int b = b0 + row;
           if ((lane & (64 / RB - 1)) == 0 && b < B) {
-            if (W == 1) rs[b] = sum;
+            if (W == 1) rs[(b & 3) * Bq + (b >> 2)] = sum;
             else
               put64(a.packets + (((size_t)parity * n + i) * W + w) * B + b,
                     (u64)(a.base + (unsigned)q + 1u) << 32 | __float_as_uint(sum));
@@ -380,7 +411,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       for (int b = tid; b < B && (W == 1 || owner); b += W == 1 ? kThreads : kOwn) {
         float dot;
         if (W == 1) {
-          dot = rs[b];
+          dot = rs[(b & 3) * Bq + (b >> 2)];
         } else {
           dot = 0.f;
           const u64* src = a.packets + ((size_t)parity * n + i) * W * B + b;
@@ -407,8 +438,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
               if (w0 + u < W) dot = w0 + u == 0 ? __uint_as_float((unsigned)got[u]) : dot + __uint_as_float((unsigned)got[u]);
           }
         }
-        const float y = targets[sampled ? rows[b] : b];
-        rs[b] = logistic ? 1.0f / (1.0f + expf(-dot)) - y : dot - y;
+        const float y = b == tid ? target : targets[sampled ? rows[b] : b];
+        rs[(b & 3) * Bq + (b >> 2)] = logistic ? 1.0f / (1.0f + expf(-dot)) - y : dot - y;
       }
       // the loads above were issued after the stores of v and have returned: v is out
       if (owner && !SYNC) {
@@ -422,15 +453,24 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         int rg, quad;
         split(f, &rg, &quad);
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-        for (int b = rg; b < B; b += 4) {
-          const float r = rs[b];
+        const float* rq = rs + rg * Bq;
+        auto row_of_group = [&](int b, float r) {
           const float4 av = TILE ? tile[b * Q + quad] : whole_quad(row_quad(sampled ? rows[b] : b, quad), quad);
           acc.x = fmaf(r, av.x, acc.x);
           acc.y = fmaf(r, av.y, acc.y);
           acc.z = fmaf(r, av.z, acc.z);
           acc.w = fmaf(r, av.w, acc.w);
+        };
+        int b = rg;
+#pragma unroll 2
+        for (; b + 12 < B; b += 16) {  // four rows of the group, their residuals in one read
+          const float4 r4 = *reinterpret_cast<const float4*>(rq + (b >> 2));
+          row_of_group(b, r4.x);
+          row_of_group(b + 4, r4.y);
+          row_of_group(b + 8, r4.z);
+          row_of_group(b + 12, r4.w);
         }
+        for (; b < B; b += 4) row_of_group(b, rq[b >> 2]);
         cp4[f] = acc;
       }
       __syncthreads();  // column sums; the tile may be overwritten
@@ -554,7 +594,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 
 size_t team_lds(const RfastDev& d, int C, int B, int tiles) {
   const size_t Qm = (size_t)(C + 3) / 4;
-  return ((size_t)tiles * B * Qm + 5 * Qm) * 16 + (size_t)B * 4 + (d.prob.batch > 0 ? 2 * (size_t)B * 4 : 0) + kBlockRounds * 4;
+  return ((size_t)tiles * B * Qm + 5 * Qm) * 16 + ((size_t)B + 15) / 16 * 64 + (d.prob.batch > 0 ? 2 * (size_t)B * 4 : 0) + kBlockRounds * 4;
 }
 
 template <int kE, bool TILE, bool SYNC>
