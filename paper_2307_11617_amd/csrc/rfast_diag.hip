@@ -141,24 +141,143 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   }
 }
 
-// sum_i f_i(xbar) for least squares and logistic regression over each node's FULL
-// local data: one wavefront per row, a . xbar reduced across the 64 lanes.
+// The same sums where p is small: with four coordinates per lane a vector of 4096 is four workgroups, each of which goes
+// through the nodes and edges one after the other (105.6 us on 32 nodes with 160 edges).  Here a workgroup takes 64
+// coordinates, and its sixteen wavefronts share out the nodes and the edges; the partial sums of a coordinate meet in
+// LDS, and the seven results, one cache line, take one atomic instruction per workgroup (n 48, p 4096, 96 edges: 68.4 ->
+// 14.7 us; with an atomic of its own for each, some 9 ns apiece, it was 23.8).
+constexpr int kSplitWaves = 16;
+__global__ void __launch_bounds__(64 * kSplitWaves) rfast_diag_split_kernel(RfastDev s, const float* xstar, double* out) {
+  __shared__ double part[kSplitWaves][8][64];  // flight, gs, sd, sd2, sh, shf, shf2, z_sq of a coordinate
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t p = s.p, k = (int64_t)blockIdx.x * 64 + lane;
+  const bool separable = s.prob.kind == RFAST_OBJ_DIAG_QUADRATIC, mine = k < p;
+  const float* hp = (const float*)s.prob.data0;
+  const float* cp = (const float*)s.prob.data1;
+  double flight = 0, gs = 0, sd = 0, sd2 = 0, sh = 0, shf = 0, shf2 = 0, z_sq = 0;
+  float x0 = 0.f, c0 = 0.f;
+  if (mine) {
+    x0 = s.x[k];
+    if (separable) c0 = cp[k];
+#pragma unroll 4
+    for (int i = wave; i < s.n; i += kSplitWaves) {
+      const size_t off = (size_t)i * p + k;
+      const int ti = s.t[i];
+      const float x = s.x[off], z = s.z[off];
+      float g;
+      if (separable) {
+        const float h = hp[off], c = cp[off];
+        g = diag_sample<1>(s, h, c, x, i, ti, k);
+        const double f = (double)c - (double)c0;
+        sh += h;
+        shf += h * f;
+        shf2 += h * f * f;
+      } else {
+        g = s.g[(size_t)(ti & 1) * s.n * p + off];
+      }
+      const double d = (double)x - (double)x0;
+      sd += d;
+      sd2 += d * d;
+      flight += z;
+      z_sq += (double)z * z;
+      gs += g;
+    }
+#pragma unroll 8
+    for (int e = wave; e < s.eC; e += kSplitWaves) {
+      const int j = s.c_src[e];
+      const int tj = s.t[j], tau = s.tau_c[e];
+      const float a = s.c_w[e];
+      const float* ring = s.sigma_ring + (size_t)j * s.M * p + k;
+      const bool in_ring = tau >= tj - (s.M - 2);
+      const float latest = ring[(size_t)(tj % s.M) * p];
+      const float last = *(in_ring ? ring + (size_t)(tau % s.M) * p : s.rho_tilde + (size_t)e * p + k);
+      flight += (double)(a * latest) - (double)(in_ring ? a * last : last);
+    }
+  }
+  double* mail = &part[wave][0][lane];
+  mail[0] = flight; mail[64] = gs; mail[128] = sd; mail[192] = sd2; mail[256] = sh; mail[320] = shf; mail[384] = shf2; mail[448] = z_sq;
+  __syncthreads();
+  if (wave != 0) return;
+  for (int w = 1; w < kSplitWaves; ++w) {
+    const double* m = &part[w][0][lane];
+    flight += m[0]; gs += m[64]; sd += m[128]; sd2 += m[192]; sh += m[256]; shf += m[320]; shf2 += m[384]; z_sq += m[448];
+  }
+  double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+  if (mine) {
+    const double dx = sd / s.n, xbar = (double)x0 + dx;
+    acc[6] = xbar * xbar;
+    acc[0] = sd2 - 2.0 * dx * sd + s.n * dx * dx;
+    if (separable) {
+      const double dc = xbar - (double)c0;
+      acc[5] = 0.5 * (dc * dc * sh - 2.0 * dc * shf + shf2);
+    }
+    const double res = flight - gs;
+    acc[2] = res * res;
+    acc[3] = gs * gs;
+    if (xstar) acc[4] = (xbar - xstar[k]) * (xbar - xstar[k]);
+    if (s.xbar) s.xbar[k] = (float)xbar;
+  }
+  acc[1] = z_sq;
+  double sum = 0.0;  // the results lie in one cache line: seven lanes add to it with one instruction
+#pragma unroll
+  for (int q = 0; q < 7; ++q) {
+    const double w = wave_sum(acc[q]);
+    if (lane == q) sum = w;
+  }
+  if (lane < 7) atomicAdd(&out[lane], sum);
+}
+
+// sum_i f_i(xbar) for least squares and logistic regression over each node's FULL local data.  The rows are read once
+// (the bound: 1 GB on 32 nodes x 2048 rows x 4096); a wavefront takes four rows at a time, so that the average is read
+// once for four, and a workgroup goes through many before it adds its sum to the one result (with one row per wavefront,
+// one float per lane and one fp64 atomic per row on that one address the same took 851 us; now 192, 5.6 TB/s).
+constexpr int kLossRows = 4;
 __global__ void __launch_bounds__(kThreads) rfast_loss_rows_kernel(RfastDev s, double* out) {
   const int i = blockIdx.y;
-  const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (row >= s.prob.samples) return;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t p = s.p;
-  const float* a = (const float*)s.prob.data0 + ((size_t)i * s.prob.samples + row) * p;
-  double acc = 0.0;
-  for (int64_t k = lane; k < p; k += 64) acc += (double)a[k] * (double)s.xbar[k];
-  acc = wave_sum(acc);
-  if (lane == 0) {
-    const double y = ((const float*)s.prob.data1)[(size_t)i * s.prob.samples + row];
-    double l;
-    if (s.prob.kind == RFAST_OBJ_LOGISTIC) l = (acc > 0 ? acc + log1p(exp(-acc)) : log1p(exp(acc))) - y * acc;
-    else l = 0.5 * (acc - y) * (acc - y);
-    atomicAdd(&out[5], l / s.prob.samples);
+  const int S = s.prob.samples;
+  const float* rows = (const float*)s.prob.data0 + (size_t)i * S * p;
+  const float* ys = (const float*)s.prob.data1 + (size_t)i * S;
+  double total = 0.0;
+  for (int r0 = (blockIdx.x * (kThreads / 64) + wave) * kLossRows; r0 < S; r0 += gridDim.x * (kThreads / 64) * kLossRows) {
+    double acc[kLossRows] = {0.0, 0.0, 0.0, 0.0};
+    const float* a_row[kLossRows];
+#pragma unroll
+    for (int u = 0; u < kLossRows; ++u) a_row[u] = rows + (size_t)(r0 + u < S ? r0 + u : S - 1) * p;
+    const int64_t full = p & ~(int64_t)3;
+#pragma unroll 2
+    for (int64_t k = 4 * lane; k < full; k += 256) {  // (no branch in here: every load of a step is in flight at once)
+      float4 a[kLossRows];
+#pragma unroll
+      for (int u = 0; u < kLossRows; ++u) a[u] = V<5>::ld(a_row[u] + k);
+      const float4 x = V<5>::ld(s.xbar + k);
+#pragma unroll
+      for (int u = 0; u < kLossRows; ++u)
+        acc[u] += (double)a[u].x * x.x + (double)a[u].y * x.y + (double)a[u].z * x.z + (double)a[u].w * x.w;
+    }
+    if (full + lane < p) {
+#pragma unroll
+      for (int u = 0; u < kLossRows; ++u) acc[u] += (double)a_row[u][full + lane] * s.xbar[full + lane];
+    }
+#pragma unroll
+    for (int u = 0; u < kLossRows; ++u) {
+      const double dot = wave_sum(acc[u]);
+      if (lane == u && r0 + u < S) {
+        const double y = ys[r0 + u];
+        if (s.prob.kind == RFAST_OBJ_LOGISTIC) total += (dot > 0 ? dot + log1p(exp(-dot)) : log1p(exp(dot))) - y * dot;
+        else total += 0.5 * (dot - y) * (dot - y);
+      }
+    }
+  }
+  __shared__ double part[kThreads / 64];
+  total = wave_sum(total);
+  if (lane == 0) part[wave] = total;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double w = 0.0;
+    for (int v = 0; v < kThreads / 64; ++v) w += part[v];
+    if (w != 0.0) atomicAdd(&out[5], w / S);
   }
 }
 
@@ -226,7 +345,14 @@ hipError_t rfast_launch_diag(rfast_ctx* c, const float* d_xstar, double* d_out) 
   int64_t blocks = group_tiles(c->d.p);
   if (blocks > 2048) blocks = 2048;  // grid-stride beyond that: 8 workgroups per CU
   const bool streaming = (double)c->d.n * (double)c->d.p * 4.0 >= 32.0e6;  // far beyond the caches: non-temporal loads
-  if (vec4 && streaming)
+  // The other form's time is its serial chain, which grows with n and hardly with p; the split form's is its p / 64
+  // workgroups.  us, other form -> split: n 4: p 8192 11.0 -> 9.7, 16384 10.9 -> 12.8; n 8: 16384 16.2 -> 13.3, 24576
+  // 16.4 -> 20.3; n 16: 32768 27.0 -> 23.8, 49152 27.2 -> 35.0; n 48: 65536 96 -> 67; n 128: 65536 364 -> 125; and with
+  // n 48 it is the slower one again at 131072 (100 -> 131).
+  if (c->d.p <= 65536 && c->d.p <= (int64_t)2048 * c->d.n)
+    hipLaunchKernelGGL(rfast_diag_split_kernel, dim3((unsigned)((c->d.p + 63) / 64)), dim3(64 * kSplitWaves), 0, c->stream, c->d,
+                       d_xstar, d_out);
+  else if (vec4 && streaming)
     hipLaunchKernelGGL(rfast_diag_kernel<-4>, dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, c->d, d_xstar, d_out);
   else if (vec4)
     hipLaunchKernelGGL(rfast_diag_kernel<4>, dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, c->d, d_xstar, d_out);
@@ -235,9 +361,11 @@ hipError_t rfast_launch_diag(rfast_ctx* c, const float* d_xstar, double* d_out) 
   else
     hipLaunchKernelGGL(rfast_diag_kernel<5>, dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, c->d, d_xstar, d_out);
   const int kind = c->d.prob.kind;
-  if (kind == RFAST_OBJ_LEAST_SQUARES || kind == RFAST_OBJ_LOGISTIC)
-    hipLaunchKernelGGL(rfast_loss_rows_kernel, dim3((c->d.prob.samples + 3) / 4, c->d.n), dim3(kThreads), 0, c->stream, c->d,
-                       d_out);
+  if (kind == RFAST_OBJ_LEAST_SQUARES || kind == RFAST_OBJ_LOGISTIC) {
+    const int per = kThreads / 64 * kLossRows, most = (c->d.prob.samples + per - 1) / per;
+    const int each = (2048 + c->d.n - 1) / c->d.n;  // eight workgroups per compute unit over all nodes
+    hipLaunchKernelGGL(rfast_loss_rows_kernel, dim3(most < each ? most : each, c->d.n), dim3(kThreads), 0, c->stream, c->d, d_out);
+  }
   if (kind == RFAST_OBJ_SOFTMAX_BF16) {
     const hipError_t e = rfast_softmax_loss(c, d_out + 5);
     if (e != hipSuccess) return e;

@@ -148,7 +148,6 @@ def _close(a, b, where, tol=2e-3):
     for f in ("X", "Z", "G"):
         x, y = a.read(f), b.read(f)
         assert np.isfinite(x).all() and np.linalg.norm(x - y) <= tol * np.linalg.norm(y), (where, f, np.linalg.norm(x - y) / np.linalg.norm(y))
-        print(where, f, np.linalg.norm(x - y) / np.linalg.norm(y))
 
 
 @pytest.mark.parametrize("case", list(SOFTMAX))
