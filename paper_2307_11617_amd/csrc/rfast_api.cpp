@@ -1008,6 +1008,19 @@ int rfast_run(rfast_ctx* c, int32_t rounds, const uint8_t* d_active, const int32
     if (c->use_blocks && rfast_chain_eligible(c)) {
       rc = chained_rounds(c, ahead, gamma, d_active + (size_t)r * d.n, d_batch_idx ? d_batch_idx + (size_t)r * d.n * B : nullptr);
       if (rc != RFAST_OK) return rc;
+    } else if (c->no_tiles && c->use_blocks && !c->profiling && d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC) {
+      for (int32_t q = 0; q < ahead;) {
+        use_plan_set(c, q);
+        int32_t len = ahead - q;  // one step size per launch (and no rebase inside: the stretch ends there)
+        if (c->gamma_step > 0) len = (int32_t)std::min<int64_t>(len, c->gamma_step - c->host_round % c->gamma_step);
+        const hipError_t g = rfast_launch_events(c, gamma_now(c, gamma), len);
+        if (g != hipSuccess) return hipfail(c, g, "event-driven iterations launch");
+        c->host_round += len - 1;
+        rc = after_round(c);
+        if (rc != RFAST_OK) return rc;
+        q += len;
+      }
+      use_plan_set(c, ahead - 1);
     } else {
       for (int32_t q = 0; q < ahead; ++q) {
         use_plan_set(c, q);
@@ -1102,9 +1115,8 @@ int rfast_run_events(rfast_ctx* c, int32_t iterations, uint64_t seed, const floa
   hipError_t e = hipMemcpyAsync(d.gen_cdf, cdf.data(), (size_t)d.n * 4, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the host vector dies with this scope
   if (e != hipSuccess) return hipfail(c, e, "uploading selection thresholds");
-  // A stretch of iterations drawn by one launch, then, for the separable objective, one pass per iteration with the
-  // resolver ahead (a multi-round launch on tiles, where one lane in n would work, is not what a single activation
-  // wants); the kernels of least squares and logistic regression skip the rounds of nodes that are not active.
+  // A stretch of iterations drawn by one launch, then, for the separable objective, up to kResolveAhead of them per launch
+  // (not on tiles in LDS, where one lane in n would work); the kernels of least squares and logistic regression skip the rounds of nodes that are not active.
   c->no_tiles = true;
   int rc = RFAST_OK;
   for (int32_t k = 0; k < iterations && rc == RFAST_OK;) {

@@ -27,6 +27,12 @@ constexpr int kThreads = 256;
 // vector load, and would form every address and branch per lane).
 __device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// An element of the graph or of the round's plan.  No kernel here writes these, which the compiler cannot see past the
+// stores of the state; said through the address space they are scalar loads wherever the index is uniform.
+template <class T> __device__ inline T fixed(const T* p) {
+  return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
 // Loads of one live in-edge of C (plan word pl): the running sum being consumed and the one
 // consumed last time (rho~ of S4), which is read from the sender's ring while it is still there.
 template <int VEC>
@@ -64,11 +70,15 @@ __device__ inline void emit_bf16_blocked(const RfastDev& s, int i, int tile, typ
 // KB: in-edge loads kept in flight per phase.  8 costs 139 registers (3 wavefronts per SIMD), 4 costs
 // 91 (5 wavefronts): graphs with many in-edges per node want the deeper batch, graphs with few want
 // the wavefronts (measured: bidirectional ring 1.53 vs 1.59 ms with 8 vs 4, tree/star 0.293 vs 0.274).
-template <int MODE, int VEC, bool MOM, int KB>
+template <int MODE, int VEC, bool MOM, int KB, bool MANY = false>
 __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, int tile, int64_t k) {
   using T = typename V<VEC>::T;
   constexpr bool kMix = MODE != RFAST_MODE_TRACK, kTrack = MODE != RFAST_MODE_MIX;
   const int i = slot.x;
+  auto at = [](auto* q) {  // (the one-pass kernels have no stores ahead of most of these, and fewer registers to spare)
+    if constexpr (MANY) return fixed(q);
+    else return *q;
+  };
   const int64_t p = s.p;
   const int M = s.M;
   const int t_old = slot.y;
@@ -77,11 +87,11 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
   const size_t node_off = (size_t)i * p + k;
   float* g_old_p = s.g + (size_t)(t_old & 1) * s.n * p + node_off;
   float* g_new_p = s.g + (size_t)((t_old + 1) & 1) * s.n * p + node_off;
-  const int re0 = s.r_ptr[i], re1 = s.r_ptr[i + 1];
-  const int ce0 = s.c_ptr[i], ce1 = s.c_ptr[i + 1];
+  const int re0 = at(s.r_ptr + i), re1 = at(s.r_ptr + i + 1);
+  const int ce0 = at(s.c_ptr + i), ce1 = at(s.c_ptr + i + 1);
   // The running sums of S2c share one factor per sender: rho_li = a_li * sigma_i with
   // sigma_i = sum of every z_half node i produced (1 read + 1 write instead of dO + dO).
-  const bool pushes = s.co_ptr[i + 1] > s.co_ptr[i];
+  const bool pushes = at(s.co_ptr + i + 1) > at(s.co_ptr + i);
 
   // ---- every load of the first batch of each phase is issued before its first use:
   //      with few wavefronts per CU this is what keeps enough bytes in flight
@@ -89,7 +99,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
   T vb[KB], sg[KB], rt[KB];
   float vw[KB], ca[KB];
   int pl[KB];  // plan words of the C in-edges of the current batch (0: nothing to do)
-  const bool spills = pushes && s.node_spill[i] == t_old + 1;
+  const bool spills = pushes && at(s.node_spill + i) == t_old + 1;
   z_i = V<VEC>::ld(s.z + node_off);
   if (kMix) {
     x_i = V<VEC>::ld(s.x + node_off);
@@ -97,8 +107,8 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
 #pragma unroll
     for (int q = 0; q < KB; ++q)
       if (re0 + q < re1) {
-        vb[q] = V<VEC>::ld(s.v_ring + ((size_t)s.r_src[re0 + q] * M + s.slot_r[re0 + q]) * p + k);
-        vw[q] = s.r_w[re0 + q];
+        vb[q] = V<VEC>::ld(s.v_ring + ((size_t)at(s.r_src + re0 + q) * M + at(s.slot_r + re0 + q)) * p + k);
+        vw[q] = at(s.r_w + re0 + q);
       }
   }
   if (kTrack) {
@@ -113,10 +123,10 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
 #pragma unroll
     for (int q = 0; q < KB; ++q) {
       const int e = ce0 + q;
-      pl[q] = e < ce1 ? s.plan_c[e] : 0;
+      pl[q] = e < ce1 ? at(s.plan_c + e) : 0;
       if (pl[q] & (1 << 16)) {
-        load_edge<VEC>(s, e, s.c_src[e], pl[q], M, p, k, &sg[q], &rt[q]);
-        ca[q] = s.c_w[e];
+        load_edge<VEC>(s, e, at(s.c_src + e), pl[q], M, p, k, &sg[q], &rt[q]);
+        ca[q] = at(s.c_w + e);
       }
     }
   }
@@ -131,19 +141,19 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
     }
     const T v = fma_s(-gamma, dir, x_i);
     // S2a: pull the stamped neighbour copies and mix with row-stochastic weights
-    x_new = mul_s(s.r_self[i], v);
+    x_new = mul_s(at(s.r_self + i), v);
 #pragma unroll
     for (int q = 0; q < KB; ++q)
       if (re0 + q < re1) x_new = fma_s(vw[q], vb[q], x_new);
     if (re0 + KB < re1) {  // in-degree above one batch: what the loads of a batch need is read during the batch before
-      int src[KB], at[KB];
+      int src[KB], ver[KB];
       auto look = [&](int eb) {  // (past the last edge: the last one, which is not used)
 #pragma unroll
         for (int q = 0; q < KB; ++q) {
           const int e = eb + q < re1 ? eb + q : re1 - 1;
-          src[q] = s.r_src[e];
-          at[q] = s.slot_r[e];
-          vw[q] = s.r_w[e];
+          src[q] = at(s.r_src + e);
+          ver[q] = at(s.slot_r + e);
+          vw[q] = at(s.r_w + e);
         }
       };
       look(re0 + KB);
@@ -151,7 +161,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
         float w_now[KB];
 #pragma unroll
         for (int q = 0; q < KB; ++q) {
-          if (eb + q < re1) vb[q] = V<VEC>::ld(s.v_ring + ((size_t)uniform(src[q]) * M + uniform(at[q])) * p + k);
+          if (eb + q < re1) vb[q] = V<VEC>::ld(s.v_ring + ((size_t)uniform(src[q]) * M + uniform(ver[q])) * p + k);
           w_now[q] = vw[q];
         }
         look(eb + KB);
@@ -193,9 +203,9 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
 #pragma unroll
       for (int q = 0; q < KB; ++q) {
         const int e = eb + q < ce1 ? eb + q : ce1 - 1;
-        src[q] = s.c_src[e];
-        pl[q] = eb + q < ce1 ? s.plan_c[e] : 0;
-        ca[q] = s.c_w[e];
+        src[q] = at(s.c_src + e);
+        pl[q] = eb + q < ce1 ? at(s.plan_c + e) : 0;
+        ca[q] = at(s.c_w + e);
       }
     };
     look(ce0 + KB);
@@ -220,7 +230,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
   z_half = sub(add(z_half, g_new), g_old);
 
   // S2c: keep a_ii; push: sigma_i grows by z_half.  S3 (rho half): new version t+1
-  V<VEC>::st(s.z + node_off, mul_s(s.c_self[i], z_half));
+  V<VEC>::st(s.z + node_off, mul_s(at(s.c_self + i), z_half));
   if (pushes) {
     V<VEC>::st(s.sigma_ring + ((size_t)i * M + slot_new) * p + k, add(sig_cur, z_half));
     // S4 for receivers that do not do it themselves in this round: version t - D of this node's
@@ -228,8 +238,8 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
     // version gets it copied to the rho~ array now (the slot read here is not the one written above).
     if (spills) {
       const T leaving = V<VEC>::ld(s.sigma_ring + ((size_t)i * M + (t_old - (M - 2)) % M) * p + k);
-      for (int o = s.co_ptr[i]; o < s.co_ptr[i + 1]; ++o)
-        if (s.plan_c[s.co_eid[o]] & (1 << 18)) V<VEC>::st(s.rho_tilde + (size_t)s.co_eid[o] * p + k, mul_s(s.co_w[o], leaving));
+      for (int o = at(s.co_ptr + i); o < at(s.co_ptr + i + 1); ++o)
+        if (at(s.plan_c + at(s.co_eid + o)) & (1 << 18)) V<VEC>::st(s.rho_tilde + (size_t)at(s.co_eid + o) * p + k, mul_s(at(s.co_w + o), leaving));
     }
   }
 }
@@ -241,6 +251,28 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
   if (slot.x < 0) return;
   const int tile = blockIdx.x - a * tiles_per_node;
   each_group<VEC>(tile, s.p, [&](auto vec, int64_t k) { state_update<MODE, decltype(vec)::value, MOM, KB>(s, gamma, slot, tile, k); });
+}
+
+// Consecutive iterations of the event-driven mode, one active node each.  A pass over one node's vectors is bound by
+// memory, but the next iterations read much of it again (this node's neighbours read the versions it has just written), so
+// a lane takes its coordinates through all of the iterations: nothing of theirs depends on another coordinate, and
+// what the coordinates under way touch stays in the caches.  16 nodes of a mesh, p 1e6: 15.1 us per iteration as a launch
+// of its own, 8.1 this way (bound by the caches behind L2: 72 MB per iteration); 11 nodes, p 144988: 7.0 -> 3.2.
+template <int VEC, bool MOM, int KB>
+__global__ void __launch_bounds__(kThreads) rfast_events_kernel(RfastDev s, float gamma, int rounds, size_t set_bytes) {
+  auto next = [&](auto*& q) { q = reinterpret_cast<std::remove_reference_t<decltype(q)>>(reinterpret_cast<char*>(q) + set_bytes); };
+  each_group<VEC>(blockIdx.x, s.p, [&](auto vec, int64_t k) {
+    RfastDev r = s;
+    for (int q = 0; q < rounds; ++q) {
+      for (int a = 0; a < s.n; ++a) {
+        const unsigned long long w = fixed(reinterpret_cast<const unsigned long long*>(r.active_plan + a));
+        const int2 slot = make_int2((int)(unsigned)w, (int)(w >> 32));
+        if (slot.x < 0) break;
+        state_update<RFAST_MODE_FUSED, decltype(vec)::value, MOM, KB, true>(r, gamma, slot, 0, k);
+      }
+      next(r.active_plan); next(r.slot_r); next(r.plan_c); next(r.node_spill);
+    }
+  });
 }
 
 // Writes the current sample of every node, g_i = sample(x_i, t_i), into g[t_i & 1][i]: the
@@ -481,6 +513,25 @@ hipError_t rfast_launch_rebase(rfast_ctx* c) {
   else
     hipLaunchKernelGGL(rfast_rebase_kernel<5>, dim3(gx, d.n), dim3(kThreads), 0, c->stream, d);
   return hipGetLastError();
+}
+
+hipError_t rfast_launch_events(rfast_ctx* c, float gamma, int rounds) {
+  const RfastDev& d = c->d;
+  auto go = [&](auto vec, auto mom, int64_t blocks) {
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    // (loads in batches of four: eight cost more registers than they hide, 2636 -> 3143 us over 200 iterations)
+    hipLaunchKernelGGL((rfast_events_kernel<decltype(vec)::value, decltype(mom)::value, 4>), dim3((unsigned)blocks), dim3(kThreads),
+                       0, c->stream, d, gamma, rounds, c->plan_set_bytes);
+    return hipGetLastError();
+  };
+  auto with = [&](auto vec, int64_t blocks) {
+    return d.mom ? go(vec, std::integral_constant<bool, true>(), blocks) : go(vec, std::integral_constant<bool, false>(), blocks);
+  };
+  // Four coordinates per lane as soon as that leaves a wavefront for every compute unit (p 1e6: 2124 us against 2636
+  // with one), one per lane below (p 45746: 68 against 71).
+  if (d.p < 65536) return with(std::integral_constant<int, 1>(), (d.p + kThreads - 1) / kThreads);
+  if (d.p % 4 == 0) return with(std::integral_constant<int, 4>(), group_tiles(d.p));
+  return with(std::integral_constant<int, 5>(), group_tiles(d.p));
 }
 
 hipError_t rfast_launch_state(rfast_ctx* c, int mode, float gamma) {
