@@ -358,7 +358,8 @@ hipError_t launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int rou
 
 // The workgroups of a team launch wait for each other, so they must all become resident: two such launches that each
 // hold a part of the chip would wait forever.  Launches on one stream follow each other; a launch on another stream
-// than the last one first waits for what that stream holds.
+// than the last one first waits for the event recorded behind that one.  (Behind the launch and not when the next one
+// comes: the other stream may by then be under capture or gone.)
 struct TeamOrder {
   bool used = false;
   hipStream_t stream = nullptr;
@@ -371,17 +372,14 @@ template <class Launch> hipError_t in_team_order(rfast_ctx* c, Launch launch) {
   if (c->device < 0 || c->device >= 64) return hipErrorInvalidDevice;
   const std::lock_guard<std::mutex> lock(g_team_mutex);
   TeamOrder& o = g_team_order[c->device];
-  if (o.used && o.stream != c->stream) {
-    hipError_t e = hipSuccess;
-    if (!o.event) e = hipEventCreateWithFlags(&o.event, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(o.event, o.stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, o.event, 0);
-    if (e != hipSuccess) return e;
-  }
-  const hipError_t e = launch();
+  hipError_t e = hipSuccess;
+  if (!o.event) e = hipEventCreateWithFlags(&o.event, hipEventDisableTiming);
+  if (e == hipSuccess && o.used && o.stream != c->stream) e = hipStreamWaitEvent(c->stream, o.event, 0);
+  if (e == hipSuccess) e = launch();
+  if (e != hipSuccess) return e;
   o.used = true;
   o.stream = c->stream;
-  return e;
+  return hipEventRecord(o.event, c->stream);
 }
 
 // the context's stream has been waited for and is about to be given up

@@ -19,6 +19,13 @@ __device__ inline u64 get64(const u64* p) { return __hip_atomic_load(p, __ATOMIC
 __device__ inline void put_f(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float get_f(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// Everything this wavefront has loaded or stored so far is done, and nothing below is moved above it.
+__device__ inline void drain() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0);
+  asm volatile("" ::: "memory");
+}
+
 __device__ inline int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 __device__ inline float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
 

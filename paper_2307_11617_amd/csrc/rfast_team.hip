@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
             put_f(own_v + kOwn * e, v[e]);
             put_f(own_z + kOwn * e, z[e]);
           }
-        __builtin_amdgcn_s_waitcnt(0);
+        drain();
         if (lane == 0) put32(flag_of(i, 0), a.base + (unsigned)(q + 1));
         wait2(lane < dR ? flag_of(r_src, 0) : nullptr, q + 1, lane < dI ? flag_of(c_src, 0) : nullptr, q + 1);
       }
@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     if (active) {
       float4* const tile = tiles + (a.buffers > 1 && parity ? B * Q : 0);        // TILE: the rows of this round
       float4* const tile_next = tiles + (a.buffers > 1 && !parity ? B * Q : 0);  // ... and of the next active one
-      if (TILE && !owner) __builtin_amdgcn_s_waitcnt(0);  // the rows on their way into LDS have arrived
+      if (TILE && !owner) drain();  // the rows on their way into LDS have arrived
       __syncthreads();  // the mixed x and the sampled rows are in LDS
       // ---- gradient, rows: eight (four) rows per wavefront at a time; lane c sums coordinates 4c .. 4c+3 (+ 256 m) of the
       // chunk, and the lanes' sums are added as a butterfly from distance 32 down to 1 whose first steps halve the rows
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       }
       // the loads above were issued after the stores of v and have returned: v is out
       if (owner && !SYNC) {
-        __builtin_amdgcn_s_waitcnt(0);
+        drain();
         if (lane == 0) put32(flag_of(i, 0), done_word);
       }
       __syncthreads();  // residuals, and the row numbers of the next active round
@@ -568,7 +568,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         for (int e = 0; e < kE; ++e)
           if (has[e]) saved[kOwn * e] = wt * get_f(ring + kOwn * e);
       }
-      __builtin_amdgcn_s_waitcnt(0);
+      drain();
       if (lane == 0) {
         if (!active) put32(flag_of(i, 0), done_word);
         put32(flag_of(i, 1), done_word);

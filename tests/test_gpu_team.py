@@ -114,6 +114,34 @@ def test_two_streams():
     _same(gpus[0], gpus[1], "streams")
 
 
+def test_last_stream_under_capture():
+    """The stream of the last team launch is being captured by the program while a context on another stream launches:
+    the library's ordering of the two must not reach into the capture."""
+    w = _workload("several_chunks_ragged")
+    gpus, streams = [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for s in streams:
+        with torch.cuda.stream(s):
+            g = harness.make_gpu(w)
+            g.init(None, w.sched.initial_batch())
+            gpus.append(g)
+    st, dev = harness.upload_chunk(gpus[0], w, 0, 40)
+    buf = torch.zeros(64, device=gpus[0].device)
+    torch.cuda.synchronize()
+    sched = [dev[k] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")]
+    gpus[0].run(40, *sched, w.gamma, dev["batch_idx"])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=streams[0], capture_error_mode="relaxed"):
+        buf.add_(1.0)
+        gpus[1].run(40, *sched, w.gamma, dev["batch_idx"])
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert (buf == 3.0).all()
+    for g in gpus:
+        g.check()
+    _same(gpus[0], gpus[1], "captured")
+
+
 # graph, n, d, K, samples, batch, momentum: feature tiles per chunk, ragged last chunk, class counts, rows per workgroup
 SOFTMAX = {
     "one_tile_chunks": ("exponential", 12, 512, 32, 256, 64, 0.9),
