@@ -359,7 +359,7 @@ hipError_t launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int rou
 // The workgroups of a team launch wait for each other, so they must all become resident: two such launches that each
 // hold a part of the chip would wait forever.  Launches on one stream follow each other; a launch on another stream
 // than the last one first waits for the event recorded behind that one.  (Behind the launch and not when the next one
-// comes: the other stream may by then be under capture or gone.)
+// comes: the other stream may by then be gone.)
 struct TeamOrder {
   bool used = false;
   hipStream_t stream = nullptr;
@@ -485,12 +485,20 @@ void context_gone() {
 }
 
 // A captured launch would be replayed with the progress words of its capture, so captured rounds take the chain; so do
-// profiled ones, whose state and gradient kernels are to be timed apart.
+// profiled ones, whose state and gradient kernels are to be timed apart, and rounds that would have to wait for a stream
+// that is under capture just now (the runtime allows no such dependency, whatever the event was recorded behind).
 bool team_usable(const rfast_ctx* c) {
   if (!c->use_blocks || c->team.W <= 0 || c->capturing || c->profiling) return false;
   if (c->stream != nullptr) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
+  }
+  if (c->device < 0 || c->device >= 64) return false;
+  const std::lock_guard<std::mutex> lock(g_team_mutex);
+  const TeamOrder& o = g_team_order[c->device];
+  if (o.used && o.stream != c->stream && o.stream != nullptr) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(o.stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
   }
   return true;
 }
