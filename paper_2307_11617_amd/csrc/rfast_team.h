@@ -62,15 +62,18 @@ __device__ inline void report_wait(const RfastDev& s, int round0, int i) {
   }
 }
 
+// A progress word read ahead of the wait for it (an absent one, or one that need not be waited for, reads as round 0).
+__device__ inline unsigned peek(const TeamArgs& a, const unsigned* f, int need) { return f != nullptr && need > 0 ? get32(f) : a.base; }
+
 // Waits until the progress words of the lanes that have one (f1, f2, or neither) are at least round `need` of the launch
-// whose rounds count from `base`.  dead: an earlier wait has run out, and nothing waits any more.
+// whose rounds count from `base`.  v1, v2: the words as read ahead (a.base: not read); where they say enough, the wait
+// costs no trip through memory.  dead: an earlier wait has run out, and nothing waits any more.
 __device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int i, const unsigned* f1, int need1, const unsigned* f2,
-                                     int need2, bool* dead) {
+                                     int need2, unsigned v1, unsigned v2, bool* dead) {
   if (need1 <= 0) f1 = nullptr;
   if (need2 <= 0) f2 = nullptr;
   if (!__any(f1 != nullptr || f2 != nullptr) || *dead) return;
   for (int spin = 0;; ++spin) {
-    const unsigned v1 = f1 ? get32(f1) : 0, v2 = f2 ? get32(f2) : 0;
     const bool ok = (!f1 || (int)(v1 - a.base) >= need1) && (!f2 || (int)(v2 - a.base) >= need2);
     if (__all(ok)) break;
     if (spin > kSpin) {
@@ -78,6 +81,8 @@ __device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int i
       report_wait(s, a.round0, i);
       break;
     }
+    v1 = f1 ? get32(f1) : 0;
+    v2 = f2 ? get32(f2) : 0;
   }
   // what the words stand for was stored before them; nothing below may be loaded before they were seen
   asm volatile("" ::: "memory");

@@ -31,8 +31,8 @@
 // chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
-// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.8; 32 nodes, p = 4096,
-// batch 64: 21.2 -> 9.2; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 8.8; one agent of 55 per
+// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.6; 32 nodes, p = 4096,
+// batch 64: 21.2 -> 9.2; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.9; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
 #include <type_traits>
@@ -152,7 +152,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     }
 
   bool dead = false;  // a wait has run out
-  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2) { wait_progress(s, a, i, f1, need1, f2, need2, &dead); };
+  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2, unsigned v1, unsigned v2) {
+    wait_progress(s, a, i, f1, need1, f2, need2, v1, v2, &dead);
+  };
 
   // ---- rows
   auto fetch_rows = [&](int q, int* to) {
@@ -233,6 +235,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     }
   }
 
+  unsigned seen_r = a.base, seen_d = a.base;  // the words that the next mix waits for, as read ahead
   while (q < rounds) {
     const int q_next = next_event(q + 1);
     const unsigned done_word = a.base + (unsigned)(q_next < rounds ? q_next : rounds);
@@ -244,8 +247,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     dead = __any(dead);
     if (owner && active) {
       // ---- S1, S2a, S3 (v half)
-      if (!SYNC) wait2(lane < dR ? flag_of(r_src, 0) : nullptr, rneed, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1);
-      else wait2(lane < dRo ? flag_of(r_dst, 0) : nullptr, q, lane < dCo ? flag_of(c_dst, 0) : nullptr, q);
+      if (!SYNC) wait2(lane < dR ? flag_of(r_src, 0) : nullptr, rneed, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1, seen_r, seen_d);
+      else wait2(lane < dRo ? flag_of(r_dst, 0) : nullptr, q, lane < dCo ? flag_of(c_dst, 0) : nullptr, q, seen_r, seen_d);
       float v[kE], xn[kE];
 #pragma unroll
       for (int e = 0; e < kE; ++e) {
@@ -265,7 +268,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
           }
         drain();
         if (lane == 0) put32(flag_of(i, 0), a.base + (unsigned)(q + 1));
-        wait2(lane < dR ? flag_of(r_src, 0) : nullptr, q + 1, lane < dI ? flag_of(c_src, 0) : nullptr, q + 1);
+        wait2(lane < dR ? flag_of(r_src, 0) : nullptr, q + 1, lane < dI ? flag_of(c_src, 0) : nullptr, q + 1, a.base, a.base);
       }
       for (int e0 = 0; e0 < dR; e0 += KB) {
         float vb[KB][kE];
@@ -299,6 +302,11 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       float4* const tile_next = tiles + (a.buffers > 1 && !parity ? B * Q : 0);  // ... and of the next active one
       if (TILE && !owner) drain();  // the rows on their way into LDS have arrived
       __syncthreads();  // the mixed x and the sampled rows are in LDS
+      unsigned seen_c = a.base, seen_o = a.base;  // the words that the running sums wait for travel during the dot products
+      if (owner && !SYNC) {
+        seen_c = peek(a, lane < dI ? flag_of(c_src, 1) : nullptr, cneed);
+        seen_o = peek(a, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+      }
       // ---- gradient, rows: eight (four) rows per wavefront at a time; lane c sums coordinates 4c .. 4c+3 (+ 256 m) of the
       // chunk, and the lanes' sums are added as a butterfly from distance 32 down to 1 whose first steps halve the rows
       const int* rows = rowi + (parity ? B : 0);
@@ -375,7 +383,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       const int qa = next_active(q + 1);
       if (owner) {
         if (!SYNC) {
-          wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+          wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1, seen_c, seen_o);
 #pragma unroll
           for (int u = 0; u < KB; ++u)
             if (u < dI) {
@@ -393,6 +401,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
               }
             }
         } else {
+          seen_r = peek(a, lane < dRo ? flag_of(r_dst, 0) : nullptr, q + 1);
+          seen_d = peek(a, lane < dCo ? flag_of(c_dst, 0) : nullptr, q + 1);
 #pragma unroll
           for (int u = 0; u < KB; ++u)
             if (u < dI) {
@@ -557,7 +567,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     if (owner && !SYNC) {
       // S4 for buffers whose version leaves the sender's ring in this round without being consumed
       u64 leaving = __ballot(lane < dI && (cword & (1 << 18)));
-      if (!active && leaving) wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, nullptr, 0);
+      if (!active && leaving) wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, nullptr, 0, a.base, a.base);
       while (leaving) {
         const int u = __ffsll((long long)leaving) - 1;
         leaving &= leaving - 1;
@@ -568,6 +578,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         for (int e = 0; e < kE; ++e)
           if (has[e]) saved[kOwn * e] = wt * get_f(ring + kOwn * e);
       }
+      // the words that the next mix waits for are read on the trip that the stores take anyway
+      seen_r = peek(a, lane < dR ? flag_of(r_src, 0) : nullptr, q_next - clamped(rd_n));
+      seen_d = peek(a, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1);
       drain();
       if (lane == 0) {
         if (!active) put32(flag_of(i, 0), done_word);

@@ -16,7 +16,12 @@
 //
 // The partial logits are rounded to fp32 per chunk where the one-kernel form keeps one accumulator over all features;
 // nothing else differs from rfast_softmax.hip.  Measured, us per round, before (four kernels) and now: 16 nodes, d 512,
-// K 32, batch 64, heavy-ball buffer: 33.6 -> 15.6; one agent of 16 per iteration, d 192: 20.6 -> 5.0.
+// K 32, batch 64, heavy-ball buffer: 33.6 -> 13.5; one agent of 16 per iteration, d 192: 20.6 -> 5.0.
+//
+// What bounds it is the chain of trips through memory in the wavefronts that own tiles, so everything else is kept out of
+// them as long as there are others (15.7 -> 13.5 us per round in the first case): the forward product, the softmax, row
+// numbers and rows of the next round go to the wavefronts without a tile first; the barrier for the weights does not
+// wait for the stores of v; progress words are read ahead on trips that are made anyway.
 #include "rfast_team.h"
 
 namespace {
@@ -53,8 +58,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   u16* const wt = xt + a.buffers * x_elems(B, FT);                           // [K][Fc + kPad]
   u16* const et = wt + wt_elems(K, FT);                                      // [K][B + kPad]
   int* const rowi = reinterpret_cast<int*>(et + et_elems(K, B));             // [2][B] sampled rows of this active round and the next
-  int* const labs = rowi + 2 * B;                                            // [R] labels of the workgroup's rows
-  int* const nodew = labs + R;                                               // [kBlockRounds] node words
+  int* const nodew = rowi + 2 * B;                                             // [kBlockRounds] node words
   const int ftw = wave / KT, kt = wave - ftw * KT;                           // the wavefront's tile
   const bool owner = ftw < FTw;
   const u16* const pool = (const u16*)s.prob.data0 + (size_t)i * s.prob.samples * d + 32 * ft0;
@@ -108,7 +112,9 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
     }
   }
   bool dead = false;
-  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2) { wait_progress(s, a, i, f1, need1, f2, need2, &dead); };
+  auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2, unsigned v1, unsigned v2) {
+    wait_progress(s, a, i, f1, need1, f2, need2, v1, v2, &dead);
+  };
 
   // ---- rows of X into LDS, straight from memory: 16-byte piece q of the tile is piece pos = q mod nc of row q / nc and
   // holds features 8 c .. 8 c + 7 of the chunk, c = pos ^ swz(row), so that the 32 rows that an operand of the forward
@@ -116,9 +122,12 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   const int nc_sh = 2 + (FT == 1 ? 0 : FT == 2 ? 1 : FT == 4 ? 2 : 3);
   const int sw_sh = nc_sh >= 4 ? 0 : 4 - nc_sh, sw_mask = nc < 16 ? nc - 1 : 15;
   auto swz = [&](int b) { return (b >> sw_sh) & sw_mask; };
+  // Wavefronts without a tile fetch them, if there are any: loads return in order, and one that polls would poll behind
+  // the rows.
+  const int busy = FTw * KT < kWaves ? FTw * KT : 0, idle = kWaves - busy;
   auto load_x = [&](const int* rows, u16* dst) {
-    const int total = B << nc_sh;
-    for (int q0 = 64 * wave; q0 < total; q0 += kTeamThreads) {
+    const int total = wave >= busy ? B << nc_sh : 0;
+    for (int q0 = 64 * (wave - busy); q0 < total; q0 += 64 * idle) {
       const int q = q0 + lane;
       const int b = q >> nc_sh, c = (q & (nc - 1)) ^ swz(b);
       if (q < total && c < 4 * FTw) {
@@ -132,7 +141,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   auto next_active = [&](int from) { return next_bit(act_mask, from); };
   auto next_event = [&](int from) { return next_bit(ev_mask, from); };
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, i, q, b, w == 0);
+    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, i, q, b, w == 0);
   };
   int parity = 0;
   {
@@ -157,6 +166,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
       put32(flag_of(i, 1), a.base + (unsigned)(q < rounds ? q : rounds));
     }
   }
+  unsigned seen_r = a.base, seen_d = a.base;  // the words that the next mix waits for, as read ahead
   const unsigned r_magic = 0xFFFFFFFFu / (unsigned)R;
   u64* const e_packets = a.packets + (size_t)2 * n * W * W * R * K;  // behind the partial logits
 
@@ -172,7 +182,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
     float z_half[16];
     if (owner && active) {
       // ---- S1, S2a, S3 (v half)
-      wait2(lane < dR ? flag_of(r_src, 0) : nullptr, rneed, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1);
+      wait2(lane < dR ? flag_of(r_src, 0) : nullptr, rneed, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1, seen_r, seen_d);
       float vn[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -209,6 +219,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
         pk.y = rfast_f32_to_bf16(x[v + 2]) | ((uint32_t)rfast_f32_to_bf16(x[v + 3]) << 16);
         *reinterpret_cast<uint2*>(to + 2 * v) = pk;
       }
+      drain();  // (rows that this wavefront fetched are in LDS; the loads of the mix were issued behind them)
 #pragma unroll
       for (int v = 0; v < 16; ++v) put_f(own_v + step(v) + at, vn[v]);
     }
@@ -217,11 +228,19 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
       const u16* X = xt + (a.buffers > 1 && parity ? x_elems(B, FT) : 0);
       u16* X_next = xt + (a.buffers > 1 && !parity ? x_elems(B, FT) : 0);
       const int qa = next_active(q + 1);
-      drain();  // the rows on their way into LDS have arrived (and v is out)
-      if (owner && lane == 0) put32(flag_of(i, 0), done_word);
+      if (!owner) drain();  // the rows on their way into LDS have arrived
       __syncthreads();  // weights and rows are in LDS
+      const int back = kWaves - 1 - wave;  // forward and softmax: the wavefronts without a tile first
+      unsigned seen_c = a.base, seen_o = a.base;
+      if (owner) {
+        // v is out; the words that the running sums wait for are read on the same trip
+        seen_c = peek(a, lane < dI ? flag_of(c_src, 1) : nullptr, cneed);
+        seen_o = peek(a, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+        drain();
+        if (lane == 0) put32(flag_of(i, 0), done_word);
+      }
       // ---- forward: partial logits, 32 rows x 32 classes at a time
-      for (int tl = wave; tl < (B / 32) * KT; tl += kWaves) {
+      for (int tl = back; tl < (B / 32) * KT; tl += kWaves) {
         const int bt = tl / KT, k2 = tl - bt * KT;
         f32x16 acc;
 #pragma unroll
@@ -245,22 +264,9 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           put64(base + ((size_t)dest * W * R + (bb - dest * R)) * K, (u64)tag << 32 | __float_as_uint(acc[v]));
         }
       }
-      if (tid < r1 - r0) {
-        int lab = labels[sampled ? rows[r0 + tid] : r0 + tid];
-        if (lab < 0 || lab >= K) {  // clamped and reported, like a sample row
-          if (atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
-            s.err[1] = a.round0 + q;
-            s.err[2] = 3;
-            s.err[3] = i;
-          }
-          lab = lab < 0 ? 0 : K - 1;
-        }
-        labs[tid] = lab;
-      }
-      if (sampled && qa < rounds) fetch_rows(qa, rowi + (parity ? 0 : B));
       // ---- S2b without the gradient, S4: z + sum over the in-edges of C, two live edges at a time
       if (owner) {
-        wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+        wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1, seen_c, seen_o);
 #pragma unroll
         for (int v = 0; v < 16; ++v) z_half[v] = z[v];
         u64 live = __ballot(lane < dI && (cword & (1 << 16)));
@@ -302,12 +308,12 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
         }
         fetch_plan(q_next);
       }
-      __syncthreads();  // labels
       // ---- softmax of the workgroup's rows: K lanes (two classes per lane above 64) per row
       {
         constexpr int G = K <= 32 ? 32 : 64, PL = K > 64 ? 2 : 1;  // lanes of a row, classes of a lane
         const int per = 64 / G, gl = lane & (G - 1);
-        for (int r = r0 + wave * per + lane / G; r < r1; r += kWaves * per) {
+        for (int r = r0 + back * per + lane / G; r < r1; r += kWaves * per) {
+          int lab = labels[sampled ? rows[r] : r];
           float lg[PL];
           const u64* src = a.packets + (((size_t)parity * n + i) * W + w) * W * R * K + (size_t)(r - r0) * K + gl;
 #pragma unroll
@@ -351,7 +357,14 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
 #pragma unroll
           for (int o = G / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
           const float inv = 1.0f / sum;
-          const int lab = labs[r - r0];
+          if (lab < 0 || lab >= K) {  // clamped and reported, like a sample row
+            if (gl == 0 && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
+              s.err[1] = a.round0 + q;
+              s.err[2] = 3;
+              s.err[3] = i;
+            }
+            lab = lab < 0 ? 0 : K - 1;
+          }
 #pragma unroll
           for (int u = 0; u < PL; ++u) {
             const int k = gl + 64 * u;
@@ -362,6 +375,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           }
         }
       }
+      if (sampled && qa < rounds) fetch_rows(qa, rowi + (parity ? 0 : B));  // while E travels
       // ---- E of all rows, class-major into LDS
       {
         const u64* src = e_packets + ((size_t)parity * n + i) * B * (K / 2);
@@ -441,7 +455,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
     if (owner) {
       // S4 for buffers whose version leaves the sender's ring in this round without being consumed
       u64 leaving = __ballot(lane < dI && (cword & (1 << 18)));
-      if (!active && leaving) wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, nullptr, 0);
+      if (!active && leaving) wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, nullptr, 0, a.base, a.base);
       while (leaving) {
         const int e = __ffsll((long long)leaving) - 1;
         leaving &= leaving - 1;
@@ -454,6 +468,9 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
 #pragma unroll
         for (int v = 0; v < 16; ++v) put_f(saved + step(v) + at, ce * val[v]);
       }
+      // the words that the next mix waits for are read on the trip that the stores take anyway
+      seen_r = peek(a, lane < dR ? flag_of(r_src, 0) : nullptr, q_next - clamped(rd_n));
+      seen_d = peek(a, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1);
       drain();
       if (lane == 0) {
         if (!active) put32(flag_of(i, 0), done_word);
@@ -477,8 +494,8 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   }
 }
 
-size_t softmax_lds(const rfast_problem* prob, int B, int FT, int W, int buffers) {
-  return 2 * (buffers * x_elems(B, FT) + wt_elems(prob->K, FT) + et_elems(prob->K, B)) + ((size_t)2 * B + (B + W - 1) / W + kBlockRounds) * 4;
+size_t softmax_lds(const rfast_problem* prob, int B, int FT, int buffers) {
+  return 2 * (buffers * x_elems(B, FT) + wt_elems(prob->K, FT) + et_elems(prob->K, B)) + ((size_t)2 * B + kBlockRounds) * 4;
 }
 
 int rows_per_gradient(const rfast_problem* prob) { return prob->batch > 0 ? prob->batch : prob->samples; }
@@ -492,7 +509,7 @@ hipError_t launch(rfast_ctx* c, const TeamArgs& a) {
     raised = true;
   }
   hipLaunchKernelGGL((rfast_team_softmax_kernel<KT, MOM>), dim3((unsigned)(c->d.n * a.W)), dim3(kTeamThreads),
-                     softmax_lds(&c->d.prob, a.B, a.C, a.W, a.buffers), c->stream, c->d, a);
+                     softmax_lds(&c->d.prob, a.B, a.C, a.buffers), c->stream, c->d, a);
   return hipGetLastError();
 }
 template <int KT>
@@ -515,7 +532,7 @@ RfastTeam rfast_team_softmax_shape(const RfastDev& d, int max_degree, int max_ou
     const int W = (DT + FT - 1) / FT;
     if ((int64_t)W * d.n > compute_units || W > B) continue;
     int buffers = 2;
-    while (buffers > 0 && softmax_lds(&d.prob, B, FT, W, buffers) > kTeamLds) --buffers;
+    while (buffers > 0 && softmax_lds(&d.prob, B, FT, buffers) > kTeamLds) --buffers;
     if (buffers == 0) continue;
     const double us = 6.0 + 0.1 * W + 0.5 * FT * KT;
     if (us < best_us) {
