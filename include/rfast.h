@@ -257,7 +257,9 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * rfast_check reports RFAST_EHIP.  While kernels are timed (rfast_profile_enable) or a stream is being captured, and
  * where a team does not fit, a round is two kernels instead of four (p a multiple of 4, no heavy-ball buffer;
  * consecutive rounds): the sampled rows' residuals, then one kernel that forms the gradient, does the tracker update
- * and mixes the same coordinates for the next round; same bits.
+ * and mixes the same coordinates for the next round; same bits.  Stretches too short to pay for the start of a
+ * multi-round launch (one to some rounds, by the sizes) and softmax regression whose rounds are faster as kernels take
+ * the kernels per round as well.
  * on == 0: always one kernel pass per round (four kernels for these objectives).  on == 2: as the default, but
  * 2 rounds are enough at any size (for measurements). */
 int rfast_use_blocks(rfast_ctx* ctx, int32_t on);

@@ -484,7 +484,7 @@ void context_gone() {
   }
 }
 
-// A captured launch would be replayed with the progress words of its capture, so captured rounds take the chain; so do
+// A captured launch would be replayed with the progress words of its capture, so captured rounds take the kernels per round; so do
 // profiled ones, whose state and gradient kernels are to be timed apart, and rounds that would have to wait for a stream
 // that is under capture just now (the runtime allows no such dependency, whatever the event was recorded behind).
 bool team_usable(const rfast_ctx* c) {
@@ -501,6 +501,27 @@ bool team_usable(const rfast_ctx* c) {
     if (hipStreamIsCapturing(o.stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
   }
   return true;
+}
+
+// The fewest rounds of a team launch that are faster than the kernels per round (bit for bit the same for least squares
+// and logistic regression), from both timed side by side.
+// Least squares, logistic: two rounds.  A single one already, unless lanes hold eight coordinates (128 nodes, p 3000:
+// 38 against 30 us) or the sampled rows are less than 1 MB (8 nodes, p 600, batch 16: 20.5 against 18.3).
+// Softmax regression: with R = B / W rows per workgroup a team's round is about 12.5 us + 3 ns R K + 0.85 ns B K (the
+// softmax of its rows, E received by everybody), the four kernels 18 to 35 us.  R K 128 and 512: 16 to 20 against 19
+// to 23 us a round, and about 20 us at its start, even from 5 rounds on; R K 1024, B K 8192: 24.5 against 24.6 with
+// every node active, 21.4 against 23.1 with half of them, even from about 16; beyond (64 nodes, d 64, K 64, batch 128:
+// 34 against 22; 8 nodes, d 1024, K 128, batch 256: 45 against 35) never.  With one agent per iteration only one node
+// pays for that: 3 iterations at any size (two: 0.94 to 1.3 times as fast, six: 1.4 to 2.3).
+int32_t team_least_rounds(const rfast_ctx* c) {
+  const RfastDev& d = c->d;
+  const int64_t B = d.prob.batch > 0 ? d.prob.batch : d.prob.samples;
+  if (c->use_blocks == 2) return 1;
+  if (d.prob.kind != RFAST_OBJ_SOFTMAX_BF16) return c->team.per_lane >= 8 || (double)d.n * (double)B * (double)d.p * 4.0 < 1.0e6 ? 2 : 1;
+  if (c->no_tiles) return 3;
+  const int64_t RK = (B + c->team.W - 1) / c->team.W * d.prob.K;
+  if (RK > 1024 || B * d.prob.K > 8192) return kBlockRounds + 1;
+  return RK <= 512 ? 5 : 16;
 }
 
 // step size of round `round`: gamma * factor^(round div step_rounds)
@@ -890,9 +911,14 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
     const int64_t to_decay = c->gamma_step - now % c->gamma_step;
     if (to_decay < len) len = (int32_t)to_decay;
   }
-  if (gemv) return len;
-  const bool large = (double)c->d.n * (double)c->d.p * 4.0 > 8.0e6;
-  return len >= (large && c->use_blocks != 2 ? kBlockMinRoundsLarge : 2) ? len : 0;
+  if (gemv) return rfast_tiny_eligible(c) || len >= team_least_rounds(c) ? len : 0;
+  // A launch moves every live ring slot, a pass per round only what the round reads: even, timed side by side, from 2
+  // rounds on up to 1 MB per array (rows that start at any address: 3), 3 up to 2 MB, 4 up to 3 MB, 5 up to 8 MB
+  // (2 rounds of 12 nodes, p 50000: 26.6 against 17.8 us; of 30 nodes, p 50000: 51.7 against 26.8).
+  const double bytes = (double)c->d.n * (double)c->d.p * 4.0;
+  int32_t least = bytes > 8.0e6 ? kBlockMinRoundsLarge : bytes > 3.0e6 ? 5 : bytes > 2.0e6 ? 4 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 3 : 2;
+  if (c->use_blocks == 2) least = 2;
+  return len >= least ? len : 0;
 }
 
 // Resolves `len` rounds (schedule arrays of round q at offset q of each pointer) into plan records,

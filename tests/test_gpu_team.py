@@ -40,6 +40,7 @@ def _workload(case):
 def _pair(case):
     w = _workload(case)
     a, b = harness.make_gpu(w), harness.make_gpu(w)
+    rfast_use_blocks(a.ctx, 2)  # stretches of any length
     rfast_use_blocks(b.ctx, False)
     x0 = (0.1 * np.random.default_rng(3).standard_normal((w.n, w.p))).astype(np.float32)
     for g in (a, b):
@@ -160,6 +161,7 @@ def _softmax(case):
     w = configs._mk(case, n, d * K, r, c, 3, gamma, 0, "softmax_bf16", problems.softmax_pool(n, d, K, samples, 4), 0.6, 0.3, 6,
                     batch=batch, samples=samples, burst=3, tol=2e-3, extra={"d": d, "K": K})
     a, b = harness.make_gpu(w), harness.make_gpu(w)
+    rfast_use_blocks(a.ctx, 2)  # stretches of any length
     rfast_use_blocks(b.ctx, False)
     x0 = (0.05 * np.random.default_rng(3).standard_normal((w.n, w.p))).astype(np.float32)
     for g in (a, b):
@@ -197,3 +199,20 @@ def test_softmax_rounds(case):
         g.check()
     _close(a, b, (case, "generated and events"))
 
+
+@pytest.mark.parametrize("softmax,case", [(False, list(CASES)[0]), (True, list(SOFTMAX)[0])])
+def test_forms_alternate(softmax, case):
+    """Stretches by the team, single rounds by the kernels per round and what the library chooses, in turn on one context."""
+    w, a, b = _softmax(case) if softmax else _pair(case)[:3]
+    st, dev = harness.upload_chunk(a, w, 0, 30)
+    for lo, hi, blocks in ((0, 9, 2), (9, 10, 0), (10, 12, 2), (12, 15, 0), (15, 16, 2), (16, 17, 1), (17, 19, 1), (19, 30, 1)):
+        rfast_use_blocks(a.ctx, blocks)
+        for g in (a, b):
+            batch = dev["batch_idx"]
+            g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma,
+                  None if batch is None else batch[lo:hi].contiguous())
+            g.check()
+        if softmax:
+            _close(a, b, (case, hi))
+        else:
+            _same(a, b, (case, hi))
