@@ -531,7 +531,7 @@ RfastTeam rfast_team_softmax_shape(const RfastDev& d, int max_degree, int max_ou
   for (int FT = 1; FT * KT <= kWaves; FT *= 2) {
     const int W = (DT + FT - 1) / FT;
     if ((int64_t)W * d.n > compute_units || W > B) continue;
-    int buffers = 2;
+    int buffers = d.prob.batch > 0 ? 2 : 1;  // two: the rows of the next round arrive during this one (all rows: they stay)
     while (buffers > 0 && softmax_lds(&d.prob, B, FT, buffers) > kTeamLds) --buffers;
     if (buffers == 0) continue;
     const double us = 6.0 + 0.1 * W + 0.5 * FT * KT;

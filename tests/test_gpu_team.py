@@ -151,15 +151,23 @@ SOFTMAX = {
     "many_rows": ("binary_tree", 7, 192, 64, 300, 256, 0.0),
     "eight_feature_tiles": ("bidirectional_ring", 128, 448, 32, 100, 64, 0.9),
     "many_in_edges": ("tree_star", 20, 64, 96, 80, 64, 0.0),
+    # all rows in every round: they stay in LDS, with and without room for a second copy
+    "all_rows": ("exponential", 12, 128, 32, 64, 0, 0.0),
+    "all_rows_several_tiles": ("binary_tree", 6, 256, 64, 128, 0, 0.9),
 }
 
 
-def _softmax(case):
+def _softmax_workload(case):
     graph, n, d, K, samples, batch, momentum = SOFTMAX[case]
     r, c = BUILD[graph](n)
     gamma = 0.05 if graph in ("exponential", "mesh", "bidirectional_ring") else 0.002
-    w = configs._mk(case, n, d * K, r, c, 3, gamma, 0, "softmax_bf16", problems.softmax_pool(n, d, K, samples, 4), 0.6, 0.3, 6,
-                    batch=batch, samples=samples, burst=3, tol=2e-3, extra={"d": d, "K": K})
+    return configs._mk(case, n, d * K, r, c, 3, gamma, 0, "softmax_bf16", problems.softmax_pool(n, d, K, samples, 4), 0.6, 0.3, 6,
+                       batch=batch, samples=samples, burst=3, tol=2e-3, extra={"d": d, "K": K})
+
+
+def _softmax(case):
+    momentum = SOFTMAX[case][-1]
+    w = _softmax_workload(case)
     a, b = harness.make_gpu(w), harness.make_gpu(w)
     rfast_use_blocks(a.ctx, 2)  # stretches of any length
     rfast_use_blocks(b.ctx, False)
@@ -172,10 +180,10 @@ def _softmax(case):
     return w, a, b
 
 
-def _close(a, b, where, tol=2e-3):
+def _close(a, b, where, tol=2e-3, fields=("X", "Z", "G")):
     for f in ("T_NODE", "TAU_R", "TAU_C", "ROUND"):
         assert np.array_equal(a.read(f), b.read(f)), (where, f)
-    for f in ("X", "Z", "G"):
+    for f in fields:
         x, y = a.read(f), b.read(f)
         assert np.isfinite(x).all() and np.linalg.norm(x - y) <= tol * np.linalg.norm(y), (where, f, np.linalg.norm(x - y) / np.linalg.norm(y))
 
@@ -189,7 +197,7 @@ def test_softmax_rounds(case):
     for lo, hi in ((0, 20), (20, 21), (21, 30)):
         for g in (a, b):
             g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma,
-                  dev["batch_idx"][lo:hi].contiguous())
+                  dev["batch_idx"][lo:hi].contiguous() if dev["batch_idx"] is not None else None)
             g.check()
         _close(a, b, (case, hi))
     p_act = torch.full((w.n,), 0.5, dtype=torch.float32)
@@ -200,7 +208,7 @@ def test_softmax_rounds(case):
     _close(a, b, (case, "generated and events"))
 
 
-@pytest.mark.parametrize("softmax,case", [(False, list(CASES)[0]), (True, list(SOFTMAX)[0])])
+@pytest.mark.parametrize("softmax,case", [(False, list(CASES)[0]), (True, list(SOFTMAX)[0]), (True, "all_rows")])
 def test_forms_alternate(softmax, case):
     """Stretches by the team, single rounds by the kernels per round and what the library chooses, in turn on one context."""
     w, a, b = _softmax(case) if softmax else _pair(case)[:3]
