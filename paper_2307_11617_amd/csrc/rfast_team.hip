@@ -28,7 +28,10 @@
 //
 // The arithmetic is, operation for operation, that of rfast_state_kernel<MIX>, rfast_rows_kernel, rfast_cols_kernel and
 // rfast_state_kernel<TRACK> (same bits); rfast_rows_kernel adds a row's terms by the chunks of RfastDev::row_chunk, the
-// chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step.
+// chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step; v goes
+// through slots 0 and 1 of the v ring (slot 0 keeps the last one, as with a kernel per step), z through the two halves of
+// the stored samples, which are in registers during the launch.  The rings of the running sums are not touched: the
+// diagnostics and reads see them as rfast_init left them.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
 // agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.6; 32 nodes, p = 4096,
@@ -116,9 +119,11 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const int ro0 = s.ro_ptr[i], dRo = s.ro_ptr[i + 1] - ro0, co0 = s.co_ptr[i], dCo = s.co_ptr[i + 1] - co0;
   const float r_self = s.r_self[i], c_self = s.c_self[i];
   int r_src = 0, c_src = 0, r_dst = 0, c_dst = 0;
+  int c_par = 0;  // SYNC: of the sender's counter before the launch
   float r_w = 0.f, c_w = 0.f;
   if (lane < dR) { r_src = s.r_src[re0 + lane]; r_w = s.r_w[re0 + lane]; }
   if (lane < dI) { c_src = s.c_src[ce0 + lane]; c_w = s.c_w[ce0 + lane]; }
+  if (SYNC && lane < dI) c_par = s.t[c_src] & 1;
   if (lane < dRo) r_dst = s.r_dst[s.ro_eid[ro0 + lane]];
   if (lane < dCo) c_dst = s.c_dst[s.co_eid[co0 + lane]];
   auto flag_of = [&](int node, int word) { return a.flags + ((size_t)(node * W + w) * kOwnWaves + wave) * kFlagWords + word; };
@@ -243,7 +248,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     const bool active = word < 0;
     const int t_old = SYNC ? t0 + q : word & 0x3FFFFFFF;
     const int rword = rw_n, cword = cw_n, rneed = q - clamped(rd_n), cneed = q - clamped(cd_n);
-    const int slot_new = SYNC ? q & 1 : (t_old + 1) % M;
+    const int slot_new = SYNC ? (rounds - 1 - q) & 1 : (t_old + 1) % M;
     dead = __any(dead);
     if (owner && active) {
       // ---- S1, S2a, S3 (v half)
@@ -259,7 +264,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       }
       float* own_v = s.v_ring + ((size_t)i * M + slot_new) * p + first + tid;
       if (SYNC) {  // everybody's v and z of this step go out before anybody's are read
-        float* own_z = s.sigma_ring + ((size_t)i * M + slot_new) * p + first + tid;
+        // step q takes half (t0 + q) mod 2: the last step's is not the one that the new sample goes to
+        float* own_z = s.g + ((size_t)(t_old & 1) * n + i) * p + first + tid;
 #pragma unroll
         for (int e = 0; e < kE; ++e)
           if (has[e]) {
@@ -406,7 +412,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 #pragma unroll
           for (int u = 0; u < KB; ++u)
             if (u < dI) {
-              const float* src = s.sigma_ring + ((size_t)lane_value(c_src, u) * M + slot_new) * p + first + tid;
+              const float* src = s.g + ((size_t)((lane_value(c_par, u) + q) & 1) * n + lane_value(c_src, u)) * p + first + tid;
 #pragma unroll
               for (int e = 0; e < kE; ++e)
                 if (has[e]) sg[u][e] = get_f(src + kOwn * e);
@@ -504,15 +510,20 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
             for (int u = 0; u < KB; ++u)
               if (e0 + u < dI) {
                 const int pl = SYNC ? 0 : lane_value(cword, e0 + u);
-                if (SYNC || (pl & (1 << 16))) {
+                if (SYNC) {
+                  const float* src = s.g + ((size_t)((lane_value(c_par, e0 + u) + q) & 1) * n + lane_value(c_src, e0 + u)) * p + first + tid;
+#pragma unroll
+                  for (int e = 0; e < kE; ++e)
+                    if (has[e]) sg[u][e] = get_f(src + kOwn * e);
+                } else if (pl & (1 << 16)) {
                   const float* ring = s.sigma_ring + (size_t)lane_value(c_src, e0 + u) * M * p + first + tid;
                   const int prev = (pl >> 8) & 0xFF;
                   const float* saved = s.rho_tilde + (size_t)(ce0 + e0 + u) * p + first + tid;
 #pragma unroll
                   for (int e = 0; e < kE; ++e)
                     if (has[e]) {
-                      sg[u][e] = get_f(ring + (size_t)(SYNC ? slot_new : pl & 0xFF) * p + kOwn * e);
-                      if (!SYNC) rt[u][e] = prev != 0xFF ? get_f(ring + (size_t)prev * p + kOwn * e) : saved[kOwn * e];
+                      sg[u][e] = get_f(ring + (size_t)(pl & 0xFF) * p + kOwn * e);
+                      rt[u][e] = prev != 0xFF ? get_f(ring + (size_t)prev * p + kOwn * e) : saved[kOwn * e];
                     }
                 }
               }
@@ -592,6 +603,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 
   // ---- write-back
   const int t_end = SYNC ? t0 + rounds : s.t[i];
+  // the half of the samples that the new one goes to held z of the step before the last: its receivers are past that
+  // step once they have published the last one
+  if (SYNC && owner && rounds > 1) wait2(nullptr, 0, lane < dCo ? flag_of(c_dst, 0) : nullptr, rounds, a.base, seen_d);
   if (owner && (SYNC ? rounds > 0 : q_prev >= 0)) {
 #pragma unroll
     for (int e = 0; e < kE; ++e)

@@ -91,7 +91,12 @@ def test_synchronous_steps(case):
         for g in (a, b):
             g.sync_run(hi - lo, w.gamma, None if dev["batch_idx"] is None else dev["batch_idx"][lo:hi].contiguous())
             g.check()
-        _same(a, b, (case, hi), ("X", "Z", "G", "T_NODE", "ROUND"))
+        # (two of these lengths leave the counters at 0 and 1 modulo the five slots of a ring)
+        _same(a, b, (case, hi), ("X", "Z", "G", "T_NODE", "ROUND", "SIGMA_RING", "RHO_RING", "RHO_TILDE"))
+        assert np.array_equal(a.read("V_RING")[:, 0], b.read("V_RING")[:, 0]), (case, hi)
+        da, db = a.diagnostics(), b.diagnostics()
+        for k in da:
+            assert abs(da[k] - db[k]) <= 1e-9 * (abs(db[k]) + db["gsum_sq"] + db["z_sq"]), (case, hi, k, da[k], db[k])
 
 
 def test_two_streams():
