@@ -349,11 +349,11 @@ void choose_team(rfast_ctx* c, int max_out_r) {
   if (c->team.W > 1) d.row_chunk = c->team.C;
 }
 
-hipError_t launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int round0, const int32_t* d_batch_idx, const int32_t* d_delay_R,
+hipError_t launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, const int32_t* d_batch_idx, const int32_t* d_delay_R,
                        const int32_t* d_delay_C) {
   return c->d.prob.kind == RFAST_OBJ_SOFTMAX_BF16
-             ? rfast_launch_team_softmax(c, rounds, gamma, round0, d_batch_idx, d_delay_R, d_delay_C)
-             : rfast_launch_team(c, sync, rounds, gamma, round0, d_batch_idx, d_delay_R, d_delay_C);
+             ? rfast_launch_team_softmax(c, rounds, gamma, d_batch_idx, d_delay_R, d_delay_C)
+             : rfast_launch_team(c, sync, rounds, gamma, d_batch_idx, d_delay_R, d_delay_C);
 }
 
 // The workgroups of a team launch wait for each other, so they must all become resident: two such launches that each
@@ -949,7 +949,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   if (e == hipSuccess) {
     time_begin(c, 0);
     if (team)
-      e = in_team_order(c, [&] { return launch_team(c, false, len, blk.gamma, (int)(c->host_round - len), d_batch_idx, d_delay_R, d_delay_C); });
+      e = in_team_order(c, [&] { return launch_team(c, false, len, blk.gamma, d_batch_idx, d_delay_R, d_delay_C); });
     else if (tiny)
       e = rfast_launch_tiny(c, blk, d_batch_idx, (int)(c->host_round - len), d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C);
     else e = rfast_wave_eligible(c) ? rfast_launch_wave(c, blk) : rfast_launch_block(c, blk);
@@ -1213,7 +1213,7 @@ int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_b
       if (fold_sync(c) != RFAST_OK) return RFAST_EHIP;
       time_begin(c, 0);
       hipError_t e = in_team_order(c, [&] {
-        return launch_team(c, true, len, gamma_now(c, gamma), (int)c->host_round, d_batch_idx ? d_batch_idx + (size_t)r * d.n * B : nullptr, nullptr, nullptr);
+        return launch_team(c, true, len, gamma_now(c, gamma), d_batch_idx ? d_batch_idx + (size_t)r * d.n * B : nullptr, nullptr, nullptr);
       });
       time_end(c, 0);
       if (e == hipSuccess) e = rfast_launch_sync_plan(c, len);

@@ -219,13 +219,13 @@ hipError_t rfast_launch_cols_track_mix(rfast_ctx* c, const int32_t* d_batch_idx,
 RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree_r, int compute_units);
 size_t rfast_team_packet_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob);
 size_t rfast_team_flag_bytes(const RfastTeam& t, int32_t n);
-hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int round0, const int32_t* d_batch_idx,
+hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, const int32_t* d_batch_idx,
                              const int32_t* d_delay_R, const int32_t* d_delay_C);
 // the same for rounds of softmax regression (RfastTeam::C: tiles of 32 features per workgroup, tiles: copies of a round's rows in LDS)
 RfastTeam rfast_team_softmax_shape(const RfastDev& d, int max_degree, int max_out_degree_r, int compute_units);
 size_t rfast_team_softmax_packet_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob);
 size_t rfast_team_softmax_flag_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob);
-hipError_t rfast_launch_team_softmax(rfast_ctx* c, int rounds, float gamma, int round0, const int32_t* d_batch_idx,
+hipError_t rfast_launch_team_softmax(rfast_ctx* c, int rounds, float gamma, const int32_t* d_batch_idx,
                                      const int32_t* d_delay_R, const int32_t* d_delay_C);
 bool rfast_tiny_eligible(const rfast_ctx* c);   // the multi-round kernel for least squares / logistic problems that fit one CU's LDS
 bool rfast_tiny_resolves(const rfast_ctx* c);   // ... and it resolves its rounds itself (no resolver launch ahead of it)

@@ -33,7 +33,6 @@ struct TeamArgs {
   int rounds, W, C, B, buffers;  // buffers: tiles of rows in LDS (two: the next round's rows arrive during this one)
   float gamma;
   unsigned base;              // progress words and packet tags count rounds from here on (they never repeat)
-  int round0;                 // number of the first round, for error reports
   const int32_t* batch_idx;   // [rounds][n][B], NULL: all rows, in order
   const int32_t* delay_R;     // [rounds][eR] (not the synchronous steps)
   const int32_t* delay_C;     // [rounds][eC]
@@ -53,6 +52,10 @@ __device__ inline int next_bit(const u64* mask, int from) {
   return w * 64 + __ffsll((long long)m) - 1;
 }
 
+// Number of the first round of the launch, from the counter on the device (the resolver has moved it past the launch's
+// rounds, a synchronous launch moves it behind them): the host's own count does not see the replays of a captured round.
+__device__ inline int first_round(const RfastDev& s, const TeamArgs& a, bool sync) { return *s.round_no - (sync ? 0 : a.rounds); }
+
 // a wait of node i has run out
 __device__ inline void report_wait(const RfastDev& s, int round0, int i) {
   if (atomicCAS(&s.err[0], 0, RFAST_EHIP) == 0) {
@@ -68,7 +71,7 @@ __device__ inline unsigned peek(const TeamArgs& a, const unsigned* f, int need) 
 // Waits until the progress words of the lanes that have one (f1, f2, or neither) are at least round `need` of the launch
 // whose rounds count from `base`.  v1, v2: the words as read ahead (a.base: not read); where they say enough, the wait
 // costs no trip through memory.  dead: an earlier wait has run out, and nothing waits any more.
-__device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int i, const unsigned* f1, int need1, const unsigned* f2,
+__device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int round0, int i, const unsigned* f1, int need1, const unsigned* f2,
                                      int need2, unsigned v1, unsigned v2, bool* dead) {
   if (need1 <= 0) f1 = nullptr;
   if (need2 <= 0) f2 = nullptr;
@@ -78,7 +81,7 @@ __device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int i
     if (__all(ok)) break;
     if (spin > kSpin) {
       *dead = true;
-      report_wait(s, a.round0, i);
+      report_wait(s, round0, i);
       break;
     }
     v1 = f1 ? get32(f1) : 0;
@@ -89,11 +92,11 @@ __device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int i
 }
 
 // sampled row b of a round as the caller gave it, clamped into the node's samples and (report) recorded if outside
-__device__ inline int team_row(const RfastDev& s, const TeamArgs& a, int i, int q, int b, bool report) {
+__device__ inline int team_row(const RfastDev& s, const TeamArgs& a, int round0, int i, int q, int b, bool report) {
   int row = a.batch_idx[((size_t)q * s.n + i) * a.B + b];
   if (row < 0 || row >= s.prob.samples) {
     if (report && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
-      s.err[1] = a.round0 + q;
+      s.err[1] = round0 + q;
       s.err[2] = 2;
       s.err[3] = i;
     }

@@ -98,12 +98,13 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 
   // ---- the rounds in which the node does something: it is active, or an S4 buffer of it has to be saved
   const int W1 = n + s.eR + s.eC + 1;
+  const int round0 = first_round(s, a, SYNC);
   if (!SYNC) {
     int word = 0;
     bool spill = false;
     if (tid < a.rounds) {
       word = s.blk_plan[(size_t)tid * W1 + i];
-      spill = s.blk_spill[(size_t)tid * n + i] == a.round0 + tid + 1;
+      spill = s.blk_spill[(size_t)tid * n + i] == round0 + tid + 1;
     }
     nodew[tid] = word;
     const u64 am = __ballot(word < 0), em = __ballot(word < 0 || spill);
@@ -158,12 +159,12 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 
   bool dead = false;  // a wait has run out
   auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2, unsigned v1, unsigned v2) {
-    wait_progress(s, a, i, f1, need1, f2, need2, v1, v2, &dead);
+    wait_progress(s, a, round0, i, f1, need1, f2, need2, v1, v2, &dead);
   };
 
   // ---- rows
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = team_row(s, a, i, q, b, w == 0);
+    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = team_row(s, a, round0, i, q, b, w == 0);
   };
   // Four coordinates of a row (unaligned where p is no multiple of four).  At the chunk's ragged end the load starts up
   // to three coordinates early, still inside the row, and whole_quad moves them into place and clears the rest.
@@ -445,7 +446,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
               if (ok || dead) break;
               if (spin > kSpin) {
                 dead = true;
-                report_wait(s, a.round0, i);
+                report_wait(s, round0, i);
                 break;
               }
             }
@@ -698,7 +699,7 @@ size_t rfast_team_packet_bytes(const RfastTeam& t, int32_t n, const rfast_proble
 size_t rfast_team_flag_bytes(const RfastTeam& t, int32_t n) { return (size_t)n * t.W * kOwnWaves * kFlagWords * 4; }
 
 // rounds: at most kBlockRounds with sync = false (their plan records are in c->d.blk_plan)
-hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, int round0, const int32_t* d_batch_idx,
+hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, const int32_t* d_batch_idx,
                              const int32_t* d_delay_R, const int32_t* d_delay_C) {
   const RfastTeam& t = c->team;
   if (t.W <= 0 || rounds < 1 || (!sync && (rounds > kBlockRounds || !c->d.blk_plan))) return hipErrorInvalidValue;
@@ -710,7 +711,6 @@ hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, i
   a.buffers = t.tiles;
   a.gamma = gamma;
   a.base = c->team_base;
-  a.round0 = round0;
   a.batch_idx = c->d.prob.batch > 0 ? d_batch_idx : nullptr;
   a.delay_R = d_delay_R;
   a.delay_C = d_delay_C;

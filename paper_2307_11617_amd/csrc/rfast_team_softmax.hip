@@ -66,12 +66,13 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
 
   // ---- the rounds in which the node does something
   const int W1 = n + s.eR + s.eC + 1;
+  const int round0 = first_round(s, a, false);
   {
     int word = 0;
     bool spill = false;
     if (tid < a.rounds) {
       word = s.blk_plan[(size_t)tid * W1 + i];
-      spill = s.blk_spill[(size_t)tid * n + i] == a.round0 + tid + 1;
+      spill = s.blk_spill[(size_t)tid * n + i] == round0 + tid + 1;
     }
     nodew[tid] = word;
     const u64 am = __ballot(word < 0), em = __ballot(word < 0 || spill);
@@ -113,7 +114,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   }
   bool dead = false;
   auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2, unsigned v1, unsigned v2) {
-    wait_progress(s, a, i, f1, need1, f2, need2, v1, v2, &dead);
+    wait_progress(s, a, round0, i, f1, need1, f2, need2, v1, v2, &dead);
   };
 
   // ---- rows of X into LDS, straight from memory: 16-byte piece q of the tile is piece pos = q mod nc of row q / nc and
@@ -141,7 +142,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   auto next_active = [&](int from) { return next_bit(act_mask, from); };
   auto next_event = [&](int from) { return next_bit(ev_mask, from); };
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, i, q, b, w == 0);
+    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, round0, i, q, b, w == 0);
   };
   int parity = 0;
   {
@@ -334,7 +335,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
                   if (ok || dead) break;
                   if (spin > kSpin) {
                     dead = true;
-                    report_wait(s, a.round0, i);
+                    report_wait(s, round0, i);
                     break;
                   }
                 }
@@ -359,7 +360,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           const float inv = 1.0f / sum;
           if (lab < 0 || lab >= K) {  // clamped and reported, like a sample row
             if (gl == 0 && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
-              s.err[1] = a.round0 + q;
+              s.err[1] = round0 + q;
               s.err[2] = 3;
               s.err[3] = i;
             }
@@ -395,7 +396,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
             if (ok || dead) break;
             if (spin > kSpin) {
               dead = true;
-              report_wait(s, a.round0, i);
+              report_wait(s, round0, i);
               break;
             }
           }
@@ -556,7 +557,7 @@ size_t rfast_team_softmax_flag_bytes(const RfastTeam& t, int32_t n, const rfast_
   return t.W > 0 ? (size_t)n * (prob->d / 32) * (prob->K / 32) * kFlagWords * 4 : 0;
 }
 
-hipError_t rfast_launch_team_softmax(rfast_ctx* c, int rounds, float gamma, int round0, const int32_t* d_batch_idx,
+hipError_t rfast_launch_team_softmax(rfast_ctx* c, int rounds, float gamma, const int32_t* d_batch_idx,
                                      const int32_t* d_delay_R, const int32_t* d_delay_C) {
   const RfastTeam& t = c->team;
   if (t.W <= 0 || rounds < 1 || rounds > kBlockRounds || !c->d.blk_plan) return hipErrorInvalidValue;
@@ -568,7 +569,6 @@ hipError_t rfast_launch_team_softmax(rfast_ctx* c, int rounds, float gamma, int 
   a.buffers = t.tiles;
   a.gamma = gamma;
   a.base = c->team_base;
-  a.round0 = round0;
   a.batch_idx = c->d.prob.batch > 0 ? d_batch_idx : nullptr;
   a.delay_R = d_delay_R;
   a.delay_C = d_delay_C;

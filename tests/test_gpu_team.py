@@ -229,3 +229,41 @@ def test_forms_alternate(softmax, case):
             _close(a, b, (case, hi))
         else:
             _same(a, b, (case, hi))
+
+
+@pytest.mark.parametrize("softmax,case", [(False, "two_tiles_in_turn"), (True, "one_tile_chunks")])
+def test_stretch_after_replayed_captures(softmax, case):
+    """Two rounds captured by the program and replayed three times, then a stretch in which half of the nodes sit still
+    for more rounds than a ring holds: their buffers (S4) have to be saved by the count of rounds that ran, not of calls."""
+    w = _softmax_workload(case) if softmax else _workload(case)
+    names = ("active", "delay_R", "delay_C", "drop_R", "drop_C")
+    x0 = (0.05 * np.random.default_rng(3).standard_normal((w.n, w.p))).astype(np.float32)
+    gpus = []
+    for blocks in (2, False):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            g = harness.make_gpu(w)
+            rfast_use_blocks(g.ctx, blocks)
+            rfast_set_rebase_interval(g.ctx, 0)
+            g.init(x0, w.sched.initial_batch())
+            st, dev = harness.upload_chunk(g, w, 0, 32)
+            dev["active"][2:27] = torch.arange(w.n, device=g.device) % 2
+            stream.synchronize()
+            part = lambda lo, hi: [dev[k][lo:hi].contiguous() for k in names]  # noqa: E731
+            rows = lambda lo, hi: dev["batch_idx"][lo:hi].contiguous()  # noqa: E731
+            first = [(part(r, r + 1), rows(r, r + 1)) for r in (0, 1)]
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream, capture_error_mode="relaxed"):
+                for sched, batch in first:
+                    g.round(*sched, w.gamma, batch)
+            for _ in range(3):
+                graph.replay()
+            g.run(30, *part(2, 32), w.gamma, rows(2, 32))
+            stream.synchronize()
+            g.check()
+        assert int(g.read("ROUND")[0]) == 36
+        gpus.append(g)
+    if softmax:
+        _close(*gpus, case, fields=("X", "Z", "G", "RHO_TILDE"))
+    else:
+        _same(*gpus, case)
