@@ -253,8 +253,9 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * number, also single ones, event-driven iterations and synchronous steps; with or without the heavy-ball buffer, any
  * p >= 4): at most 256 workgroups of up to 2048 coordinates each, one per compute unit, at most 64 edges of a kind at
  * a node.  All of them wait for each other, so launches on different streams of a process are ordered by the library
- * (by an event); a wait that cannot end (the device is kept busy by another process) gives up after some seconds and
- * rfast_check reports RFAST_EHIP.  While kernels are timed (rfast_profile_enable) or a stream is being captured, and
+ * (by an event), and no workgroup touches the state before all of a launch have started.  Where they do not within about
+ * a second (another process keeps compute units for good), one of them computes the launch's rounds alone, with the same
+ * results, and the context takes the kernels per round from then on, until the next rfast_init.  While kernels are timed (rfast_profile_enable) or a stream is being captured, and
  * where a team does not fit, a round is two kernels instead of four (p a multiple of 4, no heavy-ball buffer;
  * consecutive rounds): the sampled rows' residuals, then one kernel that forms the gradient, does the tracker update
  * and mixes the same coordinates for the next round; same bits.  Stretches too short to pay for the start of a
@@ -273,6 +274,11 @@ int rfast_block_info(rfast_ctx* ctx, int32_t* lanes_per_node, int32_t* tile_per_
  * together, so a row segment of a load or store is that many times as wide; the rounds themselves are unaffected
  * and the results are the same bits.  A value whose tiles do not fit the LDS of a CU falls back to 1. */
 int rfast_set_tile_group(rfast_ctx* ctx, int32_t wavefronts);
+
+/* How often a workgroup of a team (see rfast_use_blocks) looks before it gives up waiting, at about a microsecond each:
+ * start_polls for the others of its launch to start (0: it takes them for missing whether they are or not), wait_polls
+ * for what another workgroup publishes within the rounds.  Negative: the library's own bounds.  For tests. */
+int rfast_set_wait_limits(rfast_ctx* ctx, int32_t start_polls, int32_t wait_polls);
 
 /* One step of the synchronous push-pull recursion the method is developed from
  * (eq. (2) of the paper), on the same x, z and stored gradient samples:

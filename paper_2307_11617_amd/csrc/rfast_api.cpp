@@ -40,7 +40,7 @@ struct Offsets {
   size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_head, t_next, hist_next, ticket;
   size_t gen_active, gen_delay_r, gen_delay_c, gen_drop_r, gen_drop_c, gen_batch, gen_cdf;
   int32_t gen_depth;
-  size_t xbar, resid, gscratch, diag, team_packets, team_flags;
+  size_t xbar, resid, gscratch, diag, team_packets, team_flags, team_gate;
   size_t total;
 };
 
@@ -142,6 +142,7 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
     o.team_packets = L.take(rfast_team_packet_bytes(most, n, prob));
     o.team_flags = L.take(rfast_team_flag_bytes(most, n));
   }
+  o.team_gate = L.take(2 * 64);
   o.total = L.total;
   return o;
 }
@@ -489,6 +490,7 @@ void context_gone() {
 // that is under capture just now (the runtime allows no such dependency, whatever the event was recorded behind).
 bool team_usable(const rfast_ctx* c) {
   if (!c->use_blocks || c->team.W <= 0 || c->capturing || c->profiling) return false;
+  if (((volatile unsigned*)c->team_told)[0] != 0) return false;  // the workgroups of a team of this context do not all find room
   if (c->stream != nullptr) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
@@ -712,6 +714,7 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   c->gen_depth = o.gen_depth;
   d.xbar = (float*)(b + o.xbar);
   c->team_packets = (void*)(b + o.team_packets); c->team_flags = (unsigned*)(b + o.team_flags);
+  c->team_gate = (unsigned*)(b + o.team_gate);
   d.mom = nullptr; d.beta = 0.f; d.wd = 0.f;
   d.resid = (float*)(b + o.resid); d.gscratch = (void*)(b + o.gscratch);
   c->d_diag = (double*)(b + o.diag);
@@ -734,11 +737,15 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
     const bool softmax = prob->kind == RFAST_OBJ_SOFTMAX_BF16;
     chk(hipMemsetAsync(c->team_packets, 0, softmax ? rfast_team_softmax_packet_bytes(c->team, n, prob) : rfast_team_packet_bytes(c->team, n, prob), c->stream));
     chk(hipMemsetAsync(c->team_flags, 0, softmax ? rfast_team_softmax_flag_bytes(c->team, n, prob) : rfast_team_flag_bytes(c->team, n), c->stream));
+    chk(hipMemsetAsync(c->team_gate, 0, 2 * 64, c->stream));
+    chk(hipHostMalloc((void**)&c->team_told, 64, hipHostMallocPortable));
+    if (e == hipSuccess) c->team_told[0] = c->team_told[1] = 0;
   }
   chk(rfast_wave_prime(c));
   chk(hipStreamSynchronize(c->stream));  // the host vectors die with this scope
   if (e != hipSuccess) {
     const int r = hipfail(nullptr, e, "uploading graph");
+    if (c->team_told) (void)hipHostFree(c->team_told);
     delete c;
     return r;
   }
@@ -756,6 +763,7 @@ int rfast_init(rfast_ctx* c, const float* d_x0, const int32_t* d_batch_idx0) {
   c->sync_parity = 0;
   c->host_round = 0;
   c->needs_init = false;
+  if (c->team_told) ((volatile unsigned*)c->team_told)[0] = 0;  // a team may find room again
   hipError_t e = hipSuccess;
   auto chk = [&](hipError_t r) { if (e == hipSuccess) e = r; };
   if (d.mom) chk(hipMemsetAsync(d.mom, 0, d.n * vec, c->stream));
@@ -983,6 +991,13 @@ int rfast_set_tile_group(rfast_ctx* c, int32_t wavefronts) {
   if (wavefronts != 0 && wavefronts != 1 && wavefronts != 2 && wavefronts != 4)
     return fail(c, RFAST_EINVAL, "wavefronts per workgroup must be 0 (automatic), 1, 2 or 4");
   c->wave_group = wavefronts;
+  return RFAST_OK;
+}
+
+int rfast_set_wait_limits(rfast_ctx* c, int32_t start_polls, int32_t wait_polls) {
+  if (!c) return RFAST_EINVAL;
+  c->start_polls = start_polls;
+  c->wait_polls = wait_polls;
   return RFAST_OK;
 }
 
@@ -1518,6 +1533,7 @@ void rfast_destroy(rfast_ctx* c) {
   for (int w = 0; w < 3; ++w)
     for (int s = 0; s < 2; ++s)
       for (hipEvent_t ev : c->ev[w][s]) (void)hipEventDestroy(ev);
+  if (c->team_told) (void)hipHostFree(c->team_told);
   context_gone();
   delete c;
 }

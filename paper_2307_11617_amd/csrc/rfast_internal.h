@@ -164,6 +164,10 @@ struct rfast_ctx {
   unsigned team_base = 0;       // rounds handed to the team kernel so far (its progress words and packet tags never repeat)
   void* team_packets = nullptr;
   unsigned* team_flags = nullptr;
+  unsigned* team_gate = nullptr;    // two words on which the workgroups of a launch report, used in turn
+  unsigned team_turn = 0;           // launches so far
+  unsigned* team_told = nullptr;    // pinned host memory, written by the device: [0] a launch went on with one workgroup, [1] a wait ran out
+  int32_t start_polls = -1, wait_polls = -1;  // rfast_set_wait_limits
   int device = 0;
   bool no_tiles = false;        // event-driven iterations: no multi-round launch on coordinate tiles
   bool capturing = false;       // rounds are being captured into the context's own graph

@@ -1,13 +1,13 @@
 // What the team kernels share (rfast_team.hip: least squares and logistic regression; rfast_team_softmax.hip): accesses
 // that meet behind the L2 caches of the accelerator dies, progress words, packets, bounded waits.
 #pragma once
+#include "rfast_edge.h"
 #include "rfast_vec.h"
 
 namespace {
 
 constexpr int kTeamThreads = 512;
 constexpr int kFlagWords = 16;             // 32-bit words per progress entry (64 bytes): [0] v, [1] sums
-constexpr int kSpin = 1 << 24;             // polls before a wait gives up (some ten seconds)
 constexpr size_t kTeamLds = 156 * 1024;
 
 typedef unsigned long long u64;
@@ -38,7 +38,63 @@ struct TeamArgs {
   const int32_t* delay_C;     // [rounds][eC]
   u64* packets;
   unsigned* flags;            // [n][owning wavefronts of a node][kFlagWords]
+  unsigned* gate;             // workgroups of this launch that have started (kGone: it goes on with one of them)
+  unsigned* gate_next;        // the word of the next launch, cleared by this one
+  unsigned expect;            // workgroups of the launch
+  int gate_polls, wait_polls; // polls before a wait gives up: for the others to start, for a word or packet of a round
+  unsigned* told;             // pinned host memory: [0] a launch went on with one workgroup, [1] a wait has run out
 };
+
+// ---- Are all workgroups of the launch resident?  Nothing else of the device is waited for, but another process, or a
+// stream that has been given a part of the compute units, can keep some of them out for as long as the others wait.  So
+// nobody touches the state before all have reported; if they do not within about a second, one workgroup takes
+// that decision for all of them (a compare-and-swap on the very word that they report on), the others leave, now or as
+// soon as they start, and it computes the rounds alone: slowly, but what the call asked for.  The host sees it in pinned
+// memory and does not launch a team of this context again.
+constexpr unsigned kGone = 0x80000000u;
+
+// one lane of every workgroup, first thing
+__device__ inline unsigned team_arrive(const TeamArgs& a) {
+  if (blockIdx.x == 0) put32(a.gate_next, 0);
+  return __hip_atomic_fetch_add(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+}
+
+// ... and before the first store that anybody else sees.  0: all are there; 1: leave; 2: this workgroup is on its own.
+__device__ inline int team_complete(const TeamArgs& a, unsigned seen) {
+  for (int poll = 0;; ++poll) {
+    if (seen & kGone) return 1;
+    if (seen == a.expect) return 0;
+    if (poll < a.gate_polls) {
+      seen = get32(a.gate);
+    } else {
+      unsigned was = seen;
+      if (__hip_atomic_compare_exchange_strong(a.gate, &was, seen | kGone, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        __hip_atomic_store(a.told, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        return 2;
+      }
+      seen = was;  // somebody came or took the decision: at most once for each of them
+    }
+  }
+}
+
+// The host's side of the start and of the bounds of a launch; polls take about a microsecond.
+constexpr int kGatePolls = 1 << 20, kWaitPolls = 1 << 24;
+
+inline void team_begin(rfast_ctx* c, TeamArgs* a) {
+  a->gate = c->team_gate + (c->team_turn & 1) * kFlagWords;
+  a->gate_next = c->team_gate + (~c->team_turn & 1) * kFlagWords;
+  // (no polls asked for: one more workgroup is expected than there is)
+  a->expect = (unsigned)(c->d.n * a->W) + (c->start_polls == 0 ? 1u : 0u);
+  a->gate_polls = c->start_polls < 0 ? kGatePolls : c->start_polls;
+  a->wait_polls = c->wait_polls < 0 ? kWaitPolls : c->wait_polls;
+  a->told = c->team_told;
+}
+inline hipError_t team_end(rfast_ctx* c, int rounds, hipError_t launched) {
+  if (launched != hipSuccess) return launched;
+  c->team_base += (unsigned)rounds + 1;
+  c->team_turn++;
+  return hipSuccess;
+}
 
 // first set bit at or after `from` of a mask of kBlockRounds bits, kBlockRounds if there is none
 __device__ inline int next_bit(const u64* mask, int from) {
@@ -52,17 +108,32 @@ __device__ inline int next_bit(const u64* mask, int from) {
   return w * 64 + __ffsll((long long)m) - 1;
 }
 
+// The arguments of the kernel as a copy of their own in the constant memory they came in, out of the compiler's sight: what
+// the rare paths read of them is then not kept in scalar registers through the whole kernel.
+static_assert(alignof(RfastDev) == alignof(TeamArgs), "one behind the other");
+struct TeamKernelArgs {
+  RfastDev s;
+  TeamArgs a;
+};
+__device__ inline const TeamKernelArgs& team_kernel_args() {
+  const TeamKernelArgs* p = (const TeamKernelArgs*)(const void*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
 // Number of the first round of the launch, from the counter on the device (the resolver has moved it past the launch's
 // rounds, a synchronous launch moves it behind them): the host's own count does not see the replays of a captured round.
 __device__ inline int first_round(const RfastDev& s, const TeamArgs& a, bool sync) { return *s.round_no - (sync ? 0 : a.rounds); }
 
 // a wait of node i has run out
-__device__ inline void report_wait(const RfastDev& s, int round0, int i) {
-  if (atomicCAS(&s.err[0], 0, RFAST_EHIP) == 0) {
-    s.err[1] = round0;
-    s.err[2] = 4;
-    s.err[3] = i;
+__device__ inline void report_wait(bool sync, int i) {
+  const TeamKernelArgs& k = team_kernel_args();
+  if (atomicCAS(&k.s.err[0], 0, RFAST_EHIP) == 0) {
+    k.s.err[1] = first_round(k.s, k.a, sync);
+    k.s.err[2] = 4;
+    k.s.err[3] = i;
   }
+  __hip_atomic_store(k.a.told + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // A progress word read ahead of the wait for it (an absent one, or one that need not be waited for, reads as round 0).
@@ -71,7 +142,7 @@ __device__ inline unsigned peek(const TeamArgs& a, const unsigned* f, int need) 
 // Waits until the progress words of the lanes that have one (f1, f2, or neither) are at least round `need` of the launch
 // whose rounds count from `base`.  v1, v2: the words as read ahead (a.base: not read); where they say enough, the wait
 // costs no trip through memory.  dead: an earlier wait has run out, and nothing waits any more.
-__device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int round0, int i, const unsigned* f1, int need1, const unsigned* f2,
+__device__ inline void wait_progress(const TeamArgs& a, bool sync, int i, const unsigned* f1, int need1, const unsigned* f2,
                                      int need2, unsigned v1, unsigned v2, bool* dead) {
   if (need1 <= 0) f1 = nullptr;
   if (need2 <= 0) f2 = nullptr;
@@ -79,9 +150,9 @@ __device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int r
   for (int spin = 0;; ++spin) {
     const bool ok = (!f1 || (int)(v1 - a.base) >= need1) && (!f2 || (int)(v2 - a.base) >= need2);
     if (__all(ok)) break;
-    if (spin > kSpin) {
+    if (spin >= a.wait_polls) {
       *dead = true;
-      report_wait(s, round0, i);
+      report_wait(sync, i);
       break;
     }
     v1 = f1 ? get32(f1) : 0;
@@ -92,17 +163,64 @@ __device__ inline void wait_progress(const RfastDev& s, const TeamArgs& a, int r
 }
 
 // sampled row b of a round as the caller gave it, clamped into the node's samples and (report) recorded if outside
-__device__ inline int team_row(const RfastDev& s, const TeamArgs& a, int round0, int i, int q, int b, bool report) {
+__device__ inline int team_row(const RfastDev& s, const TeamArgs& a, bool sync, int i, int q, int b, bool report) {
   int row = a.batch_idx[((size_t)q * s.n + i) * a.B + b];
   if (row < 0 || row >= s.prob.samples) {
-    if (report && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
-      s.err[1] = round0 + q;
-      s.err[2] = 2;
-      s.err[3] = i;
-    }
+    const TeamKernelArgs& k = team_kernel_args();
+    if (report) record_error(k.s.err, RFAST_ERANGE, first_round(k.s, k.a, sync) + q, 2, i);
     row = row < 0 ? 0 : s.prob.samples - 1;
   }
   return row;
+}
+
+// ---- The steps of a round by one workgroup on its own.  Lane `tid` takes coordinates tid, tid + kTeamThreads, ... in
+// each of them, so that only the gradient, where coordinates meet, needs barriers.  slots, plan: the parts of the round's
+// record that belong to the edges of R and of C.
+__device__ inline void alone_mix(const RfastDev& s, int i, int slot_new, float gamma, const int32_t* slots) {
+  const int64_t p = s.p;
+  for (int64_t k = threadIdx.x; k < p; k += kTeamThreads) {
+    const size_t at = (size_t)i * p + k;
+    float dir = s.z[at];
+    if (s.mom) s.mom[at] = dir = fmaf(s.beta, s.mom[at], dir);
+    const float v = fmaf(-gamma, dir, s.x[at]);
+    float x = s.r_self[i] * v;
+    for (int e = s.r_ptr[i]; e < s.r_ptr[i + 1]; ++e)
+      x = fmaf(s.r_w[e], s.v_ring[((size_t)s.r_src[e] * s.M + slots[e]) * p + k], x);
+    s.v_ring[((size_t)i * s.M + slot_new) * p + k] = v;
+    s.x[at] = x;
+  }
+}
+
+template <class Gradient>
+__device__ inline void alone_track(const RfastDev& s, int i, int t_old, const int32_t* plan, Gradient gradient) {
+  const int64_t p = s.p;
+  const bool pushes = s.co_ptr[i + 1] > s.co_ptr[i];
+  float* sigma = s.sigma_ring + (size_t)i * s.M * p;
+  for (int64_t k = threadIdx.x; k < p; k += kTeamThreads) {
+    const size_t at = (size_t)i * p + k, half = (size_t)s.n * p;
+    float z = s.z[at];
+    for (int e = s.c_ptr[i]; e < s.c_ptr[i + 1]; ++e) {
+      const int pl = plan[e], prev = (pl >> 8) & 0xFF;
+      if (!(pl & (1 << 16))) continue;
+      const float* ring = s.sigma_ring + (size_t)s.c_src[e] * s.M * p + k;
+      float* saved = s.rho_tilde + (size_t)e * p + k;
+      const float cur = ring[(size_t)(pl & 0xFF) * p], last = prev != 0xFF ? ring[(size_t)prev * p] : *saved;
+      z = track_edge(z, s.c_w[e], cur, last, prev != 0xFF);
+      if (pl & (1 << 17)) *saved = s.c_w[e] * cur;
+    }
+    const float g = gradient(k), zh = (z + g) - s.g[(t_old & 1) * half + at];
+    s.g[((t_old + 1) & 1) * half + at] = g;
+    s.z[at] = s.c_self[i] * zh;
+    if (pushes) sigma[(size_t)((t_old + 1) % s.M) * p + k] = sigma[(size_t)(t_old % s.M) * p + k] + zh;
+  }
+}
+
+// S4 for buffers whose version leaves the sender's ring without being consumed
+__device__ inline void alone_save(const RfastDev& s, int i, const int32_t* plan) {
+  for (int e = s.c_ptr[i]; e < s.c_ptr[i + 1]; ++e)
+    if (plan[e] & (1 << 18))
+      for (int64_t k = threadIdx.x; k < s.p; k += kTeamThreads)
+        s.rho_tilde[(size_t)e * s.p + k] = s.c_w[e] * s.sigma_ring[((size_t)s.c_src[e] * s.M + (plan[e] & 0xFF)) * s.p + k];
 }
 
 }  // namespace

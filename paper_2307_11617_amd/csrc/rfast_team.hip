@@ -16,8 +16,9 @@
 //           instead of data, acknowledgement, flag, poll and read.
 // What a wavefront may wait for belongs to rounds before the one it is in, or (packets) to the same round of its own
 // team, whose members wait for earlier rounds only: by induction over the rounds every wait ends, as long as all
-// workgroups of the launch are resident, one per compute unit (rfast_team_shape).  The waits are bounded all the
-// same: a wait that runs out reports an error (rfast_check) and no later wait of the workgroup waits at all.
+// workgroups of the launch are resident.  They are no more than the compute units (rfast_team_shape), and none of them
+// touches the state before all have started (team_complete).  The waits are bounded all the same: a wait that runs
+// out reports an error (rfast_check) and no later wait of the workgroup waits at all.
 //   A ring slot is overwritten only when every receiver is past the rounds in which its version could be read: the
 // slot of version t + 1 held version t - D - 1, which left the readable window with the sender's previous activation,
 // so the receivers must have finished the round of that activation.
@@ -70,10 +71,97 @@ __device__ inline float fold16(float a, float b) {
   return __int_as_float(t[0]) + __int_as_float(t[1]);
 }
 
+// The rounds of a launch by one workgroup (see team_complete), in the order of operations of the team: same bits.
+// rowi: [B] words of LDS (if rows are sampled), rs: [4][Bq].
+template <bool SYNC>
+__device__ inline void alone(const RfastDev& s, const TeamArgs& a, int* rowi, float* rs) {
+  const int n = s.n, B = a.B, Bq = (B + 15) / 16 * 4, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t p = s.p;
+  const bool sampled = a.batch_idx != nullptr, logistic = s.prob.kind == RFAST_OBJ_LOGISTIC;
+  const float inv = 1.0f / (float)B, lam = (logistic ? s.prob.lambda : 0.f) + s.wd;
+  auto residuals = [&](int i, int q) {
+    const float* x = s.x + (size_t)i * p;
+    const float* data = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p;
+    for (int b = tid; sampled && b < B; b += kTeamThreads) rowi[b] = team_row(s, a, SYNC, i, q, b, true);
+    __syncthreads();  // x and the row numbers
+    for (int b = wave; b < B; b += kTeamThreads / 64) {
+      const int row = sampled ? rowi[b] : b;
+      const float* ar = data + (size_t)row * p;
+      float dot = 0.f;
+      for (int64_t c0 = 0; c0 < p; c0 += a.C) {
+        const int64_t end = c0 + a.C < p ? c0 + a.C : p;
+        float acc = 0.f;
+        for (int64_t k0 = c0 + 4 * lane; k0 < end; k0 += 256)
+          for (int64_t k = k0; k < end && k < k0 + 4; ++k) acc = fmaf(ar[k], x[k], acc);
+        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+        dot = c0 == 0 ? acc : dot + acc;
+      }
+      const float y = ((const float*)s.prob.data1)[(size_t)i * s.prob.samples + row];
+      if (lane == 0) rs[(b & 3) * Bq + (b >> 2)] = logistic ? 1.0f / (1.0f + expf(-dot)) - y : dot - y;
+    }
+    __syncthreads();
+  };
+  auto gradient = [&](int i, int64_t k) {
+    const float* col = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p + k;
+    float acc[4];
+    for (int rg = 0; rg < 4; ++rg) {
+      acc[rg] = 0.f;
+      for (int b = rg; b < B; b += 4) acc[rg] = fmaf(rs[rg * Bq + (b >> 2)], col[(size_t)(sampled ? rowi[b] : b) * p], acc[rg]);
+    }
+    return fmaf(lam, s.x[(size_t)i * p + k], (((acc[0] + acc[1]) + acc[2]) + acc[3]) * inv);
+  };
+  const size_t half = (size_t)n * p;
+  for (int q = 0; q < a.rounds; ++q) {
+    if (!SYNC) {
+      const int32_t* rec = s.blk_plan + (size_t)q * (n + s.eR + s.eC + 1);
+      for (int i = 0; i < n; ++i) {
+        const int t_old = rec[i] & 0x3FFFFFFF;
+        if (rec[i] < 0) {
+          alone_mix(s, i, (t_old + 1) % s.M, a.gamma, rec + n);
+          residuals(i, q);
+          alone_track(s, i, t_old, rec + n + s.eR, [&](int64_t k) { return gradient(i, k); });
+          __syncthreads();  // residuals and row numbers may be overwritten
+        }
+        alone_save(s, i, rec + n + s.eR);
+      }
+      continue;
+    }
+    // all of v (slot 0) before the first x'; the new z waits in slot 1 until nobody needs the old one
+    for (int64_t k = tid; k < p; k += kTeamThreads) {
+      for (int i = 0; i < n; ++i) {
+        float dir = s.z[(size_t)i * p + k];
+        if (s.mom) s.mom[(size_t)i * p + k] = dir = fmaf(s.beta, s.mom[(size_t)i * p + k], dir);
+        s.v_ring[(size_t)i * s.M * p + k] = fmaf(-a.gamma, dir, s.x[(size_t)i * p + k]);
+      }
+      for (int i = 0; i < n; ++i) {
+        float x = s.r_self[i] * s.v_ring[(size_t)i * s.M * p + k];
+        for (int e = s.r_ptr[i]; e < s.r_ptr[i + 1]; ++e) x = fmaf(s.r_w[e], s.v_ring[(size_t)s.r_src[e] * s.M * p + k], x);
+        s.x[(size_t)i * p + k] = x;
+      }
+    }
+    for (int i = 0; i < n; ++i) {
+      const size_t now = ((s.t[i] + q + 1) & 1) * half, before = ((s.t[i] + q) & 1) * half;
+      residuals(i, q);
+      for (int64_t k = tid; k < p; k += kTeamThreads) {
+        const float g = gradient(i, k);
+        s.g[now + (size_t)i * p + k] = g;
+        float z = s.c_self[i] * s.z[(size_t)i * p + k];
+        for (int e = s.c_ptr[i]; e < s.c_ptr[i + 1]; ++e) z = fmaf(s.c_w[e], s.z[(size_t)s.c_src[e] * p + k], z);
+        s.v_ring[((size_t)i * s.M + 1) * p + k] = (z + g) - s.g[before + (size_t)i * p + k];
+      }
+      __syncthreads();  // residuals and row numbers may be overwritten
+    }
+    for (int64_t k = tid; k < p; k += kTeamThreads)
+      for (int i = 0; i < n; ++i) s.z[(size_t)i * p + k] = s.v_ring[((size_t)i * s.M + 1) * p + k];
+  }
+}
+
 template <int kE, bool TILE, bool SYNC>
 __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamArgs a) {
   constexpr int KB = kE <= 2 ? 8 : (kE == 4 ? 4 : 2);  // in-edges whose ring values are in flight together
   extern __shared__ float4 lds4[];
+  __shared__ int verdict;
+  const unsigned arrived = threadIdx.x == 0 ? team_arrive(a) : 0u;
   const int n = s.n, M = s.M, W = a.W, B = a.B, S = s.prob.samples;
   const int64_t p = s.p;
   const int i = blockIdx.x / W, w = blockIdx.x - i * W;
@@ -159,12 +247,12 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 
   bool dead = false;  // a wait has run out
   auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2, unsigned v1, unsigned v2) {
-    wait_progress(s, a, round0, i, f1, need1, f2, need2, v1, v2, &dead);
+    wait_progress(a, SYNC, i, f1, need1, f2, need2, v1, v2, &dead);
   };
 
   // ---- rows
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = team_row(s, a, round0, i, q, b, w == 0);
+    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = team_row(s, a, SYNC, i, q, b, w == 0);
   };
   // Four coordinates of a row (unaligned where p is no multiple of four).  At the chunk's ragged end the load starts up
   // to three coordinates early, still inside the row, and whole_quad moves them into place and clears the rest.
@@ -235,6 +323,18 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   auto clamped = [&](int d) { return d < 0 ? 0 : (d > s.d_max ? s.d_max : d); };
   if (owner) {
     fetch_plan(q);
+  }
+  if (tid == 0) verdict = team_complete(a, arrived);
+  __syncthreads();
+  if (verdict != 0) {
+    drain();  // (rows may be on their way into LDS)
+    if (verdict == 2) {
+      const TeamKernelArgs& k = team_kernel_args();
+      alone<SYNC>(k.s, k.a, rowi, rs);
+    }
+    return;
+  }
+  if (owner) {
     if (!SYNC && lane == 0) {  // rounds before the first event: nothing to wait for
       put32(flag_of(i, 0), a.base + (unsigned)(q < rounds ? q : rounds));
       put32(flag_of(i, 1), a.base + (unsigned)(q < rounds ? q : rounds));
@@ -444,9 +544,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
               for (int u = 0; u < 8; ++u)
                 if (w0 + u < W) ok = ok && (unsigned)(got[u] >> 32) == tag;
               if (ok || dead) break;
-              if (spin > kSpin) {
+              if (spin >= a.wait_polls) {
                 dead = true;
-                report_wait(s, round0, i);
+                report_wait(SYNC, i);
                 break;
               }
             }
@@ -716,6 +816,6 @@ hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, c
   a.delay_C = d_delay_C;
   a.packets = (u64*)c->team_packets;
   a.flags = c->team_flags;
-  c->team_base += (unsigned)rounds + 1;
-  return sync ? launch_team<true>(c, a) : launch_team<false>(c, a);
+  team_begin(c, &a);
+  return team_end(c, rounds, sync ? launch_team<true>(c, a) : launch_team<false>(c, a));
 }

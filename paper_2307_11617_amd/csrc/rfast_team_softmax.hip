@@ -39,12 +39,75 @@ __host__ __device__ inline size_t x_elems(int B, int FT) { return (size_t)B * 32
 __host__ __device__ inline size_t wt_elems(int K, int FT) { return (size_t)K * (32 * FT + kPad); }
 __host__ __device__ inline size_t et_elems(int K, int B) { return (size_t)K * (B + kPad); }
 
+// The rounds of a launch by one workgroup (see team_complete).  rowi: [B] words of LDS, et: [K][B + kPad].
+template <int K>
+__device__ inline void alone(const RfastDev& s, const TeamArgs& a, int* rowi, u16* et) {
+  const int n = s.n, B = a.B, d = s.prob.d, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool sampled = a.batch_idx != nullptr;
+  const float inv_b = 1.0f / (float)B;
+  auto value = [](u16 h) { return __uint_as_float((uint32_t)h << 16); };
+  for (int q = 0; q < a.rounds; ++q) {
+    const int32_t* rec = s.blk_plan + (size_t)q * (n + s.eR + s.eC + 1);
+    for (int i = 0; i < n; ++i) {
+      const int t_old = rec[i] & 0x3FFFFFFF;
+      if (rec[i] < 0) {
+        const u16* pool = (const u16*)s.prob.data0 + (size_t)i * s.prob.samples * d;
+        const float* x = s.x + (size_t)i * s.p;
+        alone_mix(s, i, (t_old + 1) % s.M, a.gamma, rec + n);
+        for (int b = tid; b < B; b += kTeamThreads) rowi[b] = sampled ? team_row(s, a, false, i, q, b, true) : b;
+        __syncthreads();  // x and the row numbers
+        // logits in the packets' place (as packets of round 0, which nobody waits for)
+        for (int f = tid; f < B * K; f += kTeamThreads) {
+          const int b = f / K, k = f - b * K;
+          float acc = 0.f;
+          for (int c = 0; c < d; ++c) acc = fmaf(value(pool[(size_t)rowi[b] * d + c]), value(rfast_f32_to_bf16(x[(size_t)c * K + k])), acc);
+          a.packets[f] = __float_as_uint(acc);
+        }
+        __syncthreads();
+        for (int b = wave; b < B; b += kTeamThreads / 64) {
+          int lab = ((const int32_t*)s.prob.data1)[(size_t)i * s.prob.samples + rowi[b]];
+          if (lab < 0 || lab >= K) {
+            if (lane == 0) record_error(s.err, RFAST_ERANGE, first_round(s, a, false) + q, 3, i);
+            lab = lab < 0 ? 0 : K - 1;
+          }
+          float lg[2], mx = -INFINITY, sum = 0.f;
+          for (int u = 0; u < 2; ++u) {
+            lg[u] = lane + 64 * u < K ? __uint_as_float((unsigned)a.packets[b * K + lane + 64 * u]) : -INFINITY;
+            mx = fmaxf(mx, lg[u]);
+          }
+          for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+          for (int u = 0; u < 2; ++u) {
+            lg[u] = lane + 64 * u < K ? __expf(lg[u] - mx) : 0.f;
+            sum += lg[u];
+          }
+          for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+          for (int u = 0; u < 2; ++u) {
+            const int k = lane + 64 * u;
+            if (k < K) et[(size_t)k * (B + kPad) + b] = rfast_f32_to_bf16((lg[u] * (1.0f / sum) - (k == lab ? 1.0f : 0.0f)) * inv_b);
+          }
+        }
+        __syncthreads();
+        alone_track(s, i, t_old, rec + n + s.eR, [&](int64_t at) {
+          const int f = (int)(at / K), k = (int)(at - (int64_t)f * K);
+          float acc = 0.f;
+          for (int b = 0; b < B; ++b) acc = fmaf(value(pool[(size_t)rowi[b] * d + f]), value(et[(size_t)k * (B + kPad) + b]), acc);
+          return s.wd != 0.f ? fmaf(s.wd, x[at], acc) : acc;
+        });
+        __syncthreads();  // E and the row numbers may be overwritten
+      }
+      alone_save(s, i, rec + n + s.eR);
+    }
+  }
+}
+
 // a.C: feature tiles per chunk (1, 2, 4 or 8)
 template <int KT, bool MOM>
 __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastDev s, TeamArgs a) {
   constexpr int K = 32 * KT;
   extern __shared__ float4 lds4[];
   __shared__ u64 act_mask[kBlockRounds / 64], ev_mask[kBlockRounds / 64];
+  __shared__ int verdict;
+  const unsigned arrived = threadIdx.x == 0 ? team_arrive(a) : 0u;
   const int n = s.n, M = s.M, W = a.W, B = a.B, FT = a.C, d = s.prob.d;
   const int64_t p = s.p;
   const int i = blockIdx.x / W, w = blockIdx.x - i * W;
@@ -114,7 +177,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   }
   bool dead = false;
   auto wait2 = [&](const unsigned* f1, int need1, const unsigned* f2, int need2, unsigned v1, unsigned v2) {
-    wait_progress(s, a, round0, i, f1, need1, f2, need2, v1, v2, &dead);
+    wait_progress(a, false, i, f1, need1, f2, need2, v1, v2, &dead);
   };
 
   // ---- rows of X into LDS, straight from memory: 16-byte piece q of the tile is piece pos = q mod nc of row q / nc and
@@ -142,7 +205,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   auto next_active = [&](int from) { return next_bit(act_mask, from); };
   auto next_event = [&](int from) { return next_bit(ev_mask, from); };
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, round0, i, q, b, w == 0);
+    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, false, i, q, b, w == 0);
   };
   int parity = 0;
   {
@@ -162,6 +225,18 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   auto clamped = [&](int dl) { return dl < 0 ? 0 : (dl > s.d_max ? s.d_max : dl); };
   if (owner) {
     fetch_plan(q);
+  }
+  if (tid == 0) verdict = team_complete(a, arrived);
+  __syncthreads();
+  if (verdict != 0) {
+    drain();  // (rows may be on their way into LDS)
+    if (verdict == 2) {
+      const TeamKernelArgs& k = team_kernel_args();
+      alone<K>(k.s, k.a, rowi, et);
+    }
+    return;
+  }
+  if (owner) {
     if (lane == 0) {
       put32(flag_of(i, 0), a.base + (unsigned)(q < rounds ? q : rounds));
       put32(flag_of(i, 1), a.base + (unsigned)(q < rounds ? q : rounds));
@@ -333,9 +408,9 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
                   for (int c = 0; c < 8; ++c)
                     if (w0 + c < W) ok = ok && (unsigned)(got[c] >> 32) == tag;
                   if (ok || dead) break;
-                  if (spin > kSpin) {
+                  if (spin >= a.wait_polls) {
                     dead = true;
-                    report_wait(s, round0, i);
+                    report_wait(false, i);
                     break;
                   }
                 }
@@ -359,11 +434,8 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           for (int o = G / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
           const float inv = 1.0f / sum;
           if (lab < 0 || lab >= K) {  // clamped and reported, like a sample row
-            if (gl == 0 && atomicCAS(&s.err[0], 0, RFAST_ERANGE) == 0) {
-              s.err[1] = round0 + q;
-              s.err[2] = 3;
-              s.err[3] = i;
-            }
+            const TeamKernelArgs& k = team_kernel_args();
+            if (gl == 0) record_error(k.s.err, RFAST_ERANGE, first_round(k.s, k.a, false) + q, 3, i);
             lab = lab < 0 ? 0 : K - 1;
           }
 #pragma unroll
@@ -394,9 +466,9 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
             for (int c = 0; c < 8; ++c)
               if (f0 + c * kTeamThreads + tid < total) ok = ok && (unsigned)(got[c] >> 32) == tag;
             if (ok || dead) break;
-            if (spin > kSpin) {
+            if (spin >= a.wait_polls) {
               dead = true;
-              report_wait(s, round0, i);
+              report_wait(false, i);
               break;
             }
           }
@@ -574,11 +646,11 @@ hipError_t rfast_launch_team_softmax(rfast_ctx* c, int rounds, float gamma, cons
   a.delay_C = d_delay_C;
   a.packets = (u64*)c->team_packets;
   a.flags = c->team_flags;
-  c->team_base += (unsigned)rounds + 1;
+  team_begin(c, &a);
   switch (c->d.prob.K / 32) {
-    case 1: return launch<1>(c, a);
-    case 2: return launch<2>(c, a);
-    case 3: return launch<3>(c, a);
-    default: return launch<4>(c, a);
+    case 1: return team_end(c, rounds, launch<1>(c, a));
+    case 2: return team_end(c, rounds, launch<2>(c, a));
+    case 3: return team_end(c, rounds, launch<3>(c, a));
+    default: return team_end(c, rounds, launch<4>(c, a));
   }
 }

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2307_11617_amd import rfast_set_rebase_interval, rfast_use_blocks
+from paper_2307_11617_amd import rfast_set_rebase_interval, rfast_set_wait_limits, rfast_use_blocks
 from rfast_workloads import configs, graphs, problems
 
 import harness
@@ -267,3 +267,36 @@ def test_stretch_after_replayed_captures(softmax, case):
         _close(*gpus, case, fields=("X", "Z", "G", "RHO_TILDE"))
     else:
         _same(*gpus, case)
+
+
+@pytest.mark.parametrize("softmax,case", [(False, c) for c in CASES] + [(True, c) for c in ("ragged_last_chunk", "one_tile_chunks", "all_rows")])
+def test_one_workgroup_goes_on_alone(softmax, case):
+    """The workgroups of a launch do not all find room (one more is expected than there is): one of them computes its
+    rounds, later calls take the kernels per round, and rfast_init gives the team another chance."""
+    w, a, b = _softmax(case) if softmax else _pair(case)[:3]
+    st, dev = harness.upload_chunk(a, w, 0, 30)
+    batch = dev["batch_idx"]
+    same = (lambda where: _close(a, b, where)) if softmax else (lambda where: _same(a, b, where))
+    for limit in (0, -1):
+        rfast_set_wait_limits(a.ctx, limit, -1)
+        for lo, hi in ((0, 17), (17, 30)):
+            for g in (a, b):
+                g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma,
+                      None if batch is None else batch[lo:hi].contiguous())
+                g.check()
+            same((case, limit, hi))
+        for g in (a, b):
+            g.init(None, w.sched.initial_batch())
+
+
+@pytest.mark.parametrize("case", ["chunk_of_one_row_piece", "several_chunks_aligned", "eight_coordinates_per_lane"])
+def test_one_workgroup_steps_alone(case):
+    w, a, b, _ = _pair(case)
+    st, dev = harness.upload_chunk(a, w, 0, 18)
+    rfast_set_wait_limits(a.ctx, 0, -1)
+    for lo, hi in ((0, 15), (15, 18)):
+        for g in (a, b):
+            g.sync_run(hi - lo, w.gamma, None if dev["batch_idx"] is None else dev["batch_idx"][lo:hi].contiguous())
+            g.check()
+        _same(a, b, (case, hi), ("X", "Z", "G", "T_NODE", "ROUND", "SIGMA_RING", "RHO_TILDE"))
+        assert np.array_equal(a.read("V_RING")[:, 0], b.read("V_RING")[:, 0]), (case, hi)
