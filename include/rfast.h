@@ -339,7 +339,10 @@ int rfast_set_optimizer(rfast_ctx* ctx, float momentum, float weight_decay, floa
 int rfast_set_gamma_schedule(rfast_ctx* ctx, int32_t step_rounds, float factor);
 
 /* Waits for the stream, then returns RFAST_OK or the first error a round
- * recorded on the device (RFAST_ERANGE) with its round and edge in the text. */
+ * recorded on the device (RFAST_ERANGE) with its round and edge in the text.
+ * RFAST_EHIP before all others: a workgroup of a team launch (rfast_use_blocks) waited
+ * in vain for another one although all had started, and the state is not valid.  Rounds,
+ * steps, reads of fields and diagnostics then return RFAST_EHIP too, until rfast_init. */
 int rfast_check(rfast_ctx* ctx);
 
 /* Waits for the stream and copies one field to HOST memory.  `bytes` must be

@@ -754,6 +754,19 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   return RFAST_OK;
 }
 
+// RFAST_EHIP if a wait within a team launch has run out since the last rfast_init: the state is not that of any run.  The
+// device leaves word of it in pinned memory, so that a call asks the device itself (and waits for it) only then.
+static int state_usable(rfast_ctx* c) {
+  volatile unsigned* told = c->team_told;
+  if (!told || told[1] == 0 || c->capturing) return RFAST_OK;
+  int32_t code = 0;
+  const hipError_t e = to_host(c, &code, c->d.err, 4);
+  if (e != hipSuccess) return hipfail(c, e, "reading device status");
+  if (code == RFAST_EHIP) return rfast_check(c);
+  told[1] = 0;  // from before an rfast_init
+  return RFAST_OK;
+}
+
 int rfast_init(rfast_ctx* c, const float* d_x0, const int32_t* d_batch_idx0) {
   if (!c) return RFAST_EINVAL;
   RfastDev& d = c->d;
@@ -818,7 +831,7 @@ static int check_round_args(rfast_ctx* c, const uint8_t* d_active, const int32_t
   if (!separable && d.prob.batch > 0 && !d_batch_idx) return fail(c, RFAST_EINVAL, "sample rows are required when batch > 0");
   if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
   if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
-  return RFAST_OK;
+  return state_usable(c);
 }
 
 static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx);
@@ -1011,6 +1024,7 @@ int rfast_run(rfast_ctx* c, int32_t rounds, const uint8_t* d_active, const int32
               const uint8_t* d_drop_R, const uint8_t* d_drop_C, float gamma, const int32_t* d_batch_idx) {
   if (!c) return RFAST_EINVAL;
   if (rounds < 0) return fail(c, RFAST_EINVAL, "rounds < 0");
+  if (const int rc = state_usable(c)) return rc;
   const RfastDev& d = c->d;
   const size_t B = d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC ? 0 : (size_t)d.prob.batch;
   for (int32_t r = 0; r < rounds; ++r) {
@@ -1099,6 +1113,7 @@ int rfast_run_generated(rfast_ctx* c, int32_t rounds, uint64_t seed, const float
   // generator reads the round number on the device), so kGraphRounds of them are
   // captured once into a HIP graph and replayed: one launch per kGraphRounds rounds.
   if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
+  if (const int rc = state_usable(c)) return rc;
   const bool graphs = c->use_graphs && !c->profiling;
   while (rounds > 0) {
     // a graph bakes the step size in, so a replay must not straddle a decay step of the schedule,
@@ -1144,6 +1159,7 @@ int rfast_run_events(rfast_ctx* c, int32_t iterations, uint64_t seed, const floa
   if (!(p_drop >= 0.f && p_drop <= 1.f)) return fail(c, RFAST_ERANGE, "p_drop must lie in [0, 1]");
   if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
   if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
+  if (const int rc = state_usable(c)) return rc;
   // selection thresholds: node i is drawn when cdf[i-1] <= u < cdf[i], u a 32-bit word
   std::vector<uint32_t> cdf(d.n);
   double total = 0.0;
@@ -1188,6 +1204,7 @@ int rfast_sync_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx) {
   if (!separable && d.prob.batch > 0 && !d_batch_idx) return fail(c, RFAST_EINVAL, "sample rows are required when batch > 0");
   if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
   if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
+  if (const int rc = state_usable(c)) return rc;
   if (d.prob.kind != RFAST_OBJ_SOFTMAX_BF16 && team_usable(c)) return rfast_sync_run(c, 1, gamma, d_batch_idx);
   gamma = gamma_now(c, gamma);
   hipError_t e;
@@ -1213,6 +1230,7 @@ int rfast_sync_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx) {
 int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_batch_idx) {
   if (!c) return RFAST_EINVAL;
   if (rounds < 0) return fail(c, RFAST_EINVAL, "rounds < 0");
+  if (const int rc = state_usable(c)) return rc;
   const RfastDev& d = c->d;
   const size_t B = d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC ? 0 : (size_t)d.prob.batch;
   const bool multi = c->use_blocks && rfast_sync_wave_eligible(c);
@@ -1307,7 +1325,7 @@ int rfast_check(rfast_ctx* c) {
   const hipError_t e = to_host(c, err, c->d.err, 24);
   if (e != hipSuccess) return hipfail(c, e, "reading device status");
   const uint64_t edge = (uint64_t)(uint32_t)err[5] << 32 | (uint32_t)err[4];  // the earliest delay out of range
-  if (edge != ~0ull && (err[0] == 0 || (int32_t)(edge >> 32) <= err[1])) {
+  if (edge != ~0ull && err[0] != RFAST_EHIP && (err[0] == 0 || (int32_t)(edge >> 32) <= err[1])) {
     err[0] = RFAST_ERANGE;
     err[1] = (int32_t)(edge >> 32);
     err[2] = (int32_t)(edge >> 31 & 1);
@@ -1315,7 +1333,9 @@ int rfast_check(rfast_ctx* c) {
   }
   if (err[0] == 0) return RFAST_OK;
   static const char* kinds[] = {"delay on R edge", "delay on C edge", "sample row of node", "class label of a sample of node"};
-  if (err[0] == RFAST_EHIP) return fail(c, RFAST_EHIP, "a workgroup waited in vain for another one in the rounds from " + std::to_string(err[1]) + " on: the state is not valid");
+  if (err[0] == RFAST_EHIP)
+    return fail(c, RFAST_EHIP, "a workgroup waited in vain for another one in the rounds from " + std::to_string(err[1]) +
+                                   " on: the state is not valid before the next rfast_init");
   const char* what = err[2] >= 0 && err[2] <= 3 ? kinds[err[2]] : "value";
   return fail(c, err[0], std::string(what) + " " + std::to_string(err[3]) + " out of range in round " + std::to_string(err[1]) +
                              " (clamped on the device)");
@@ -1411,7 +1431,7 @@ int rfast_read_state(rfast_ctx* c, int32_t field, void* host_dst, size_t bytes) 
       e = zero_dead_slots(c, field == RFAST_SIGMA_RING, (float*)host_dst, d.n, nullptr);
   }
   if (e != hipSuccess) return hipfail(c, e, "copying state to host");
-  return RFAST_OK;
+  return state_usable(c);
 }
 
 int rfast_write_state(rfast_ctx* c, int32_t field, const void* host_src, size_t bytes) {
@@ -1473,7 +1493,7 @@ int rfast_diagnostics(rfast_ctx* c, const float* d_xstar, rfast_diag* host_out) 
   // variant each add n * coefficient/2 * ||xbar||^2
   const double l2 = (c->d.prob.kind == RFAST_OBJ_LOGISTIC ? (double)c->d.prob.lambda : 0.0) + (double)c->d.wd;
   host_out->loss_at_xbar = h[5] + 0.5 * l2 * c->d.n * h[6];
-  return RFAST_OK;
+  return state_usable(c);
 }
 
 int rfast_diagnostics_static(rfast_ctx* c, const float* d_xstar, double* d_out) {
@@ -1482,6 +1502,7 @@ int rfast_diagnostics_static(rfast_ctx* c, const float* d_xstar, double* d_out) 
     return fail(c, RFAST_ERANGE, "rfast_diagnostics_static: p = " + std::to_string(c->d.p) + " exceeds the " +
                                      std::to_string(rfast_static_max_coords()) +
                                      " coordinates its static scratch holds for this objective (use rfast_diagnostics)");
+  if (const int rc = state_usable(c)) return rc;
   if (fold_sync(c) != RFAST_OK) return RFAST_EHIP;
   const double l2 = (c->d.prob.kind == RFAST_OBJ_LOGISTIC ? (double)c->d.prob.lambda : 0.0) + (double)c->d.wd;
   const hipError_t e = rfast_launch_diag_static(c, d_xstar, d_out, 0.5 * l2 * c->d.n);

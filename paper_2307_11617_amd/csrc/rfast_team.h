@@ -128,7 +128,7 @@ __device__ inline int first_round(const RfastDev& s, const TeamArgs& a, bool syn
 // a wait of node i has run out
 __device__ inline void report_wait(bool sync, int i) {
   const TeamKernelArgs& k = team_kernel_args();
-  if (atomicCAS(&k.s.err[0], 0, RFAST_EHIP) == 0) {
+  if (atomicExch(&k.s.err[0], RFAST_EHIP) != RFAST_EHIP) {  // whatever has been clamped before, this is worse
     k.s.err[1] = first_round(k.s, k.a, sync);
     k.s.err[2] = 4;
     k.s.err[3] = i;

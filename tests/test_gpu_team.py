@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2307_11617_amd import rfast_set_rebase_interval, rfast_set_wait_limits, rfast_use_blocks
+from paper_2307_11617_amd import RFastError, rfast_set_rebase_interval, rfast_set_wait_limits, rfast_use_blocks
 from rfast_workloads import configs, graphs, problems
 
 import harness
@@ -300,3 +300,34 @@ def test_one_workgroup_steps_alone(case):
             g.check()
         _same(a, b, (case, hi), ("X", "Z", "G", "T_NODE", "ROUND", "SIGMA_RING", "RHO_TILDE"))
         assert np.array_equal(a.read("V_RING")[:, 0], b.read("V_RING")[:, 0]), (case, hi)
+
+
+@pytest.mark.parametrize("softmax,case", [(False, "several_chunks_ragged"), (True, "one_tile_chunks")])
+def test_wait_that_runs_out_is_reported_everywhere(softmax, case):
+    """Waits within the rounds give up at once: whatever would go on with the state or hand it out says so, whether or not
+    a delay has been clamped before, until rfast_init."""
+    w, a, b = _softmax(case) if softmax else _pair(case)[:3]
+    st, dev = harness.upload_chunk(a, w, 0, 40)
+    names = ("active", "delay_R", "delay_C", "drop_R", "drop_C")
+    run = lambda g, lo, hi: g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in names], w.gamma, dev["batch_idx"][lo:hi].contiguous())  # noqa: E731
+    dev["active"][0] = 1
+    dev["delay_R"][0, 0] = 99
+    run(a, 0, 5)
+    with pytest.raises(RFastError, match="delay on R edge 0 out of range in round 0"):
+        a.check()
+    rfast_set_wait_limits(a.ctx, -1, 0)
+    run(a, 5, 35)
+    calls = [a.check, lambda: a.read("X"), lambda: run(a, 35, 40), lambda: a.run_events(3, 1, None, 1, 0.0, w.gamma),
+             lambda: a.run_generated(3, 1, torch.full((w.n,), 0.5, device=a.device), 1, 0.0, w.gamma),
+             lambda: a.sync_run(2, w.gamma, dev["batch_idx"][:2].contiguous()), a.diagnostics]
+    for call in calls:
+        with pytest.raises(RFastError, match="waited in vain") as err:
+            call()
+        assert err.value.code == -6
+    rfast_set_wait_limits(a.ctx, -1, -1)
+    dev["delay_R"][0, 0] = 0
+    for g in (a, b):
+        g.init(None, w.sched.initial_batch())
+        run(g, 0, 20)
+        g.check()
+    (_close if softmax else _same)(a, b, case)
