@@ -357,10 +357,12 @@ hipError_t launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, const i
              : rfast_launch_team(c, sync, rounds, gamma, d_batch_idx, d_delay_R, d_delay_C);
 }
 
-// The workgroups of a team launch wait for each other, so they must all become resident: two such launches that each
-// hold a part of the chip would wait forever.  Launches on one stream follow each other; a launch on another stream
+// The workgroups of a team launch wait for each other to start, so two such launches that each hold a part of the chip
+// would both wait until they give up (team_complete).  Launches on one stream follow each other; a launch on another stream
 // than the last one first waits for the event recorded behind that one.  (Behind the launch and not when the next one
-// comes: the other stream may by then be gone.)
+// comes: the other stream may by then be gone.)  hipStreamPerThread is one handle for a stream of every thread's own.
+// The order is for speed, the result does not depend on it: where the runtime refuses a wait or a record, as it does
+// while the other stream is under capture, the launch goes out without.
 struct TeamOrder {
   bool used = false;
   hipStream_t stream = nullptr;
@@ -369,18 +371,21 @@ struct TeamOrder {
 std::mutex g_team_mutex;
 TeamOrder g_team_order[64];
 
+bool same_stream(hipStream_t a, hipStream_t b) { return a == b && a != hipStreamPerThread; }
+
 template <class Launch> hipError_t in_team_order(rfast_ctx* c, Launch launch) {
   if (c->device < 0 || c->device >= 64) return hipErrorInvalidDevice;
   const std::lock_guard<std::mutex> lock(g_team_mutex);
   TeamOrder& o = g_team_order[c->device];
-  hipError_t e = hipSuccess;
-  if (!o.event) e = hipEventCreateWithFlags(&o.event, hipEventDisableTiming);
-  if (e == hipSuccess && o.used && o.stream != c->stream) e = hipStreamWaitEvent(c->stream, o.event, 0);
-  if (e == hipSuccess) e = launch();
+  if (!o.event && hipEventCreateWithFlags(&o.event, hipEventDisableTiming) != hipSuccess) o.event = nullptr;
+  if (o.event && o.used && !same_stream(o.stream, c->stream)) (void)hipStreamWaitEvent(c->stream, o.event, 0);
+  (void)hipGetLastError();
+  const hipError_t e = launch();
   if (e != hipSuccess) return e;
-  o.used = true;
+  o.used = o.event && hipEventRecord(o.event, c->stream) == hipSuccess;
   o.stream = c->stream;
-  return hipEventRecord(o.event, c->stream);
+  (void)hipGetLastError();
+  return hipSuccess;
 }
 
 // the context's stream has been waited for and is about to be given up
@@ -388,7 +393,7 @@ void leave_team_order(rfast_ctx* c) {
   if (c->device < 0 || c->device >= 64) return;
   const std::lock_guard<std::mutex> lock(g_team_mutex);
   TeamOrder& o = g_team_order[c->device];
-  if (o.used && o.stream == c->stream) o.used = false;
+  if (o.used && same_stream(o.stream, c->stream)) o.used = false;
 }
 
 // Copies to pageable host memory.  The runtime's own copy of such memory reaches 4-9 GB/s and 18 us at the least; a

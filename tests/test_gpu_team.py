@@ -1,5 +1,7 @@
 """Least squares and logistic regression with a team of workgroups per node (several rounds per launch): the same bits
 as one chain of kernels per round, at the edges of its chunks, tiles and batches, in every way rounds are asked for."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -118,6 +120,40 @@ def test_two_streams():
     for g in gpus:
         g.check()
     _same(gpus[0], gpus[1], "streams")
+
+
+def test_stream_of_every_thread():
+    """hipStreamPerThread: the same handle in two threads names two streams, whose launches are ordered all the same."""
+    w = _workload("several_chunks_ragged")
+    st, dev = None, None
+    ref = harness.make_gpu(w)
+    ref.init(None, w.sched.initial_batch())
+    st, dev = harness.upload_chunk(ref, w, 0, 40)
+    sched = [dev[k] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        ref.run(40, *sched, w.gamma, dev["batch_idx"])
+    ref.check()
+    got, gate = {}, threading.Barrier(2)
+
+    def work(key):
+        with torch.cuda.stream(torch.cuda.ExternalStream(2)):
+            g = harness.make_gpu(w)
+            g.init(None, w.sched.initial_batch())
+            gate.wait()
+            for _ in range(5):
+                g.run(40, *sched, w.gamma, dev["batch_idx"])
+            g.check()
+            got[key] = {f: g.read(f) for f in ("X", "Z", "G", "T_NODE")}
+            g.close()
+    threads = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for key in (0, 1):
+        for f, v in got[key].items():
+            assert np.array_equal(v, ref.read(f)), (key, f)
 
 
 def test_last_stream_under_capture():
