@@ -341,6 +341,15 @@ void choose_team(rfast_ctx* c, int max_out_r) {
       hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
     return;
   units = std::min(units, kTeamMost);
+  // a stream may have been given a part of the compute units (one bit each)
+  uint32_t mask[(kTeamMost + 31) / 32 * 2] = {};
+  if (hipExtStreamGetCUMask(c->stream, sizeof(mask) / sizeof(mask[0]), mask) == hipSuccess) {
+    int given = 0;
+    for (uint32_t m : mask) given += __builtin_popcount(m);
+    if (given > 0) units = std::min(units, given);
+  } else {
+    (void)hipGetLastError();
+  }
   if (rfast_tiny_eligible(c)) units = std::min(units, d.n);  // one workgroup per node at most
   if (d.prob.kind == RFAST_OBJ_SOFTMAX_BF16) {
     c->team = rfast_team_softmax_shape(d, c->max_degree, max_out_r, units);

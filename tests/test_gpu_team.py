@@ -1,6 +1,8 @@
 """Least squares and logistic regression with a team of workgroups per node (several rounds per launch): the same bits
 as one chain of kernels per round, at the edges of its chunks, tiles and batches, in every way rounds are asked for."""
+import ctypes
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -154,6 +156,35 @@ def test_stream_of_every_thread():
     for key in (0, 1):
         for f, v in got[key].items():
             assert np.array_equal(v, ref.read(f)), (key, f)
+
+
+@pytest.mark.parametrize("units", [128, 8])
+def test_stream_with_a_part_of_the_compute_units(units):
+    """A team is no larger than the part of the chip its stream may use: every launch finds room, on as few as one
+    workgroup's place per node, and a graph with more nodes than that takes the kernels per round."""
+    w = _workload("several_chunks_ragged")
+    hip = ctypes.CDLL("libamdhip64.so")
+    raw = ctypes.c_void_p()
+    bits = (ctypes.c_uint32 * 8)(*[min(max(units - 32 * q, 0), 32) and (1 << min(units - 32 * q, 32)) - 1 for q in range(8)])
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(raw), 8, bits) == 0
+    got = []
+    for stream in (torch.cuda.ExternalStream(raw.value), torch.cuda.current_stream()):
+        with torch.cuda.stream(stream):
+            g = harness.make_gpu(w)
+            # (the chunks of a row's sum go with the size of the team: none for the reference)
+            rfast_use_blocks(g.ctx, 2 if not got else False)
+            g.init(None, w.sched.initial_batch())
+            st, dev = harness.upload_chunk(g, w, 0, 40)
+            stream.synchronize()
+            began = time.perf_counter()
+            for _ in range(3):
+                g.run(40, *[dev[k] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma, dev["batch_idx"])
+            g.check()
+            took = time.perf_counter() - began
+            got.append(g)
+            if len(got) == 1:
+                assert took < 0.2, took   # nobody has waited for a workgroup that found no room
+    _close(*got, units, 1e-5)
 
 
 def test_last_stream_under_capture():
