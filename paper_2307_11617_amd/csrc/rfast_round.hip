@@ -67,10 +67,14 @@ __device__ inline void emit_bf16_blocked(const RfastDev& s, int i, int tile, typ
 
 // MOM: the optimizer variant's heavy-ball buffer is in use (a template flag so that the
 // plain method carries neither the branch nor the registers).
-// KB: in-edge loads kept in flight per phase.  8 costs 139 registers (3 wavefronts per SIMD), 4 costs
+// KB: in-edge loads kept in flight per phase.  8 costs 146 registers (3 wavefronts per SIMD), 4 costs
 // 91 (5 wavefronts): graphs with many in-edges per node want the deeper batch, graphs with few want
 // the wavefronts (measured: bidirectional ring 1.53 vs 1.59 ms with 8 vs 4, tree/star 0.293 vs 0.274).
-template <int MODE, int VEC, bool MOM, int KB, bool MANY = false>
+// DEEP: nodes may have more in-edges than one batch.  What the loop over further batches reads ahead costs the one-pass
+// form up to 31 registers (heavy-ball buffer, batches of eight: 179 against 148, 2 against 3 wavefronts per SIMD), so
+// graphs without such nodes go without it: 16 nodes of a bidirectional ring, p 11.2 M, heavy-ball: 1845 -> 1799 us per
+// round.  The two-pass forms lose nothing by it (128 nodes, in-degree 7, softmax: 177.5 us per round with, 178.7 without).
+template <int MODE, int VEC, bool MOM, int KB, bool DEEP, bool MANY = false>
 __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, int tile, int64_t k) {
   using T = typename V<VEC>::T;
   constexpr bool kMix = MODE != RFAST_MODE_TRACK, kTrack = MODE != RFAST_MODE_MIX;
@@ -145,7 +149,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
 #pragma unroll
     for (int q = 0; q < KB; ++q)
       if (re0 + q < re1) x_new = fma_s(vw[q], vb[q], x_new);
-    if (re0 + KB < re1) {  // in-degree above one batch: what the loads of a batch need is read during the batch before
+    if (DEEP && re0 + KB < re1) {  // in-degree above one batch: what the loads of a batch need is read during the batch before
       int src[KB], ver[KB];
       auto look = [&](int eb) {  // (past the last edge: the last one, which is not used)
 #pragma unroll
@@ -197,7 +201,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
       z_half = track_edge(z_half, ca[q], sg[q], rt[q], ((pl[q] >> 8) & 0xFF) != 0xFF);
       if (pl[q] & (1 << 17)) V<VEC>::st(s.rho_tilde + (size_t)(ce0 + q) * p + k, mul_s(ca[q], sg[q]));
     }
-  if (ce0 + KB < ce1) {  // in-degree above one batch, in the same way
+  if (DEEP && ce0 + KB < ce1) {  // in-degree above one batch, in the same way
     int src[KB];
     auto look = [&](int eb) {
 #pragma unroll
@@ -244,13 +248,13 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
   }
 }
 
-template <int MODE, int VEC, bool MOM, int KB>
+template <int MODE, int VEC, bool MOM, int KB, bool DEEP>
 __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float gamma, int tiles_per_node) {
   const int a = blockIdx.x / tiles_per_node;
   const int2 slot = s.active_plan[a];  // {node, its counter at the start of the round}, node < 0: no work
   if (slot.x < 0) return;
   const int tile = blockIdx.x - a * tiles_per_node;
-  each_group<VEC>(tile, s.p, [&](auto vec, int64_t k) { state_update<MODE, decltype(vec)::value, MOM, KB>(s, gamma, slot, tile, k); });
+  each_group<VEC>(tile, s.p, [&](auto vec, int64_t k) { state_update<MODE, decltype(vec)::value, MOM, KB, DEEP>(s, gamma, slot, tile, k); });
 }
 
 // Consecutive iterations of the event-driven mode, one active node each.  A pass over one node's vectors is bound by
@@ -268,7 +272,7 @@ __global__ void __launch_bounds__(kThreads) rfast_events_kernel(RfastDev s, floa
         const unsigned long long w = fixed(reinterpret_cast<const unsigned long long*>(r.active_plan + a));
         const int2 slot = make_int2((int)(unsigned)w, (int)(w >> 32));
         if (slot.x < 0) break;
-        state_update<RFAST_MODE_FUSED, decltype(vec)::value, MOM, KB, true>(r, gamma, slot, 0, k);
+        state_update<RFAST_MODE_FUSED, decltype(vec)::value, MOM, KB, true, true>(r, gamma, slot, 0, k);
       }
       next(r.active_plan); next(r.slot_r); next(r.plan_c); next(r.node_spill);
     }
@@ -432,8 +436,8 @@ __global__ void __launch_bounds__(kThreads) rfast_sync_fold_kernel(RfastDev s) {
   });
 }
 
-template <int MODE, bool MOM, int KB>
-hipError_t launch(rfast_ctx* c, float gamma) {
+template <int MODE, bool MOM, int KB, bool DEEP>
+hipError_t launch_deep(rfast_ctx* c, float gamma) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
   const int64_t tiles = group_tiles(d.p);
@@ -444,14 +448,21 @@ hipError_t launch(rfast_ctx* c, float gamma) {
   // 2 (capped through reserved LDS: +11 %) and at 4 or 5 (+2 %, +4 %); the register count of KB sets it.
   const bool streaming = (double)d.n * (double)d.p * 4.0 >= 32.0e6;
   if (vec4 && streaming)
-    hipLaunchKernelGGL((rfast_state_kernel<MODE, -4, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
+    hipLaunchKernelGGL((rfast_state_kernel<MODE, -4, MOM, KB, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else if (vec4)
-    hipLaunchKernelGGL((rfast_state_kernel<MODE, 4, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
+    hipLaunchKernelGGL((rfast_state_kernel<MODE, 4, MOM, KB, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else if (streaming)
-    hipLaunchKernelGGL((rfast_state_kernel<MODE, -5, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
+    hipLaunchKernelGGL((rfast_state_kernel<MODE, -5, MOM, KB, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else
-    hipLaunchKernelGGL((rfast_state_kernel<MODE, 5, MOM, KB>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
+    hipLaunchKernelGGL((rfast_state_kernel<MODE, 5, MOM, KB, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   return hipGetLastError();
+}
+
+template <int MODE, bool MOM, int KB>
+hipError_t launch(rfast_ctx* c, float gamma) {
+  if constexpr (MODE == RFAST_MODE_FUSED)
+    if (c->max_in_degree <= KB) return launch_deep<MODE, MOM, KB, false>(c, gamma);
+  return launch_deep<MODE, MOM, KB, true>(c, gamma);
 }
 
 }  // namespace

@@ -1,0 +1,33 @@
+"""The one-pass round of the separable objective at the edges of its batches of in-edges (four and eight): graphs whose
+largest in-degree is one batch take another instantiation than graphs with one more."""
+import numpy as np
+import pytest
+
+from paper_2307_11617_amd import rfast_use_blocks
+from rfast_workloads import configs, graphs, problems
+
+import harness
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+@pytest.mark.parametrize("degree,p", [(8, 1001), (9, 1001), (8, 516), (9, 516), (4, 286_000), (5, 286_000), (4, 286_001), (5, 286_001)])
+def test_in_degree_of_one_batch_and_one_more(degree, p, momentum, monkeypatch):
+    n = 14
+    adj = np.eye(n) + np.roll(np.eye(n), 1, axis=0)   # a directed ring, and further in-edges of node 0
+    adj[0, :] = 0.0
+    adj[0, 0] = adj[0, n - 1] = 1.0
+    adj[0, 2:degree + 1] = 1.0
+    assert (adj[0] != 0).sum() - 1 == degree   # (batches of eight below 4 M values, of four beyond)
+    w = configs._mk("ring_and_hub", n, p, adj / adj.sum(1, keepdims=True), adj / adj.sum(0, keepdims=True), 3, 0.01, 0, "diag_quadratic",
+                    problems.diag_quadratic(n, p, 5), 0.7, 0.2, 5, noise_std=0.1, burst=3)
+    make = harness.make_gpu
+
+    def one_pass(w):
+        g = make(w)
+        rfast_use_blocks(g.ctx, False)
+        return g
+    monkeypatch.setattr(harness, "make_gpu", one_pass)
+    coords = None if p < 5000 else np.unique(np.concatenate([np.arange(0, p, 4099), [p - 2, p - 1]]))
+    harness.run_parity(w, 60, every=20, coords=coords, momentum=momentum, weight_decay=1e-3 if momentum else 0.0, check_rings=coords is None)
