@@ -25,9 +25,9 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// coordinates k .. k+3 of a vector that ends at `end`, zeros past it (at any float's address)
-__device__ inline float4 ld_quad(const float* v, int64_t k, int64_t end) { return ld_group<true>(v + k, (int)(end - k < 4 ? end - k : 4)); }
-__device__ inline void st_quad(float* v, int64_t k, int64_t end, float4 t) { st_group<true>(v + k, (int)(end - k < 4 ? end - k : 4), t); }
+// coordinates k .. k+3 of a vector that ends at `end`, zeros past it (ANY: at any float's address, `end` no multiple of four)
+template <bool ANY> __device__ inline float4 ld_quad(const float* v, int64_t k, int64_t end) { return ld_group<ANY>(v + k, (int)(end - k < 4 ? end - k : 4)); }
+template <bool ANY> __device__ inline void st_quad(float* v, int64_t k, int64_t end, float4 t) { st_group<ANY>(v + k, (int)(end - k < 4 ? end - k : 4), t); }
 
 // a sampled row number as read from the caller's array: clamped into the node's samples, and reported, if outside
 __device__ inline int checked_row(const RfastDev& s, int i, int row) {
@@ -70,6 +70,8 @@ __device__ inline int pick_node(const RfastDev& s, bool init, int* t_old) {
 
 // active != NULL: blockIdx.y is the node itself and active[node] says whether the round activates it (the caller's
 // schedule): the row number is then fetched at the same time as the flag, not after a look at the list of work slots.
+// ANY: p is no multiple of four, and the rows start at any float's address.
+template <bool ANY>
 __global__ void __launch_bounds__(kThreads) rfast_rows_kernel(RfastDev s, const int32_t* batch_idx, int B, bool init,
                                                               const uint8_t* active) {
   const int b = blockIdx.x * kWaves + (threadIdx.x >> 6);
@@ -94,36 +96,44 @@ __global__ void __launch_bounds__(kThreads) rfast_rows_kernel(RfastDev s, const 
   // the target goes out with the row, not after the dot product (one round trip to memory less at the end)
   const float y = ((const float*)s.prob.data1)[(size_t)i * s.prob.samples + row];
   // Lane c sums the products of coordinates 4c .. 4c+3 (+ 256 m) of a chunk, the lanes' sums are added as a butterfly,
-  // and the chunks (one, unless the team kernel splits the coordinates of a node) in order.
-  float total = 0.f;
-  const int64_t chunk = s.row_chunk;
-  for (int64_t c0 = 0; c0 < p; c0 += chunk) {
-    const int64_t end = c0 + chunk < p ? c0 + chunk : p;
-    float acc = 0.f;
-    // sixteen 1 KiB pieces of the row (4096 coordinates) per step, all thirty-two loads issued before the first
-    // use: one wavefront per row has nothing else to hide the memory latency with, and a step costs a round trip
-    constexpr int kPieces = 16;
-    for (int64_t k0 = c0 + (int64_t)lane * 4; k0 < end; k0 += 256 * kPieces) {
-      float4 av[kPieces], xv[kPieces];
+  // and the chunks (whole pieces of 256 coordinates, or one chunk) in order.  Sixteen 1 KiB pieces of the row per step, all
+  // thirty-two loads issued before the first use, whatever chunks they belong to: one wavefront per row has nothing else to
+  // hide the memory latency with, and a step costs a round trip (32 nodes, p 4096 in chunks of 512, 64 rows: 26.9 us per
+  // round of two kernels with a step per chunk, 24.1 so).
+  constexpr int kPieces = 16;
+  float total = 0.f, acc = 0.f;
+  const int per_chunk = s.row_chunk < p ? s.row_chunk / 256 : 0x7fffffff;
+  int left = per_chunk;
+  bool first = true;
+  for (int64_t k0 = 0; k0 < p; k0 += 256 * kPieces) {
+    float4 av[kPieces], xv[kPieces];
 #pragma unroll
-      for (int u = 0; u < kPieces; ++u)
-        if (k0 + 256 * u < end) {
-          av[u] = ld_quad(a, k0 + 256 * u, end);
-          xv[u] = ld_quad(x, k0 + 256 * u, end);
-        }
+    for (int u = 0; u < kPieces; ++u) {
+      const int64_t k = k0 + 256 * u + 4 * lane;
+      if (k < p) {
+        av[u] = ld_quad<ANY>(a, k, p);
+        xv[u] = ld_quad<ANY>(x, k, p);
+      }
+    }
 #pragma unroll
-      for (int u = 0; u < kPieces; ++u)
-        if (k0 + 256 * u < end) {
+    for (int u = 0; u < kPieces; ++u)
+      if (k0 + 256 * u < p) {
+        if (k0 + 256 * u + 4 * lane < p) {
           acc = fmaf(av[u].x, xv[u].x, acc);
           acc = fmaf(av[u].y, xv[u].y, acc);
           acc = fmaf(av[u].z, xv[u].z, acc);
           acc = fmaf(av[u].w, xv[u].w, acc);
         }
-    }
-    acc = wave_sum(acc);
-    total = c0 == 0 ? acc : total + acc;
+        if (--left == 0 || k0 + 256 * (u + 1) >= p) {  // the end of a chunk
+          acc = wave_sum(acc);
+          total = first ? acc : total + acc;
+          first = false;
+          acc = 0.f;
+          left = per_chunk;
+        }
+      }
   }
-  const float acc = total;
+  acc = total;
   if (lane == 0) {
     const float r = s.prob.kind == RFAST_OBJ_LOGISTIC ? 1.0f / (1.0f + expf(-acc)) - y : acc - y;
     s.resid[(size_t)i * B + b] = r;
@@ -135,6 +145,7 @@ __global__ void __launch_bounds__(kThreads) rfast_rows_kernel(RfastDev s, const 
 // number is wavefront-uniform) and the four partial sums meet in LDS.  That gives p/256
 // workgroups per node instead of p/1024 and a quarter of the loop per lane: with a few dozen
 // rows per node there is not enough work to hide the latency otherwise.
+template <bool ANY>
 __global__ void __launch_bounds__(kThreads) rfast_cols_kernel(RfastDev s, const int32_t* batch_idx, int B, bool init) {
   extern __shared__ float sh[];  // [B] residuals, [B] row numbers, then [4][64] float4 partial sums
   int t_old;
@@ -159,7 +170,7 @@ __global__ void __launch_bounds__(kThreads) rfast_cols_kernel(RfastDev s, const 
     const float* base = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p;
 #pragma unroll 4
     for (int b = rg; b < B; b += kWaves) {
-      const float4 av = ld_quad(base + (size_t)row_sh[b] * p, k, p);
+      const float4 av = ld_quad<ANY>(base + (size_t)row_sh[b] * p, k, p);
       const float r = r_sh[b];
       acc.x = fmaf(r, av.x, acc.x);
       acc.y = fmaf(r, av.y, acc.y);
@@ -176,8 +187,8 @@ __global__ void __launch_bounds__(kThreads) rfast_cols_kernel(RfastDev s, const 
       const float4 o = part[q * 64 + lane];
       acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
     }
-    const float4 xv = ld_quad(s.x + (size_t)i * p, k, p);
-    st_quad(g_new, k, p, make_float4(fmaf(lam, xv.x, acc.x * inv), fmaf(lam, xv.y, acc.y * inv), fmaf(lam, xv.z, acc.z * inv),
+    const float4 xv = ld_quad<ANY>(s.x + (size_t)i * p, k, p);
+    st_quad<ANY>(g_new, k, p, make_float4(fmaf(lam, xv.x, acc.x * inv), fmaf(lam, xv.y, acc.y * inv), fmaf(lam, xv.z, acc.z * inv),
                                      fmaf(lam, xv.w, acc.w * inv)));
   }
 }
@@ -412,16 +423,24 @@ __global__ void __launch_bounds__(kThreads) rfast_copy_z_kernel(RfastDev s) {
   for (size_t q = (size_t)blockIdx.x * kThreads + threadIdx.x; q < tot; q += (size_t)gridDim.x * kThreads) s.z[q] = s.g[q];
 }
 
+hipError_t launch_rows(rfast_ctx* c, const int32_t* bi, int B, bool init, const uint8_t* active) {
+  const RfastDev& d = c->d;
+  const dim3 grid((B + kWaves - 1) / kWaves, d.n);
+  if (d.p % 4 == 0) hipLaunchKernelGGL(rfast_rows_kernel<false>, grid, dim3(kThreads), 0, c->stream, d, bi, B, init, active);
+  else hipLaunchKernelGGL(rfast_rows_kernel<true>, grid, dim3(kThreads), 0, c->stream, d, bi, B, init, active);
+  return hipGetLastError();
+}
+
 hipError_t gemv_pair(rfast_ctx* c, const int32_t* batch_idx, bool init) {
   const RfastDev& d = c->d;
   const int B = d.prob.batch > 0 ? d.prob.batch : d.prob.samples;
   const int32_t* bi = d.prob.batch > 0 ? batch_idx : nullptr;
-  hipLaunchKernelGGL(rfast_rows_kernel, dim3((B + kWaves - 1) / kWaves, d.n), dim3(kThreads), 0, c->stream, d, bi, B, init, nullptr);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = launch_rows(c, bi, B, init, nullptr);
   if (e != hipSuccess) return e;
   const unsigned gx = (unsigned)((d.p + 255) / 256);
   const size_t shm = (size_t)((2 * B + 3) & ~3) * 4 + (size_t)kWaves * 64 * 16;
-  hipLaunchKernelGGL(rfast_cols_kernel, dim3(gx, d.n), dim3(kThreads), shm, c->stream, d, bi, B, init);
+  if (d.p % 4 == 0) hipLaunchKernelGGL(rfast_cols_kernel<false>, dim3(gx, d.n), dim3(kThreads), shm, c->stream, d, bi, B, init);
+  else hipLaunchKernelGGL(rfast_cols_kernel<true>, dim3(gx, d.n), dim3(kThreads), shm, c->stream, d, bi, B, init);
   return hipGetLastError();
 }
 
@@ -440,9 +459,7 @@ bool rfast_chain_eligible(const rfast_ctx* c) {
 hipError_t rfast_launch_rows(rfast_ctx* c, const int32_t* batch_idx, const uint8_t* d_active) {
   const RfastDev& d = c->d;
   const int B = d.prob.batch > 0 ? d.prob.batch : d.prob.samples;
-  hipLaunchKernelGGL(rfast_rows_kernel, dim3((B + kWaves - 1) / kWaves, d.n), dim3(kThreads), 0, c->stream, d,
-                     d.prob.batch > 0 ? batch_idx : nullptr, B, false, d_active);
-  return hipGetLastError();
+  return launch_rows(c, d.prob.batch > 0 ? batch_idx : nullptr, B, false, d_active);
 }
 
 // g' and the tracker update of the round whose plan arrays c->d points at and whose activity flags are d_active, and
