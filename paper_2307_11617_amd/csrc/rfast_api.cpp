@@ -521,8 +521,11 @@ bool team_usable(const rfast_ctx* c) {
 
 // The fewest rounds of a team launch that are faster than the kernels per round (bit for bit the same for least squares
 // and logistic regression), from both timed side by side.
-// Least squares, logistic: two rounds.  A single one already, unless lanes hold eight coordinates (128 nodes, p 3000:
-// 38 against 30 us) or the sampled rows are less than 1 MB (8 nodes, p 600, batch 16: 20.5 against 18.3).
+// Least squares, logistic: two rounds (1.03 to 1.6 times as fast over 16 sizes).  A single one only where rows are longer
+// than the rows kernel takes in one step (p 4096, 32 nodes: 27.8 against 29.8 us; 16384, 8 nodes: 27.2 against 36; 16384,
+// 16 nodes: 45.5 against 49.7; 8192, 4 nodes: 46.7 against 48.1): below, the kernels of a round are through before the
+// workgroups of a team have all reported (p 784, 31 nodes: 21.3 against 18.8; 1001, 16 nodes: 27.6 against 21.7; 3000, 64
+// nodes: 37.1 against 34.3).
 // Softmax regression: with R = B / W rows per workgroup a team's round is about 12.5 us + 3 ns R K + 0.85 ns B K (the
 // softmax of its rows, E received by everybody), the four kernels 18 to 35 us.  R K 128 and 512: 16 to 20 against 19
 // to 23 us a round, and about 20 us at its start, even from 5 rounds on; R K 1024, B K 8192: 24.5 against 24.6 with
@@ -533,7 +536,7 @@ int32_t team_least_rounds(const rfast_ctx* c) {
   const RfastDev& d = c->d;
   const int64_t B = d.prob.batch > 0 ? d.prob.batch : d.prob.samples;
   if (c->use_blocks == 2) return 1;
-  if (d.prob.kind != RFAST_OBJ_SOFTMAX_BF16) return c->team.per_lane >= 8 || (double)d.n * (double)B * (double)d.p * 4.0 < 1.0e6 ? 2 : 1;
+  if (d.prob.kind != RFAST_OBJ_SOFTMAX_BF16) return d.p >= 4096 ? 1 : 2;
   if (c->no_tiles) return 3;
   const int64_t RK = (B + c->team.W - 1) / c->team.W * d.prob.K;
   if (RK > 1024 || B * d.prob.K > 8192) return kBlockRounds + 1;
