@@ -406,21 +406,24 @@ void leave_team_order(rfast_ctx* c) {
 }
 
 // Copies to pageable host memory.  The runtime's own copy of such memory reaches 4-9 GB/s and 18 us at the least; a
-// copy into pinned memory takes 54 GB/s and 6 us.  So what is read goes through a small pinned buffer that all contexts
-// share (lazily allocated, given back with the last context), and, where it is large, several threads move it on:
+// copy into pinned memory takes 54 GB/s and 6 us.  So what is read goes through a pinned buffer that all contexts
+// share (lazily allocated, given back with the last context; one of its own for small reads, which need not pay for the
+// 16 MB of the other), and, where it is large, several threads move it on:
 // most of their time goes into the page faults of a destination that has never been written.  Measured, a field of
 // 9 KB 30 -> 17 us, 36 MB 3.6 -> 1.4 ms, 128 MB 12.4 -> 4.3 ms.
 constexpr size_t kStageSlot = (size_t)1 << 20;
+constexpr size_t kStageSmall = (size_t)64 << 10;
 constexpr int kStageThreads = 8, kStageSlots = 2 * kStageThreads;
-std::mutex g_stage_mutex;   // whoever holds it owns the buffer; others copy without it
+std::mutex g_stage_mutex;   // whoever holds it owns the buffers; others copy without them
 char* g_stage = nullptr;
+char* g_stage_small = nullptr;
 std::atomic<int> g_contexts{0};
 
-hipError_t stage_ready() {
-  if (g_stage) return hipSuccess;
+hipError_t stage_ready(char** stage, size_t bytes) {
+  if (*stage) return hipSuccess;
   void* p = nullptr;
-  const hipError_t e = hipHostMalloc(&p, kStageSlots * kStageSlot, hipHostMallocPortable);
-  if (e == hipSuccess) g_stage = (char*)p;
+  const hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocPortable);
+  if (e == hipSuccess) *stage = (char*)p;
   return e;
 }
 
@@ -455,15 +458,17 @@ hipError_t copy_pieces(rfast_ctx* c, char* dst, const char* src, size_t bytes, i
 // Copies to host memory behind everything on the context's stream and waits for it.
 hipError_t to_host(rfast_ctx* c, void* dst, const void* src, size_t bytes) {
   std::unique_lock<std::mutex> own(g_stage_mutex, std::try_to_lock);
-  if (!own.owns_lock() || stage_ready() != hipSuccess) {
+  const bool small = bytes <= kStageSmall;
+  if (!own.owns_lock() || (small ? stage_ready(&g_stage_small, kStageSmall) : stage_ready(&g_stage, kStageSlots * kStageSlot)) != hipSuccess) {
     (void)hipGetLastError();
     const hipError_t e = hipStreamSynchronize(c->stream);
     return e == hipSuccess ? hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) : e;
   }
   if (bytes <= kStageSlot) {
-    hipError_t e = hipMemcpyAsync(g_stage, src, bytes, hipMemcpyDeviceToHost, c->stream);
+    char* stage = small ? g_stage_small : g_stage;
+    hipError_t e = hipMemcpyAsync(stage, src, bytes, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess) memcpy(dst, g_stage, bytes);
+    if (e == hipSuccess) memcpy(dst, stage, bytes);
     return e;
   }
   const size_t pieces = (bytes + kStageSlot - 1) / kStageSlot;
@@ -493,10 +498,12 @@ void context_made() { g_contexts++; }
 void context_gone() {
   if (--g_contexts > 0) return;
   const std::lock_guard<std::mutex> lock(g_stage_mutex);
-  if (g_stage && g_contexts == 0) {
-    (void)hipHostFree(g_stage);
-    g_stage = nullptr;
-  }
+  if (g_contexts != 0) return;
+  for (char** stage : {&g_stage, &g_stage_small})
+    if (*stage) {
+      (void)hipHostFree(*stage);
+      *stage = nullptr;
+    }
 }
 
 // A captured launch would be replayed with the progress words of its capture, so captured rounds take the kernels per round; so do

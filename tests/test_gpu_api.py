@@ -302,3 +302,22 @@ def test_profiling_hooks_count_launches():
     gpu.run(10, dev["active"], dev["delay_R"], dev["delay_C"], dev["drop_R"], dev["drop_C"], w.gamma, dev["batch_idx"])
     assert [rf.rfast_kernel_time(gpu.ctx, q)[1] for q in (0, 1, 2)] == [20, 10, 1]
     rf.rfast_profile_enable(gpu.ctx, False)
+
+
+def test_small_reads_pin_little_memory():
+    """rfast_check and reads of a few words: a buffer of a few pages, not the one that large reads go through."""
+    def mapped():
+        with open("/proc/self/status") as f:
+            return next(int(line.split()[1]) for line in f if line.startswith("VmSize"))
+    w = configs.config0(rounds=5)
+    grown = []
+    for _ in range(3):    # (whatever else the runtime maps, it does once)
+        gpu = harness.make_gpu(w)
+        gpu.init()
+        torch.cuda.synchronize()
+        before = mapped()
+        gpu.check()
+        gpu.read("T_NODE")
+        grown.append(mapped() - before)
+        gpu.close()
+    assert min(grown) < 8 * 1024, grown   # kB
