@@ -260,6 +260,21 @@ def _close(a, b, where, tol=2e-3, fields=("X", "Z", "G")):
         assert np.isfinite(x).all() and np.linalg.norm(x - y) <= tol * np.linalg.norm(y), (where, f, np.linalg.norm(x - y) / np.linalg.norm(y))
 
 
+def _tight(a, b, where):
+    """State, rings and buffers at the rounding of a sum: logits that differ in their last bits (2^-24) tip the bf16
+    rounding (2^-8) of one in some 10^4 entries of E, sqrt(1e-4) * 2^-8 = 4e-5 of a gradient and what is tracked of it at
+    most (1.2e-5 is the most measured over the cases); x and v move by gamma times that, with hundredths of z in them
+    (4.7e-8).  Running sums right after a rebase are small differences: theirs is taken against the gradients."""
+    for f in ("T_NODE", "TAU_R", "TAU_C", "ROUND"):
+        assert np.array_equal(a.read(f), b.read(f)), (where, f)
+    scale = np.linalg.norm(b.read("G"))
+    for f, tol, floor in (("X", 2e-7, 0.0), ("V_RING", 2e-7, 0.0), ("Z", 5e-5, 0.0), ("G", 5e-5, 0.0), ("SIGMA_RING", 5e-5, scale),
+                          ("RHO_TILDE", 5e-5, scale)):
+        x, y = a.read(f).astype(np.float64), b.read(f).astype(np.float64)
+        err, ref = np.linalg.norm(x - y), max(np.linalg.norm(y), floor)
+        assert np.isfinite(x).all() and err <= tol * ref, (where, f, err / ref)
+
+
 @pytest.mark.parametrize("case", list(SOFTMAX))
 def test_softmax_rounds(case):
     """The partial logits of a chunk are rounded to fp32 before they are added, so the two forms agree to the rounding of
@@ -271,13 +286,13 @@ def test_softmax_rounds(case):
             g.run(hi - lo, *[dev[k][lo:hi].contiguous() for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma,
                   dev["batch_idx"][lo:hi].contiguous() if dev["batch_idx"] is not None else None)
             g.check()
-        _close(a, b, (case, hi))
+        _tight(a, b, (case, hi))
     p_act = torch.full((w.n,), 0.5, dtype=torch.float32)
     for g in (a, b):
         g.run_generated(15, 5, p_act.to(g.device), w.sched.d_max, 0.1, w.gamma)
         g.run_events(20, 6, None, w.sched.d_max, 0.2, w.gamma)
         g.check()
-    _close(a, b, (case, "generated and events"))
+    _tight(a, b, (case, "generated and events"))
 
 
 @pytest.mark.parametrize("softmax,case", [(False, list(CASES)[0]), (True, list(SOFTMAX)[0]), (True, "all_rows")])
@@ -293,7 +308,7 @@ def test_forms_alternate(softmax, case):
                   None if batch is None else batch[lo:hi].contiguous())
             g.check()
         if softmax:
-            _close(a, b, (case, hi))
+            _tight(a, b, (case, hi))
         else:
             _same(a, b, (case, hi))
 
@@ -331,7 +346,7 @@ def test_stretch_after_replayed_captures(softmax, case):
         assert int(g.read("ROUND")[0]) == 36
         gpus.append(g)
     if softmax:
-        _close(*gpus, case, fields=("X", "Z", "G", "RHO_TILDE"))
+        _tight(*gpus, case)
     else:
         _same(*gpus, case)
 
@@ -343,7 +358,7 @@ def test_one_workgroup_goes_on_alone(softmax, case):
     w, a, b = _softmax(case) if softmax else _pair(case)[:3]
     st, dev = harness.upload_chunk(a, w, 0, 30)
     batch = dev["batch_idx"]
-    same = (lambda where: _close(a, b, where)) if softmax else (lambda where: _same(a, b, where))
+    same = (lambda where: _tight(a, b, where)) if softmax else (lambda where: _same(a, b, where))
     for limit in (0, -1):
         rfast_set_wait_limits(a.ctx, limit, -1)
         for lo, hi in ((0, 17), (17, 30)):
@@ -397,4 +412,4 @@ def test_wait_that_runs_out_is_reported_everywhere(softmax, case):
         g.init(None, w.sched.initial_batch())
         run(g, 0, 20)
         g.check()
-    (_close if softmax else _same)(a, b, case)
+    (_tight if softmax else _same)(a, b, case)
