@@ -450,7 +450,10 @@ def main():
                 "note": "bytes_per_launch counts what the state kernels read and write, edges whose stamp did not move "
                         "skipped (computed per round from the stamps before and after it); layout_*: the words of this "
                         "layout with no skip credited; algorithmic_*: the literal count of Algorithm 1, which the layout "
-                        "undercuts, so its rate may exceed the peak and is not a fraction of it"}
+                        "undercuts, so its rate may exceed the peak and is not a fraction of it" +
+                        ("" if separable or args.no_blocks else
+                         "; these are kernels per round: the rounds of `value` are taken by teams of workgroups where the "
+                         "sizes allow it, several per launch, in which state and gradient cannot be timed apart")}
 
     out = {
         "metric": "node-updates/sec",

@@ -250,29 +250,33 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * the stamps of its rounds itself (no resolver kernel runs ahead of it).
  * Where these objectives do not fit one workgroup, every node gets a team of workgroups that keep its state in
  * registers and its sampled rows in LDS over the same stretches of rounds and meet through memory (rounds of any
- * number, also single ones, event-driven iterations and synchronous steps; with or without the heavy-ball buffer, any
+ * number, event-driven iterations and synchronous steps; with or without the heavy-ball buffer, any
  * p >= 4): at most 256 workgroups of up to 2048 coordinates each, one per compute unit, at most 64 edges of a kind at
  * a node.  All of them wait for each other, so launches on different streams of a process are ordered by the library
  * (by an event), and no workgroup touches the state before all of a launch have started.  Where they do not within about
- * a second (another process keeps compute units for good), one of them computes the launch's rounds alone, with the same
- * results, and the context takes the kernels per round from then on, until the next rfast_init.  While kernels are timed (rfast_profile_enable) or a stream is being captured, and
- * where a team does not fit, a round is two kernels instead of four (p a multiple of 4, no heavy-ball buffer;
- * consecutive rounds): the sampled rows' residuals, then one kernel that forms the gradient, does the tracker update
- * and mixes the same coordinates for the next round; same bits.  Stretches too short to pay for the start of a
- * multi-round launch (one to some rounds, by the sizes) and softmax regression whose rounds are faster as kernels take
- * the kernels per round as well.
+ * a second (another process keeps compute units for good), one of them computes the launch's rounds alone, with
+ * the same results, and the context takes the kernels per round from then on, until the next rfast_init.  While
+ * kernels are timed (rfast_profile_enable) or a stream is being captured, and where a team does not fit, a round
+ * is two kernels instead of four (p a multiple of 4, no heavy-ball buffer; consecutive rounds): the sampled rows'
+ * residuals, then one kernel that forms the gradient, does the tracker update and mixes the same coordinates for
+ * the next round; same bits.  Stretches too short to pay for the start of a multi-round launch (one to some rounds,
+ * by the sizes) and softmax regression whose rounds are faster as kernels take the kernels per round as well (the
+ * latter still lays out the packets of its team for event-driven iterations, which are twice as fast by it: 8
+ * nodes, d 1024, K 128, batch 256 have 136 MB of them in 282 MB of workspace).
  * on == 0: always one kernel pass per round (four kernels for these objectives).  on == 2: as the default, but
- * 2 rounds are enough at any size (for measurements). */
+ * 2 rounds (a team: one) are enough at any size (for measurements). */
 int rfast_use_blocks(rfast_ctx* ctx, int32_t on);
-/* *lanes_per_node = 0 if a call of rfast_run for several rounds would now run without tiles in LDS, or
- * with tiles that start at any float's address (p no multiple of 4), else the number of lanes per node of the multi-round kernel (its tile is 4 * lanes coordinates;
- * 1024 / n, at least 1, for the single workgroup of the non-separable objectives);
+/* *lanes_per_node = 0 if a call of rfast_run for several rounds would now run without tiles in LDS, and also
+ * where p is no multiple of 4 (the tiles of the multi-round kernel then start at any float's address), else the number
+ * of lanes per node of the multi-round kernel (its tile is 4 * lanes coordinates; 1024 / n, at least 1, for the
+ * single workgroup of the non-separable objectives);
  * *tile_per_wavefront (may be NULL) = 1 if a tile belongs to one wavefront, 0 if to a workgroup. */
 int rfast_block_info(rfast_ctx* ctx, int32_t* lanes_per_node, int32_t* tile_per_wavefront);
 /* Tuning knob of the wavefront-tile kernel of rfast_use_blocks: wavefronts per workgroup (1, 2 or 4; 0 = chosen by
  * the library).  The wavefronts of a workgroup own neighbouring tiles and move their rings between HBM and LDS
  * together, so a row segment of a load or store is that many times as wide; the rounds themselves are unaffected
- * and the results are the same bits.  A value whose tiles do not fit the LDS of a CU falls back to 1. */
+ * and the results are the same bits.  A value whose tiles do not fit the LDS of a CU falls back to 1, as does any where
+ * p is no multiple of 4 (no row segment is a whole cache line there). */
 int rfast_set_tile_group(rfast_ctx* ctx, int32_t wavefronts);
 
 /* How often a workgroup of a team (see rfast_use_blocks) looks before it gives up waiting, at about a microsecond each:
@@ -377,7 +381,11 @@ int rfast_diagnostics_static(rfast_ctx* ctx, const float* d_xstar, double* d_out
  * the gradient kernels of each round (at most 4096 rounds are kept since the
  * last enable).  rfast_kernel_time waits for the stream and returns the summed
  * milliseconds and the number of timed launches of `which`
- * (0 = fused/mix+track state kernels, 1 = gradient kernels, 2 = resolver). */
+ * (0 = fused/mix+track state kernels, 1 = gradient kernels, 2 = resolver).
+ * Rounds that teams of workgroups would take (rfast_use_blocks: least squares, logistic
+ * and softmax regression) run as kernels per round while this is on, whose state and
+ * gradient kernels can be told apart: the times are those of that form, not of the one
+ * that runs while it is off. */
 int rfast_profile_enable(rfast_ctx* ctx, int32_t on);
 int rfast_kernel_time(rfast_ctx* ctx, int32_t which, double* ms_sum, int64_t* launches);
 

@@ -35,7 +35,7 @@ constexpr int kPlanPerLane = 10;
 // the compiler may use; kDeg: edge slots per node and kind (2 for rings and paths, else kMaxDeg).
 // More than 32 nodes at 16 lanes each are more than 512 lanes, so the kernel runs with 128 registers: with two
 // edge slots it fits them (four ring slots in flight while the tile moves instead of eight), with four it
-// spills some 55 to scratch.  The alternative without spills, 8 lanes per node in workgroups of 512 with 186
+// spills 66 to 72 to scratch.  The alternative without spills, 8 lanes per node in workgroups of 512 with 186
 // registers, was measured and is slower, because it halves the wavefronts per CU: 0.201 against 0.192 ms per
 // round on a 6 x 6 mesh at p = 1 M, 0.149 against 0.088 ms on a ring of 36 nodes.
 template <int kLanes, int TPB, int kDeg, bool ANY>
