@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
 // memory, but the next iterations read much of it again (this node's neighbours read the versions it has just written), so
 // a lane takes its coordinates through all of the iterations: nothing of theirs depends on another coordinate, and
 // what the coordinates under way touch stays in the caches.  16 nodes of a mesh, p 1e6: 15.1 us per iteration as a launch
-// of its own, 8.1 this way (bound by the caches behind L2: 72 MB per iteration); 11 nodes, p 144988: 7.0 -> 3.2.
+// of its own, 8.9 this way (bound by the caches behind L2: 72 MB per iteration); 11 nodes, p 144988: 7.0 -> 3.2.
 template <int VEC, bool MOM, int KB>
 __global__ void __launch_bounds__(kThreads) rfast_events_kernel(RfastDev s, float gamma, int rounds, size_t set_bytes) {
   auto next = [&](auto*& q) { q = reinterpret_cast<std::remove_reference_t<decltype(q)>>(reinterpret_cast<char*>(q) + set_bytes); };

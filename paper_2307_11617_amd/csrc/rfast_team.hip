@@ -35,8 +35,8 @@
 // diagnostics and reads see them as rfast_init left them.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
-// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.6; 32 nodes, p = 4096,
-// batch 64: 21.2 -> 9.2; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.9; one agent of 55 per
+// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.7; 32 nodes, p = 4096,
+// batch 64: 21.2 -> 9.0; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 7.3; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
 #include <type_traits>

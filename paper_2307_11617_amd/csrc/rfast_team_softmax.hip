@@ -16,14 +16,14 @@
 //
 // The partial logits are rounded to fp32 per chunk where the one-kernel form keeps one accumulator over all features;
 // nothing else differs from rfast_softmax.hip.  Measured, us per round, before (four kernels) and now: 16 nodes, d 512,
-// K 32, batch 64, heavy-ball buffer: 33.6 -> 13.5; one agent of 16 per iteration, d 192: 20.6 -> 5.0.
+// K 32, batch 64, heavy-ball buffer: 33.6 -> 13.6; one agent of 16 per iteration, d 192: 20.6 -> 5.0.
 //
 // With 256 registers per lane the five arrays of a tile (x, z, sample, running sum, heavy-ball buffer: 64 or 80 registers)
 // and the ring values in flight beside them do not all fit: 69 to 120 registers are spilled over the eight instantiations
 // (192 to 320 B of scratch per lane), some of them reloaded between the parts of a round.
 //
 // What bounds it is the chain of trips through memory in the wavefronts that own tiles, so everything else is kept out of
-// them as long as there are others (15.7 -> 13.5 us per round in the first case): the forward product, the softmax, row
+// them as long as there are others (15.7 -> 13.6 us per round in the first case): the forward product, the softmax, row
 // numbers and rows of the next round go to the wavefronts without a tile first; the barrier for the weights does not
 // wait for the stores of v; progress words are read ahead on trips that are made anyway.
 #include "rfast_team.h"
