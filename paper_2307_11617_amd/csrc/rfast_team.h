@@ -109,13 +109,14 @@ __device__ inline int next_bit(const u64* mask, int from) {
 }
 
 // The arguments of the kernel as a copy of their own in the constant memory they came in, out of the compiler's sight: what
-// the rare paths read of them is then not kept in scalar registers through the whole kernel.
+// the rare paths read of them is then not kept in scalar registers through the whole kernel.  (Only a kernel has them:
+// whoever asks is inlined.)
 static_assert(alignof(RfastDev) == alignof(TeamArgs), "one behind the other");
 struct TeamKernelArgs {
   RfastDev s;
   TeamArgs a;
 };
-__device__ inline const TeamKernelArgs& team_kernel_args() {
+__device__ __forceinline__ const TeamKernelArgs& team_kernel_args() {
   const TeamKernelArgs* p = (const TeamKernelArgs*)(const void*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
   return *p;
@@ -126,7 +127,7 @@ __device__ inline const TeamKernelArgs& team_kernel_args() {
 __device__ inline int first_round(const RfastDev& s, const TeamArgs& a, bool sync) { return *s.round_no - (sync ? 0 : a.rounds); }
 
 // a wait of node i has run out
-__device__ inline void report_wait(bool sync, int i) {
+__device__ __forceinline__ void report_wait(bool sync, int i) {
   const TeamKernelArgs& k = team_kernel_args();
   if (atomicExch(&k.s.err[0], RFAST_EHIP) != RFAST_EHIP) {  // whatever has been clamped before, this is worse
     k.s.err[1] = first_round(k.s, k.a, sync);
@@ -142,7 +143,7 @@ __device__ inline unsigned peek(const TeamArgs& a, const unsigned* f, int need) 
 // Waits until the progress words of the lanes that have one (f1, f2, or neither) are at least round `need` of the launch
 // whose rounds count from `base`.  v1, v2: the words as read ahead (a.base: not read); where they say enough, the wait
 // costs no trip through memory.  dead: an earlier wait has run out, and nothing waits any more.
-__device__ inline void wait_progress(const TeamArgs& a, bool sync, int i, const unsigned* f1, int need1, const unsigned* f2,
+__device__ __forceinline__ void wait_progress(const TeamArgs& a, bool sync, int i, const unsigned* f1, int need1, const unsigned* f2,
                                      int need2, unsigned v1, unsigned v2, bool* dead) {
   if (need1 <= 0) f1 = nullptr;
   if (need2 <= 0) f2 = nullptr;
@@ -163,7 +164,7 @@ __device__ inline void wait_progress(const TeamArgs& a, bool sync, int i, const 
 }
 
 // sampled row b of a round as the caller gave it, clamped into the node's samples and (report) recorded if outside
-__device__ inline int team_row(const RfastDev& s, const TeamArgs& a, bool sync, int i, int q, int b, bool report) {
+__device__ __forceinline__ int team_row(const RfastDev& s, const TeamArgs& a, bool sync, int i, int q, int b, bool report) {
   int row = a.batch_idx[((size_t)q * s.n + i) * a.B + b];
   if (row < 0 || row >= s.prob.samples) {
     const TeamKernelArgs& k = team_kernel_args();

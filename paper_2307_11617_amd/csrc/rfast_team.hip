@@ -74,7 +74,7 @@ __device__ inline float fold16(float a, float b) {
 // The rounds of a launch by one workgroup (see team_complete), in the order of operations of the team: same bits.
 // rowi: [B] words of LDS (if rows are sampled), rs: [4][Bq].
 template <bool SYNC>
-__device__ inline void alone(const RfastDev& s, const TeamArgs& a, int* rowi, float* rs) {
+__device__ __forceinline__ void alone(const RfastDev& s, const TeamArgs& a, int* rowi, float* rs) {
   const int n = s.n, B = a.B, Bq = (B + 15) / 16 * 4, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t p = s.p;
   const bool sampled = a.batch_idx != nullptr, logistic = s.prob.kind == RFAST_OBJ_LOGISTIC;

@@ -45,7 +45,7 @@ __host__ __device__ inline size_t et_elems(int K, int B) { return (size_t)K * (B
 
 // The rounds of a launch by one workgroup (see team_complete).  rowi: [B] words of LDS, et: [K][B + kPad].
 template <int K>
-__device__ inline void alone(const RfastDev& s, const TeamArgs& a, int* rowi, u16* et) {
+__device__ __forceinline__ void alone(const RfastDev& s, const TeamArgs& a, int* rowi, u16* et) {
   const int n = s.n, B = a.B, d = s.prob.d, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool sampled = a.batch_idx != nullptr;
   const float inv_b = 1.0f / (float)B;
