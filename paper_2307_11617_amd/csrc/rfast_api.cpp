@@ -142,7 +142,7 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
     o.team_packets = L.take(rfast_team_packet_bytes(most, n, prob));
     o.team_flags = L.take(rfast_team_flag_bytes(most, n));
   }
-  o.team_gate = L.take(2 * 64);
+  o.team_gate = L.take(2 * kGateBytes);
   o.total = L.total;
   return o;
 }
@@ -529,10 +529,10 @@ bool team_usable(const rfast_ctx* c) {
 // The fewest rounds of a team launch that are faster than the kernels per round (bit for bit the same for least squares
 // and logistic regression), from both timed side by side.
 // Least squares, logistic: two rounds (1.03 to 1.6 times as fast over 16 sizes).  A single one only where rows are longer
-// than the rows kernel takes in one step (p 4096, 32 nodes: 27.8 against 29.8 us; 16384, 8 nodes: 27.2 against 36; 16384,
-// 16 nodes: 45.5 against 49.7; 8192, 4 nodes: 46.7 against 48.1): below, the kernels of a round are through before the
-// workgroups of a team have all reported (p 784, 31 nodes: 21.3 against 18.8; 1001, 16 nodes: 27.6 against 21.7; 3000, 64
-// nodes: 37.1 against 34.3).
+// than the rows kernel takes in one step (p 4096, 32 nodes: 25.9 against 29.4 us; 16384, 8 nodes: 25.2 against 35.7; 16384,
+// 16 nodes: 45.6 against 50.0; 8192, 4 nodes: 46.5 against 47.8): below, the kernels of a round are through before the
+// workgroups of a team have fetched what they keep (p 784, 31 nodes: 20.1 against 18.8; 1001, 16 nodes: 27.0 against 21.7;
+// 3000, 64 nodes: 35.9 against 34.4; 600, 36 nodes, 300 rows: 30.5 against 31.1, the only one of twelve the other way).
 // Softmax regression: with R = B / W rows per workgroup a team's round is about 12.5 us + 3 ns R K + 0.85 ns B K (the
 // softmax of its rows, E received by everybody), the four kernels 18 to 35 us.  R K 128 and 512: 16 to 20 against 19
 // to 23 us a round, and about 20 us at its start, even from 5 rounds on; R K 1024, B K 8192: 24.5 against 24.6 with
@@ -762,7 +762,7 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
     const bool softmax = prob->kind == RFAST_OBJ_SOFTMAX_BF16;
     chk(hipMemsetAsync(c->team_packets, 0, softmax ? rfast_team_softmax_packet_bytes(c->team, n, prob) : rfast_team_packet_bytes(c->team, n, prob), c->stream));
     chk(hipMemsetAsync(c->team_flags, 0, softmax ? rfast_team_softmax_flag_bytes(c->team, n, prob) : rfast_team_flag_bytes(c->team, n), c->stream));
-    chk(hipMemsetAsync(c->team_gate, 0, 2 * 64, c->stream));
+    chk(hipMemsetAsync(c->team_gate, 0, 2 * kGateBytes, c->stream));
     chk(hipHostMalloc((void**)&c->team_told, 64, hipHostMallocPortable));
     if (e == hipSuccess) c->team_told[0] = c->team_told[1] = 0;
   }

@@ -165,7 +165,7 @@ struct rfast_ctx {
   unsigned team_base = 0;       // rounds handed to the team kernel so far (its progress words and packet tags never repeat)
   void* team_packets = nullptr;
   unsigned* team_flags = nullptr;
-  unsigned* team_gate = nullptr;    // two words on which the workgroups of a launch report, used in turn
+  unsigned* team_gate = nullptr;    // two sets of words on which the workgroups of a launch report, used in turn
   unsigned team_turn = 0;           // launches so far
   unsigned* team_told = nullptr;    // pinned host memory, written by the device: [0] a launch went on with one workgroup, [1] a wait ran out
   int32_t start_polls = -1, wait_polls = -1;  // rfast_set_wait_limits
@@ -188,6 +188,8 @@ enum { RFAST_MODE_FUSED = 0, RFAST_MODE_MIX = 1, RFAST_MODE_TRACK = 2 };
 // plus 0.33 ms per round against 1.53 ms per round of the streaming kernel: even from 6 rounds on)
 constexpr int kHeadWords = 16;  // words per node in RfastDev::blk_head
 constexpr int kBlockRounds = 512;
+constexpr int kGateWords = 8;      // words on which the workgroups of a team launch report, 64 bytes apart ...
+constexpr size_t kGateBytes = (kGateWords + 1) * 64;  // ... and one more
 constexpr int kTeamMost = 256;  // workgroups of a team launch at most
 constexpr int kPlanChunk = 16;
 constexpr int kBlockMinRoundsLarge = 8;

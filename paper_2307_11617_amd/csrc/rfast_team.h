@@ -38,41 +38,53 @@ struct TeamArgs {
   const int32_t* delay_C;     // [rounds][eC]
   u64* packets;
   unsigned* flags;            // [n][owning wavefronts of a node][kFlagWords]
-  unsigned* gate;             // workgroups of this launch that have started (kGone: it goes on with one of them)
-  unsigned* gate_next;        // the word of the next launch, cleared by this one
-  unsigned expect;            // workgroups of the launch
-  int gate_polls, wait_polls; // polls before a wait gives up: for the others to start, for a word or packet of a round
+  unsigned* gate;             // kGateWords words: workgroups of this launch that have started (kGone in one of them: the
+                              // launch goes on with one workgroup); behind them the word by which one gets to decide that
+  unsigned* gate_next;        // those of the next launch, cleared by this one
+  // polls before a wait gives up: for the others to start (0: one more is expected than there is), for a word or packet
+  int gate_polls, wait_polls;
   unsigned* told;             // pinned host memory: [0] a launch went on with one workgroup, [1] a wait has run out
 };
 
 // ---- Are all workgroups of the launch resident?  Nothing else of the device is waited for, but another process, or a
 // stream that has been given a part of the compute units, can keep some of them out for as long as the others wait.  So
-// nobody touches the state before all have reported; if they do not within about a second, one workgroup takes
-// that decision for all of them (a compare-and-swap on the very word that they report on), the others leave, now or as
-// soon as they start, and it computes the rounds alone: slowly, but what the call asked for.  The host sees it in pinned
-// memory and does not launch a team of this context again.
+// nobody touches the state before all have reported; if they do not within about a second, one workgroup (the first to
+// swap a word) marks a word on which reports are missing, by a compare-and-swap, so that nobody can find them complete
+// any more; the others leave, now or as soon as they start, and it computes the rounds alone: slowly, but what the call
+// asked for.  The host sees it in pinned memory and launches no team of this context again before the next rfast_init.
 constexpr unsigned kGone = 0x80000000u;
 
-// one lane of every workgroup, first thing
-__device__ inline unsigned team_arrive(const TeamArgs& a) {
-  if (blockIdx.x == 0) put32(a.gate_next, 0);
-  return __hip_atomic_fetch_add(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+// One lane of every workgroup, first thing.  Eight words, taken in turn: additions to one word follow each other, and
+// those of 64 to 256 workgroups to a single one cost a launch 2 us, this way 0.1 to 0.5 (32 words: the same).
+__device__ inline void team_arrive(const TeamArgs& a) {
+  (void)__hip_atomic_fetch_add(a.gate + (blockIdx.x % kGateWords) * kFlagWords, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// ... and before the first store that anybody else sees.  0: all are there; 1: leave; 2: this workgroup is on its own.
-__device__ inline int team_complete(const TeamArgs& a, unsigned seen) {
+// The first wavefront of every workgroup, before the first store that anybody else sees.  0: all are there; 1: leave;
+// 2: this workgroup is on its own.
+__device__ inline int team_complete(const TeamArgs& a, int lane) {
+  if (blockIdx.x == 0 && lane <= kGateWords) put32(a.gate_next + lane * kFlagWords, 0);
+  const bool mine = lane < kGateWords;
+  unsigned* const word = a.gate + lane * kFlagWords;
+  const unsigned want = (gridDim.x + kGateWords - 1 - lane) / kGateWords + (a.gate_polls == 0 && lane == 0 ? 1u : 0u);
+  bool decide = false;
   for (int poll = 0;; ++poll) {
-    if (seen & kGone) return 1;
-    if (seen == a.expect) return 0;
-    if (poll < a.gate_polls) {
-      seen = get32(a.gate);
-    } else {
+    const unsigned seen = mine ? get32(word) : 0u;
+    if (__any(mine && (seen & kGone))) return 1;
+    const unsigned long long missing = __ballot(mine && seen != want);
+    if (missing == 0) return 0;
+    if (poll == a.gate_polls) {  // one workgroup at most may decide
+      unsigned was = 0;
+      decide = __any(lane == kGateWords && __hip_atomic_compare_exchange_strong(word, &was, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    if (decide) {
       unsigned was = seen;
-      if (__hip_atomic_compare_exchange_strong(a.gate, &was, seen | kGone, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-        __hip_atomic_store(a.told, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      const bool set = lane == __ffsll((long long)missing) - 1 &&
+                       __hip_atomic_compare_exchange_strong(word, &was, seen | kGone, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__any(set)) {
+        if (lane == 0) __hip_atomic_store(a.told, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         return 2;
       }
-      seen = was;  // somebody came or took the decision: at most once for each of them
     }
   }
 }
@@ -81,10 +93,8 @@ __device__ inline int team_complete(const TeamArgs& a, unsigned seen) {
 constexpr int kGatePolls = 1 << 20, kWaitPolls = 1 << 24;
 
 inline void team_begin(rfast_ctx* c, TeamArgs* a) {
-  a->gate = c->team_gate + (c->team_turn & 1) * kFlagWords;
-  a->gate_next = c->team_gate + (~c->team_turn & 1) * kFlagWords;
-  // (no polls asked for: one more workgroup is expected than there is)
-  a->expect = (unsigned)(c->d.n * a->W) + (c->start_polls == 0 ? 1u : 0u);
+  a->gate = c->team_gate + (c->team_turn & 1) * kGateBytes / 4;
+  a->gate_next = c->team_gate + (~c->team_turn & 1) * kGateBytes / 4;
   a->gate_polls = c->start_polls < 0 ? kGatePolls : c->start_polls;
   a->wait_polls = c->wait_polls < 0 ? kWaitPolls : c->wait_polls;
   a->told = c->team_told;

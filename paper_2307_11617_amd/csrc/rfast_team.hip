@@ -35,8 +35,8 @@
 // diagnostics and reads see them as rfast_init left them.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
-// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.7; 32 nodes, p = 4096,
-// batch 64: 21.2 -> 9.0; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 7.3; one agent of 55 per
+// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.6; 32 nodes, p = 4096,
+// batch 64: 21.2 -> 9.0; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 7.4; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
 #include <type_traits>
@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   constexpr int KB = kE <= 2 ? 8 : (kE == 4 ? 4 : 2);  // in-edges whose ring values are in flight together
   extern __shared__ float4 lds4[];
   __shared__ int verdict;
-  const unsigned arrived = threadIdx.x == 0 ? team_arrive(a) : 0u;
+  if (threadIdx.x == 0) team_arrive(a);
   const int n = s.n, M = s.M, W = a.W, B = a.B, S = s.prob.samples;
   const int64_t p = s.p;
   const int i = blockIdx.x / W, w = blockIdx.x - i * W;
@@ -324,7 +324,10 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   if (owner) {
     fetch_plan(q);
   }
-  if (tid == 0) verdict = team_complete(a, arrived);
+  if (wave == 0) {
+    const int all = team_complete(a, lane);
+    if (lane == 0) verdict = all;
+  }
   __syncthreads();
   if (verdict != 0) {
     drain();  // (rows may be on their way into LDS)

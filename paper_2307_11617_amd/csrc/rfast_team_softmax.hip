@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   extern __shared__ float4 lds4[];
   __shared__ u64 act_mask[kBlockRounds / 64], ev_mask[kBlockRounds / 64];
   __shared__ int verdict;
-  const unsigned arrived = threadIdx.x == 0 ? team_arrive(a) : 0u;
+  if (threadIdx.x == 0) team_arrive(a);
   const int n = s.n, M = s.M, W = a.W, B = a.B, FT = a.C, d = s.prob.d;
   const int64_t p = s.p;
   const int i = blockIdx.x / W, w = blockIdx.x - i * W;
@@ -230,7 +230,10 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   if (owner) {
     fetch_plan(q);
   }
-  if (tid == 0) verdict = team_complete(a, arrived);
+  if (wave == 0) {
+    const int all = team_complete(a, lane);
+    if (lane == 0) verdict = all;
+  }
   __syncthreads();
   if (verdict != 0) {
     drain();  // (rows may be on their way into LDS)
