@@ -40,7 +40,7 @@ struct Offsets {
   size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_head, t_next, hist_next, ticket;
   size_t gen_active, gen_delay_r, gen_delay_c, gen_drop_r, gen_drop_c, gen_batch, gen_cdf;
   int32_t gen_depth;
-  size_t xbar, resid, gscratch, diag, team_packets, team_flags, team_gate;
+  size_t xbar, resid, gscratch, diag, team_packets, team_gate, team_flags;  // (flags right behind the gate)
   size_t total;
 };
 
@@ -136,13 +136,13 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
     shape.prob = *prob;
     most = rfast_team_softmax_shape(shape, 0, 0, kTeamMost);
     o.team_packets = L.take(rfast_team_softmax_packet_bytes(most, n, prob));
-    o.team_flags = L.take(rfast_team_softmax_flag_bytes(most, n, prob));
+    o.team_gate = L.take(2 * kGateBytes + rfast_team_softmax_flag_bytes(most, n, prob));
   } else {
     if (prob->kind != RFAST_OBJ_DIAG_QUADRATIC && n <= kTeamMost) most.W = std::min(32, kTeamMost / n);
     o.team_packets = L.take(rfast_team_packet_bytes(most, n, prob));
-    o.team_flags = L.take(rfast_team_flag_bytes(most, n));
+    o.team_gate = L.take(2 * kGateBytes + rfast_team_flag_bytes(most, n));
   }
-  o.team_gate = L.take(2 * kGateBytes);
+  o.team_flags = o.team_gate + 2 * kGateBytes;
   o.total = L.total;
   return o;
 }
@@ -395,6 +395,41 @@ template <class Launch> hipError_t in_team_order(rfast_ctx* c, Launch launch) {
   o.stream = c->stream;
   (void)hipGetLastError();
   return hipSuccess;
+}
+
+// Pinned words through which the device speaks to the host, a cache line per context: a page that all contexts of the
+// process share and that stays (like the events above; allocating pinned memory takes some 100 us, a fifth of what making
+// a small context does), and an allocation of its own for each context beyond the 64 that it holds.
+std::mutex g_told_mutex;
+char* g_told = nullptr;
+uint64_t g_told_used = 0;
+
+hipError_t take_told(rfast_ctx* c) {
+  const std::lock_guard<std::mutex> lock(g_told_mutex);
+  hipError_t e = hipSuccess;
+  if (!g_told) e = hipHostMalloc((void**)&g_told, 64 * 64, hipHostMallocPortable);
+  if (e != hipSuccess) {
+    g_told = nullptr;
+  } else if (~g_told_used != 0) {
+    const int slot = __builtin_ctzll(~g_told_used);
+    g_told_used |= 1ull << slot;
+    c->team_told = (unsigned*)(g_told + 64 * slot);
+  } else {
+    e = hipHostMalloc((void**)&c->team_told, 64, hipHostMallocPortable);
+    if (e != hipSuccess) c->team_told = nullptr;
+  }
+  if (c->team_told) c->team_told[0] = c->team_told[1] = 0;
+  return e;
+}
+
+// (nothing on the device writes to it any more)
+void drop_told(rfast_ctx* c) {
+  if (!c->team_told) return;
+  const std::lock_guard<std::mutex> lock(g_told_mutex);
+  const ptrdiff_t at = g_told ? (char*)c->team_told - g_told : -1;
+  if (at >= 0 && at < 64 * 64) g_told_used &= ~(1ull << (at / 64));
+  else (void)hipHostFree(c->team_told);
+  c->team_told = nullptr;
 }
 
 // the context's stream has been waited for and is about to be given up
@@ -761,16 +796,14 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   if (c->team.W > 0) {
     const bool softmax = prob->kind == RFAST_OBJ_SOFTMAX_BF16;
     chk(hipMemsetAsync(c->team_packets, 0, softmax ? rfast_team_softmax_packet_bytes(c->team, n, prob) : rfast_team_packet_bytes(c->team, n, prob), c->stream));
-    chk(hipMemsetAsync(c->team_flags, 0, softmax ? rfast_team_softmax_flag_bytes(c->team, n, prob) : rfast_team_flag_bytes(c->team, n), c->stream));
-    chk(hipMemsetAsync(c->team_gate, 0, 2 * kGateBytes, c->stream));
-    chk(hipHostMalloc((void**)&c->team_told, 64, hipHostMallocPortable));
-    if (e == hipSuccess) c->team_told[0] = c->team_told[1] = 0;
+    chk(hipMemsetAsync(c->team_gate, 0, 2 * kGateBytes + (softmax ? rfast_team_softmax_flag_bytes(c->team, n, prob) : rfast_team_flag_bytes(c->team, n)), c->stream));
+    chk(take_told(c));
   }
   chk(rfast_wave_prime(c));
   chk(hipStreamSynchronize(c->stream));  // the host vectors die with this scope
   if (e != hipSuccess) {
     const int r = hipfail(nullptr, e, "uploading graph");
-    if (c->team_told) (void)hipHostFree(c->team_told);
+    drop_told(c);
     delete c;
     return r;
   }
@@ -1579,7 +1612,7 @@ void rfast_destroy(rfast_ctx* c) {
   for (int w = 0; w < 3; ++w)
     for (int s = 0; s < 2; ++s)
       for (hipEvent_t ev : c->ev[w][s]) (void)hipEventDestroy(ev);
-  if (c->team_told) (void)hipHostFree(c->team_told);
+  drop_told(c);
   context_gone();
   delete c;
 }

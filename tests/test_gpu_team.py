@@ -413,3 +413,32 @@ def test_wait_that_runs_out_is_reported_everywhere(softmax, case):
         run(g, 0, 20)
         g.check()
     (_tight if softmax else _same)(a, b, case)
+
+
+def test_more_contexts_than_the_shared_page_holds():
+    """The words by which the device tells the host about a team's launches: contexts beyond the 64 of the shared page,
+    and contexts in places that were given back, see their own and nobody else's."""
+    w = _workload("fewer_coordinates_than_a_quad_pair")
+    gpus = [harness.make_gpu(w) for _ in range(67)]
+    st, dev = harness.upload_chunk(gpus[0], w, 0, 20)
+    for k, g in enumerate(gpus):
+        g.init(None, w.sched.initial_batch())
+        if k in (3, 65):
+            rfast_set_wait_limits(g.ctx, -1, 0)
+        g.run(20, *[dev[f] for f in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma, dev["batch_idx"])
+    for k, g in enumerate(gpus):
+        if k in (3, 65):
+            with pytest.raises(RFastError, match="waited in vain"):
+                g.read("X")
+        else:
+            g.check()
+            assert np.array_equal(g.read("X"), gpus[0].read("X")), k
+    for k in (3, 66, 65, 10):
+        gpus[k].close()
+    for _ in range(3):
+        g = harness.make_gpu(w)
+        g.init(None, w.sched.initial_batch())
+        g.run(20, *[dev[f] for f in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma, dev["batch_idx"])
+        g.check()
+        assert np.array_equal(g.read("X"), gpus[0].read("X"))
+        gpus.append(g)
