@@ -33,6 +33,14 @@ template <class T> __device__ inline T fixed(const T* p) {
   return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
 }
 
+// What is read from another node's ring.  Its other readers run beside this one, and find the line in L2 or behind it if
+// it came there by an ordinary load; everything else a pass touches once, and streams past (V<-4>, V<-5>).  Measured, us
+// per round, rings streamed too -> rings cached -> also the rings' stores and z cached -> everything: 128 nodes of an
+// exponential graph, p 100000: 100.7 -> 81.5 -> 82.5 -> 87.4; softmax 128 x 131072: 176.8 -> 161.7 -> 168.0 -> 173.6;
+// mesh of 36, p 250001: 51.9 -> 45.9 -> 46.4 -> 47.6; tree of 64, p 1 M (little to share): 272 -> 264 -> 281 -> 291;
+// 16 nodes of a bidirectional ring, p 11.2 M: 1529 -> 1514 -> 1571 -> 1648.
+template <int VEC> using Ring = V<(VEC == -4 ? 4 : VEC == -5 ? 5 : VEC)>;
+
 // Loads of one live in-edge of C (plan word pl): the running sum being consumed and the one
 // consumed last time (rho~ of S4), which is read from the sender's ring while it is still there.
 template <int VEC>
@@ -41,8 +49,8 @@ __device__ inline void load_edge(const RfastDev& s, int e, int src, int pl, int 
   const float* ring = s.sigma_ring + (size_t)src * M * p + k;
   const int prev = (pl >> 8) & 0xFF;
   const float* last = prev != 0xFF ? ring + (size_t)prev * p : s.rho_tilde + (size_t)e * p + k;
-  *sg = V<VEC>::ld(ring + (size_t)(pl & 0xFF) * p);
-  *rt = V<VEC>::ld(last);
+  *sg = Ring<VEC>::ld(ring + (size_t)(pl & 0xFF) * p);
+  *rt = Ring<VEC>::ld(last);
 }
 
 // Softmax objective: the GEMMs read the weights as bf16, 8 consecutive features of one class per
@@ -111,7 +119,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
 #pragma unroll
     for (int q = 0; q < KB; ++q)
       if (re0 + q < re1) {
-        vb[q] = V<VEC>::ld(s.v_ring + ((size_t)at(s.r_src + re0 + q) * M + at(s.slot_r + re0 + q)) * p + k);
+        vb[q] = Ring<VEC>::ld(s.v_ring + ((size_t)at(s.r_src + re0 + q) * M + at(s.slot_r + re0 + q)) * p + k);
         vw[q] = at(s.r_w + re0 + q);
       }
   }
@@ -165,7 +173,7 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
         float w_now[KB];
 #pragma unroll
         for (int q = 0; q < KB; ++q) {
-          if (eb + q < re1) vb[q] = V<VEC>::ld(s.v_ring + ((size_t)uniform(src[q]) * M + uniform(ver[q])) * p + k);
+          if (eb + q < re1) vb[q] = Ring<VEC>::ld(s.v_ring + ((size_t)uniform(src[q]) * M + uniform(ver[q])) * p + k);
           w_now[q] = vw[q];
         }
         look(eb + KB);
@@ -254,6 +262,7 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
   const int2 slot = s.active_plan[a];  // {node, its counter at the start of the round}, node < 0: no work
   if (slot.x < 0) return;
   const int tile = blockIdx.x - a * tiles_per_node;
+  if (tile >= (int)group_tiles(s.p)) return;  // (the last coordinates of a ragged row must not be taken twice)
   each_group<VEC>(tile, s.p, [&](auto vec, int64_t k) { state_update<MODE, decltype(vec)::value, MOM, KB, DEEP>(s, gamma, slot, tile, k); });
 }
 
@@ -381,7 +390,7 @@ __device__ inline void sum_edges(const int32_t* src, const float* w, int e0, int
     float w_now[KB];
 #pragma unroll
     for (int q = 0; q < KB; ++q) {
-      if (eb + q < e1) vb[q] = V<VEC>::ld(row(uniform(from[q])));
+      if (eb + q < e1) vb[q] = Ring<VEC>::ld(row(uniform(from[q])));
       w_now[q] = wt[q];
     }
     look(eb + KB);
@@ -440,13 +449,19 @@ template <int MODE, bool MOM, int KB, bool DEEP>
 hipError_t launch_deep(rfast_ctx* c, float gamma) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  const int64_t tiles = group_tiles(d.p);
+  // Consecutive workgroups go round the eight dies, each with an L2 of its own: a multiple of eight tiles per node puts
+  // a tile of every node, which shares its neighbours' rows, on one die (128 nodes of an exponential graph, p 100000:
+  // 81.4 -> 77.6 us per round, p 66000: 57.7 -> 53.4; up to seven workgroups per node that find nothing are the price).
+  int64_t tiles = group_tiles(d.p);
+  if (tiles >= 32) tiles = (tiles + 7) / 8 * 8;
   const int64_t blocks = tiles * d.n;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  // Stream past the caches once the state dwarfs them (256 MB of last-level cache).  Wavefronts per
+  // Stream past the caches (but for the rings, see Ring) once the state is too large for them: at 8 to 10 MB per array
+  // both are even, below streaming loses (64 nodes, p 30000: 16.8 against 17.7 us per round), above it gains (128 nodes,
+  // p 50000: 43.9 against 42.7; mesh of 36, p 220001: 41.5 against 39.8; a star of 20, p 300000, loses 2 %).  Wavefronts per
   // SIMD matter: the bidirectional ring (about 15 streams per node-update) is fastest at 3, slower at
   // 2 (capped through reserved LDS: +11 %) and at 4 or 5 (+2 %, +4 %); the register count of KB sets it.
-  const bool streaming = (double)d.n * (double)d.p * 4.0 >= 32.0e6;
+  const bool streaming = (double)d.n * (double)d.p * 4.0 >= 16.0e6;
   if (vec4 && streaming)
     hipLaunchKernelGGL((rfast_state_kernel<MODE, -4, MOM, KB, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else if (vec4)
