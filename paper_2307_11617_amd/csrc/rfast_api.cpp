@@ -37,7 +37,7 @@ struct Offsets {
   size_t x, z, g, v_ring, sigma_ring, rho_tilde;
   size_t r_ptr, r_src, r_dst, r_w, r_self, c_ptr, c_src, c_dst, c_w, c_self, co_ptr, co_eid, co_w, ro_ptr, ro_eid;
   size_t t, t_hist, tau_r, tau_c, deliv_r, deliv_c, round_no, err;
-  size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_head, t_next, hist_next, ticket;
+  size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_far, blk_head, t_next, hist_next, ticket;
   size_t gen_active, gen_delay_r, gen_delay_c, gen_drop_r, gen_drop_c, gen_batch, gen_cdf;
   int32_t gen_depth;
   size_t xbar, resid, gscratch, diag, team_packets, team_gate, team_flags;  // (flags right behind the gate)
@@ -105,6 +105,7 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
   (void)L.take((size_t)(kResolveAhead - 1) * o.plan_set_bytes);
   o.blk_plan = L.take((size_t)kBlockRounds * ((size_t)n + eR + eC + 1) * 4);
   o.blk_spill = L.take((size_t)kBlockRounds * n * 4);
+  o.blk_far = L.take(prob->kind == RFAST_OBJ_DIAG_QUADRATIC && n <= 32 ? (size_t)n * kFarWords * 4 : 0);
   o.blk_head = L.take((kHeadWords * (size_t)n + eC) * 4);
   o.t_next = L.take(n * 4);
   o.hist_next = L.take(n * H * 4);
@@ -761,6 +762,8 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   d.blk_spill = (int32_t*)(b + o.blk_spill);
   d.t_next = (int32_t*)(b + o.t_next); d.hist_next = (int32_t*)(b + o.hist_next); d.ticket = (int32_t*)(b + o.ticket);
   d.blk_head = nullptr;
+  d.blk_slots = 0;
+  d.blk_far = (int32_t*)(b + o.blk_far);
   c->blk_plan_base = (int32_t*)(b + o.blk_plan);
   c->blk_head_base = (int32_t*)(b + o.blk_head);
   c->plan_set0 = b + o.n_active;
@@ -991,11 +994,22 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
     if (to_decay < len) len = (int32_t)to_decay;
   }
   if (gemv) return rfast_tiny_eligible(c) || len >= team_least_rounds(c) ? len : 0;
-  // A launch moves every live ring slot, a pass per round only what the round reads: even, timed side by side, from 2
-  // rounds on up to 1 MB per array (rows that start at any address: 3), 3 up to 2 MB, 4 up to 3 MB, 5 up to 8 MB
-  // (2 rounds of 12 nodes, p 50000: 26.6 against 17.8 us; of 30 nodes, p 50000: 51.7 against 26.8).
+  // A launch moves every live ring slot, a pass per round only what the round reads.  One pass per round against a launch of
+  // r rounds, timed side by side with half of the nodes active: how many rounds it takes depends on the state and on the
+  // wavefronts of the launch that a compute unit holds (12 or more, 8, fewer: delays of up to 4, 8, 16 rounds).
+  // Even at r = 2, 2, 3 rounds up to 1 MB per array (mesh of 16, p 7000: 16.1 / 15.8 us at r = 2, delays of up to 16:
+  // 1.03 at r = 3); 3, 3, 6 up to 2 MB; 4, 5, 10 up to 8 MB (8 nodes, p 200000: 1.06 at r = 3, 1.07 at 5, 0.91 at 9);
+  // 4 or 5, 6, 11 or 12 beyond (16 nodes, p 11.2 M: 0.94 at r = 4, 1.15 at 5; 32 nodes, p 1 M, delays of up to 8: 0.80 at 5,
+  // 1.02 at 6; 16 nodes, p 2 M, delays of up to 16: 0.64 at 8).
   const double bytes = (double)c->d.n * (double)c->d.p * 4.0;
-  int32_t least = bytes > 8.0e6 ? kBlockMinRoundsLarge : bytes > 3.0e6 ? 5 : bytes > 2.0e6 ? 4 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 3 : 2;
+  int32_t least;
+  if (rfast_wave_eligible(c)) {
+    const int held = rfast_wave_held(c), row = bytes > 8.0e6 ? 3 : bytes > 2.0e6 ? 2 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 1 : 0;
+    static const int32_t table[4][3] = {{2, 2, 3}, {3, 3, 6}, {4, 5, 10}, {5, 6, 12}};
+    least = table[row][held >= 12 ? 0 : held >= 8 ? 1 : 2];
+  } else {
+    least = bytes > 8.0e6 ? kBlockMinRoundsLarge : bytes > 3.0e6 ? 5 : bytes > 2.0e6 ? 4 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 3 : 2;
+  }
   if (c->use_blocks == 2) least = 2;
   return len >= least ? len : 0;
 }
@@ -1019,6 +1033,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   hipError_t e = hipSuccess;
   d.blk_plan = c->blk_plan_base;
   d.blk_head = tiny || team ? nullptr : c->blk_head_base;
+  blk.slots = d.blk_slots = !tiny && !team && rfast_wave_eligible(c) ? rfast_wave_slots(c) : 0;
   if (!own_resolver) {
     time_begin(c, 2);
     e = rfast_launch_resolve(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C, len);
@@ -1036,6 +1051,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   }
   d.blk_plan = nullptr;
   d.blk_head = nullptr;
+  d.blk_slots = 0;
   if (e != hipSuccess) return hipfail(c, e, "multi-round launch");
   if (rebase_due && !blk.rebase) {
     e = rfast_launch_rebase(c);

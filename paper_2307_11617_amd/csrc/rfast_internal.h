@@ -86,8 +86,16 @@ struct RfastDev {
   // in LDS over several rounds (NULL: not wanted): [n] node words (bit 31 active, low 30 bits the
   // counter at the start of the round), [eR] ring slot per R edge, [eC] plan word per C edge.
   int32_t* blk_plan;
-  int32_t* blk_spill;     // [rounds][n] beside the records: round number + 1 if some in-edge of C of the node has bit 18 set (other
-                          // values: no such edge)
+  int32_t* blk_spill;     // [rounds][n] beside the records: round number + 1 if some in-edge of C of the node has bit 18 set, or,
+                          // records for the wavefront-tile kernel, if the node does anything rare (other values: no such edge)
+  // Records for the wavefront-tile kernel, which holds the latest blk_slots versions of a node on chip, version t in slot t mod
+  // blk_slots (0: records of the other kernels, in slots of the rings in memory).  Word of an edge: the slot there in the low 24 bits,
+  // or, bit 30, bits 24-29 the ring slot in memory of a version that is no longer on chip; bit 31 (graph C): what was
+  // consumed last time has left the sender's ring of M.  Node word: bit 31 active; bit 30 set if nothing rare happens (no
+  // edge with bit 30 or 31, no bit 29); bit 29: the version whose place on chip the round takes goes to the ring in memory.
+  int32_t blk_slots;
+  int32_t* blk_far;       // [n][kFarWords]: version + 1 at version mod kFarWords if the version is read after it has left the chip (other
+                          // values: not, or in an earlier run, where it does no harm)
   // graphs of more than one resolver workgroup: counters and history after the launch, workgroups that are through
   int32_t* t_next;        // [n]
   int32_t* hist_next;     // [n][H]
@@ -104,8 +112,14 @@ struct RfastDev {
   //   12      one bit per slot: the launch writes the slot
   //   13, 14  as 10, 11, for after the launch (what is stored is a slot of 12 that is also one of 13 or 14; with a
   //           rebase on the way out, every slot of 14)
-  // (rings of up to 32 slots).  Then [eC] per C edge: bit 0 set if its S4 buffer was in the rho_tilde array before
-  // (its version outside the sender's ring), bit 1 if it is after.
+  // (rings of up to 32 slots; 8 to 14 for the tile-per-workgroup kernel).  For the wavefront-tile kernel, bit a standing for the
+  // version a activations before the latest:
+  //   6       sums that can still be picked up after the launch
+  //   8, 9    ring slot of the latest version before, its slot on chip; 10, 11 versions and sums to be loaded
+  //   12, 13  as 8, 9 for after; 14, 15 versions and sums to be stored (of those on chip)
+  // Then [eC] per C edge: bit 0 set if its S4 buffer was in the rho_tilde array before
+  // (its version outside the sender's ring), bit 1 if it is after; for the wavefront-tile kernel also bit 2 if its version
+  // is on chip before the launch, bits 8-15 and 16-23 the version's slot in the ring and on chip.
   int32_t* blk_head;
   // schedule of the current round when it is generated on the device
   uint8_t* gen_active;    // [n]
@@ -158,6 +172,7 @@ struct rfast_ctx {
   int32_t use_blocks = 1;       // 1: where it pays, 2: wherever possible; rfast_run / rfast_run_generated may advance several rounds per launch
   int32_t wave_group = 0;       // wavefronts per workgroup of the wavefront-tile kernel (0: chosen by the launcher)
   int32_t* blk_plan_base = nullptr;  // kBlockRounds plan records
+  int32_t* blk_far_base = nullptr;   // kFarWords words per node (graphs of the wavefront-tile kernel)
   int32_t* blk_head_base = nullptr;  // kHeadWords n + eC words, see RfastDev::blk_head
   int32_t max_in_degree = 0;    // most in-edges of R or of C at any node
   int32_t max_degree = 0;       // most in-edges of R, in-edges of C or out-edges of C at any node
@@ -188,6 +203,7 @@ enum { RFAST_MODE_FUSED = 0, RFAST_MODE_MIX = 1, RFAST_MODE_TRACK = 2 };
 // plus 0.33 ms per round against 1.53 ms per round of the streaming kernel: even from 6 rounds on)
 constexpr int kHeadWords = 16;  // words per node in RfastDev::blk_head
 constexpr int kBlockRounds = 512;
+constexpr int kFarWords = 1024;    // words per node in RfastDev::blk_far: more than a launch's rounds and a ring's slots together
 constexpr int kGateWords = 8;      // words on which the workgroups of a team launch report, 64 bytes apart ...
 constexpr size_t kGateBytes = (kGateWords + 1) * 64;  // ... and one more
 constexpr int kTeamMost = 256;  // workgroups of a team launch at most
@@ -199,6 +215,7 @@ struct RfastBlock {
   float gamma;                // step size of its rounds (a launch does not straddle a decay step)
   int32_t rounds;             // 1 .. kBlockRounds
   int32_t rebase;             // wavefront-tile kernel: the running sums are rebased as the tiles are written back
+  int32_t slots;              // wavefront-tile kernel: versions of a node on chip
 };
 
 // launchers (each enqueues on ctx->stream and returns a hipError_t)
@@ -212,6 +229,8 @@ hipError_t rfast_launch_rebase(rfast_ctx* c);
 // several rounds of the separable objective on LDS-resident tiles; the rounds' plans are in blk_plan
 bool rfast_wave_eligible(const rfast_ctx* c);   // the multi-round kernel with one tile per wavefront
 int rfast_wave_lanes(const rfast_ctx* c);       // its lanes per node
+int rfast_wave_slots(const rfast_ctx* c);       // versions of a node it keeps on chip
+int rfast_wave_held(const rfast_ctx* c);        // wavefronts of it that a compute unit holds
 hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk);
 hipError_t rfast_wave_prime(rfast_ctx* c);      // loads the kernels this context can launch, with launches that do nothing
 bool rfast_block_eligible(const rfast_ctx* c);  // the multi-round kernel with one tile per workgroup

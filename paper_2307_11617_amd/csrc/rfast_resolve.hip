@@ -57,7 +57,7 @@ struct Sched {
 
 // Where a lane's edge starts from.
 struct EdgeState {
-  int i, j, old, tj, st;  // receiver, sender, stamp held, the sender's counter and the ring slot of that version
+  int i, j, old, tj, st;  // receiver, sender, stamp held, the sender's counter and the ring slot of that version (FORM 2: slot on chip)
   u64 dl, hist;           // delivery bits (bit k: version tj - k), activity of the sender (bit k: k+1 rounds ago)
 };
 
@@ -97,11 +97,16 @@ __device__ inline void edge_begin(const RfastDev& s, int e, int r0, int rounds, 
   }
 }
 
+// What the resolver writes for a round: the per-round plan arrays, a record of ring slots, or a record for the
+// wavefront-tile kernel (RfastDev::blk_slots).
+enum { kPlans = 0, kRecords = 1, kOnChip = 2 };
+
 // Decides the edge for round r: delay d0 and loss flag as the schedule has them.  Returns the slot read (-1: the
-// receiver is idle) and the plan word.
-template <int KIND>
-__device__ inline int edge_round(const RfastDev& s, int e, int r, int d0, bool dropped, bool act_i, bool act_j, EdgeState& q, int* word, bool* spilled) {
+// receiver is idle; kOnChip: 0 otherwise) and the plan word.  *aside: the sender or the receiver saves the buffer (graph C); kOnChip: anything rare.
+template <int KIND, int FORM>
+__device__ inline int edge_round(const RfastDev& s, int e, int r, int d0, bool dropped, bool act_i, bool act_j, EdgeState& q, int* word, bool* aside) {
   const int M = s.M, tj = q.tj, lo = tj - (M - 2);  // oldest version that stays readable in j's ring during this round
+  const int slots = FORM == kOnChip ? s.blk_slots : M;
   const int d = d0 < 0 ? 0 : (d0 > s.d_max ? s.d_max : d0);
   if (act_i && d != d0) record_edge_error(s, r, KIND, e);  // resolved with the clamped delay
   const int seen = tj - __popcll(q.hist & ((1ull << d) - 1));  // the sender's counter at the start of round r - d
@@ -113,10 +118,19 @@ __device__ inline int edge_round(const RfastDev& s, int e, int r, int d0, bool d
   const int u = seen - back > 0 ? seen - back : 0;
   const int old = q.old;
   const int now = act_i && u > old ? u : old;
-  const int sn = q.st - (tj - now), now_slot = sn < 0 ? sn + M : sn;  // wherever it is used, now lies within the ring
+  const int sn = q.st - (tj - now), now_slot = sn < 0 ? sn + slots : sn;  // wherever it is used, now lies within the ring
   q.old = now;
-  *spilled = false;
-  if (KIND == 0) {
+  *aside = false;
+  if (FORM == kOnChip) {
+    const bool far = act_i && tj - now >= slots;               // the version is no longer on chip
+    const bool gone = KIND && act_i && now != old && old < lo; // what was consumed last time has left the ring
+    *word = act_i ? now_slot : 0;
+    *aside = far || gone;
+    if (*aside) {
+      *word = (far ? 1 << 30 | FastMod(M)(now) << 24 : now_slot) | (gone ? (int)0x80000000 : 0);
+      if (far) s.blk_far[(size_t)q.j * kFarWords + now % kFarWords] = now + 1;
+    }
+  } else if (KIND == 0) {
     *word = act_i ? now_slot : 0;
   } else {
     const bool live = now != old;                // never with an idle receiver
@@ -131,7 +145,7 @@ __device__ inline int edge_round(const RfastDev& s, int e, int r, int d0, bool d
     const int on = now_slot | old_slot << 8 | (live ? 1 << 16 : 0) | (live && leaves ? 1 << 17 : 0) | (spill ? 1 << 18 : 0) |
                    (usual ? 1 << 30 : 0) | (live && !usual ? (int)0x80000000 : 0);
     *word = act_i ? on : (spill ? now_slot | 1 << 18 : 0);
-    *spilled = spill;
+    *aside = spill;
   }
   // the sender publishes version t_j + 1 this round (if it is active): lost only if the schedule says so and not all
   // of the burst-1 versions before it were lost too (versions up to 0 count as delivered)
@@ -139,19 +153,20 @@ __device__ inline int edge_round(const RfastDev& s, int e, int r, int d0, bool d
   if (act_j) {
     q.dl = (q.dl << 1) | ((!dropped || all_lost) ? 1u : 0u);
     q.tj = tj + 1;
-    q.st = q.st + 1 == M ? 0 : q.st + 1;
+    q.st = q.st + 1 == slots ? 0 : q.st + 1;
   }
   q.hist = (q.hist << 1) | (act_j ? 1u : 0u);
-  return act_i ? now_slot : -1;
+  return !act_i ? -1 : FORM == kOnChip ? 0 : now_slot;
 }
 
 // One edge through all rounds.  barrier: called once everything read from the state arrays is in registers.
-// RECORDS: plan records (s.blk_plan) instead of per-round plan arrays.  The body of the loop is straight-line but for
+// FORM: what is written per round; *rare (kOnChip) is set if an edge does anything rare.  The body of the loop is straight-line but for
 // the rare spill, and loads nothing but the inputs of the next chunk: memory operations complete in order, so a load
 // inside a round would wait for the stores of the rounds before it (0.5 us per round instead of 0.35).
-template <int KIND, bool RECORDS, class Barrier>
-__device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds, size_t plan_stride, const Sched& sc, bool mine,
+template <int KIND, int FORM, class Barrier>
+__device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds, size_t plan_stride, const Sched& sc, bool mine, int* rare,
                                    Barrier barrier) {
+  constexpr bool RECORDS = FORM != kPlans;
   EdgeState q;
   const int32_t* delay = (KIND ? sc.delay_C : sc.delay_R) + e;
   if (mine) edge_begin<KIND>(s, e, r0, rounds, delay, &q);
@@ -161,6 +176,7 @@ __device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds,
   const uint8_t* drop = (KIND ? sc.drop_C : sc.drop_R) + e;
   const int W1 = s.n + s.eR + s.eC + 1;
   const int lo0 = q.old, t0 = q.tj;
+  if (FORM == kOnChip) q.st = FastMod(s.blk_slots)(t0);
   int d[kChunk];
   uint8_t x[kChunk], ai[kChunk], aj[kChunk];
   auto fetch = [&](int base) {  // (past the last round: the last one again, which is not used)
@@ -192,11 +208,14 @@ __device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds,
       const int rq = base + u;
       if (rq >= rounds) break;
       bool spilled;
-      slot = edge_round<KIND>(s, e, r0 + rq, dn[u], fl[u] & 1u, fl[u] & 2u, fl[u] & 4u, q, &word, &spilled);
+      slot = edge_round<KIND, FORM>(s, e, r0 + rq, dn[u], fl[u] & 1u, fl[u] & 2u, fl[u] & 4u, q, &word, &spilled);
       if (RECORDS) {
         *rec = word;
         rec += W1;
-        if (KIND && spilled) s.blk_spill[(size_t)rq * s.n + q.i] = r0 + rq + 1;
+        if ((KIND || FORM == kOnChip) && spilled) {
+          s.blk_spill[(size_t)rq * s.n + q.i] = r0 + rq + 1;
+          if (FORM == kOnChip) *rare = 1;
+        }
       } else {
         *slot_out = slot;
         slot_out = shifted(slot_out, plan_stride);
@@ -207,6 +226,10 @@ __device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds,
         }
       }
     }
+  }
+  if (FORM == kOnChip) {  // back to slots of the ring in memory
+    q.st = FastMod(s.M)(q.tj);
+    if (slot >= 0) slot = FastMod(s.M)(q.old);
   }
   if (RECORDS) {  // of the per-round arrays only the last round's slots are looked at (reads of the slot fields)
     *slot_out = slot;
@@ -219,7 +242,11 @@ __device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds,
     int32_t* H = s.blk_head;
     atomicMin(&H[kHeadWords * q.j + (KIND ? 3 : 2)], lo0);
     atomicMin(&H[kHeadWords * q.j + (KIND ? 5 : 4)], q.old);
-    if (KIND) H[kHeadWords * s.n + e] = (lo0 < t0 - (s.M - 2) ? 1 : 0) | (q.old < q.tj - (s.M - 2) ? 2 : 0);
+    if (KIND) {
+      int w = (lo0 < t0 - (s.M - 2) ? 1 : 0) | (q.old < q.tj - (s.M - 2) ? 2 : 0);
+      if (FORM == kOnChip) w |= (t0 - lo0 < s.blk_slots ? 4 : 0) | FastMod(s.M)(lo0) << 8 | FastMod(s.blk_slots)(lo0) << 16;
+      H[kHeadWords * s.n + e] = w;
+    }
   }
 }
 
@@ -250,7 +277,7 @@ __device__ inline int node_rounds(const RfastDev& s, int node, int wave, int lan
       const bool on = an[u] != 0;
       if (s.blk_plan) {
         int32_t* rec = s.blk_plan + (size_t)rq * W1;
-        if (mine) rec[node] = (t & 0x3FFFFFFF) | (on ? (int)0x80000000 : 0);
+        if (mine) rec[node] = (t & (s.blk_slots ? 0x1FFFFFFF : 0x3FFFFFFF)) | (on ? (s.blk_slots ? (int)0xC0000000 : (int)0x80000000) : 0);
         if (node == 0) rec[W1 - 1] = 0;  // a record ends with a word that is always zero
       }
       if (!s.blk_plan || rq + 1 == rounds) {
@@ -283,6 +310,68 @@ __device__ inline int node_rounds(const RfastDev& s, int node, int wave, int lan
   return t;
 }
 
+// What a launch of the wavefront-tile kernel finds about the nodes before its first and after its last round
+// (RfastDev::blk_head), and, where anything rare happens, the marks in the node words.  By the whole workgroup.
+__device__ inline void on_chip_heads(const RfastDev& s, int r0, int rounds, int* rare) {
+  const int M = s.M, K = s.blk_slots;
+  auto word = [&](int j, int w) { return __hip_atomic_load(&s.blk_head[kHeadWords * j + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  // Versions that somebody holds after the launch and that are still in the ring of M then: from this one on
+  auto kept = [&](int te, int lo_v, int lo_s) {
+    const int lo = lo_v < lo_s ? lo_v : lo_s;
+    return lo > te - (M - 1) ? lo : te - (M - 1);
+  };
+  for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
+    const int t0 = word(j, 0), te = word(j, 1), lo_v0 = word(j, 2), lo_s0 = word(j, 3), lo_v1 = word(j, 4), lo_s1 = word(j, 5);
+    unsigned in_v = 0, in_s = 0, put_v = 0, put_s = 0, sums = 0;
+    for (int a = 0; a < M && a < 32; ++a) {
+      const unsigned bit = 1u << a;
+      if (a < K && t0 - a >= lo_v0) in_v |= bit;
+      if (a < K && t0 - a >= lo_s0) in_s |= bit;
+      if (a < K && te - a > t0 && te - a >= lo_v1) put_v |= bit;
+      if (a < K && te - a > t0 && te - a >= lo_s1) put_s |= bit;
+      if (te - a >= lo_s1) sums |= bit;
+    }
+    int32_t* H = s.blk_head + kHeadWords * j;
+    H[6] = (int)sums;
+    H[8] = t0 % M;
+    H[9] = t0 % K;
+    H[10] = (int)in_v;
+    H[11] = (int)in_s;
+    H[12] = te % M;
+    H[13] = te % K;
+    H[14] = (int)put_v;
+    H[15] = (int)put_s;
+    const int first = kept(te, lo_v1, lo_s1);
+    if (te - K >= (first > t0 ? first : t0 + 1)) *rare = 1;
+  }
+  __syncthreads();
+  if (!*rare) return;
+  const int W1 = s.n + s.eR + s.eC + 1, cells = rounds * s.n;
+  constexpr int kAhead = 4;
+  for (int c0 = threadIdx.x; c0 < cells; c0 += kAhead * blockDim.x) {
+    int w[kAhead], mark[kAhead], j[kAhead];
+    int32_t* at[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int c = c0 + u * (int)blockDim.x < cells ? c0 + u * (int)blockDim.x : c0, q = c / s.n;
+      j[u] = c - q * s.n;
+      at[u] = s.blk_plan + (size_t)q * W1 + j[u];
+      w[u] = __hip_atomic_load(at[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      mark[u] = __hip_atomic_load(&s.blk_spill[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r0 + q + 1;
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (w[u] >= 0 || c0 + u * (int)blockDim.x >= cells) continue;
+      const int t0 = word(j[u], 0), te = word(j[u], 1);
+      const int t = t0 + (((w[u] & 0x1FFFFFFF) - t0) & 0x1FFFFFFF), leaves = t + 1 - K;  // the place of this version is taken
+      const bool keep = leaves > t0 && (leaves >= kept(te, word(j[u], 4), word(j[u], 5)) ||
+                                        __hip_atomic_load(&s.blk_far[(size_t)j[u] * kFarWords + leaves % kFarWords], __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT) == leaves + 1);
+      if (keep || mark[u]) *at[u] = (w[u] & ~(1 << 30)) | (keep ? 1 << 29 : 0);
+    }
+  }
+}
+
 // rounds > 1: consecutive rounds in one launch, the schedule arrays of round q at offset q of each
 // pointer, its plan record (multi-round kernels) behind the previous one, or, without records, its per-round plan
 // arrays plan_stride bytes behind those of the previous round.
@@ -296,6 +385,8 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
   const bool single = gridDim.x == 1;
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
+  __shared__ int rare;
+  if (threadIdx.x == 0) rare = 0;
   auto barrier = [&] {
     if (single) __syncthreads();
   };
@@ -318,12 +409,14 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
     }
   } else if (id < lanes_n + lanes_R) {
     const int e = id - lanes_n;
-    if (s.blk_plan) edge_rounds<0, true>(s, e, r0, rounds, plan_stride, sc, e < s.eR, barrier);
-    else edge_rounds<0, false>(s, e, r0, rounds, plan_stride, sc, e < s.eR, barrier);
+    if (s.blk_plan && s.blk_slots) edge_rounds<0, kOnChip>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
+    else if (s.blk_plan) edge_rounds<0, kRecords>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
+    else edge_rounds<0, kPlans>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
   } else {
     const int e = id - lanes_n - lanes_R;
-    if (s.blk_plan) edge_rounds<1, true>(s, e, r0, rounds, plan_stride, sc, e < s.eC, barrier);
-    else edge_rounds<1, false>(s, e, r0, rounds, plan_stride, sc, e < s.eC, barrier);
+    if (s.blk_plan && s.blk_slots) edge_rounds<1, kOnChip>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
+    else if (s.blk_plan) edge_rounds<1, kRecords>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
+    else edge_rounds<1, kPlans>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
   }
   __syncthreads();
   if (!single) {
@@ -346,7 +439,7 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
     if (threadIdx.x == 0) *s.ticket = 0;
   }
   // what the lanes of a multi-round launch test per ring slot (RfastDev::blk_head), from the counters and stamps
-  if (s.blk_head)
+  if (s.blk_head && !s.blk_slots)
     for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
       int32_t* H = s.blk_head + kHeadWords * j;
       const int M = s.M, t0 = H[0], te = H[1];
@@ -374,6 +467,7 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
       H[13] = (int)out_v;
       H[14] = (int)out_s;
     }
+  if (s.blk_head && s.blk_slots) on_chip_heads(s, r0, rounds, &rare);
   if (threadIdx.x == 0) *s.round_no = r0 + rounds;
 }
 

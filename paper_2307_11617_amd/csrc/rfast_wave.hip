@@ -9,11 +9,19 @@
 // any other wavefront, the wavefronts of a CU drift out of step, and while one waits for its LDS
 // reads another computes.  The plan words of a round are read from global memory one round ahead
 // (the records of all rounds are a few KB that every wavefront of the chip reads, so they stay in the
-// caches), which leaves LDS to the rings and takes the plan reads out of the critical path.  The S4
-// buffers live in the registers of the receiving node's lanes: a buffer is needed only after its
-// version has left the sender's ring, and in the round in which it leaves the receiver's lanes copy
-// it from that ring themselves (the resolver marks the round and names the slot), whether the
-// receiver is active or not.  So the round loop touches global memory for the plan words only.
+// caches), which leaves LDS to the rings and takes the plan reads out of the critical path.  What was
+// consumed last time over an edge (S4) lives in the registers of the receiving node's lanes, and so does a
+// node's own latest sum, so a round reads one value per edge from LDS and touches global memory for the
+// plan words only.
+//
+// LDS holds the latest K versions of a node, not the M = D + 2 of the ring in memory: the reads of a round come before its
+// publications in the program of the wavefront, so that the oldest version gives its place to the new one (M - 1 versions
+// always suffice), and a version older than the longest delay is read only after several losses in a row.  Such a read
+// is marked in the plan; the version goes to the ring in memory when it loses its place on chip, if anybody
+// reads it later or holds it after the launch, and comes from there.  The fewer versions, the more
+// wavefronts: that decides (500 rounds of 16 nodes, p 11.2 M, us per round: 192.7 with nine versions of which eight
+// wavefronts fit a CU, 167 with the same eight and the round's work cut, 139.5 with twelve at six versions, 137.8 with sixteen at
+// five; a SIMD is busy with its vector ALU only from three wavefronts on).
 //
 // The arithmetic is, operation for operation, that of rfast_state_kernel<FUSED> and of
 // rfast_block_kernel: the three paths give the same bits.  (One liberty: where those skip a missing
@@ -59,9 +67,8 @@ __device__ inline void wave_sync() {
 // its own for every workgroup at the start, up to 14 us, and what depends on the node alone set up once
 // per wavefront, 10 rounds took 5.1 ms against 5.3, but 20 rounds 7.4 against 7.1 and 500 rounds 101.8
 // against 93.9: the same round loop, instruction for instruction, ran 8 % slower.)
-// Occupancy is pinned to two wavefronts per SIMD, which is what the LDS of a CU holds at nine ring
-// slots: once the registers allowed three, the eight wavefronts of a CU were spread unevenly over
-// its SIMDs and the launch took 4 % longer.
+// PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 registers), 3 at four (164), 2 at six (three
+// would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).
 //
 // Only what can matter is moved.  Stamps never go back (S2a / S2b take the largest stamp received), so
 // a version older than every stamp held on its sender's out-edges will never be read again: such a
@@ -70,6 +77,7 @@ __device__ inline void wave_sync() {
 // not write are not stored either, nor x and z of a node it never activated, and an S4 buffer is moved
 // only while its version is outside its sender's ring.  With the delays of the bidirectional-ring
 // workload that is 30 rows per node instead of 46.
+//
 // Multipliers for the two divisions of a lane number that the kernel starts with, by the lanes per node and by the
 // lanes of a row segment: x / d = (x * ceil(2^16 / d)) >> 16 for x < 256 and d <= 256 (the error of the quotient,
 // x (d ceil(2^16 / d) - 2^16) / (2^16 d), stays below 1 / d).  The division itself is some 25 instructions, which
@@ -84,11 +92,11 @@ static WaveDiv wave_div(int lw, int W) {
   return dv;
 }
 
-template <int kDeg, bool MOM, int W, bool ANY>
-__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) rfast_wave_kernel(RfastDev s, RfastBlock blk, int lw, WaveDiv dv) {
+template <int kDeg, bool MOM, int W, bool ANY, int PER>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER, PER))) rfast_wave_kernel(RfastDev s, RfastBlock blk, int lw, WaveDiv dv) {
   constexpr int VEC = 4;
   extern __shared__ float4 lds4[];
-  const int n = s.n, M = s.M;
+  const int n = s.n, M = s.M, K = blk.slots;
   const int64_t p = s.p;
   const int W1 = n + s.eR + s.eC + 1;  // words of a plan record; the last one is always zero
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -107,15 +115,22 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   const bool wave_has = k_wg + (int64_t)wave * lw * 4 < p;  // this wavefront has a tile (the last workgroup may be ragged)
   const bool mine = i < n && k < p;
   const int left = p - k < 4 ? (int)(p - k) : 4;  // ANY: coordinates of the row from the lane's first one on
-  const size_t ring_f4 = (size_t)n * M * lw;   // float4 of one ring of one wavefront's tile
-  float4* v_l = lds4 + (size_t)wave * 2 * ring_f4;  // [n][M][lw], the tile of this wavefront
-  float4* sg_l = v_l + ring_f4;                     // [n][M][lw]
-  // LDS addresses are byte offsets: column of the lane in a node's ring + slot * bytes per slot, one
-  // 24-bit multiply-add each
+  const size_t ring_f4 = (size_t)n * K * lw;   // float4 of one ring of one wavefront's tile: [n][K][lw], first v, then the sums
+  // LDS addresses proper (32 bits, the start of the array included): column of the lane in a node's ring + slot * bytes
+  // per slot, one 24-bit multiply-add each, which leaves the high byte of a plan word to its flags.
   const unsigned slot_bytes = (unsigned)lw * sizeof(float4);
-  auto at = [&](float4* ring, unsigned column, int slot) -> float4& {
-    return *reinterpret_cast<float4*>(reinterpret_cast<char*>(ring) + (__umul24((unsigned)slot, slot_bytes) + column));
+  typedef float Vec4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) Vec4 LdsVec4;
+  auto lds_ld = [&](unsigned a) {
+    const Vec4 t = *(LdsVec4*)(uintptr_t)a;
+    return make_float4(t.x, t.y, t.z, t.w);
   };
+  auto lds_st = [&](unsigned a, float4 w) {
+    const Vec4 t = {w.x, w.y, w.z, w.w};
+    *(LdsVec4*)(uintptr_t)a = t;
+  };
+  const unsigned sg_off = (unsigned)n * K * slot_bytes;  // from a node's ring of v to its ring of sums
+  const unsigned tile = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds4 + (unsigned)wave * 2 * sg_off;
   // Moving the rings: lane T of the workgroup moves column cT (of the lw W columns of a row segment) of
   // node iT, i.e. column lT of the tile of wavefront wT.  With W = 1 that is the lane's own column.
   const int seg = lw * W;
@@ -124,30 +139,29 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   const int64_t kT = k_wg + 4 * cT;
   const bool moves = iT < n && kT < p;
   const int leftT = p - kT < 4 ? (int)(p - kT) : 4;
-  float4* mv_l = lds4 + (size_t)wT * 2 * ring_f4 + (size_t)iT * M * lw + lT;  // + slot * lw (+ ring_f4 for the sums)
-  // What the resolver, which has been through all rounds of the launch already, left about the moved node: the slot
-  // of its latest version after the launch and, one bit per ring slot, which slots hold versions that a receiver
-  // can still pick up before the launch (the others are not loaded), which the launch writes, and which hold
-  // versions that can still be picked up after it (RfastDev::blk_head).
-  int se_T = 0;
-  unsigned in_v = 0, in_s = 0, put_v = 0, put_s = 0;
+  float4* mv_l = lds4 + (size_t)wT * 2 * ring_f4 + (size_t)iT * K * lw + lT;  // + slot * lw (+ ring_f4 for the sums)
+  // What the resolver, which has been through all rounds of the launch already, left about the moved node: the places of
+  // its latest version before the launch, in memory and on chip, and, one bit per version counted back from it, which
+  // versions a receiver can still pick up (the others are not loaded); and the same for after the launch, where a version
+  // goes back if the launch wrote it, still holds it and somebody can still read it, and with a rebase every readable sum
+  // is shifted, whether the launch wrote it or not and wherever it is.
+  int4 head = make_int4(0, 0, 0, 0), tail = head;
   if (moves) {
-    const int4 a = *reinterpret_cast<const int4*>(s.blk_head + kHeadWords * iT + 8);   // s0, se, in_v, in_s
-    const int4 b = *reinterpret_cast<const int4*>(s.blk_head + kHeadWords * iT + 12);  // written, out_v, out_s
-    se_T = a.y; in_v = (unsigned)a.z; in_s = (unsigned)a.w;
-    // a slot goes back if the launch wrote it and somebody can still read its version; with a rebase on the way
-    // out every readable slot of the running sums is shifted, written or not
-    put_v = (unsigned)b.x & (unsigned)b.y;
-    put_s = blk.rebase ? (unsigned)b.z : (unsigned)b.x & (unsigned)b.z;
+    head = *reinterpret_cast<const int4*>(s.blk_head + kHeadWords * iT + 8);
+    tail = *reinterpret_cast<const int4*>(s.blk_head + kHeadWords * iT + 12);
+    if (blk.rebase) tail.w = s.blk_head[kHeadWords * iT + 6];
   }
 
   float4 x, z, g, h, c, m = make_float4(0.f, 0.f, 0.f, 0.f);
   const bool momentum = MOM && s.mom != nullptr;  // the heavy-ball buffer of the optimizer variant is in use
   int ce0 = 0, dR = 0, dI = 0, dO = 0;
-  // The S4 buffers of the node's in-edges, in registers: a buffer matters only once its version has left
-  // the sender's ring, and the receiver's own lanes copy it from that ring in the round in which it leaves
-  // (active or not), so no other lane and no global memory is involved between load and store.
-  float4 rt[kDeg];
+  // What was consumed last time over each in-edge of C, in registers: the sender's running sum of that version, or (bit u of
+  // `prod`) its product with the weight, which is what the array of S4 buffers holds.  So a round reads one sum per edge from LDS,
+  // and a buffer is written only at the end of a launch, if its version is outside the sender's ring then.
+  float4 last[kDeg];
+  unsigned prod = 0, outside = 0;  // outside: the same for after the launch, edge by edge (RfastDev::blk_head)
+  int where[kDeg];
+  float4 sig = make_float4(0.f, 0.f, 0.f, 0.f);  // the node's own latest running sum
   float r_self = 0.f, c_self = 0.f;
   // the node's edges, in registers for the whole launch: LDS column of the sender's ring, weight,
   // position of the edge's plan word in a record; a missing edge has weight zero, the node's own
@@ -156,18 +170,15 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   // positions of plan words as unsigned byte offsets: a 32-bit offset from a uniform base, no 64-bit address arithmetic
   unsigned r_pw[kDeg], c_pw[kDeg];
   float r_w[kDeg], c_w[kDeg];
-  int c_from[kDeg];  // sender of each in-edge of C
-  int rt_where[kDeg], end_slot[kDeg];
 #pragma unroll
   for (int u = 0; u < kDeg; ++u) {
-    rt_where[u] = end_slot[u] = 0;
-    r_col[u] = c_col[u] = 0;
+    r_col[u] = c_col[u] = tile;
+    where[u] = 0;
     r_pw[u] = c_pw[u] = 4u * (W1 - 1);
     r_w[u] = c_w[u] = 0.f;
-    c_from[u] = 0;
-    rt[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    last[u] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  const unsigned own = (unsigned)(i * M * lw + ln) * sizeof(float4);  // this lane's column in the rings of its node
+  const unsigned a_own = tile + (unsigned)(i * K * lw + ln) * sizeof(float4);  // this lane's column in the rings of its node
   unsigned node_pw = 4u * (W1 - 1);
   if (mine) {
     node_pw = 4u * i;
@@ -181,11 +192,10 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int u = 0; u < kDeg; ++u) {
       const bool hr = u < dR, hc = u < dI;
-      r_col[u] = (unsigned)((hr ? s.r_src[re0 + u] : i) * M * lw + ln) * sizeof(float4);
+      r_col[u] = tile + (unsigned)((hr ? s.r_src[re0 + u] : i) * K * lw + ln) * sizeof(float4);
       r_w[u] = hr ? s.r_w[re0 + u] : 0.f;
       r_pw[u] = 4u * (hr ? n + re0 + u : W1 - 1);
-      c_from[u] = hc ? s.c_src[ce0 + u] : i;
-      c_col[u] = (unsigned)(c_from[u] * M * lw + ln) * sizeof(float4);
+      c_col[u] = tile + sg_off + (unsigned)((hc ? s.c_src[ce0 + u] : i) * K * lw + ln) * sizeof(float4);
       c_w[u] = hc ? s.c_w[ce0 + u] : 0.f;
       c_pw[u] = 4u * (hc ? n + s.eR + ce0 + u : W1 - 1);
     }
@@ -220,99 +230,101 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
     h = ld_group<ANY>((const float*)s.prob.data0 + off, left);
     c = ld_group<ANY>((const float*)s.prob.data1 + off, left);
     if (momentum) m = ld_group<ANY>(s.mom + off, left);
-    // an S4 buffer is in the rho_tilde array only while its version is outside its sender's ring (rare)
+    // (a version that neither the array of S4 buffers nor the part of the ring on chip holds comes from the ring in memory)
 #pragma unroll
     for (int u = 0; u < kDeg; ++u)
       if (u < dI) {
-        rt_where[u] = s.blk_head[kHeadWords * n + ce0 + u];
-        end_slot[u] = s.blk_head[kHeadWords * c_from[u] + 9];  // of the sender's latest version after the launch
-        if (rt_where[u] & 1) rt[u] = ld_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left);
+        where[u] = s.blk_head[kHeadWords * n + ce0 + u];
+        outside |= (unsigned)(where[u] >> 1 & 1) << u;
+        if (where[u] & 1) {
+          last[u] = ld_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left);
+          prod |= 1u << u;
+        } else if (!(where[u] & 4)) {
+          last[u] = ld_group<ANY>(s.sigma_ring + ((size_t)s.c_src[ce0 + u] * M + (where[u] >> 8 & 0xFF)) * p + k, left);
+        }
       }
   }
-  // rings: kBatch slots of both rings in flight at a time (rings of up to twelve slots in one round trip to
-  // memory), then into LDS; a slot whose version nobody can read any more gets zeros instead
-  constexpr int kBatch = kDeg <= 2 ? 12 : (kDeg <= 4 ? 10 : 8);
+  // rings, from the latest version back: kBatch versions of both in flight at a time, then into LDS; a version
+  // that nobody can read any more is zeros instead (the multiply-adds with weight zero need finite values)
+  constexpr int kBatch = PER >= 4 ? 5 : PER >= 3 ? 6 : kDeg <= 2 ? 12 : (kDeg <= 4 ? 10 : 8);
+  const int64_t back_to_last = (int64_t)(M - 1) * p, to_sums = s.sigma_ring - s.v_ring;
   if (moves) {
-    const float* vg = s.v_ring + (size_t)iT * M * p + kT;
-    const float* sgg = s.sigma_ring + (size_t)iT * M * p + kT;
-    for (int m0 = 0; m0 < M; m0 += kBatch) {
+    int at_g = head.x, at_l = head.y;
+    const float* vg = s.v_ring + ((size_t)iT * M + at_g) * p + kT;
+    for (int a0 = 0; a0 < K; a0 += kBatch) {
       float4 tv[kBatch], ts[kBatch];
-      const unsigned get_v = in_v >> m0, get_s = in_s >> m0;  // bits past the last slot are clear
+      const unsigned get_v = (unsigned)head.z >> a0, get_s = (unsigned)head.w >> a0;  // bits past the oldest are clear
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         tv[u] = ts[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (get_v & (1u << u)) tv[u] = ld_group<ANY>(vg, leftT);
-        if (get_s & (1u << u)) ts[u] = ld_group<ANY>(sgg, leftT);
-        vg += p;
-        sgg += p;
+        if (get_s & (1u << u)) ts[u] = ld_group<ANY>(vg + to_sums, leftT);
+        vg += at_g == 0 ? back_to_last : -p;
+        at_g = at_g == 0 ? M - 1 : at_g - 1;
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)
-        if (m0 + u < M) {
-          mv_l[(size_t)(m0 + u) * lw] = tv[u];
-          mv_l[ring_f4 + (size_t)(m0 + u) * lw] = ts[u];
+        if (a0 + u < K) {
+          mv_l[__umul24((unsigned)at_l, (unsigned)lw)] = tv[u];
+          mv_l[ring_f4 + __umul24((unsigned)at_l, (unsigned)lw)] = ts[u];
+          at_l = at_l == 0 ? K - 1 : at_l - 1;
         }
     }
   }
   // The stored sample of S2b is a function of (x_i, t_i); from here on it lives in registers, and so
   // does the LDS address of the node's current version in its v ring (advanced by one slot per activation,
   // back to the first slot after the last: no division, no multiplication).
-  // These are LDS addresses proper (32 bits, the start of the array included), so that the access needs no
-  // further addition.
-  typedef float Vec4 __attribute__((ext_vector_type(4)));
-  typedef __attribute__((address_space(3))) Vec4 LdsVec4;
-  const unsigned a_own =
-      (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds4 + (unsigned)(wave * 2 * ring_f4 * sizeof(float4)) + own;
   unsigned a_cur = a_own;
   int ver_next = 1, ver_first = 1;  // version of the node's next activation (counted here: the plan's copy would need a mask and an add)
-  const unsigned a_end = a_own + __umul24((unsigned)M, slot_bytes), sg_off = (unsigned)n * M * slot_bytes;
-  auto own_ld = [&](unsigned a) {
-    const Vec4 t = *(LdsVec4*)(uintptr_t)a;
-    return make_float4(t.x, t.y, t.z, t.w);
-  };
-  auto own_st = [&](unsigned a, float4 w) {
-    const Vec4 t = {w.x, w.y, w.z, w.w};
-    *(LdsVec4*)(uintptr_t)a = t;
-  };
+  const unsigned a_end = a_own + __umul24((unsigned)K, slot_bytes);
   if (mine) {
-    const int t0 = plan_a.node & 0x3FFFFFFF;
+    const int t0 = s.blk_head[kHeadWords * i];
     g = diag_sample<VEC, MOM>(s, h, c, x, i, t0, k);
-    a_cur = a_own + __umul24((unsigned)s.blk_head[kHeadWords * i + 8], slot_bytes);  // the slot of version t0
+    a_cur = a_own + __umul24((unsigned)s.blk_head[kHeadWords * i + 9], slot_bytes);  // the place of version t0
     ver_next = ver_first = t0 + 1;
   }
   if (W > 1) __syncthreads();  // the tiles of the workgroup are in LDS
   else wave_sync();
 
+  if (mine) {
+    sig = lds_ld(a_cur + sg_off);
+#pragma unroll
+    for (int u = 0; u < kDeg; ++u)
+      if (where[u] & 4) last[u] = lds_ld(c_col[u] + __umul24((unsigned)(where[u] >> 16 & 0xFF), slot_bytes));
+  }
+
   // one round with the plan words P, while those of the round after it arrive in N
   auto round = [&](int q, const Plan& P, Plan& N) {
-    const bool active = P.node < 0;  // bit 31: node i is activated in this round (never set in the zero word)
-    const unsigned a_new = a_cur + slot_bytes == a_end ? a_own : a_cur + slot_bytes;
-    float4 nb[kDeg], cur[kDeg], last[kDeg], sig_cur;
-    // S4 for a buffer whose version leaves its sender's ring in this round without the receiver consuming
-    // a newer one (bit 18; the word then names the slot of that version): copied while it is still there
-    // (rare: one test for all in-edges of the node)
-    int leaving = 0;
-#pragma unroll
-    for (int u = 0; u < kDeg; ++u) leaving |= P.c[u];
-    if (leaving & (1 << 18)) {
-#pragma unroll
-      for (int u = 0; u < kDeg; ++u)
-        if (P.c[u] & (1 << 18)) rt[u] = mul_s(c_w[u], at(sg_l, c_col[u], P.c[u] & 0xFF));
-    }
     // the plan words of the next round, from global memory, used one round from now
     fetch(min(q + 1, blk.rounds - 1), N);
-    if (active) {
-      // every ring value of the round in one batch of LDS reads (what a missing or idle edge reads
-      // is a valid address; its value is multiplied by zero)
+    if (P.node < 0) {  // bit 31: node i is activated in this round (never set in the zero word)
+      float4 nb[kDeg], cur[kDeg];
+      const unsigned a_new = a_cur + slot_bytes == a_end ? a_own : a_cur + slot_bytes;
+      // every ring value of the round in one batch of LDS reads (what a missing edge reads is a valid address; its value
+      // is multiplied by zero)
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) nb[u] = at(v_l, r_col[u], P.r[u]);
+      for (int u = 0; u < kDeg; ++u) nb[u] = lds_ld(r_col[u] + __umul24((unsigned)P.r[u], slot_bytes));
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) {
-        const int prev = (P.c[u] >> 8) & 0xFF;  // 0xFF: not in the ring (any slot will do, the value is not used)
-        cur[u] = at(sg_l, c_col[u], P.c[u] & 0xFF);
-        last[u] = at(sg_l, c_col[u], min(prev, M - 1));
+      for (int u = 0; u < kDeg; ++u) cur[u] = lds_ld(c_col[u] + __umul24((unsigned)P.c[u], slot_bytes));
+      const bool rare = P.node < (int)0xC0000000;  // bit 30 clear: one test for whatever is not the usual round
+      if (rare) {
+        // a version that the chip no longer holds: from the ring in memory, where it has been all along or was put when
+        // it lost its place
+        const int re0 = s.r_ptr[i];
+#pragma unroll
+        for (int u = 0; u < kDeg; ++u) {
+          if (P.r[u] & (1 << 30)) nb[u] = ld_group<ANY>(s.v_ring + ((size_t)s.r_src[re0 + u] * M + (P.r[u] >> 24 & 0x3F)) * p + k, left);
+          if (P.c[u] & (1 << 30)) cur[u] = ld_group<ANY>(s.sigma_ring + ((size_t)s.c_src[ce0 + u] * M + (P.c[u] >> 24 & 0x3F)) * p + k, left);
+        }
+        // vmcnt(0), here: with these loads under way on one of two paths, every round waited for the plan words just asked for
+        // (20 rounds of 16 nodes, p 11.2 M: 296 -> 263 us per round)
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (P.node & (1 << 29)) {  // the version whose place this round takes
+          float* to = s.v_ring + ((size_t)i * M + (unsigned)(ver_next - K) % (unsigned)M) * p + k;
+          st_group<ANY>(to, left, lds_ld(a_new));
+          if (dO > 0) st_group<ANY>(to + to_sums, left, lds_ld(a_new + sg_off));
+        }
       }
-      sig_cur = own_ld(a_cur + sg_off);
       // S1: local descent; with the optimizer variant along the heavy-ball buffer m <- beta m + z
       if (momentum) m = fma_s(s.beta, m, z);
       const float4 v = fma_s(-blk.gamma, momentum ? m : z, x);
@@ -323,27 +335,30 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
       for (int u = 0; u < kDeg; ++u) x_new = fma_s(r_w[u], nb[u], x_new);
       const float4 g_new = diag_sample<VEC, MOM>(s, h, c, x_new, i, ver_next, k);
       ++ver_next;
-      // S2b: tracker sum over the in-edges of C; S4: buffer what was consumed
+      // S2b: tracker sum over the in-edges of C; S4: keep what was consumed.  An idle edge, whose stamp did not move, reads
+      // the sum it holds already and adds zero: no branch.
       float4 z_half = z;
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) {
-        // The usual case — a live edge (bit 16) whose previous version is still in the ring (bits 8-15 below
-        // 0xFF) and whose consumed version does not leave it (bit 17 clear) — and the idle edge run through the
-        // same multiply-add, the idle edge with weight zero (it adds zero to z): no branch; the other live
-        // cases are rare and branch.
-        // (bits 30 and 31 of the word say which case it is: one signed compare each)
-        const float a_eff = P.c[u] > 0x3FFFFFFF ? c_w[u] : 0.f;
-        z_half = track_edge(z_half, a_eff, cur[u], last[u], true);
-        if (P.c[u] < 0) {
-          if (((P.c[u] >> 8) & 0xFF) != 0xFF) z_half = track_edge(z_half, c_w[u], cur[u], last[u], true);
-          else z_half = track_edge(z_half, c_w[u], cur[u], rt[u], false);  // the version consumed last time has left the ring
-          if (P.c[u] & (1 << 17)) rt[u] = mul_s(c_w[u], cur[u]);  // consumed, and leaving the ring in this round
+      for (int u = 0; u < kDeg; ++u) z_half = track_edge(z_half, c_w[u], cur[u], last[u], true);
+      if (rare) {  // once more, with what left the sender's ring of M before it was consumed as the product it was kept as
+        z_half = z;
+#pragma unroll
+        for (int u = 0; u < kDeg; ++u) {
+          if (P.c[u] < 0) {
+            z_half = track_edge(z_half, c_w[u], cur[u], prod >> u & 1 ? last[u] : mul_s(c_w[u], last[u]), false);
+            prod &= ~(1u << u);
+          } else {
+            z_half = track_edge(z_half, c_w[u], cur[u], last[u], true);
+          }
         }
       }
+#pragma unroll
+      for (int u = 0; u < kDeg; ++u) last[u] = cur[u];
       z_half = sub(add(z_half, g_new), g);
-      // S3: publish version t+1 (slots nobody reads in this round); S2c: keep a_ii, push
-      own_st(a_new, v);
-      if (dO > 0) own_st(a_new + sg_off, add(sig_cur, z_half));
+      // S3: publish version t+1 (in the place of the oldest one, whose readers of this round are through); S2c: keep a_ii, push
+      lds_st(a_new, v);
+      sig = add(sig, z_half);
+      if (dO > 0) lds_st(a_new + sg_off, sig);
       x = x_new;
       z = mul_s(c_self, z_half);
       g = g_new;
@@ -351,6 +366,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
     }
     wave_sync();  // S5: the round is over, its publications are visible to the lanes of this wavefront
   };
+  // (two loops, each unrolled by two, so that each keeps its values where it likes)
   if (wave_has) {
     for (int q = 0; q < blk.rounds; q += 2) {
       round(q, plan_a, plan_b);
@@ -370,7 +386,6 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 
   // Write-back.  With blk.rebase the running sums are rebased on the way (what rfast_rebase_kernel does, and with
   // its operations): sender j's latest sum leaves every slot of its ring, and a_ij times it every buffer it feeds.
-  // s.t holds the counters after the launch, and t mod M is the slot of a node's latest version then.
   if (mine) {
     const size_t off = (size_t)i * p + k;
     if (ver_next != ver_first) {  // x and z of a node that was not activated are what they were
@@ -381,38 +396,52 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int u = 0; u < kDeg; ++u)
       // the buffer lives in the array only if its version is outside the sender's ring now
-      if (u < dI && (rt_where[u] & 2)) {
-        if (blk.rebase) rt[u] = sub(rt[u], mul_s(c_w[u], at(sg_l, c_col[u], end_slot[u])));
-        st_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left, rt[u]);
+      if (outside >> u & 1) {
+        float4 rt = prod >> u & 1 ? last[u] : mul_s(c_w[u], last[u]);
+        if (blk.rebase) {
+          const int end = s.blk_head[kHeadWords * s.c_src[ce0 + u] + 13];  // of the sender's latest version
+          rt = sub(rt, mul_s(c_w[u], lds_ld(c_col[u] + __umul24((unsigned)end, slot_bytes))));
+        }
+        st_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left, rt);
       }
   }
   if (W > 1) __syncthreads();  // every wavefront of the workgroup is through with its rounds
   else wave_sync();
   if (moves) {
+    const unsigned put_v = (unsigned)tail.z, put_s = (unsigned)tail.w;
     float4 base = make_float4(0.f, 0.f, 0.f, 0.f);
     const bool shift = blk.rebase && put_s != 0;  // nobody reads the sums of a node without out-edges
-    if (shift) base = mv_l[ring_f4 + (size_t)se_T * lw];
-    float* vg = s.v_ring + (size_t)iT * M * p + kT;
-    float* sgg = s.sigma_ring + (size_t)iT * M * p + kT;
-    for (int m0 = 0; m0 < M; m0 += kBatch) {
+    if (shift) base = mv_l[ring_f4 + __umul24((unsigned)tail.y, (unsigned)lw)];
+    int at_g = tail.x, at_l = tail.y;
+    float* vg = s.v_ring + ((size_t)iT * M + at_g) * p + kT;
+    for (int a0 = 0; a0 < K; a0 += kBatch) {
       float4 tv[kBatch], ts[kBatch];
-      const unsigned back_v = put_v >> m0, back_s = put_s >> m0;  // bits past the last slot are clear
+      const unsigned back_v = put_v >> a0, back_s = put_s >> a0;  // bits past the oldest are clear
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        if (back_v & (1u << u)) tv[u] = mv_l[(size_t)(m0 + u) * lw];
-        if (back_s & (1u << u)) {
-          ts[u] = mv_l[ring_f4 + (size_t)(m0 + u) * lw];
-          if (shift) ts[u] = sub(ts[u], base);
+      for (int u = 0; u < kBatch; ++u)
+        if (a0 + u < K) {
+          if (back_v & (1u << u)) tv[u] = mv_l[__umul24((unsigned)at_l, (unsigned)lw)];
+          if (back_s & (1u << u)) {
+            ts[u] = mv_l[ring_f4 + __umul24((unsigned)at_l, (unsigned)lw)];
+            if (shift) ts[u] = sub(ts[u], base);
+          }
+          at_l = at_l == 0 ? K - 1 : at_l - 1;
         }
-      }
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        if (back_v & (1u << u)) st_group<ANY>(vg, leftT, tv[u]);
-        if (back_s & (1u << u)) st_group<ANY>(sgg, leftT, ts[u]);
-        vg += p;
-        sgg += p;
-      }
+      for (int u = 0; u < kBatch; ++u)
+        if (a0 + u < K) {
+          if (back_v & (1u << u)) st_group<ANY>(vg, leftT, tv[u]);
+          if (back_s & (1u << u)) st_group<ANY>(vg + to_sums, leftT, ts[u]);
+          vg += at_g == 0 ? back_to_last : -p;
+          at_g = at_g == 0 ? M - 1 : at_g - 1;
+        }
     }
+    if (shift)
+      for (int a = K; a < M; ++a) {  // sums that are no longer on chip
+        if (put_s >> a & 1) st_group<ANY>(vg + to_sums, leftT, sub(ld_group<ANY>(vg + to_sums, leftT), base));
+        vg += at_g == 0 ? back_to_last : -p;
+        at_g = at_g == 0 ? M - 1 : at_g - 1;
+      }
   }
 }
 
@@ -493,64 +522,90 @@ __global__ void __launch_bounds__(64) rfast_sync_wave_kernel(RfastDev s, float g
   st_group<ANY>(s.v_ring + (size_t)i * s.M * p + k, left, v);
 }
 
-size_t wave_lds_bytes(const RfastDev& d, int lw) { return (size_t)2 * d.n * d.M * lw * sizeof(float4); }
+constexpr size_t kCuLds = 160 * 1024, kLdsGrain = 1280;  // LDS of a compute unit, and what it is handed out in
+
+// LDS of one wavefront's tile with `slots` versions per node
+size_t wave_lds_bytes(const RfastDev& d, int slots) { return (size_t)2 * d.n * slots * (64 / d.n) * sizeof(float4); }
+// Wavefronts of that size that a compute unit holds, `per` to a SIMD at most.
+int wave_resident(const RfastDev& d, int slots, int per) {
+  const size_t one = (wave_lds_bytes(d, slots) + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
+  return (int)std::min<size_t>(kCuLds / one, (size_t)(4 * per));
+}
+
 
 }  // namespace
 
 // The separable objective, at most 32 nodes with at most kWaveMaxDeg edges of a
-// kind each, rings of at most 32 slots (one bit per slot in the records of the resolver), and the rings of one
-// wavefront's tile fitting into LDS.
+// kind each, rings of at most 32 slots (one bit per version in the records of the resolver; the LDS of one
+// wavefront's tile is 64 KB at most then).
 bool rfast_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg &&
-         d.n <= kWaveMaxNodes && d.M <= 32 && wave_lds_bytes(d, 64 / d.n) <= 156 * 1024;
+  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes && d.M <= 32;
 }
 
 int rfast_wave_lanes(const rfast_ctx* c) { return 64 / c->d.n; }
 
-// Wavefronts per workgroup.  Short launches, which are mostly tile movement, gain from row segments of a
-// whole cache line of 128 B (as many wavefronts, 2 or 4, as that takes, unless LDS then holds fewer
-// wavefronts per CU); long ones lose more to the workgroup's barriers and to its wavefronts leaving together
-// than the wider segments save.  Measured on 16 nodes x 11.2 M coordinates, nine ring slots, ms per launch
-// with 1 / 2 / 4 wavefronts: 10 rounds 5.60 / 5.29 / 5.35, 20 rounds 7.15 / 7.17 / 7.27, 100 rounds
-// 22.5 / 23.4 / 23.1.
-static int wave_group(const rfast_ctx* c, int rounds) {
+// Wavefronts per SIMD (the instantiation) and versions of a node on chip.  At least as many versions as the longest delay
+// reads, and one more: with none to spare the reads of versions that have left the chip cost more than the wavefronts bring
+// (16 nodes, p 11.2 M, delays of up to 4, five versions and sixteen wavefronts against six and twelve, us per round of
+// 20: 255 against 263 where 2 % of the packets are lost, 353 against 274 where 20 % are).  Then as many more as
+// LDS has room for at that number of wavefronts.
+struct WaveShape {
+  int per, slots;
+};
+static WaveShape wave_shape(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  const int lw = 64 / d.n;
-  const size_t one = wave_lds_bytes(d, lw), cu = 160 * 1024;
-  if (c->wave_group == 1 || c->wave_group == 2 || c->wave_group == 4) return (size_t)c->wave_group * one <= cu ? c->wave_group : 1;
-  if (rounds >= 16) return 1;
-  const size_t resident = std::min<size_t>(cu / one, 8);  // wavefronts of this kernel a CU holds (two per SIMD at most)
+  const int least = std::min(d.M - 1, d.d_max + 2);
+  WaveShape w;
+  for (w.per = c->max_degree <= 2 ? 4 : c->max_degree <= 4 ? 3 : 2; w.per > 2 && wave_resident(d, least, w.per) < 4 * w.per;) --w.per;
+  w.slots = least;
+  while (w.slots < d.M - 1 && wave_resident(d, w.slots + 1, w.per) == wave_resident(d, least, w.per)) ++w.slots;
+  return w;
+}
+int rfast_wave_slots(const rfast_ctx* c) { return wave_shape(c).slots; }
+int rfast_wave_held(const rfast_ctx* c) { return wave_resident(c->d, wave_shape(c).slots, wave_shape(c).per); }
+
+// Wavefronts per workgroup, as many as LDS holds without losing a resident wavefront.  Short launches, which are
+// mostly tile movement, gain from row segments of whole cache lines; in long ones the barriers of a workgroup weigh as much.
+// Measured with 1 / 2 / 4 wavefronts, us per round: 16 nodes x 11.2 M, 8 rounds 530 / 496 / 486, 20 rounds 260 / 250 /
+// 244, 32 rounds 206 / 202 / 202, 64 and more even; 32 nodes x 1 M, six edge slots, 10 rounds 149 / 138 / 140, 20 rounds 93 / 88 / 87; 8 nodes
+// x 3 M, 20 rounds 26.3 / 26.4 / 25.4.
+static int wave_group(const rfast_ctx* c, int rounds, WaveShape shape) {
+  const RfastDev& d = c->d;
+  const size_t one = wave_lds_bytes(d, shape.slots);
+  if (c->wave_group == 1 || c->wave_group == 2 || c->wave_group == 4) return (size_t)c->wave_group * one <= kCuLds ? c->wave_group : 1;
+  if (rounds > 64) return 1;
+  const size_t most = (size_t)(4 * shape.per), resident = (size_t)wave_resident(d, shape.slots, shape.per);
   int w = 1;
-  while (w < 4 && (size_t)(w * lw) * sizeof(float4) < 128 && std::min<size_t>(cu / (2 * w * one) * (2 * w), 8) >= resident) w *= 2;
+  while (w < 4 && std::min<size_t>(kCuLds / (2 * w * one) * (2 * w), most) >= resident) w *= 2;
   return w;
 }
 
-template <int kDeg, bool MOM, int W, bool ANY>
+template <int kDeg, bool MOM, int W, bool ANY, int PER>
 static hipError_t launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   static bool raised = false;
   if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY>,
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY, PER>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
   }
   const RfastDev& d = c->d;
-  if (!d.blk_plan || !d.blk_head) return hipErrorInvalidValue;
+  if (!d.blk_plan || !d.blk_head || blk.slots < 1 || blk.slots > d.M - 1 || blk.slots != d.blk_slots) return hipErrorInvalidValue;
   const int lw = 64 / d.n;
   const int64_t run = (int64_t)kXcds * (kTileRun / W), per = (int64_t)4 * lw * W;
   const int64_t groups = ((d.p + per - 1) / per + run - 1) / run * run;  // whole runs: a workgroup past the end leaves at once
   if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY>), dim3((unsigned)groups), dim3(64 * W), (size_t)W * wave_lds_bytes(d, lw),
-                     c->stream, c->d, blk, lw, wave_div(lw, W));
+  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY, PER>), dim3((unsigned)groups), dim3(64 * W),
+                     (size_t)W * wave_lds_bytes(d, blk.slots), c->stream, c->d, blk, lw, wave_div(lw, W));
   return hipGetLastError();
 }
 
 // A launch that does nothing (one workgroup that finds no coordinates and leaves): the first launch of a kernel
 // pays for loading its code, about 0.7 ms, which belongs to setting a context up and not to its first run.
-template <int kDeg, bool MOM, int W, bool ANY>
+template <int kDeg, bool MOM, int W, bool ANY, int PER>
 static hipError_t prime_wave(rfast_ctx* c) {
-  const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY, PER>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e != hipSuccess) return e;
   RfastDev none = c->d;
   none.p = 0;
@@ -558,46 +613,58 @@ static hipError_t prime_wave(rfast_ctx* c) {
   blk.gamma = 0.f;
   blk.rounds = 0;
   blk.rebase = 0;
-  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY>), dim3(1), dim3(64 * W), 0, c->stream, none, blk, 64 / c->d.n, wave_div(64 / c->d.n, W));
+  blk.slots = 1;
+  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY, PER>), dim3(1), dim3(64 * W), 0, c->stream, none, blk, 64 / c->d.n, wave_div(64 / c->d.n, W));
   return hipGetLastError();
 }
 
-template <int kDeg, bool MOM>
-static hipError_t prime_wave_w(rfast_ctx* c) {
-  const size_t one = wave_lds_bytes(c->d, 64 / c->d.n), cu = 160 * 1024;
-  if (c->d.p % 4 != 0) return prime_wave<kDeg, MOM, 1, true>(c);
-  hipError_t e = prime_wave<kDeg, MOM, 1, false>(c);
-  if (e == hipSuccess && 2 * one <= cu) e = prime_wave<kDeg, MOM, 2, false>(c);
-  if (e == hipSuccess && 4 * one <= cu) e = prime_wave<kDeg, MOM, 4, false>(c);
+template <int kDeg, bool MOM, int PER>
+static hipError_t prime_wave_w(rfast_ctx* c, int slots) {
+  const size_t one = wave_lds_bytes(c->d, slots);
+  if (c->d.p % 4 != 0) return prime_wave<kDeg, MOM, 1, true, PER>(c);
+  hipError_t e = prime_wave<kDeg, MOM, 1, false, PER>(c);
+  if (e == hipSuccess && 2 * one <= kCuLds) e = prime_wave<kDeg, MOM, 2, false, PER>(c);
+  if (e == hipSuccess && 4 * one <= kCuLds) e = prime_wave<kDeg, MOM, 4, false, PER>(c);
   return e;
+}
+
+// The instantiation for the edges of this context, its optimizer and a launch of that many rounds: f(degree, optimizer, per SIMD).
+template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per, F f) {
+  using T = std::true_type;
+  using N = std::false_type;
+  const int deg = c->max_degree;
+  auto by_deg = [&](auto mom) {
+    if (deg > 4) return f(std::integral_constant<int, kWaveMaxDeg>(), mom, std::integral_constant<int, 2>());
+    if (deg > 2)
+      return per == 3 ? f(std::integral_constant<int, 4>(), mom, std::integral_constant<int, 3>())
+                      : f(std::integral_constant<int, 4>(), mom, std::integral_constant<int, 2>());
+    if (per == 4) return f(std::integral_constant<int, 2>(), mom, std::integral_constant<int, 4>());
+    return per == 3 ? f(std::integral_constant<int, 2>(), mom, std::integral_constant<int, 3>())
+                    : f(std::integral_constant<int, 2>(), mom, std::integral_constant<int, 2>());
+  };
+  return c->d.mom || c->d.wd != 0.f ? by_deg(T()) : by_deg(N());
 }
 
 // Loads the instantiations of the multi-round kernel that this context can launch (rfast_create,
 // rfast_set_optimizer).
 hipError_t rfast_wave_prime(rfast_ctx* c) {
   if (!rfast_wave_eligible(c)) return hipSuccess;
-  const int deg = c->max_degree;
-  if (c->d.mom || c->d.wd != 0.f)
-    return deg <= 2 ? prime_wave_w<2, true>(c) : (deg <= 4 ? prime_wave_w<4, true>(c) : prime_wave_w<kWaveMaxDeg, true>(c));
-  return deg <= 2 ? prime_wave_w<2, false>(c) : (deg <= 4 ? prime_wave_w<4, false>(c) : prime_wave_w<kWaveMaxDeg, false>(c));
-}
-
-template <int kDeg, bool MOM>
-static hipError_t launch_wave_w(rfast_ctx* c, const RfastBlock& blk) {
-  // rows that start at any address: a segment is never a whole cache line, one wavefront per workgroup
-  if (c->d.p % 4 != 0) return launch_wave<kDeg, MOM, 1, true>(c, blk);
-  switch (wave_group(c, blk.rounds)) {
-    case 4: return launch_wave<kDeg, MOM, 4, false>(c, blk);
-    case 2: return launch_wave<kDeg, MOM, 2, false>(c, blk);
-    default: return launch_wave<kDeg, MOM, 1, false>(c, blk);
-  }
+  const WaveShape shape = wave_shape(c);
+  return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) { return prime_wave_w<deg.value, mom.value, per.value>(c, shape.slots); });
 }
 
 hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk) {
-  const int deg = c->max_degree;
-  if (c->d.mom || c->d.wd != 0.f)
-    return deg <= 2 ? launch_wave_w<2, true>(c, blk) : (deg <= 4 ? launch_wave_w<4, true>(c, blk) : launch_wave_w<kWaveMaxDeg, true>(c, blk));
-  return deg <= 2 ? launch_wave_w<2, false>(c, blk) : (deg <= 4 ? launch_wave_w<4, false>(c, blk) : launch_wave_w<kWaveMaxDeg, false>(c, blk));
+  const WaveShape shape = wave_shape(c);
+  if (shape.slots != blk.slots) return hipErrorInvalidValue;
+  return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) {
+    // rows that start at any address: a segment is never a whole cache line, one wavefront per workgroup
+    if (c->d.p % 4 != 0) return launch_wave<deg.value, mom.value, 1, true, per.value>(c, blk);
+    switch (wave_group(c, blk.rounds, shape)) {
+      case 4: return launch_wave<deg.value, mom.value, 4, false, per.value>(c, blk);
+      case 2: return launch_wave<deg.value, mom.value, 2, false, per.value>(c, blk);
+      default: return launch_wave<deg.value, mom.value, 1, false, per.value>(c, blk);
+    }
+  });
 }
 
 // The synchronous mode through the multi-step kernel: the separable objective,
