@@ -105,7 +105,7 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
   (void)L.take((size_t)(kResolveAhead - 1) * o.plan_set_bytes);
   o.blk_plan = L.take((size_t)kBlockRounds * ((size_t)n + eR + eC + 1) * 4);
   o.blk_spill = L.take((size_t)kBlockRounds * n * 4);
-  o.blk_far = L.take(prob->kind == RFAST_OBJ_DIAG_QUADRATIC && n <= 32 ? (size_t)n * kFarWords * 4 : 0);
+  o.blk_far = L.take(prob->kind == RFAST_OBJ_DIAG_QUADRATIC && n <= 64 ? (size_t)n * kFarWords * 4 : 0);
   o.blk_head = L.take((kHeadWords * (size_t)n + eC) * 4);
   o.t_next = L.take(n * 4);
   o.hist_next = L.take(n * H * 4);
@@ -1006,7 +1006,9 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
   if (rfast_wave_eligible(c)) {
     const int held = rfast_wave_held(c), row = bytes > 8.0e6 ? 3 : bytes > 2.0e6 ? 2 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 1 : 0;
     static const int32_t table[4][3] = {{2, 2, 3}, {3, 3, 6}, {4, 5, 10}, {5, 6, 12}};
-    least = table[row][held >= 12 ? 0 : held >= 8 ? 1 : 2];
+    // more than 32 nodes, a lane each: row segments of 16 bytes per tile, so that moving them takes longer
+    static const int32_t narrow[4][3] = {{2, 2, 3}, {3, 3, 6}, {5, 6, 10}, {7, 10, 22}};
+    least = (c->d.n > 32 ? narrow : table)[row][held >= 12 ? 0 : held >= 8 ? 1 : 2];
   } else {
     least = bytes > 8.0e6 ? kBlockMinRoundsLarge : bytes > 3.0e6 ? 5 : bytes > 2.0e6 ? 4 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 3 : 2;
   }
@@ -1308,7 +1310,6 @@ int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_b
   const RfastDev& d = c->d;
   const size_t B = d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC ? 0 : (size_t)d.prob.batch;
   const bool multi = c->use_blocks && rfast_sync_wave_eligible(c);
-  const bool large = (double)d.n * (double)d.p * 4.0 > 8.0e6;
   const bool team = d.prob.kind != RFAST_OBJ_SOFTMAX_BF16 && team_usable(c);
   for (int32_t r = 0; r < rounds;) {
     if (team) {  // least squares / logistic regression: the steps up to the next decay of the step size in one launch
@@ -1335,7 +1336,7 @@ int rfast_sync_run(rfast_ctx* c, int32_t rounds, float gamma, const int32_t* d_b
       const int64_t to_decay = c->gamma_step - c->host_round % c->gamma_step;
       if (to_decay < len) len = (int32_t)to_decay;
     }
-    if (len >= (large && c->use_blocks != 2 ? kBlockMinRoundsLarge : 2)) {
+    if (len >= 2) {
       if (!std::isfinite(gamma)) return fail(c, RFAST_EINVAL, "gamma is not finite");
       if (c->needs_init) return fail(c, RFAST_EINVAL, "rfast_init must follow rfast_set_optimizer");
       if (fold_sync(c) != RFAST_OK) return RFAST_EHIP;

@@ -252,6 +252,7 @@ __device__ inline void edge_rounds(const RfastDev& s, int e, int r0, int rounds,
 
 // The node side: counters, their history, the list of active nodes of every round (or the node words of its record).
 // Lane = node; every wavefront counts the active nodes of the others by itself.  Returns the lane's counter at the end.
+template <bool CHIP>
 __device__ inline int node_rounds(const RfastDev& s, int node, int wave, int lane, int r0, int rounds, size_t plan_stride,
                                   const uint8_t* active, int t, int32_t* hist) {
   const int n = s.n, waves = (n + 63) / 64, W1 = n + s.eR + s.eC + 1;
@@ -277,7 +278,7 @@ __device__ inline int node_rounds(const RfastDev& s, int node, int wave, int lan
       const bool on = an[u] != 0;
       if (s.blk_plan) {
         int32_t* rec = s.blk_plan + (size_t)rq * W1;
-        if (mine) rec[node] = (t & (s.blk_slots ? 0x1FFFFFFF : 0x3FFFFFFF)) | (on ? (s.blk_slots ? (int)0xC0000000 : (int)0x80000000) : 0);
+        if (mine) rec[node] = (t & (CHIP ? 0x1FFFFFFF : 0x3FFFFFFF)) | (on ? (CHIP ? (int)0xC0000000 : (int)0x80000000) : 0);
         if (node == 0) rec[W1 - 1] = 0;  // a record ends with a word that is always zero
       }
       if (!s.blk_plan || rq + 1 == rounds) {
@@ -379,6 +380,8 @@ __device__ inline void on_chip_heads(const RfastDev& s, int r0, int rounds, int*
 // A graph whose lanes fit one workgroup has one barrier, between the last read of the state arrays and the first
 // write to them.  Larger graphs take several workgroups, which leave the counters and the history in a second set of
 // arrays; the last workgroup to finish copies them over (only there does anybody write what another workgroup reads).
+// CHIP: records for the wavefront-tile kernel (a kernel of its own: the others are a hundredth faster without what it needs).
+template <bool CHIP>
 __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, int rounds, size_t plan_stride, Sched sc, int lanes_n,
                                                                     int lanes_R, int lanes_C) {
   const int r0 = *s.round_no;
@@ -386,7 +389,7 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
   __shared__ int rare;
-  if (threadIdx.x == 0) rare = 0;
+  if (CHIP && threadIdx.x == 0) rare = 0;
   auto barrier = [&] {
     if (single) __syncthreads();
   };
@@ -399,7 +402,7 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
   if (id < lanes_n) {
     const int t0 = id < s.n ? s.t[id] : 0;
     barrier();
-    const int t = node_rounds(s, id, id >> 6, lane, r0, rounds, plan_stride, sc.active, t0, single ? s.t_hist : s.hist_next);
+    const int t = node_rounds<CHIP>(s, id, id >> 6, lane, r0, rounds, plan_stride, sc.active, t0, single ? s.t_hist : s.hist_next);
     if (id < s.n) {
       (single ? s.t : s.t_next)[id] = t;
       if (s.blk_head) {
@@ -409,12 +412,12 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
     }
   } else if (id < lanes_n + lanes_R) {
     const int e = id - lanes_n;
-    if (s.blk_plan && s.blk_slots) edge_rounds<0, kOnChip>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
+    if (CHIP) edge_rounds<0, kOnChip>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
     else if (s.blk_plan) edge_rounds<0, kRecords>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
     else edge_rounds<0, kPlans>(s, e, r0, rounds, plan_stride, sc, e < s.eR, &rare, barrier);
   } else {
     const int e = id - lanes_n - lanes_R;
-    if (s.blk_plan && s.blk_slots) edge_rounds<1, kOnChip>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
+    if (CHIP) edge_rounds<1, kOnChip>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
     else if (s.blk_plan) edge_rounds<1, kRecords>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
     else edge_rounds<1, kPlans>(s, e, r0, rounds, plan_stride, sc, e < s.eC, &rare, barrier);
   }
@@ -439,7 +442,7 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
     if (threadIdx.x == 0) *s.ticket = 0;
   }
   // what the lanes of a multi-round launch test per ring slot (RfastDev::blk_head), from the counters and stamps
-  if (s.blk_head && !s.blk_slots)
+  if (!CHIP && s.blk_head)
     for (int j = threadIdx.x; j < s.n; j += blockDim.x) {
       int32_t* H = s.blk_head + kHeadWords * j;
       const int M = s.M, t0 = H[0], te = H[1];
@@ -467,7 +470,7 @@ __global__ void __launch_bounds__(kGroupLanes) rfast_resolve_kernel(RfastDev s, 
       H[13] = (int)out_v;
       H[14] = (int)out_s;
     }
-  if (s.blk_head && s.blk_slots) on_chip_heads(s, r0, rounds, &rare);
+  if (CHIP) on_chip_heads(s, r0, rounds, &rare);
   if (threadIdx.x == 0) *s.round_no = r0 + rounds;
 }
 
@@ -482,12 +485,16 @@ hipError_t rfast_launch_resolve(rfast_ctx* c, const uint8_t* active, const int32
   const int64_t lanes = (int64_t)lanes_n + lanes_R + lanes_C;
   // One workgroup as long as it holds every lane; beyond, workgroups of two wavefronts, which spread over the chip.
   const bool single = lanes <= kGroupLanes;
-  if (!single && d.blk_head) return hipErrorInvalidValue;  // the kernels that read it take graphs of at most 64 nodes
+  if (!single && (d.blk_head || d.blk_slots)) return hipErrorInvalidValue;  // the kernels that read it take graphs of at most 64 nodes
   const int threads = single ? (int)lanes : 128;
   const int64_t groups = (lanes + threads - 1) / threads;
   if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
   const Sched sc = {active, delay_R, delay_C, drop_R, drop_C};
-  hipLaunchKernelGGL(rfast_resolve_kernel, dim3((unsigned)groups), dim3(threads), 0, c->stream, d, rounds, plan_stride, sc, lanes_n,
-                     lanes_R, lanes_C);
+  if (d.blk_plan && d.blk_slots)
+    hipLaunchKernelGGL(rfast_resolve_kernel<true>, dim3((unsigned)groups), dim3(threads), 0, c->stream, d, rounds, plan_stride, sc, lanes_n,
+                       lanes_R, lanes_C);
+  else
+    hipLaunchKernelGGL(rfast_resolve_kernel<false>, dim3((unsigned)groups), dim3(threads), 0, c->stream, d, rounds, plan_stride, sc, lanes_n,
+                       lanes_R, lanes_C);
   return hipGetLastError();
 }

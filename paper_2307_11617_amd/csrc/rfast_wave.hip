@@ -37,7 +37,7 @@ namespace {
 constexpr int kWaveMaxDeg = 6;  // most in-edges of R, in-edges of C and out-edges of C a node may have on this path
                                 // (kernels for 2, 4 and 6 edge slots per node: an exponential graph on 32 nodes has 5
                                 // edges per node and kind; 8 slots would not fit the registers of two wavefronts per SIMD)
-constexpr int kWaveMaxNodes = 32;  // at least 2 lanes (8 coordinates, 32 B of a row) per node
+constexpr int kWaveMaxNodes = 64;  // at least one lane (4 coordinates, 16 B of a row) per node
 constexpr unsigned kXcds = 8;      // accelerator dies; consecutive workgroups go round them
 constexpr unsigned kTileRun = 64;  // neighbouring tiles that one XCD takes in a row
 constexpr unsigned kSyncTileRun = 4;  // the same for the multi-step synchronous kernel (measured: 4 is 3 % faster there than 64)
@@ -535,11 +535,16 @@ int wave_resident(const RfastDev& d, int slots, int per) {
 
 }  // namespace
 
-// The separable objective, at most 32 nodes with at most kWaveMaxDeg edges of a
+// The separable objective, at most 64 nodes with at most kWaveMaxDeg edges of a
 // kind each, rings of at most 32 slots (one bit per version in the records of the resolver; the LDS of one
 // wavefront's tile is 64 KB at most then).
 bool rfast_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
+  // More than 32 nodes on rings of at most three slots (delays of one round at most, no losses): the kernel with a tile per
+  // workgroup, whose wide tiles fit LDS then (us per round, tile per workgroup against tile per wavefront: 36 nodes of a
+  // bidirectional ring, two slots, p 1 M: 153.7 / 263.5 in calls of 4 rounds, 59.9 / 69.7 of 100; 48 nodes, three slots: 237 / 313
+  // and 88 / 72; beyond it loses from 20 rounds on, 36 nodes of a mesh, five slots: 252 / 156).
+  if (d.n > 32 && d.M <= 3 && rfast_block_eligible(c)) return false;
   return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes && d.M <= 32;
 }
 
@@ -621,7 +626,10 @@ static hipError_t prime_wave(rfast_ctx* c) {
 template <int kDeg, bool MOM, int PER>
 static hipError_t prime_wave_w(rfast_ctx* c, int slots) {
   const size_t one = wave_lds_bytes(c->d, slots);
-  if (c->d.p % 4 != 0) return prime_wave<kDeg, MOM, 1, true, PER>(c);
+  if (c->d.p % 4 != 0) {
+    const hipError_t e = prime_wave<kDeg, MOM, 1, true, PER>(c);
+    return e == hipSuccess && 4 * one <= kCuLds ? prime_wave<kDeg, MOM, 4, true, PER>(c) : e;
+  }
   hipError_t e = prime_wave<kDeg, MOM, 1, false, PER>(c);
   if (e == hipSuccess && 2 * one <= kCuLds) e = prime_wave<kDeg, MOM, 2, false, PER>(c);
   if (e == hipSuccess && 4 * one <= kCuLds) e = prime_wave<kDeg, MOM, 4, false, PER>(c);
@@ -657,8 +665,9 @@ hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   const WaveShape shape = wave_shape(c);
   if (shape.slots != blk.slots) return hipErrorInvalidValue;
   return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) {
-    // rows that start at any address: a segment is never a whole cache line, one wavefront per workgroup
-    if (c->d.p % 4 != 0) return launch_wave<deg.value, mom.value, 1, true, per.value>(c, blk);
+    if (c->d.p % 4 != 0)
+      return c->wave_group == 0 && wave_group(c, blk.rounds, shape) == 4 ? launch_wave<deg.value, mom.value, 4, true, per.value>(c, blk)
+                                                                         : launch_wave<deg.value, mom.value, 1, true, per.value>(c, blk);
     switch (wave_group(c, blk.rounds, shape)) {
       case 4: return launch_wave<deg.value, mom.value, 4, false, per.value>(c, blk);
       case 2: return launch_wave<deg.value, mom.value, 2, false, per.value>(c, blk);
@@ -668,7 +677,8 @@ hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk) {
 }
 
 // The synchronous mode through the multi-step kernel: the separable objective,
-// at most 32 nodes with at most kWaveMaxDeg in-edges of a kind each.
+// at most 64 nodes with at most kWaveMaxDeg in-edges of a kind each (64 nodes of a mesh, p 500000, calls of 50: 367 us per
+// step one launch each, 25 this way; calls of 4: 367 / 135).
 bool rfast_sync_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
   return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes;
