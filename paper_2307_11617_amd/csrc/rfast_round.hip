@@ -105,6 +105,8 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
   // sigma_i = sum of every z_half node i produced (1 read + 1 write instead of dO + dO).
   const bool pushes = at(s.co_ptr + i + 1) > at(s.co_ptr + i);
 
+  const bool pulled = kMix && at(s.ro_ptr + i + 1) > at(s.ro_ptr + i);
+
   // ---- every load of the first batch of each phase is issued before its first use:
   //      with few wavefronts per CU this is what keeps enough bytes in flight
   T x_i, z_i, g_old, g_new, h, c, sig_cur, m_i;
@@ -182,8 +184,9 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
           if (eb + q < re1) x_new = fma_s(w_now[q], vb[q], x_new);
       }
     }
-    // S3 (v half): publish version t+1
-    V<VEC>::st(s.v_ring + ((size_t)i * M + slot_new) * p + k, v);
+    // S3 (v half): publish version t+1, unless nobody pulls from this node (the leaves of an in-tree: tree/star of 64 nodes,
+    // p 1 M, half of them leaves: 258.5 -> 248.3 us per round; softmax over a binary tree of 128: 115.7 -> 112.8)
+    if (pulled) V<VEC>::st(s.v_ring + ((size_t)i * M + slot_new) * p + k, v);
     V<VEC>::st(s.x + node_off, x_new);
     if (MODE == RFAST_MODE_MIX) {
       if constexpr (VEC == 4 || VEC == -4) {  // p is a multiple of 2048 for this objective: every tile is full

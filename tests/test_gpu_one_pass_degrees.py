@@ -31,3 +31,34 @@ def test_in_degree_of_one_batch_and_one_more(degree, p, momentum, monkeypatch):
     monkeypatch.setattr(harness, "make_gpu", one_pass)
     coords = None if p < 5000 else np.unique(np.concatenate([np.arange(0, p, 4099), [p - 2, p - 1]]))
     harness.run_parity(w, 60, every=20, coords=coords, momentum=momentum, weight_decay=1e-3 if momentum else 0.0, check_rings=coords is None)
+
+
+@pytest.mark.parametrize("p", [1001, 64_000, 500_001])
+def test_versions_nobody_pulls_are_not_kept(p, monkeypatch):
+    """The leaves of a tree that everybody pulls from above: their versions read as zero, everything else as in the oracle."""
+    n = 9
+    r, c = graphs.tree_pull_star_push(n)
+    w = configs._mk("tree_star", n, p, r, c, 3, 0.002, 0, "diag_quadratic", problems.diag_quadratic(n, p, 5), 0.7, 0.2, 5,
+                    noise_std=0.1, burst=3)
+    make = harness.make_gpu
+
+    def one_pass(w):
+        g = make(w)
+        rfast_use_blocks(g.ctx, False)
+        return g
+    monkeypatch.setattr(harness, "make_gpu", one_pass)
+    coords = None if p < 5000 else np.unique(np.concatenate([np.arange(0, p, 4099), [p - 2, p - 1]]))
+    harness.run_parity(w, 40, every=20, coords=coords, check_rings=coords is None)
+    g = one_pass(w)
+    g.init(None, None)
+    rng = np.random.default_rng(3)
+    R, C = w.R, w.C
+    import torch
+    up = lambda a: torch.as_tensor(a).cuda()  # noqa: E731
+    g.run(6, up(np.ones((6, n), np.uint8)), up(rng.integers(0, 4, (6, R.nnz_off), np.int32)), up(rng.integers(0, 4, (6, C.nnz_off), np.int32)),
+          up(np.zeros((6, R.nnz_off), np.uint8)), up(np.zeros((6, C.nnz_off), np.uint8)), 0.002, None)
+    ring = np.asarray(g.read("V_RING")).reshape(n, -1, p)
+    off = r - np.diag(np.diag(r))
+    leaves = (off != 0).sum(axis=0) == 0
+    assert 0 < leaves.sum() < n
+    assert not ring[leaves].any() and all(ring[i].any() for i in np.flatnonzero(~leaves))
