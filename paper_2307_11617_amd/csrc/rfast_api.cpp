@@ -793,7 +793,11 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   for (int i = 0; i < n; ++i)
     c->max_degree = std::max({c->max_degree, gr.ptr[i + 1] - gr.ptr[i], gc.ptr[i + 1] - gc.ptr[i], gc.out_ptr[i + 1] - gc.out_ptr[i]});
   int max_out_r = 0;
-  for (int i = 0; i < n; ++i) max_out_r = std::max(max_out_r, gr.out_ptr[i + 1] - gr.out_ptr[i]);
+  d.leaves = 0;
+  for (int i = 0; i < n; ++i) {
+    max_out_r = std::max(max_out_r, gr.out_ptr[i + 1] - gr.out_ptr[i]);
+    if (gr.out_ptr[i + 1] == gr.out_ptr[i]) d.leaves = 1;
+  }
   chk(hipMemsetAsync(d.ticket, 0, 4, c->stream));
   choose_team(c, max_out_r);
   if (c->team.W > 0) {

@@ -30,6 +30,7 @@
 // ---------------------------------------------------------------------------
 struct RfastDev {
   int32_t n, M, H, eR, eC, d_max, burst;
+  int32_t leaves;         // some node has no out-edges over R
   int64_t p;
   float* x;
   float* z;

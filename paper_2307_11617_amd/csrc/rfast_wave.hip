@@ -623,17 +623,17 @@ static hipError_t prime_wave(rfast_ctx* c) {
   return hipGetLastError();
 }
 
+// (the forms of long and of short launches: a third that rfast_set_tile_group may choose cost every context 0.2 ms)
 template <int kDeg, bool MOM, int PER>
-static hipError_t prime_wave_w(rfast_ctx* c, int slots) {
-  const size_t one = wave_lds_bytes(c->d, slots);
+static hipError_t prime_wave_w(rfast_ctx* c, WaveShape shape) {
+  const int brief = wave_group(c, 1, shape);
   if (c->d.p % 4 != 0) {
     const hipError_t e = prime_wave<kDeg, MOM, 1, true, PER>(c);
-    return e == hipSuccess && 4 * one <= kCuLds ? prime_wave<kDeg, MOM, 4, true, PER>(c) : e;
+    return e == hipSuccess && brief == 4 ? prime_wave<kDeg, MOM, 4, true, PER>(c) : e;
   }
-  hipError_t e = prime_wave<kDeg, MOM, 1, false, PER>(c);
-  if (e == hipSuccess && 2 * one <= kCuLds) e = prime_wave<kDeg, MOM, 2, false, PER>(c);
-  if (e == hipSuccess && 4 * one <= kCuLds) e = prime_wave<kDeg, MOM, 4, false, PER>(c);
-  return e;
+  const hipError_t e = prime_wave<kDeg, MOM, 1, false, PER>(c);
+  if (e == hipSuccess && brief == 2) return prime_wave<kDeg, MOM, 2, false, PER>(c);
+  return e == hipSuccess && brief == 4 ? prime_wave<kDeg, MOM, 4, false, PER>(c) : e;
 }
 
 // The instantiation for the edges of this context, its optimizer and a launch of that many rounds: f(degree, optimizer, per SIMD).
@@ -658,7 +658,7 @@ template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per,
 hipError_t rfast_wave_prime(rfast_ctx* c) {
   if (!rfast_wave_eligible(c)) return hipSuccess;
   const WaveShape shape = wave_shape(c);
-  return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) { return prime_wave_w<deg.value, mom.value, per.value>(c, shape.slots); });
+  return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) { return prime_wave_w<deg.value, mom.value, per.value>(c, shape); });
 }
 
 hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk) {
