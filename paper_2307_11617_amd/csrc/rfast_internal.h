@@ -173,7 +173,6 @@ struct rfast_ctx {
   int32_t use_blocks = 1;       // 1: where it pays, 2: wherever possible; rfast_run / rfast_run_generated may advance several rounds per launch
   int32_t wave_group = 0;       // wavefronts per workgroup of the wavefront-tile kernel (0: chosen by the launcher)
   int32_t* blk_plan_base = nullptr;  // kBlockRounds plan records
-  int32_t* blk_far_base = nullptr;   // kFarWords words per node (graphs of the wavefront-tile kernel)
   int32_t* blk_head_base = nullptr;  // kHeadWords n + eC words, see RfastDev::blk_head
   int32_t max_in_degree = 0;    // most in-edges of R or of C at any node
   int32_t max_degree = 0;       // most in-edges of R, in-edges of C or out-edges of C at any node
