@@ -105,8 +105,11 @@ __device__ inline void state_update(const RfastDev& s, float gamma, int2 slot, i
   // sigma_i = sum of every z_half node i produced (1 read + 1 write instead of dO + dO).
   const bool pushes = at(s.co_ptr + i + 1) > at(s.co_ptr + i);
 
-  // (a graph without such nodes is spared the look, and so are stretches of single activations: 1.2 % of theirs)
-  const bool pulled = MANY || !s.leaves || at(s.ro_ptr + i + 1) > at(s.ro_ptr + i);
+  // Whether anybody pulls from this node.  Only where the state streams past the caches is a row not written worth the look:
+  // small rounds wait for it (binary tree of 120 nodes, p 1392: 6.29 us per round without it, 6.75 with it), and so do
+  // stretches of single activations (1.2 %).  A graph without such nodes is spared it too.
+  constexpr bool kLook = VEC <= -4 && !MANY;
+  const bool pulled = !kLook || !s.leaves || at(s.ro_ptr + i + 1) > at(s.ro_ptr + i);
 
   // ---- every load of the first batch of each phase is issued before its first use:
   //      with few wavefronts per CU this is what keeps enough bytes in flight
