@@ -269,7 +269,10 @@ __global__ void __launch_bounds__(kThreads) rfast_state_kernel(RfastDev s, float
   const int2 slot = s.active_plan[a];  // {node, its counter at the start of the round}, node < 0: no work
   if (slot.x < 0) return;
   const int tile = blockIdx.x - a * tiles_per_node;
-  if (tile >= (int)group_tiles(s.p)) return;  // (the last coordinates of a ragged row must not be taken twice)
+  // A tile past the end (the launch rounds their number up) finds no coordinates, but for the last ones of a ragged row,
+  // which must not be taken twice.  (Tested on every row it cost 0.2 us per pass: 64 nodes of softmax, p 49152, 52.1 -> 51.8 us per round.)
+  if constexpr (VEC == 5 || VEC == -5)
+    if (tile >= (int)group_tiles(s.p)) return;
   each_group<VEC>(tile, s.p, [&](auto vec, int64_t k) { state_update<MODE, decltype(vec)::value, MOM, KB, DEEP>(s, gamma, slot, tile, k); });
 }
 
@@ -456,19 +459,28 @@ template <int MODE, bool MOM, int KB, bool DEEP>
 hipError_t launch_deep(rfast_ctx* c, float gamma) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  // Consecutive workgroups go round the eight dies, each with an L2 of its own: a multiple of eight tiles per node puts
-  // a tile of every node, which shares its neighbours' rows, on one die (128 nodes of an exponential graph, p 100000:
-  // 81.4 -> 77.6 us per round, p 66000: 57.7 -> 53.4; up to seven workgroups per node that find nothing are the price).
-  int64_t tiles = group_tiles(d.p);
-  if (tiles >= 32) tiles = (tiles + 7) / 8 * 8;
-  const int64_t blocks = tiles * d.n;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   // Stream past the caches (but for the rings, see Ring) once the state is too large for them: at 8 to 10 MB per array
   // both are even, below streaming loses (64 nodes, p 30000: 16.8 against 17.7 us per round), above it gains (128 nodes,
-  // p 50000: 43.9 against 42.7; mesh of 36, p 220001: 41.5 against 39.8; a star of 20, p 300000, loses 2 %).  Wavefronts per
-  // SIMD matter: the bidirectional ring (about 15 streams per node-update) is fastest at 3, slower at
-  // 2 (capped through reserved LDS: +11 %) and at 4 or 5 (+2 %, +4 %); the register count of KB sets it.
+  // p 50000: 43.9 against 42.7; mesh of 36, p 220001: 41.5 against 39.8; a star of 20, p 300000, loses 2 %).
   const bool streaming = (double)d.n * (double)d.p * 4.0 >= 16.0e6;
+  // Consecutive workgroups go round the eight dies, each with an L2 of its own: a multiple of eight tiles per node puts
+  // a tile of every node, which shares its neighbours' rows, on one die.  The price is up to seven workgroups per node that find
+  // nothing, and dies that get up to a fifth more than others.  Time with it over time without:
+  // Three and more in-edges per graph on average: mesh of 8, p 256248, 0.93; exponential graph of 100, p 70000, 0.92; softmax on 64 nodes
+  // of one, p 43008, 0.98.  Of 36 to 52 tiles every other node shares a die as it is: mesh of 100, p 36000, 1.02, so only from five in-edges on.
+  // Fewer in-edges: a single pass of few nodes gains (tree of 30, p 68332: 0.95; of 64, p 33052: 0.95; star of 20, p 300000: 0.99), of many it
+  // does not (star of 100, p 42500: 1.02), nor from 49 nodes on where it streams (tree of 64, p 156248: 1.04); two passes with
+  // matrix products between them do not (softmax, 36 tiles: tree of 100, 1.03; ring of 120, 1.02).
+  // Event-driven iterations have one active node at a time, which shares with nobody.
+  int64_t tiles = group_tiles(d.p);
+  const bool half = tiles % 8 == 4 && tiles < 56;
+  const bool shared = (int64_t)d.eR + d.eC >= (half ? 10 : 6) * (int64_t)d.n;
+  const bool few = MODE == RFAST_MODE_FUSED && !half && d.n <= (streaming ? 48 : 64);
+  if (tiles >= 32 && !c->no_tiles && (shared || few)) tiles = (tiles + 7) / 8 * 8;
+  const int64_t blocks = tiles * d.n;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  // Wavefronts per SIMD matter: the bidirectional ring (about 15 streams per node-update) is fastest at 3, slower at
+  // 2 (capped through reserved LDS: +11 %) and at 4 or 5 (+2 %, +4 %); the register count of KB sets it.
   if (vec4 && streaming)
     hipLaunchKernelGGL((rfast_state_kernel<MODE, -4, MOM, KB, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, c->stream, d, gamma, (int)tiles);
   else if (vec4)

@@ -62,3 +62,25 @@ def test_versions_nobody_pulls_are_not_kept(p, monkeypatch):
     leaves = (off != 0).sum(axis=0) == 0
     assert 0 < leaves.sum() < n
     assert not ring[leaves].any() and all(ring[i].any() for i in np.flatnonzero(~leaves))
+
+
+# 33, 42 and 43 tiles of 1024 coordinates per node, rounded up to a multiple of eight where rows have several readers or few nodes
+# take a single pass; the last tile of the ragged row must be taken once
+@pytest.mark.parametrize("kind,graph,n,p", [
+    ("diag_quadratic", "mesh", 8, 33_001), ("diag_quadratic", "mesh", 8, 43_008), ("diag_quadratic", "mesh", 8, 43_009),
+    ("diag_quadratic", "binary_tree", 20, 33_003), ("softmax_bf16", "exponential", 6, 43_008), ("softmax_bf16", "binary_tree", 6, 43_008)])
+def test_tiles_rounded_up(kind, graph, n, p, monkeypatch):
+    r, c = getattr(graphs, graph)(n)
+    if kind == "softmax_bf16":
+        w = configs._mk("tiles_softmax", n, p, r, c, 2, 0.05, 0, kind, problems.softmax_pool(n, 448, 96, 128, 5), 0.7, 0.1, 5, batch=64,
+                        samples=128, burst=2, tol=2e-3, extra={"d": 448, "K": 96})
+    else:
+        w = configs._mk("tiles", n, p, r, c, 2, 0.02, 0, kind, problems.diag_quadratic(n, p, 5), 0.7, 0.2, 5, noise_std=0.1, burst=3)
+    make = harness.make_gpu
+
+    def one_pass(w):
+        g = make(w)
+        rfast_use_blocks(g.ctx, False)
+        return g
+    monkeypatch.setattr(harness, "make_gpu", one_pass)
+    harness.run_parity(w, 20, every=(1, 3, 16))
