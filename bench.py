@@ -89,13 +89,14 @@ def one_pass_bytes(w, edges, before, after, active):
     run between a mixing and a tracking pass), from the stamps before and after it.  Per active node and coordinate,
     separable objective (`rfast_state_kernel<FUSED>`): reads x, z, h, c, one v per in-edge of R, the node's own current
     running sum (if it has out-edges over C) and two running sums (the one consumed now, the one consumed last time)
-    per in-edge of C whose stamp moved; writes x, z, v (from 16 MB per array on only if it has out-edges over R) and the new running sum.  Other objectives (`<MIX>` then
+    per in-edge of C whose stamp moved; writes x, z, v (from 32 MB per array on, where every pass
+    streams, only if it has out-edges over R) and the new running sum.  Other objectives (`<MIX>` then
     `<TRACK>`): x, z, the v's in and x, v out (softmax: plus the bf16 copy of the weights, half a word), then z, the old
     and the new sample, the own running sum and the two sums per moved edge in, z and the new running sum out.  (The
     rare copies of an S4 buffer that leaves its sender's ring are not counted.)"""
     dR, dI, dO = degrees(w)
     (r_src, _), (c_src, c_dst) = edges
-    pulled = ((np.bincount(r_src, minlength=w.n) > 0) | (4.0 * w.n * w.p < 16.0e6)).astype(np.float64)
+    pulled = ((np.bincount(r_src, minlength=w.n) > 0) | (4.0 * w.n * w.p < 32.0e6)).astype(np.float64)
     live = np.zeros(w.n, dtype=np.int64)
     moved = after["tau_c"] != before["tau_c"]
     np.add.at(live, c_dst[moved], 1)

@@ -899,7 +899,7 @@ static int check_round_args(rfast_ctx* c, const uint8_t* d_active, const int32_t
   return state_usable(c);
 }
 
-static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx);
+static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx, bool warm);
 static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round = -1);
 static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const int32_t* d_delay_R, const int32_t* d_delay_C,
                      const uint8_t* d_drop_R, const uint8_t* d_drop_C, float gamma, const int32_t* d_batch_idx);
@@ -916,23 +916,24 @@ int rfast_round(rfast_ctx* c, const uint8_t* d_active, const int32_t* d_delay_R,
   const hipError_t e = rfast_launch_resolve(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C);
   time_end(c, 2);
   if (e != hipSuccess) return hipfail(c, e, "resolver launch");
-  return float_round(c, gamma, d_batch_idx);
+  return float_round(c, gamma, d_batch_idx, c->capturing);  // (a graph holds several rounds)
 }
 
-// The floating-point part of a round whose plan the resolver has written into the current plan set.
-static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx) {
+// The floating-point part of a round whose plan the resolver has written into the current plan set.  warm: a round of a call
+// of many.
+static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx, bool warm) {
   const bool separable = c->d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC;
   gamma = gamma_now(c, gamma);
   hipError_t e;
   if (separable) {
     time_begin(c, 0);
-    e = rfast_launch_state(c, RFAST_MODE_FUSED, gamma);
+    e = rfast_launch_state(c, RFAST_MODE_FUSED, gamma, warm);
     time_end(c, 0);
     if (e != hipSuccess) return hipfail(c, e, "fused round launch");
     return after_round(c);
   }
   time_begin(c, 0);
-  e = rfast_launch_state(c, RFAST_MODE_MIX, gamma);
+  e = rfast_launch_state(c, RFAST_MODE_MIX, gamma, warm);
   time_end(c, 0);
   if (e != hipSuccess) return hipfail(c, e, "mix launch");
   time_begin(c, 1);
@@ -940,7 +941,7 @@ static int float_round(rfast_ctx* c, float gamma, const int32_t* d_batch_idx) {
   time_end(c, 1);
   if (e != hipSuccess) return hipfail(c, e, "gradient launch");
   time_begin(c, 0);
-  e = rfast_launch_state(c, RFAST_MODE_TRACK, gamma);
+  e = rfast_launch_state(c, RFAST_MODE_TRACK, gamma, warm);
   time_end(c, 0);
   if (e != hipSuccess) return hipfail(c, e, "track launch");
   return after_round(c);
@@ -955,7 +956,7 @@ static int chained_rounds(rfast_ctx* c, int32_t count, float gamma, const uint8_
   const size_t rows = (size_t)d.n * (size_t)d.prob.batch;
   use_plan_set(c, 0);
   time_begin(c, 0);
-  hipError_t e = rfast_launch_state(c, RFAST_MODE_MIX, gamma_now(c, gamma));
+  hipError_t e = rfast_launch_state(c, RFAST_MODE_MIX, gamma_now(c, gamma), true);
   time_end(c, 0);
   if (e != hipSuccess) return hipfail(c, e, "mix launch");
   for (int32_t q = 0; q < count; ++q) {
@@ -1165,7 +1166,7 @@ int rfast_run(rfast_ctx* c, int32_t rounds, const uint8_t* d_active, const int32
     } else {
       for (int32_t q = 0; q < ahead; ++q) {
         use_plan_set(c, q);
-        rc = float_round(c, gamma, d_batch_idx ? d_batch_idx + (size_t)(r + q) * d.n * B : nullptr);
+        rc = float_round(c, gamma, d_batch_idx ? d_batch_idx + (size_t)(r + q) * d.n * B : nullptr, rounds >= 8);
         if (rc != RFAST_OK) return rc;
       }
     }

@@ -222,7 +222,7 @@ struct RfastBlock {
 hipError_t rfast_launch_resolve(rfast_ctx* c, const uint8_t* active, const int32_t* delay_R,
                                 const int32_t* delay_C, const uint8_t* drop_R, const uint8_t* drop_C, int rounds = 1,
                                 size_t plan_stride = 0);
-hipError_t rfast_launch_state(rfast_ctx* c, int mode, float gamma);
+hipError_t rfast_launch_state(rfast_ctx* c, int mode, float gamma, bool warm);  // warm: in a call of several rounds
 // `rounds` event-driven iterations of the separable objective, whose plans are in the plan sets from the current one on
 hipError_t rfast_launch_events(rfast_ctx* c, float gamma, int rounds);
 hipError_t rfast_launch_rebase(rfast_ctx* c);

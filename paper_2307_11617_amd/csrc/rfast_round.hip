@@ -455,14 +455,24 @@ __global__ void __launch_bounds__(kThreads) rfast_sync_fold_kernel(RfastDev s) {
   });
 }
 
+// Bytes per array from which on the passes stream past the caches (but for the rings, see Ring): 16 MB, or more where the
+// rounds before this one have left the state in the caches (`warm`: a call of eight or more rounds).  Time streamed over time
+// cached, contexts in turn (the caches hold somebody else's state) and one context over and over: single rounds, 24 to 28 MB: mesh of 16 0.92 and
+// 1.01, star of 20 0.93 and 1.02, ring of 128 0.96 and 1.04; calls of four, 17 to 28 MB: 0.95 to 1.0 and 1.0 to 1.07.  Calls of eight, 17 to
+// 31 MB: star of 64 0.99 to 1.05 and 1.01 to 1.14, ring of 16 1.01 to 1.04 and 1.01 to 1.03, tree of 64 0.99 to 1.03 and 1.01 to 1.08, at 60 MB all
+// 0.91 to 0.98; where a row has several readers even from 17 to 24 MB and 0.96 to 0.99 from there on (mesh of 30, exponential graph of 16).  The
+// softmax passes: 1.01 to 1.05 at 17 to 22 MB, 0.97 at 27 to 29.  Least squares and logistic regression read their data between the
+// passes, which leaves the caches cold: 0.95 at 18 MB.
+double stream_from(const RfastDev& d, bool warm) {
+  if (!warm || (d.prob.kind != RFAST_OBJ_SOFTMAX_BF16 && d.prob.kind != RFAST_OBJ_DIAG_QUADRATIC)) return 16.0e6;
+  return d.prob.kind == RFAST_OBJ_SOFTMAX_BF16 || (int64_t)d.eR + d.eC >= 6 * (int64_t)d.n ? 24.0e6 : 32.0e6;
+}
+
 template <int MODE, bool MOM, int KB, bool DEEP>
-hipError_t launch_deep(rfast_ctx* c, float gamma) {
+hipError_t launch_deep(rfast_ctx* c, float gamma, bool warm) {
   const RfastDev& d = c->d;
   const bool vec4 = (d.p % 4) == 0;
-  // Stream past the caches (but for the rings, see Ring) once the state is too large for them: at 8 to 10 MB per array
-  // both are even, below streaming loses (64 nodes, p 30000: 16.8 against 17.7 us per round), above it gains (128 nodes,
-  // p 50000: 43.9 against 42.7; mesh of 36, p 220001: 41.5 against 39.8; a star of 20, p 300000, loses 2 %).
-  const bool streaming = (double)d.n * (double)d.p * 4.0 >= 16.0e6;
+  const bool streaming = (double)d.n * (double)d.p * 4.0 >= stream_from(d, warm);
   // Consecutive workgroups go round the eight dies, each with an L2 of its own: a multiple of eight tiles per node puts
   // a tile of every node, which shares its neighbours' rows, on one die.  The price is up to seven workgroups per node that find
   // nothing, and dies that get up to a fifth more than others.  Time with it over time without:
@@ -493,10 +503,10 @@ hipError_t launch_deep(rfast_ctx* c, float gamma) {
 }
 
 template <int MODE, bool MOM, int KB>
-hipError_t launch(rfast_ctx* c, float gamma) {
+hipError_t launch(rfast_ctx* c, float gamma, bool warm) {
   if constexpr (MODE == RFAST_MODE_FUSED)
-    if (c->max_in_degree <= KB) return launch_deep<MODE, MOM, KB, false>(c, gamma);
-  return launch_deep<MODE, MOM, KB, true>(c, gamma);
+    if (c->max_in_degree <= KB) return launch_deep<MODE, MOM, KB, false>(c, gamma, warm);
+  return launch_deep<MODE, MOM, KB, true>(c, gamma, warm);
 }
 
 }  // namespace
@@ -579,19 +589,19 @@ hipError_t rfast_launch_events(rfast_ctx* c, float gamma, int rounds) {
   return with(std::integral_constant<int, 5>(), group_tiles(d.p));
 }
 
-hipError_t rfast_launch_state(rfast_ctx* c, int mode, float gamma) {
+hipError_t rfast_launch_state(rfast_ctx* c, int mode, float gamma, bool warm) {
   const bool mom = c->d.mom != nullptr;
   // three or more in-edges per node on average (both graphs together), or a state so small that wavefronts are few
   // anyway and only the trips through memory count: the deeper load batch
   const bool deep = (int64_t)c->d.eR + c->d.eC >= 3 * (int64_t)c->d.n || (double)c->d.n * (double)c->d.p < 4.0e6;
   switch (mode) {
     case RFAST_MODE_FUSED:
-      if (deep) return mom ? launch<RFAST_MODE_FUSED, true, 8>(c, gamma) : launch<RFAST_MODE_FUSED, false, 8>(c, gamma);
-      return mom ? launch<RFAST_MODE_FUSED, true, 4>(c, gamma) : launch<RFAST_MODE_FUSED, false, 4>(c, gamma);
+      if (deep) return mom ? launch<RFAST_MODE_FUSED, true, 8>(c, gamma, warm) : launch<RFAST_MODE_FUSED, false, 8>(c, gamma, warm);
+      return mom ? launch<RFAST_MODE_FUSED, true, 4>(c, gamma, warm) : launch<RFAST_MODE_FUSED, false, 4>(c, gamma, warm);
     case RFAST_MODE_MIX:
-      if (deep) return mom ? launch<RFAST_MODE_MIX, true, 8>(c, gamma) : launch<RFAST_MODE_MIX, false, 8>(c, gamma);
-      return mom ? launch<RFAST_MODE_MIX, true, 4>(c, gamma) : launch<RFAST_MODE_MIX, false, 4>(c, gamma);
+      if (deep) return mom ? launch<RFAST_MODE_MIX, true, 8>(c, gamma, warm) : launch<RFAST_MODE_MIX, false, 8>(c, gamma, warm);
+      return mom ? launch<RFAST_MODE_MIX, true, 4>(c, gamma, warm) : launch<RFAST_MODE_MIX, false, 4>(c, gamma, warm);
     default:  // S1 is not part of this pass
-      return deep ? launch<RFAST_MODE_TRACK, false, 8>(c, gamma) : launch<RFAST_MODE_TRACK, false, 4>(c, gamma);
+      return deep ? launch<RFAST_MODE_TRACK, false, 8>(c, gamma, warm) : launch<RFAST_MODE_TRACK, false, 4>(c, gamma, warm);
   }
 }

@@ -64,6 +64,63 @@ def test_versions_nobody_pulls_are_not_kept(p, monkeypatch):
     assert not ring[leaves].any() and all(ring[i].any() for i in np.flatnonzero(~leaves))
 
 
+def _raw_v_ring(g):
+    """The rings of versions as they lie in the workspace (a read of the field returns zeros for what nobody can pick up): behind
+    x, z and the two arrays of samples, each on a 256-byte boundary."""
+    import torch
+    up = lambda b: -(-b // 256) * 256  # noqa: E731
+    row = g.n * g.p * 4
+    off = 2 * up(row) + up(2 * row)
+    return g.workspace[off:off + g.M * row].view(torch.float32).view(g.n, g.M, g.p)
+
+
+# Which rows stream past the caches: 16 MB per array in calls of fewer than eight rounds, 32 MB (softmax: 24) in longer ones
+@pytest.mark.parametrize("kind,n,p,rounds,kept", [
+    ("diag_quadratic", 9, 500_000, 6, False), ("diag_quadratic", 9, 500_001, 6, False), ("diag_quadratic", 9, 900_000, 9, False),
+    ("diag_quadratic", 9, 900_001, 9, False), ("diag_quadratic", 9, 500_000, 9, True), ("diag_quadratic", 9, 64_000, 6, True),
+    ("softmax_bf16", 48, 131_072, 9, False), ("softmax_bf16", 36, 131_072, 3, False)])
+def test_rows_nobody_pulls_are_not_written(kind, n, p, rounds, kept):
+    """Where the state streams past the caches, the rows of nodes without out-edges over R keep what was there before; x, z and
+    everything else are those of a context whose rows held something else, and the oracle's."""
+    if kind == "softmax_bf16":
+        r, c = graphs.binary_tree(n)
+        w = configs._mk("tree_softmax", n, p, r, c, 2, 0.05, 0, kind, problems.softmax_pool(n, 1024, 128, 128, 5), 0.7, 0.1, 5,
+                        batch=64, samples=128, burst=2, tol=2e-3, extra={"d": 1024, "K": 128})
+    else:
+        r, c = graphs.tree_pull_star_push(n)
+        w = configs._mk("tree_star", n, p, r, c, 3, 0.002, 0, kind, problems.diag_quadratic(n, p, 5), 0.7, 0.2, 5, noise_std=0.1, burst=3)
+    leaves = ((r != 0) & ~np.eye(n, dtype=bool)).sum(axis=0) == 0
+    assert 0 < leaves.sum() < n
+    pair = [harness.make_gpu(w), harness.make_gpu(w)]
+    st, dev = harness.upload_chunk(pair[0], w, 0, rounds)
+    for g, mark in zip(pair, (7.5, -3.25)):
+        rfast_use_blocks(g.ctx, False)
+        g.init(None, w.sched.initial_batch())
+        ring = _raw_v_ring(g)
+        assert not ring.any()
+        for i in np.flatnonzero(leaves):
+            ring[i] = mark
+        g.run(rounds, *(dev[k] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")), w.gamma, dev["batch_idx"])
+        g.check()
+        moved = g.read("T_NODE") > 0
+        for i in range(n):
+            if leaves[i] and moved[i]:
+                assert bool((ring[i][:, :p // 4 * 4] == mark).all()) != kept, i   # (the end of a ragged row is written)
+            elif moved[i]:
+                assert bool(ring[i].any())
+        assert not g.read("V_RING")[leaves].any()
+    for f in ("X", "Z", "SIGMA_RING", "TAU_R", "TAU_C"):
+        assert np.array_equal(pair[0].read(f), pair[1].read(f)), f
+    coords = None if kind == "softmax_bf16" else np.unique(np.concatenate([np.arange(0, p, 4099), [p - 2, p - 1]]))
+    orc = harness.make_oracle(w, coords)
+    for q in range(rounds):
+        orc.round(*(st[k][q] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")), w.gamma,
+                  None if st["batch_idx"] is None else st["batch_idx"][q])
+    sel = slice(None) if coords is None else coords
+    assert harness.rel_l2(pair[0].read("X")[:, sel], orc.x) <= w.tol
+    assert harness.rel_l2(pair[0].read("Z")[:, sel], orc.z, 1e-3 * float(np.linalg.norm(orc.g))) <= w.tol
+
+
 # 33, 42 and 43 tiles of 1024 coordinates per node, rounded up to a multiple of eight where rows have several readers or few nodes
 # take a single pass; the last tile of the ragged row must be taken once
 @pytest.mark.parametrize("kind,graph,n,p", [
