@@ -232,8 +232,8 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * launch where that is possible and pays -- the separable objective (diagonal quadratic, with or
  * without the optimizer variant), at most 64 nodes, no node with more than 6 in-edges of R, in-edges of C or out-edges of
  * C (64 / n lanes of one wavefront per node, 4 coordinates per lane; LDS holds as many of a node's latest versions as
- * the longest delay reads and some more; 33 to 64 nodes with at most 4 edges of a kind on rings of at most three slots: at
- * least 16 lanes of one workgroup per node instead), and enough rounds to run before the next multiple of the
+ * the longest delay reads and some more; 33 to 64 nodes with at most 2 edges of a kind on rings of at most three slots, in short
+ * launches: at least 16 lanes of one workgroup per node instead), and enough rounds to run before the next multiple of the
  * rebase interval and the next decay step of the step-size schedule (2 to 22: a launch moves every ring slot that can still be
  * read in and out once, which a large state earns back only over some rounds, the more the longer
  * the delays), rings of at most 32 slots (D <= 30); rounds that do not qualify run one pass
@@ -269,7 +269,8 @@ int rfast_use_blocks(rfast_ctx* ctx, int32_t on);
  * where p is no multiple of 4 (the tiles of the multi-round kernel then start at any float's address), else the number
  * of lanes per node of the multi-round kernel (its tile is 4 * lanes coordinates; 1024 / n, at least 1, for the
  * single workgroup of the non-separable objectives);
- * *tile_per_wavefront (may be NULL) = 1 if a tile belongs to one wavefront, 0 if to a workgroup. */
+ * *tile_per_wavefront (may be NULL) = 1 if a tile belongs to one wavefront, 0 if to a workgroup (of the kernel of short
+ * launches where short and long ones have different ones). */
 int rfast_block_info(rfast_ctx* ctx, int32_t* lanes_per_node, int32_t* tile_per_wavefront);
 /* Tuning knob of the wavefront-tile kernel of rfast_use_blocks: wavefronts per workgroup (1, 2 or 4; 0 = chosen by
  * the library).  The wavefronts of a workgroup own neighbouring tiles and move their rings between HBM and LDS

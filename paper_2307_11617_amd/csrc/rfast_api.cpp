@@ -986,7 +986,7 @@ static int chained_rounds(rfast_ctx* c, int32_t count, float gamma, const uint8_
 static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round) {
   if (!c->use_blocks || c->capturing) return 0;
   const bool gemv = rfast_tiny_eligible(c) || c->team.W > 0;  // (every round of these takes the multi-round kernels)
-  if (!gemv && (c->no_tiles || !(rfast_wave_eligible(c) || rfast_block_eligible(c)))) return 0;
+  if (!gemv && (c->no_tiles || !rfast_wave_eligible(c))) return 0;
   if (gemv && !rfast_tiny_eligible(c) && !team_usable(c)) return 0;
   const int64_t now = at_round >= 0 ? at_round : c->host_round;  // the round the launch would start with
   int32_t len = rounds < kBlockRounds ? rounds : kBlockRounds;
@@ -1008,14 +1008,17 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
   // 1.02 at 6; 16 nodes, p 2 M, delays of up to 16: 0.64 at 8).
   const double bytes = (double)c->d.n * (double)c->d.p * 4.0;
   int32_t least;
-  if (rfast_wave_eligible(c)) {
+  if (!rfast_block_takes(c, len)) {
     const int held = rfast_wave_held(c), row = bytes > 8.0e6 ? 3 : bytes > 2.0e6 ? 2 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 1 : 0;
     static const int32_t table[4][3] = {{2, 2, 3}, {3, 3, 6}, {4, 5, 10}, {5, 6, 12}};
     // more than 32 nodes, a lane each: row segments of 16 bytes per tile, so that moving them takes longer
     static const int32_t narrow[4][3] = {{2, 2, 3}, {3, 3, 6}, {5, 6, 10}, {7, 10, 22}};
     least = (c->d.n > 32 ? narrow : table)[row][held >= 12 ? 0 : held >= 8 ? 1 : 2];
   } else {
-    least = bytes > 8.0e6 ? kBlockMinRoundsLarge : bytes > 3.0e6 ? 5 : bytes > 2.0e6 ? 4 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 3 : 2;
+    // (one pass per round / a launch, rings of two or three slots: ring of 36, p 416664, 73 / 77 us per round in calls of 4, 74 / 59 of
+    // 6; p 97220: 22.6 / 26.4 of 3, 22.0 / 22.0 of 4; p 27776: 11.2 / 12.5 of 2, 10.2 / 9.7 of 3; p 6944: 9.0 / 7.5 of 2; ring of 48 and
+    // tree of 64 alike)
+    least = bytes > 20.0e6 ? 5 : bytes > 8.0e6 ? 4 : bytes > 2.0e6 || c->d.p % 4 != 0 ? 3 : 2;
   }
   if (c->use_blocks == 2) least = 2;
   return len >= least ? len : 0;
@@ -1031,16 +1034,16 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   RfastBlock blk;
   blk.rounds = len;
   // a rebase that falls due when these rounds are done costs the wavefront-tile kernel nothing: it shifts the
-  // running sums while it writes its tiles back (the other kernel is followed by the rebase kernel)
+  // running sums while it writes its tiles back (the other kernels are followed by the rebase kernel)
+  const bool tiny = rfast_tiny_eligible(c), team = !tiny && c->team.W > 0, wave = !tiny && !team && !rfast_block_takes(c, len);
   const bool rebase_due = c->rebase_interval > 0 && (c->host_round + len) % c->rebase_interval == 0;
-  blk.rebase = rebase_due && rfast_wave_eligible(c) ? 1 : 0;
-  const bool tiny = rfast_tiny_eligible(c), team = !tiny && c->team.W > 0;
+  blk.rebase = rebase_due && wave ? 1 : 0;
   blk.gamma = gamma_now(c, gamma);  // of the first round: a launch does not straddle a decay step
   const bool own_resolver = rfast_tiny_resolves(c);  // the one-workgroup kernel resolves its rounds itself
   hipError_t e = hipSuccess;
   d.blk_plan = c->blk_plan_base;
   d.blk_head = tiny || team ? nullptr : c->blk_head_base;
-  blk.slots = d.blk_slots = !tiny && !team && rfast_wave_eligible(c) ? rfast_wave_slots(c) : 0;
+  blk.slots = d.blk_slots = wave ? rfast_wave_slots(c) : 0;
   if (!own_resolver) {
     time_begin(c, 2);
     e = rfast_launch_resolve(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C, len);
@@ -1053,7 +1056,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
       e = in_team_order(c, [&] { return launch_team(c, false, len, blk.gamma, d_batch_idx, d_delay_R, d_delay_C); });
     else if (tiny)
       e = rfast_launch_tiny(c, blk, d_batch_idx, (int)(c->host_round - len), d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C);
-    else e = rfast_wave_eligible(c) ? rfast_launch_wave(c, blk) : rfast_launch_block(c, blk);
+    else e = wave ? rfast_launch_wave(c, blk) : rfast_launch_block(c, blk);
     time_end(c, 0);
   }
   d.blk_plan = nullptr;
@@ -1069,7 +1072,7 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
 
 int rfast_block_info(rfast_ctx* c, int32_t* lanes_per_node, int32_t* tile_per_wavefront) {
   if (!c || !lanes_per_node) return RFAST_EINVAL;
-  const bool taken = block_length(c, kBlockRounds) > 0 && c->d.p % 4 == 0 && (rfast_tiny_eligible(c) || c->team.W <= 0), wave = rfast_wave_eligible(c);
+  const bool taken = block_length(c, kBlockRounds) > 0 && c->d.p % 4 == 0 && (rfast_tiny_eligible(c) || c->team.W <= 0), wave = rfast_wave_eligible(c) && !rfast_block_eligible(c);
   if (taken && rfast_tiny_eligible(c)) {  // one workgroup holds the whole problem
     *lanes_per_node = 1024 / c->d.n > 0 ? 1024 / c->d.n : 1;
     if (tile_per_wavefront) *tile_per_wavefront = 0;

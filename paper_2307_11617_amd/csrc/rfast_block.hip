@@ -1,6 +1,7 @@
 // Several activation rounds per launch with the state of a tile of coordinates resident in LDS,
-// one tile per WORKGROUP: the form for graphs of 33 to 64 nodes (smaller graphs take the kernel of
-// rfast_wave.hip, whose tile belongs to one wavefront and which needs no barrier).
+// one tile per WORKGROUP: the form of short launches for 33 to 64 nodes with at most two edges of a kind on rings of at most
+// three slots, whose wide tiles fit LDS (everything else takes the kernel of rfast_wave.hip, whose tile belongs to one
+// wavefront and which needs no barrier; rfast_block_takes has the measurements).
 //
 // Everything in a round of Algorithm 1 is elementwise in the coordinate k: coordinate k of every
 // node, ring slot and buffer depends, over any number of rounds, only on coordinate k of the
@@ -25,23 +26,21 @@
 
 namespace {
 
-constexpr int kMaxDeg = 4;  // most in-edges of R, in-edges of C and out-edges of C a node may have on this path
-// Plan words a lane moves per refill: a record has at most (1 + 2 kMaxDeg) n + 1 words and a workgroup at
-// least 16 n lanes, so kPlanChunk records are at most 16 (9 n + 1) <= 10 * 16 n words.
-constexpr int kPlanPerLane = 10;
+constexpr int kMaxSlots = 3;  // ring slots
+constexpr int kDeg = 2;  // most in-edges of R, in-edges of C and out-edges of C a node may have on this path.  (With four the registers of
+                         // sixteen wavefronts do not hold them, 66 to 72 spill: mesh of 36, p 416664, 107 us per round in calls of 100, 88 one
+                         // pass at a time, 50 with a tile per wavefront.)
+// Plan words a lane moves per refill: a record has at most (1 + 2 kDeg) n + 1 words and a workgroup at
+// least 16 n lanes, so kPlanChunk records are at most 16 (5 n + 1) <= 6 * 16 n words.
+constexpr int kPlanPerLane = 6;
 
-// kLanes: lanes per node, each owning 4 coordinates of a tile of 4 kLanes; TPB: upper bound of the
-// workgroup size (n kLanes lanes, rounded up to whole wavefronts), which sets how many registers
-// the compiler may use; kDeg: edge slots per node and kind (2 for rings and paths, else kMaxDeg).
-// More than 32 nodes at 16 lanes each are more than 512 lanes, so the kernel runs with 128 registers: with two
-// edge slots it fits them (four ring slots in flight while the tile moves instead of eight), with four it
-// spills 66 to 72 to scratch.  The alternative without spills, 8 lanes per node in workgroups of 512 with 186
-// registers, was measured and is slower, because it halves the wavefronts per CU: 0.201 against 0.192 ms per
-// round on a 6 x 6 mesh at p = 1 M, 0.149 against 0.088 ms on a ring of 36 nodes.
-template <int kLanes, int TPB, int kDeg, bool ANY>
-__global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock blk) {
+// kLanes: lanes per node, each owning 4 coordinates of a tile of 4 kLanes.  More than 32 nodes at 16 lanes each are more than
+// 512 lanes, so the kernel runs with 128 registers, which hold two edge slots.  The alternative, 8 lanes per node in workgroups of 512
+// with 186 registers, was measured and is slower, because it halves the wavefronts per CU: 0.149 against 0.088 ms on a ring of 36 nodes.
+template <int kLanes, bool ANY>
+__global__ void __launch_bounds__(1024) rfast_block_kernel(RfastDev s, RfastBlock blk) {
   constexpr int VEC = 4;
-  constexpr int kRingBatch = TPB > 512 ? 4 : 8;  // ring slots (of both rings) in flight while the tile is moved
+  constexpr int kRingBatch = kMaxSlots;  // ring slots (of both rings) in flight while the tile is moved
   extern __shared__ float4 lds4[];
   const int n = s.n, M = s.M;
   const int64_t p = s.p;
@@ -104,7 +103,7 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
       o_pw[u] = ho ? n + s.eR + oe : PL;
       o_eid[u] = oe;
     }
-    // rings: eight slots of both rings (sixteen loads) in flight at a time, then into LDS.  Only what can matter
+    // rings: every slot of both rings in flight, then into LDS.  Only what can matter
     // is moved, as in the kernel with one tile per wavefront: the resolver has left one bit per slot saying whether
     // a receiver can still pick up the version it holds (RfastDev::blk_head); the other slots are zeros in LDS
     // (finite, for the multiply-adds with weight zero) and, further down, a slot goes back only if the launch wrote
@@ -115,22 +114,19 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
     put_s = (unsigned)he.x & (unsigned)he.z;
     const float* vg = s.v_ring + (size_t)i * M * p + k;
     const float* sgg = s.sigma_ring + (size_t)i * M * p + k;
-    for (int m0 = 0; m0 < M; m0 += kRingBatch) {
-      float4 tv[kRingBatch], ts[kRingBatch];
-      const unsigned get_v = (unsigned)hd.z >> m0, get_s = (unsigned)hd.w >> m0;  // bits past the last slot are clear
+    float4 tv[kRingBatch], ts[kRingBatch];
 #pragma unroll
-      for (int u = 0; u < kRingBatch; ++u) {
-        tv[u] = ts[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (get_v & (1u << u)) tv[u] = ld_group<ANY>(vg + (size_t)(m0 + u) * p, left);
-        if (get_s & (1u << u)) ts[u] = ld_group<ANY>(sgg + (size_t)(m0 + u) * p, left);
-      }
-#pragma unroll
-      for (int u = 0; u < kRingBatch; ++u)
-        if (m0 + u < M) {
-          v_l[own + (m0 + u) * kLanes] = tv[u];
-          sg_l[own + (m0 + u) * kLanes] = ts[u];
-        }
+    for (int u = 0; u < kRingBatch; ++u) {
+      tv[u] = ts[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if ((unsigned)hd.z & (1u << u)) tv[u] = ld_group<ANY>(vg + (size_t)u * p, left);  // bits past the last slot are clear
+      if ((unsigned)hd.w & (1u << u)) ts[u] = ld_group<ANY>(sgg + (size_t)u * p, left);
     }
+#pragma unroll
+    for (int u = 0; u < kRingBatch; ++u)
+      if (u < M) {
+        v_l[own + u * kLanes] = tv[u];
+        sg_l[own + u * kLanes] = ts[u];
+      }
   }
   __syncthreads();
   // The stored sample of S2b is a function of (x_i, t_i); from here on it lives in registers, and so
@@ -180,7 +176,7 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
       float4 nb[kDeg], cur[kDeg], last[kDeg];
 #pragma unroll
       for (int u = 0; u < kDeg; ++u) nb[u] = v_l[r_col[u] + r_slot[u] * kLanes];
-      if (TPB > 512) __builtin_amdgcn_sched_barrier(0);  // registers: do not start the next batch early
+      __builtin_amdgcn_sched_barrier(0);  // registers: do not start the next batch early
 #pragma unroll
       for (int u = 0; u < kDeg; ++u) {
         const int prev = (c_pl[u] >> 8) & 0xFF;
@@ -243,19 +239,10 @@ __global__ void __launch_bounds__(TPB) rfast_block_kernel(RfastDev s, RfastBlock
     if (momentum) st_group<ANY>(s.mom + off, left, m);
     float* vg = s.v_ring + (size_t)i * M * p + k;
     float* sgg = s.sigma_ring + (size_t)i * M * p + k;
-    for (int m0 = 0; m0 < M; m0 += kRingBatch) {
-      float4 tv[kRingBatch], ts[kRingBatch];
-      const unsigned back_v = put_v >> m0, back_s = put_s >> m0;
 #pragma unroll
-      for (int u = 0; u < kRingBatch; ++u) {
-        if (back_v & (1u << u)) tv[u] = v_l[own + (m0 + u) * kLanes];
-        if (back_s & (1u << u)) ts[u] = sg_l[own + (m0 + u) * kLanes];
-      }
-#pragma unroll
-      for (int u = 0; u < kRingBatch; ++u) {
-        if (back_v & (1u << u)) st_group<ANY>(vg + (size_t)(m0 + u) * p, left, tv[u]);
-        if (back_s & (1u << u)) st_group<ANY>(sgg + (size_t)(m0 + u) * p, left, ts[u]);
-      }
+    for (int u = 0; u < kRingBatch; ++u) {
+      if (put_v & (1u << u)) st_group<ANY>(vg + (size_t)u * p, left, v_l[own + u * kLanes]);
+      if (put_s & (1u << u)) st_group<ANY>(sgg + (size_t)u * p, left, sg_l[own + u * kLanes]);
     }
   }
 }
@@ -265,8 +252,7 @@ size_t block_lds_bytes(const RfastDev& d, int lanes) {
 }
 
 // Lanes per node: the widest tile that fits LDS and 1024 lanes; a tile wider than 16 lanes per
-// node must leave two tiles per CU of the chip to schedule.  (Graphs of up to 32 nodes take the
-// kernel with one tile per wavefront instead, so a workgroup here has more than 512 lanes.)
+// node must leave two tiles per CU of the chip to schedule.
 constexpr int kLaneChoices[] = {28, 24, 16};
 constexpr size_t kLdsBudget = 156 * 1024;
 
@@ -282,52 +268,56 @@ int block_lanes(const RfastDev& d) {
 
 }  // namespace
 
-// The tile of every node must fit into the LDS of one CU next to the plans, a workgroup holds at
-// least 16 lanes per node, no node has more than kMaxDeg edges of a kind, and the path exists for the
-// separable objective (the heavy-ball buffer of the optimizer variant is one more register set).
+// The tile of every node must fit into the LDS of one CU next to the plans, a workgroup holds at least 16 lanes per node, and the
+// path exists for the separable objective (the heavy-ball buffer of the optimizer variant is one more register set).
 bool rfast_block_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kMaxDeg && d.M <= 32 &&
-         block_lanes(d) != 0;  // (rings of at most 32 slots: one bit per slot in the records of the resolver)
+  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && d.n > 32 && c->max_degree <= kDeg && d.M <= kMaxSlots && block_lanes(d) != 0;
+}
+
+// Whether a launch of that many rounds is better off here than with a tile per wavefront, which starts slower (rows in
+// segments of 16 bytes) and uses n of 64 lanes in its rounds.  us per round, tile per workgroup / per wavefront, two or three slots:
+// ring of 36, p 416664: 117 / 206 in calls of 2, 50 / 73 of 8, 26 / 30 of 100; p 97220: 34 / 44, 15.1 / 17.1, 7.3 / 7.6; p 27776: 12.5 / 14.5
+// of 2, 4.7 / 4.7 of 12, 3.4 / 3.2 of 40.  Ring of 48, p 312500: 135 / 193 of 2, 48 / 49 of 12, 40 / 36 of 20, 29.6 / 24.1 of 100; p 72916:
+// 24.2 / 24.9 of 4, 19.0 / 18.6 of 6, 7.7 / 6.2 of 100; p 20832: 10.0 / 10.1 of 3, 8.4 / 8.3 of 4, 3.3 / 2.7 of 100.  Tree of 64: the same from 12 and
+// 7 rounds on; p 15624, where most nodes leave an edge slot empty, which costs nothing here, 2.0 / 2.1 of 100.
+bool rfast_block_takes(const rfast_ctx* c, int32_t rounds) {
+  if (!rfast_block_eligible(c)) return false;
+  const RfastDev& d = c->d;
+  const double bytes = (double)d.n * (double)d.p * 4.0;
+  if (bytes <= 5.0e6) return rounds < (d.n > 40 ? 4 : 12) || (bytes > 2.0e6 && (int64_t)d.eR + d.eC < 3 * (int64_t)d.n);
+  return d.n <= 40 || rounds < (bytes > 20.0e6 ? 13 : 6);
 }
 
 int rfast_block_lanes(const rfast_ctx* c) { return block_lanes(c->d); }
 
-template <int kLanes, int TPB, int kDeg, bool ANY>
-static hipError_t launch_block_any(rfast_ctx* c, const RfastBlock& blk, unsigned threads) {
+template <int kLanes, bool ANY>
+static hipError_t launch_block_any(rfast_ctx* c, const RfastBlock& blk) {
   static bool raised = false;
   if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    const hipError_t e = hipFuncSetAttribute((const void*)rfast_block_kernel<kLanes, TPB, kDeg, ANY>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_block_kernel<kLanes, ANY>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
   }
-  const int64_t tiles = (c->d.p + 4 * kLanes - 1) / (4 * kLanes);
+  const RfastDev& d = c->d;
+  if (!d.blk_plan || !d.blk_head || d.blk_slots != 0) return hipErrorInvalidValue;
+  const int64_t tiles = (d.p + 4 * kLanes - 1) / (4 * kLanes);
   if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rfast_block_kernel<kLanes, TPB, kDeg, ANY>), dim3((unsigned)tiles), dim3(threads), block_lds_bytes(c->d, kLanes),
-                     c->stream, c->d, blk);
+  hipLaunchKernelGGL((rfast_block_kernel<kLanes, ANY>), dim3((unsigned)tiles), dim3((unsigned)((d.n * kLanes + 63) / 64 * 64)),
+                     block_lds_bytes(d, kLanes), c->stream, d, blk);
   return hipGetLastError();
 }
 
-template <int kLanes, int TPB, int kDeg>
-static hipError_t launch_block(rfast_ctx* c, const RfastBlock& blk, unsigned threads) {
-  return c->d.p % 4 == 0 ? launch_block_any<kLanes, TPB, kDeg, false>(c, blk, threads) : launch_block_any<kLanes, TPB, kDeg, true>(c, blk, threads);
-}
-
 template <int kLanes>
-static hipError_t launch_block_lanes(rfast_ctx* c, const RfastBlock& blk) {
-  const unsigned threads = (unsigned)((c->d.n * kLanes + 63) / 64 * 64);
-  if (threads <= 512) return c->max_degree <= 2 ? launch_block<kLanes, 512, 2>(c, blk, threads)
-                                                : launch_block<kLanes, 512, kMaxDeg>(c, blk, threads);
-  return c->max_degree <= 2 ? launch_block<kLanes, 1024, 2>(c, blk, threads)
-                            : launch_block<kLanes, 1024, kMaxDeg>(c, blk, threads);
+static hipError_t launch_block(rfast_ctx* c, const RfastBlock& blk) {
+  return c->d.p % 4 == 0 ? launch_block_any<kLanes, false>(c, blk) : launch_block_any<kLanes, true>(c, blk);
 }
 
 hipError_t rfast_launch_block(rfast_ctx* c, const RfastBlock& blk) {
   switch (block_lanes(c->d)) {
-    case 28: return launch_block_lanes<28>(c, blk);
-    case 24: return launch_block_lanes<24>(c, blk);
-    case 16: return launch_block_lanes<16>(c, blk);
+    case 28: return launch_block<28>(c, blk);
+    case 24: return launch_block<24>(c, blk);
+    case 16: return launch_block<16>(c, blk);
     default: return hipErrorInvalidValue;
   }
 }

@@ -197,18 +197,13 @@ struct rfast_ctx {
 
 enum { RFAST_MODE_FUSED = 0, RFAST_MODE_MIX = 1, RFAST_MODE_TRACK = 2 };
 
-// rounds that one launch of the LDS-resident kernel can advance, rounds whose plan records it holds
-// in LDS at a time, and the shortest launch that pays where the state is large (the launch moves
-// every ring slot in and out once: measured on 16 nodes x 11.2 M coordinates, about 7 ms per launch
-// plus 0.33 ms per round against 1.53 ms per round of the streaming kernel: even from 6 rounds on)
 constexpr int kHeadWords = 16;  // words per node in RfastDev::blk_head
-constexpr int kBlockRounds = 512;
+constexpr int kBlockRounds = 512;  // rounds that one launch of a multi-round kernel can advance
 constexpr int kFarWords = 1024;    // words per node in RfastDev::blk_far: more than a launch's rounds and a ring's slots together
 constexpr int kGateWords = 8;      // words on which the workgroups of a team launch report, 64 bytes apart ...
 constexpr size_t kGateBytes = (kGateWords + 1) * 64;  // ... and one more
 constexpr int kTeamMost = 256;  // workgroups of a team launch at most
-constexpr int kPlanChunk = 16;
-constexpr int kBlockMinRoundsLarge = 8;
+constexpr int kPlanChunk = 16;  // rounds whose plan records the tile-per-workgroup kernel holds in LDS at a time
 // rounds the resolver may run ahead of the kernels that read its plans (rfast_run, one pass per round)
 constexpr int kResolveAhead = 32;
 struct RfastBlock {
@@ -233,7 +228,8 @@ int rfast_wave_slots(const rfast_ctx* c);       // versions of a node it keeps o
 int rfast_wave_held(const rfast_ctx* c);        // wavefronts of it that a compute unit holds
 hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk);
 hipError_t rfast_wave_prime(rfast_ctx* c);      // loads the kernels this context can launch, with launches that do nothing
-bool rfast_block_eligible(const rfast_ctx* c);  // the multi-round kernel with one tile per workgroup
+bool rfast_block_eligible(const rfast_ctx* c);  // the multi-round kernel with one tile per workgroup (where it is, the other one is too)
+bool rfast_block_takes(const rfast_ctx* c, int32_t rounds);  // a launch of that many rounds is its
 int rfast_block_lanes(const rfast_ctx* c);  // lanes per node of the multi-round kernel, 0 if no tile fits
 hipError_t rfast_launch_block(rfast_ctx* c, const RfastBlock& blk);
 // least squares / logistic regression: consecutive rounds as two kernels each (rows; columns + track + the next mixing)

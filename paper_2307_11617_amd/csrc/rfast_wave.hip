@@ -540,11 +540,6 @@ int wave_resident(const RfastDev& d, int slots, int per) {
 // wavefront's tile is 64 KB at most then).
 bool rfast_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  // More than 32 nodes on rings of at most three slots (delays of one round at most, no losses): the kernel with a tile per
-  // workgroup, whose wide tiles fit LDS then (us per round, tile per workgroup against tile per wavefront: 36 nodes of a
-  // bidirectional ring, two slots, p 1 M: 153.7 / 263.5 in calls of 4 rounds, 59.9 / 69.7 of 100; 48 nodes, three slots: 237 / 313
-  // and 88 / 72; beyond it loses from 20 rounds on, 36 nodes of a mesh, five slots: 252 / 156).
-  if (d.n > 32 && d.M <= 3 && rfast_block_eligible(c)) return false;
   return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes && d.M <= 32;
 }
 
@@ -656,7 +651,7 @@ template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per,
 // Loads the instantiations of the multi-round kernel that this context can launch (rfast_create,
 // rfast_set_optimizer).
 hipError_t rfast_wave_prime(rfast_ctx* c) {
-  if (!rfast_wave_eligible(c)) return hipSuccess;
+  if (!rfast_wave_eligible(c) || rfast_block_takes(c, kBlockRounds)) return hipSuccess;
   const WaveShape shape = wave_shape(c);
   return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) { return prime_wave_w<deg.value, mom.value, per.value>(c, shape); });
 }

@@ -52,7 +52,7 @@ def test_uploaded_schedules(seed):
     off = lambda m: (m != 0) & ~np.eye(n, dtype=bool)
     degree = max(off(wr).sum(1).max(), off(wc).sum(1).max(), off(wc).sum(0).max())   # in R, in C, out C
     assert degree == [2, 3, 4, 4, 6, 8, 5][seed]
-    assert (rfast_block_info(a.ctx) != 0) == (degree <= (6 if n <= 32 else 4)), degree
+    assert (rfast_block_info(a.ctx) != 0) == (degree <= 6), degree
     x0 = rng.standard_normal((n, p)).astype(np.float32)
     for g in (a, b):
         rfast_set_rebase_interval(g.ctx, 23)       # launches end on multiples of 23
@@ -77,8 +77,8 @@ def test_uploaded_schedules(seed):
 
 
 # n, d_max, burst, p, lanes per node the library must choose: up to 32 nodes one tile per wavefront
-# (64 // n lanes per node); beyond, one tile per workgroup (the widest that fits LDS and 1024 lanes and
-# leaves 512 tiles, from 64, 48, 32, 28, 24, 16); every p ends in a ragged tile
+# (64 // n lanes per node); beyond, on rings of two and three slots, one tile per workgroup in short launches (the widest that fits
+# LDS and 1024 lanes and leaves 512 tiles, from 28, 24, 16); every p ends in a ragged tile
 TILES = [(16, 4, 4, 65_540, 4), (16, 5, 4, 49_156, 4), (5, 0, 1, 131_076, 12), (9, 3, 4, 98_308, 7),
          (14, 7, 4, 57_348, 4), (24, 1, 2, 65_540, 2), (32, 2, 2, 8_196, 2), (16, 4, 4, 4_100, 4),
          (1, 0, 1, 4_100, 64), (2, 1, 1, 4_100, 32), (3, 1, 2, 4_100, 21),
@@ -103,6 +103,42 @@ def test_tile_widths(n, d_max, burst, p, lanes):
         g.run(40, *args, w.gamma)
         g.check()
     _same(a, b, lanes)
+
+
+# 33 to 64 nodes on rings of two and three slots: at most two edges of a kind take a tile per workgroup in short launches (28, 24
+# and 16 lanes per node) and a tile per wavefront in long ones, three to six edges the latter only
+@pytest.mark.parametrize("graph,n,p,d_max,burst,momentum,lanes", [
+    ("bidirectional_ring", 36, 57_348, 1, 1, 0.0, 28), ("bidirectional_ring", 36, 57_347, 0, 2, 0.9, 28), ("bidirectional_ring", 40, 49_153, 1, 1, 0.0, 24),
+    ("bidirectional_ring", 48, 1_028, 0, 2, 0.9, 16), ("binary_tree", 64, 1_027, 1, 1, 0.0, 16), ("binary_tree", 64, 66, 0, 2, 0.9, 16),
+    ("directed_ring", 33, 2_052, 0, 1, 0.9, 16), ("line_tree", 50, 3, 1, 1, 0.0, 16),
+    ("mesh", 36, 1_028, 1, 1, 0.0, None), ("mesh", 36, 1_027, 0, 2, 0.9, None), ("exponential", 64, 260, 1, 1, 0.0, None),
+    ("exponential", 40, 129, 3, 2, 0.9, None)])
+def test_short_and_long_launches_of_more_than_32_nodes(graph, n, p, d_max, burst, momentum, lanes):
+    wr, wc = getattr(graphs, graph)(n)
+    R, C = graphs.from_dense(wr), graphs.from_dense(wc)
+    p_act = np.where(np.arange(n) % 4 == 1, 0.1, 0.9)
+    sched = ScheduleSpec(n, R.nnz_off, C.nnz_off, p_act, d_max, 0.4, seed=n)
+    w = configs.Workload(f"short_long_{graph}", n, p, R, C, d_max + burst - 1, burst, 0.02, 0, "diag_quadratic",
+                         problems.diag_quadratic(n, p, n), sched, 0.1, 90 + n, 1e-4)
+    a, b = _pair(w)
+    rfast_use_blocks(a.ctx, 2)
+    if p % 4 == 0:
+        assert rfast_block_info(a.ctx, with_kind=True) == ((lanes, False) if lanes else (64 // n, True))
+    x0 = np.random.default_rng(n).standard_normal((n, p)).astype(np.float32)
+    for g in (a, b):
+        rfast_set_rebase_interval(g.ctx, 23)
+        if momentum:
+            g.set_optimizer(momentum, 0.01)
+        g.init(x0, None)
+    st, dev = harness.upload_chunk(a, w, 0, 108)
+    cut = lambda lo, hi: [dev[k][lo:hi] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")]
+    # short; as many as fill a record's sixteen rounds and one more; short of a rebase and on it; a single pass in between
+    for lo, hi in ((0, 3), (3, 20), (20, 22), (22, 23), (23, 26), (26, 46), (46, 86), (86, 88), (88, 108)):
+        for g in (a, b):
+            g.run(hi - lo, *cut(lo, hi), w.gamma)
+            g.check()
+        if hi in (3, 23, 46, 88, 108):
+            _same(a, b, (graph, hi), ("MOMENTUM",) if momentum else ())
 
 
 @pytest.mark.parametrize("n,d_max,burst,wave", [(8, 12, 4, True), (4, 29, 4, False)])
