@@ -234,7 +234,7 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * C (64 / n lanes of one wavefront per node, 4 coordinates per lane; LDS holds as many of a node's latest versions as
  * the longest delay reads and some more; 33 to 64 nodes with at most 2 edges of a kind on rings of at most three slots, in short
  * launches: at least 16 lanes of one workgroup per node instead), and enough rounds to run before the next multiple of the
- * rebase interval and the next decay step of the step-size schedule (2 to 22: a launch moves every ring slot that can still be
+ * rebase interval and the next decay step of the step-size schedule (2 to some 40: a launch moves every ring slot that can still be
  * read in and out once, which a large state earns back only over some rounds, the more the longer
  * the delays), rings of at most 32 slots (D <= 30); rounds that do not qualify run one pass
  * each.  Every step of a round is elementwise in the coordinate, so a tile of coordinates can stay

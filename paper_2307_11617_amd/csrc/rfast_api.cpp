@@ -978,6 +978,44 @@ static int chained_rounds(rfast_ctx* c, int32_t count, float gamma, const uint8_
   return RFAST_OK;
 }
 
+// Rounds from which on a launch of the wavefront-tile kernel pays.  It moves every live ring slot, a pass per round only what the
+// round reads, so it takes the more rounds the larger the state and the longer the delays, that is, the more versions are live; and
+// the fewer, the more nodes are active, which the host does not know: with all of them active a launch is even after little more than
+// half as many rounds as with half of them.  One pass per round over a launch, contexts in turn, half / all active:
+// Up to 32 nodes, by the wavefronts of the launch that a compute unit holds (12 or more, 8, fewer: delays of up to 4, 8, 16 rounds):
+//   to 1 MB per array   mesh of 16, p 14840: 0.96 / 1.07 in calls of 2; delays of up to 8 0.88 / 0.98 of 2, 1.15 / 1.25 of 3 (a ring with
+//                       one edge of a kind, p 6248, 1.05 / 1.03 of 2); of up to 16 0.95 / 1.01 of 3
+//   to 2 MB             mesh of 16, p 26560: 1.16 / 1.30 of 3; 1.04 / 1.17 of 3; 0.96 / 0.99 of 5
+//   to 8 MB             p 62500: 0.84 / 1.27 of 3, 1.05 / 1.47 of 4; 0.93 / 1.31 of 4, 1.11 / 1.49 of 5; 0.90 / 1.24 of 8, 1.01 / 1.45 of 10
+//   beyond              p 937500: 0.98 / 1.60 of 4, 1.20 / 1.90 of 5; 0.94 / 1.5 of 5, 1.10 / 1.7 of 6; 0.77 / 1.36 of 12, 0.95 / 1.6 of 16
+// 33 to 64 nodes, a lane each (rows in segments of 16 bytes), by the versions that the longest delay reads (delays of up to 4, 8, 16; between
+// them by interpolation), ring and mesh of 36, mesh of 60, tree of 64:
+//   to 1 MB             0.82 to 0.95 / 0.88 to 1.02 of 2, 1.1 to 1.3 of 3; the same; 0.62 to 0.89 / 0.66 to 0.98 of 3, 0.76 to 1.1 of 4
+//   to 2 MB             0.98 to 1.17 / 1.06 to 1.25 of 3; 0.95 to 1.05 / 1.02 to 1.11 of 3; 0.94 to 1.05 of 6
+//   to 8 MB             0.83 to 1.3 / 1.3 to 1.8 of 5; 0.78 to 1.1 / 1.2 to 1.5 of 5, 0.88 to 1.3 of 6; 0.82 to 1.02 / 1.2 to 1.4 of 10
+//   to 20 MB            0.88 to 1.2 / 1.3 of 6, 0.99 and more of 7; 0.88 to 1.1 / 1.4 of 7; 0.95 to 1.02 / 1.5 of 16, 1.1 to 1.25 of 20
+//   to 50 MB            0.89 to 1.2 / 1.5 of 7; 0.77 to 0.92 / 1.2 to 1.4 of 7, 0.86 to 0.98 of 8; 0.93 to 0.97 / 1.4 of 20, 1.0 to 1.1 of 24
+//   beyond              0.82 to 1.02 / 1.4 of 7; 0.82 to 0.87 / 1.4 of 8, 0.94 to 1.01 of 10; 0.8 to 0.9 / 1.4 of 20, 0.9 to 0.99 of 24
+// and with five and six edges of a kind (exponential graph of 40) 0.93 / 1.07 of 4 to 2 MB, 0.88 to 1.0 / 1.3 of 6 and 7 to 8 MB, 0.9 to 1.04 /
+// 1.4 of 9 and 10 beyond.
+static int32_t wave_least_rounds(const rfast_ctx* c) {
+  const RfastDev& d = c->d;
+  const double mb = (double)d.n * (double)d.p * 4.0e-6;
+  int row = mb > 8.0 ? 3 : mb > 2.0 ? 2 : mb > 1.0 || d.p % 4 != 0 ? 1 : 0;
+  if (d.n <= 32) {
+    static const int32_t few[4][3] = {{2, 3, 3}, {3, 3, 6}, {4, 5, 10}, {5, 6, 12}};
+    const int held = rfast_wave_held(c), col = held >= 12 ? 0 : held >= 8 ? 1 : 2;
+    return row == 0 && col == 1 && c->max_degree < 2 ? 2 : few[row][col];
+  }
+  static const float many[6][3] = {{3, 3, 4}, {3, 3, 6}, {5, 6, 10}, {7, 7, 16}, {7, 8, 20}, {7, 9, 22}};
+  static const float many_edges[6][3] = {{3, 3, 4}, {4, 4, 6}, {6, 7, 10}, {9, 9, 16}, {9, 10, 20}, {9, 10, 22}};
+  if (row == 3) row += mb > 50.0 ? 2 : mb > 20.0 ? 1 : 0;
+  const float* v = c->max_degree > 4 ? many_edges[row] : many[row];
+  const int reach = std::min(d.M - 1, d.d_max + 2);  // versions that the longest delay reads, and one more
+  const float least = reach <= 6 ? v[0] : reach <= 10 ? v[0] + (v[1] - v[0]) * (float)(reach - 6) / 4.f : v[1] + (v[2] - v[1]) * (float)(reach - 10) / 8.f;
+  return (int32_t)(least + 0.5f);
+}
+
 // How many of the next `rounds` rounds one launch of the LDS-resident kernel should take (0: run
 // the next round as one pass).  A launch holds no rebase, so it must end at the latest on the next
 // multiple of the rebase interval, and it runs with one step size, so it must end with the current
@@ -999,21 +1037,10 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
     if (to_decay < len) len = (int32_t)to_decay;
   }
   if (gemv) return rfast_tiny_eligible(c) || len >= team_least_rounds(c) ? len : 0;
-  // A launch moves every live ring slot, a pass per round only what the round reads.  One pass per round against a launch of
-  // r rounds, timed side by side with half of the nodes active: how many rounds it takes depends on the state and on the
-  // wavefronts of the launch that a compute unit holds (12 or more, 8, fewer: delays of up to 4, 8, 16 rounds).
-  // Even at r = 2, 2, 3 rounds up to 1 MB per array (mesh of 16, p 7000: 16.1 / 15.8 us at r = 2, delays of up to 16:
-  // 1.03 at r = 3); 3, 3, 6 up to 2 MB; 4, 5, 10 up to 8 MB (8 nodes, p 200000: 1.06 at r = 3, 1.07 at 5, 0.91 at 9);
-  // 4 or 5, 6, 11 or 12 beyond (16 nodes, p 11.2 M: 0.94 at r = 4, 1.15 at 5; 32 nodes, p 1 M, delays of up to 8: 0.80 at 5,
-  // 1.02 at 6; 16 nodes, p 2 M, delays of up to 16: 0.64 at 8).
   const double bytes = (double)c->d.n * (double)c->d.p * 4.0;
   int32_t least;
   if (!rfast_block_takes(c, len)) {
-    const int held = rfast_wave_held(c), row = bytes > 8.0e6 ? 3 : bytes > 2.0e6 ? 2 : bytes > 1.0e6 || c->d.p % 4 != 0 ? 1 : 0;
-    static const int32_t table[4][3] = {{2, 2, 3}, {3, 3, 6}, {4, 5, 10}, {5, 6, 12}};
-    // more than 32 nodes, a lane each: row segments of 16 bytes per tile, so that moving them takes longer
-    static const int32_t narrow[4][3] = {{2, 2, 3}, {3, 3, 6}, {5, 6, 10}, {7, 10, 22}};
-    least = (c->d.n > 32 ? narrow : table)[row][held >= 12 ? 0 : held >= 8 ? 1 : 2];
+    least = wave_least_rounds(c);
   } else {
     // (one pass per round / a launch, rings of two or three slots: ring of 36, p 416664, 73 / 77 us per round in calls of 4, 74 / 59 of
     // 6; p 97220: 22.6 / 26.4 of 3, 22.0 / 22.0 of 4; p 27776: 11.2 / 12.5 of 2, 10.2 / 9.7 of 3; p 6944: 9.0 / 7.5 of 2; ring of 48 and

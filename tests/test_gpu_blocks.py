@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2307_11617_amd import rfast_block_info, rfast_use_blocks, rfast_set_rebase_interval
+from paper_2307_11617_amd import rfast_block_info, rfast_kernel_time, rfast_profile_enable, rfast_use_blocks, rfast_set_rebase_interval
 from rfast_workloads import configs, graphs, problems
 from rfast_workloads.schedule import ScheduleSpec
 
@@ -165,8 +165,8 @@ def test_deep_rings(n, d_max, burst, wave):
 
 
 def test_large_state_short_and_long_calls():
-    """Above 8 MB of x a launch needs 8 rounds to pay: shorter calls run one pass per round, longer
-    ones take the multi-round kernel (four refills of its plan records at 70 rounds), same bits."""
+    """Calls of several lengths on a state of 8 MB per array, where a launch pays from five rounds on, same bits as one pass per
+    round."""
     w = configs.config2(p=131_076, rounds=0)
     a, b = _pair(w)
     for g in (a, b):
@@ -178,6 +178,37 @@ def test_large_state_short_and_long_calls():
             g.run(hi - lo, *cut(lo, hi), w.gamma)
             g.check()
         _same(a, b, hi)
+
+
+@pytest.mark.parametrize("graph,n,p,least", [("bidirectional_ring", 16, 131_076, 5), ("mesh", 16, 131_077, 5), ("mesh", 36, 58_084, 7)])
+def test_calls_of_both_forms_in_turn(graph, n, p, least):
+    """A few rounds, fewer than a launch pays for, run one pass each; the next call is one launch, the next passes again: what the one
+    leaves (ring slots, buffers outside their rings) the other goes on from, with losses and stragglers.  The count of timed launches
+    says which form a call took."""
+    wr, wc = getattr(graphs, graph)(n)
+    R, C = graphs.from_dense(wr), graphs.from_dense(wc)
+    p_act = np.where(np.arange(n) % 5 == 1, 0.05, 0.8)
+    sched = ScheduleSpec(n, R.nnz_off, C.nnz_off, p_act, 4, 0.4, seed=n)
+    w = configs.Workload(f"in_turn_{graph}", n, p, R, C, 7, 4, 0.02, 0, "diag_quadratic", problems.diag_quadratic(n, p, n), sched, 0.1, 90 + n, 1e-4)
+    a, b = _pair(w)
+    for g in (a, b):
+        rfast_set_rebase_interval(g.ctx, 37)
+        g.init(None, None)
+    st, dev = harness.upload_chunk(a, w, 0, 100)
+    cut = lambda lo, hi: [dev[k][lo:hi] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")]
+    short = least - 1
+    ends = np.cumsum([short, 20, short, least, short, short, 30])
+    for lo, hi in zip([0, *ends[:-1]], ends):
+        for g in (a, b):
+            g.run(int(hi - lo), *cut(lo, hi), w.gamma)
+            g.check()
+        _same(a, b, (graph, int(hi)))
+    # what the calls above took: float kernels per call
+    rfast_profile_enable(a.ctx, True)
+    for rounds, launches in ((short, short), (least, 1)):
+        before = rfast_kernel_time(a.ctx, 0)[1]
+        a.run(rounds, *cut(0, rounds), w.gamma)
+        assert rfast_kernel_time(a.ctx, 0)[1] - before == launches, rounds
 
 
 @pytest.mark.parametrize("n,variant", [(16, False), (16, True), (5, False), (24, True)])
