@@ -238,7 +238,8 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * read in and out once, which a large state earns back only over some rounds, the more the longer
  * the delays), rings of at most 32 slots (D <= 30); rounds that do not qualify run one pass
  * each.  Every step of a round is elementwise in the coordinate, so a tile of coordinates can stay
- * in LDS over several rounds; the results are the same bits as round-by-round execution.
+ * in LDS over several rounds; the results are the same bits as round-by-round execution (finite values: in a run that has
+ * diverged to infinity, NaN may come an activation earlier).
  * Least squares and logistic regression (whose gradient couples the coordinates of a node, so that
  * there are no tiles) take the same stretches of rounds with one launch of a single workgroup when the
  * whole problem fits the LDS of one CU: p a multiple of 4, no heavy-ball buffer, (3 + 2 (D+2)) n p +

@@ -25,9 +25,10 @@
 //
 // The arithmetic is, operation for operation, that of rfast_state_kernel<FUSED> and of
 // rfast_block_kernel: the three paths give the same bits.  (One liberty: where those skip a missing
-// or idle edge, this kernel runs it through the multiply-add with weight zero, which spares the round
+// or idle edge, this kernel runs it through the multiply-add with weight zero or a difference of zero, which spares the round
 // loop most of its branches.  Adding zero changes nothing but the sign of a sum that is exactly zero,
-// as long as the ring values are finite.)
+// as long as the ring values are finite; an infinity of a node with fewer edges than the kernel has slots can turn to NaN here
+// an activation before it does elsewhere, where infinity minus infinity follows in the next tracker sum.)
 #include <algorithm>
 
 #include "rfast_vec.h"
@@ -67,8 +68,12 @@ __device__ inline void wave_sync() {
 // its own for every workgroup at the start, up to 14 us, and what depends on the node alone set up once
 // per wavefront, 10 rounds took 5.1 ms against 5.3, but 20 rounds 7.4 against 7.1 and 500 rounds 101.8
 // against 93.9: the same round loop, instruction for instruction, ran 8 % slower.)
-// PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 registers), 3 at four (164), 2 at six (three
-// would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).
+// PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 to 128 registers), 3 at four (164 to 168), 2 at six (three
+// would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).  At four edge slots
+// the heavy-ball buffer and several wavefronts per workgroup spill up to 5 registers, outside the loop, and three still win: us per round in
+// calls of 20 / 60 / 200 at two and three wavefronts, heavy-ball buffer in use: mesh of 16, p 1 M, 34.8 / 27.7 / 22.1 and 29.0 / 19.7 / 17.6; mesh of
+// 40, p 300000, 45.2 / 36.2 / 28.7 and 38.1 / 26.2 / 23.3.  The forms for three and four at two edge slots take the same registers, but order
+// their loads and rounds differently: three wavefronts of the form for four are 1 to 4 % slower (500 rounds of 16 nodes, p 11.2 M: 69.8 -> 72.3 ms).
 //
 // Only what can matter is moved.  Stamps never go back (S2a / S2b take the largest stamp received), so
 // a version older than every stamp held on its sender's out-edges will never be read again: such a
@@ -366,7 +371,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     }
     wave_sync();  // S5: the round is over, its publications are visible to the lanes of this wavefront
   };
-  // (two loops, each unrolled by two, so that each keeps its values where it likes)
+  // (two rounds at a time, so that the two sets of plan words stay where they are)
   if (wave_has) {
     for (int q = 0; q < blk.rounds; q += 2) {
       round(q, plan_a, plan_b);
