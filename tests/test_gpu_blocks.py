@@ -253,7 +253,7 @@ def test_generated_schedules_and_events():
 
 
 def test_odd_p_runs_one_pass_per_round_and_momentum_variant_same_bits():
-    """p not a multiple of four: the call must simply run one pass per round.  The optimizer variant
+    """p not a multiple of four: tiles start at any float's address (no lanes are reported then), same bits.  The optimizer variant
     (heavy-ball buffer, weight decay, step-size schedule) goes through the multi-round kernel."""
     w = configs.config2(p=1027, rounds=0)
     a, b = _pair(w)
