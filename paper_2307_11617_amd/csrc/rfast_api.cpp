@@ -1039,9 +1039,9 @@ static int32_t block_length(const rfast_ctx* c, int32_t rounds, int64_t at_round
   if (gemv) return rfast_tiny_eligible(c) || len >= team_least_rounds(c) ? len : 0;
   const double bytes = (double)c->d.n * (double)c->d.p * 4.0;
   int32_t least;
-  if (!rfast_block_takes(c, len)) {
+  if (!rfast_block_eligible(c)) {
     least = wave_least_rounds(c);
-  } else {
+  } else {  // (the longer launches that take the other kernel do so because it is faster still)
     // (one pass per round / a launch, rings of two or three slots: ring of 36, p 416664, 73 / 77 us per round in calls of 4, 74 / 59 of
     // 6; p 97220: 22.6 / 26.4 of 3, 22.0 / 22.0 of 4; p 27776: 11.2 / 12.5 of 2, 10.2 / 9.7 of 3; p 6944: 9.0 / 7.5 of 2; ring of 48 and
     // tree of 64 alike)

@@ -211,6 +211,26 @@ def test_calls_of_both_forms_in_turn(graph, n, p, least):
         assert rfast_kernel_time(a.ctx, 0)[1] - before == launches, rounds
 
 
+@pytest.mark.parametrize("n,p,least", [(48, 20_832, 3), (48, 72_916, 4), (36, 27_776, 3)])
+def test_a_longer_call_is_no_more_launches(n, p, least):
+    """Where short and long launches have different kernels: from the shortest call that is one launch on every longer one is, too."""
+    wr, wc = graphs.bidirectional_ring(n)
+    R, C = graphs.from_dense(wr), graphs.from_dense(wc)
+    sched = ScheduleSpec(n, R.nnz_off, C.nnz_off, np.full(n, 0.7), 1, 0.0, seed=n)
+    w = configs.Workload("launches", n, p, R, C, 1, 1, 0.02, 0, "diag_quadratic", problems.diag_quadratic(n, p, n), sched, 0.1, 90 + n, 1e-4)
+    a, b = _pair(w)
+    for g in (a, b):
+        g.init(None, None)
+    st, dev = harness.upload_chunk(a, w, 0, 14)
+    rfast_profile_enable(a.ctx, True)
+    for rounds in range(1, 15):
+        before = rfast_kernel_time(a.ctx, 0)[1]
+        for g in (a, b):
+            g.run(rounds, *[dev[k][:rounds] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")], w.gamma)
+        assert rfast_kernel_time(a.ctx, 0)[1] - before == (1 if rounds >= least else rounds), rounds
+    _same(a, b, n)
+
+
 @pytest.mark.parametrize("n,variant", [(16, False), (16, True), (5, False), (24, True)])
 def test_synchronous_steps_per_launch(n, variant):
     """rfast_sync_run through the multi-step kernel against one step per launch: same bits, with the
