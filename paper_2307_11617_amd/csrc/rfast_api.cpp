@@ -792,6 +792,24 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   for (int i = 0; i < n; ++i) c->max_in_degree = std::max({c->max_in_degree, gr.ptr[i + 1] - gr.ptr[i], gc.ptr[i + 1] - gc.ptr[i]});
   for (int i = 0; i < n; ++i)
     c->max_degree = std::max({c->max_degree, gr.ptr[i + 1] - gr.ptr[i], gc.ptr[i + 1] - gc.ptr[i], gc.out_ptr[i + 1] - gc.out_ptr[i]});
+  int max_in_r = 0, max_in_c = 0, v_rows = 0, s_rows = 0;
+  bool one_receiver = true;
+  for (int i = 0; i < n; ++i) {
+    max_in_r = std::max(max_in_r, gr.ptr[i + 1] - gr.ptr[i]);
+    max_in_c = std::max(max_in_c, gc.ptr[i + 1] - gc.ptr[i]);
+    v_rows += gr.out_ptr[i + 1] > gr.out_ptr[i] ? 1 : 0;
+    s_rows += gc.out_ptr[i + 1] > gc.out_ptr[i] ? 1 : 0;
+  }
+  for (int32_t to : gc.dst) one_receiver = one_receiver && to == gc.dst[0];
+  c->v_rows = c->s_rows = n;
+  if (v_rows > 0 && s_rows > 0 && max_in_r <= 1) {
+    if (one_receiver && max_in_c > 2) c->hub = gc.dst[0];
+    else c->tree = max_in_c <= 2 && c->max_degree <= 2 && v_rows + s_rows < 2 * n;
+    if (c->hub >= 0 || c->tree) {
+      c->v_rows = v_rows;
+      c->s_rows = s_rows;
+    }
+  }
   int max_out_r = 0;
   d.leaves = 0;
   for (int i = 0; i < n; ++i) {
@@ -998,9 +1016,20 @@ static int chained_rounds(rfast_ctx* c, int32_t count, float gamma, const uint8_
 //   beyond              0.82 to 1.02 / 1.4 of 7; 0.82 to 0.87 / 1.4 of 8, 0.94 to 1.01 of 10; 0.8 to 0.9 / 1.4 of 20, 0.9 to 0.99 of 24
 // and with five and six edges of a kind (exponential graph of 40) 0.93 / 1.07 of 4 to 2 MB, 0.88 to 1.0 / 1.3 of 6 and 7 to 8 MB, 0.9 to 1.04 /
 // 1.4 of 9 and 10 beyond.
+// One receiver of all edges of C, half of the nodes active (one pass has a node with up to 63 in-edges to wait for, so a launch pays earlier
+// where the state is small), delays of up to 4 / 16, even at: 12 and 24 nodes, 0.2 MB 2 / 3 rounds, 2 MB 3 / 5, 16 MB 7.5 / 11.5, 48 MB 11 / 19;
+// 48 and 64 nodes, to 2 MB 2 / 2, 16 MB 3.5 / 6, 48 MB 7 / 10, 268 MB 10 / 14; 64 nodes, 2 MB, 20 rounds 6.2 / 5.2 times as fast.
 static int32_t wave_least_rounds(const rfast_ctx* c) {
   const RfastDev& d = c->d;
   const double mb = (double)d.n * (double)d.p * 4.0e-6;
+  if (c->hub >= 0) {
+    static const float star[2][5][2] = {{{2, 3}, {3, 5}, {5, 8}, {8, 12}, {12, 19}}, {{2, 2}, {2, 2}, {3, 4}, {4, 6}, {8, 10}}};
+    const int size = mb > 20.0 ? 4 : mb > 8.0 ? 3 : mb > 2.5 ? 2 : mb > 0.5 ? 1 : 0;
+    const float* v = star[d.n > 32][size];
+    const int reach = std::min(d.M - 1, d.d_max + 2);
+    const float at = std::min(std::max((float)(reach - 6) / 12.f, 0.f), 1.f), more = d.n > 32 && mb > 100.0 ? 4.f : 0.f;
+    return (int32_t)(v[0] + (v[1] - v[0]) * at + more + 0.5f);
+  }
   int row = mb > 8.0 ? 3 : mb > 2.0 ? 2 : mb > 1.0 || d.p % 4 != 0 ? 1 : 0;
   if (d.n <= 32) {
     static const int32_t few[4][3] = {{2, 3, 3}, {3, 3, 6}, {4, 5, 10}, {5, 6, 12}};
@@ -1071,6 +1100,9 @@ static int run_block(rfast_ctx* c, int32_t len, const uint8_t* d_active, const i
   d.blk_plan = c->blk_plan_base;
   d.blk_head = tiny || team ? nullptr : c->blk_head_base;
   blk.slots = d.blk_slots = wave ? rfast_wave_slots(c) : 0;
+  blk.hub = c->hub;
+  blk.v_rows = c->v_rows;
+  blk.s_rows = c->s_rows;
   if (!own_resolver) {
     time_begin(c, 2);
     e = rfast_launch_resolve(c, d_active, d_delay_R, d_delay_C, d_drop_R, d_drop_C, len);

@@ -176,6 +176,9 @@ struct rfast_ctx {
   int32_t* blk_head_base = nullptr;  // kHeadWords n + eC words, see RfastDev::blk_head
   int32_t max_in_degree = 0;    // most in-edges of R or of C at any node
   int32_t max_degree = 0;       // most in-edges of R, in-edges of C or out-edges of C at any node
+  int32_t hub = -1;             // wavefront-tile kernel: at most one in-edge of R per node, and every edge of C leads to this node
+  bool tree = false;            // ... at most one in-edge of R and two of C, and not every node is read over both graphs
+  int32_t v_rows = 0, s_rows = 0;  // rings that it keeps on chip: of every node, with hub or tree of those with out-edges over R, over C
   RfastTeam team;
   unsigned team_base = 0;       // rounds handed to the team kernel so far (its progress words and packet tags never repeat)
   void* team_packets = nullptr;
@@ -211,6 +214,7 @@ struct RfastBlock {
   int32_t rounds;             // 1 .. kBlockRounds
   int32_t rebase;             // wavefront-tile kernel: the running sums are rebased as the tiles are written back
   int32_t slots;              // wavefront-tile kernel: versions of a node on chip
+  int32_t hub, v_rows, s_rows;  // wavefront-tile kernel: rfast_ctx::hub, rings of v and of sums on chip
 };
 
 // launchers (each enqueues on ctx->stream and returns a hipError_t)

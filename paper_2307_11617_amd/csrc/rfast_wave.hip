@@ -51,7 +51,39 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// lw: lanes per node (64 / n, rounded down); kDeg: edge slots per node and kind; MOM: the optimizer
+// The sum over the nodes of a value per lane, column by column (lane = node * lw + column; lanes past the last node bring
+// zeros), in all lanes of a column.
+__device__ inline float4 sum_of_nodes(float4 t, int lane, int n, int i, int ln, int lw) {
+  if (lw == 1) {
+    // Halves, then rows of 16 lanes are added so that two, then all four coordinates share a register, a row each; then
+    // within the rows: 14 instructions where a butterfly over four registers takes 48.
+    auto u = [](float v) { return __float_as_uint(v); };
+    auto f = [](unsigned v) { return __uint_as_float(v); };
+    const auto xz = __builtin_amdgcn_permlane32_swap(u(t.x), u(t.z), false, false);
+    const auto yw = __builtin_amdgcn_permlane32_swap(u(t.y), u(t.w), false, false);
+    const auto r = __builtin_amdgcn_permlane16_swap(u(f(xz[0]) + f(xz[1])), u(f(yw[0]) + f(yw[1])), false, false);
+    float v = f(r[0]) + f(r[1]);  // rows: x, y, z, w
+    auto ror = [](float a, auto by) {
+      return a + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), 0x120 + decltype(by)::value, 0xF, 0xF, false));
+    };
+    v = ror(v, std::integral_constant<int, 8>());
+    v = ror(v, std::integral_constant<int, 4>());
+    v = ror(v, std::integral_constant<int, 2>());
+    v = ror(v, std::integral_constant<int, 1>());
+    auto at = [&](int from) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from)); };
+    return make_float4(at(0), at(16), at(32), at(48));
+  }
+  int step = 1;
+  while (2 * step < n) step *= 2;
+  for (; step > 0; step >>= 1) {
+    const int from = lane + step * lw;
+    const float4 o = make_float4(__shfl(t.x, from), __shfl(t.y, from), __shfl(t.z, from), __shfl(t.w, from));
+    if (i < step && i + step < n) t = add(t, o);
+  }
+  return make_float4(__shfl(t.x, ln), __shfl(t.y, ln), __shfl(t.z, ln), __shfl(t.w, ln));
+}
+
+// lw: lanes per node (64 / n, rounded down); kR, kC: edge slots per node over R and over C; MOM: the optimizer
 // variant is in use, heavy-ball buffer, weight decay or both (a template flag, so that the plain method
 // carries neither the registers and the copies at the join nor the tests).
 // ANY: p is not a multiple of four: rows start at any float's address, and the last group of a row may be short (its
@@ -68,6 +100,13 @@ __device__ inline void wave_sync() {
 // its own for every workgroup at the start, up to 14 us, and what depends on the node alone set up once
 // per wavefront, 10 rounds took 5.1 ms against 5.3, but 20 rounds 7.4 against 7.1 and 500 rounds 101.8
 // against 93.9: the same round loop, instruction for instruction, ran 8 % slower.)
+// kC = 0: every edge of C leads to one node (a star, at most one in-edge of R per node: any tree), which as a lane of its own
+// would need a slot per sender.  Instead the lanes of every sender, which have its sums in their own column, form its term
+// a (sigma - what was consumed last) and keep what belongs to the edge (S4), and the terms are added up across the wavefront.  That is
+// another order of a sum of up to 63 terms than that of one pass per round (the depth of the tree, not the number of terms, bounds its
+// error), so these launches agree with it to the rounding of that sum and not bit for bit.  Tree and star of 64 nodes, p 1 M, delays of up
+// to 16, 100 rounds: 25.0 ms one pass per round (6.0 TB/s), 11.4 this way, 94 us per round and 2 ms of tile movement.
+// FEW: only nodes with readers have rings on chip: a tree is read over half of its nodes, the others publish no v.
 // PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 to 128 registers), 3 at four (164 to 168), 2 at six (three
 // would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).  At four edge slots
 // the heavy-ball buffer and several wavefronts per workgroup spill up to 5 registers, and three still win: us per round in
@@ -97,9 +136,10 @@ static WaveDiv wave_div(int lw, int W) {
   return dv;
 }
 
-template <int kDeg, bool MOM, int W, bool ANY, int PER>
+template <int kR, int kC, bool FEW, bool MOM, int W, bool ANY, int PER>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER, PER))) rfast_wave_kernel(RfastDev s, RfastBlock blk, int lw, WaveDiv dv) {
   constexpr int VEC = 4;
+  constexpr bool HUB = kC == 0;
   extern __shared__ float4 lds4[];
   const int n = s.n, M = s.M, K = blk.slots;
   const int64_t p = s.p;
@@ -120,7 +160,24 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   const bool wave_has = k_wg + (int64_t)wave * lw * 4 < p;  // this wavefront has a tile (the last workgroup may be ragged)
   const bool mine = i < n && k < p;
   const int left = p - k < 4 ? (int)(p - k) : 4;  // ANY: coordinates of the row from the lane's first one on
-  const size_t ring_f4 = (size_t)n * K * lw;   // float4 of one ring of one wavefront's tile: [n][K][lw], first v, then the sums
+  // float4 of the rings of v of one wavefront's tile, [rows][K][lw]; the rings of sums follow.  FEW: only nodes whose v or
+  // sums somebody reads have a ring, in the order of their numbers (bit lw j of a mask: node j has one).
+  const int v_rows = FEW ? blk.v_rows : n, s_rows = FEW ? blk.s_rows : n;
+  const size_t ring_f4 = (size_t)v_rows * K * lw;
+  unsigned long long has_v = 0, has_s = 0;
+  bool pulled = true;
+  if (FEW) {
+    int out_r = 0, out_c = 0;
+    if (i < n) {
+      out_r = s.ro_ptr[i + 1] - s.ro_ptr[i];
+      out_c = s.co_ptr[i + 1] - s.co_ptr[i];
+    }
+    pulled = out_r > 0;
+    has_v = __ballot(pulled && ln == 0);
+    has_s = __ballot(out_c > 0 && ln == 0);
+  }
+  auto has = [&](unsigned long long rows, int j) { return !FEW || (rows >> (j * lw) & 1) != 0; };
+  auto row = [&](unsigned long long rows, int j) { return FEW ? __popcll(rows & ((1ull << (j * lw)) - 1)) : j; };
   // LDS addresses proper (32 bits, the start of the array included): column of the lane in a node's ring + slot * bytes
   // per slot, one 24-bit multiply-add each, which leaves the high byte of a plan word to its flags.
   const unsigned slot_bytes = (unsigned)lw * sizeof(float4);
@@ -134,8 +191,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     const Vec4 t = {w.x, w.y, w.z, w.w};
     *(LdsVec4*)(uintptr_t)a = t;
   };
-  const unsigned sg_off = (unsigned)n * K * slot_bytes;  // from a node's ring of v to its ring of sums
-  const unsigned tile = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds4 + (unsigned)wave * 2 * sg_off;
+  const unsigned sg_off = (unsigned)v_rows * K * slot_bytes;  // from the rings of v to those of sums
+  const unsigned tile_f4 = (unsigned)(v_rows + s_rows) * K * lw;
+  const unsigned tile = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds4 + (unsigned)wave * tile_f4 * (unsigned)sizeof(float4);
   // Moving the rings: lane T of the workgroup moves column cT (of the lw W columns of a row segment) of
   // node iT, i.e. column lT of the tile of wavefront wT.  With W = 1 that is the lane's own column.
   const int seg = lw * W;
@@ -144,7 +202,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   const int64_t kT = k_wg + 4 * cT;
   const bool moves = iT < n && kT < p;
   const int leftT = p - kT < 4 ? (int)(p - kT) : 4;
-  float4* mv_l = lds4 + (size_t)wT * 2 * ring_f4 + (size_t)iT * K * lw + lT;  // + slot * lw (+ ring_f4 for the sums)
+  const bool mv_has_v = has(has_v, iT), mv_has_s = has(has_s, iT);
+  float4* mv_v = lds4 + (size_t)wT * tile_f4 + (size_t)row(has_v, iT) * K * lw + lT;  // + slot * lw
+  float4* mv_s = lds4 + (size_t)wT * tile_f4 + ring_f4 + (size_t)row(has_s, iT) * K * lw + lT;
   // What the resolver, which has been through all rounds of the launch already, left about the moved node: the places of
   // its latest version before the launch, in memory and on chip, and, one bit per version counted back from it, which
   // versions a receiver can still pick up (the others are not loaded); and the same for after the launch, where a version
@@ -163,27 +223,38 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   // What was consumed last time over each in-edge of C, in registers: the sender's running sum of that version, or (bit u of
   // `prod`) its product with the weight, which is what the array of S4 buffers holds.  So a round reads one sum per edge from LDS,
   // and a buffer is written only at the end of a launch, if its version is outside the sender's ring then.
-  float4 last[kDeg];
+  // HUB: every edge of C leads to one node.  A sender's lanes hold this for their edge to it (in place 0), form its term of the
+  // sum in their own columns and add the terms up across the wavefront.
+  constexpr int kL = kC > 0 ? kC : 1;
+  float4 last[kL];
   unsigned prod = 0, outside = 0;  // outside: the same for after the launch, edge by edge (RfastDev::blk_head)
-  int where[kDeg];
+  int where[kL];
   float4 sig = make_float4(0.f, 0.f, 0.f, 0.f);  // the node's own latest running sum
   float r_self = 0.f, c_self = 0.f;
   // the node's edges, in registers for the whole launch: LDS column of the sender's ring, weight,
   // position of the edge's plan word in a record; a missing edge has weight zero, the node's own
   // column and the zero word of the record
-  unsigned r_col[kDeg], c_col[kDeg];
+  unsigned r_col[kR], c_col[kL];
   // positions of plan words as unsigned byte offsets: a 32-bit offset from a uniform base, no 64-bit address arithmetic
-  unsigned r_pw[kDeg], c_pw[kDeg];
-  float r_w[kDeg], c_w[kDeg];
+  unsigned r_pw[kR], c_pw[kL];
+  float r_w[kR], c_w[kL];
 #pragma unroll
-  for (int u = 0; u < kDeg; ++u) {
-    r_col[u] = c_col[u] = tile;
+  for (int u = 0; u < kR; ++u) {
+    r_col[u] = tile;
+    r_pw[u] = 4u * (W1 - 1);
+    r_w[u] = 0.f;
+  }
+#pragma unroll
+  for (int u = 0; u < kL; ++u) {
+    c_col[u] = tile;
     where[u] = 0;
-    r_pw[u] = c_pw[u] = 4u * (W1 - 1);
-    r_w[u] = c_w[u] = 0.f;
+    c_pw[u] = 4u * (W1 - 1);
+    c_w[u] = 0.f;
     last[u] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  const unsigned a_own = tile + (unsigned)(i * K * lw + ln) * sizeof(float4);  // this lane's column in the rings of its node
+  // this lane's column in the ring of v of its node, and from there to its column in the node's ring of sums
+  const unsigned a_own = tile + (unsigned)(row(has_v, i) * K * lw + ln) * sizeof(float4);
+  const unsigned to_sum = FEW ? sg_off + (unsigned)((row(has_s, i) - row(has_v, i)) * K * lw) * (unsigned)sizeof(float4) : sg_off;
   unsigned node_pw = 4u * (W1 - 1);
   if (mine) {
     node_pw = 4u * i;
@@ -194,13 +265,27 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     dO = s.co_ptr[i + 1] - s.co_ptr[i];
     r_self = s.r_self[i];
     c_self = s.c_self[i];
+    if (HUB) {  // the node's edge to the hub, if it has one
+      dI = dO;
+      ce0 = dO > 0 ? s.co_eid[s.co_ptr[i]] : 0;
+    }
 #pragma unroll
-    for (int u = 0; u < kDeg; ++u) {
-      const bool hr = u < dR, hc = u < dI;
-      r_col[u] = tile + (unsigned)((hr ? s.r_src[re0 + u] : i) * K * lw + ln) * sizeof(float4);
+    for (int u = 0; u < kR; ++u) {
+      const bool hr = u < dR;
+      // (a missing edge reads the first ring there is)
+      r_col[u] = tile + (unsigned)((hr ? row(has_v, s.r_src[re0 + u]) : FEW ? 0 : i) * K * lw + ln) * sizeof(float4);
       r_w[u] = hr ? s.r_w[re0 + u] : 0.f;
       r_pw[u] = 4u * (hr ? n + re0 + u : W1 - 1);
-      c_col[u] = tile + sg_off + (unsigned)((hc ? s.c_src[ce0 + u] : i) * K * lw + ln) * sizeof(float4);
+    }
+    if (HUB && dI > 0) {
+      c_col[0] = a_own + to_sum;
+      c_w[0] = s.c_w[ce0];
+      c_pw[0] = 4u * (n + s.eR + ce0);
+    }
+#pragma unroll
+    for (int u = 0; u < kC; ++u) {
+      const bool hc = u < dI;
+      c_col[u] = tile + sg_off + (unsigned)((hc ? row(has_s, s.c_src[ce0 + u]) : FEW ? 0 : i) * K * lw + ln) * sizeof(float4);
       c_w[u] = hc ? s.c_w[ce0 + u] : 0.f;
       c_pw[u] = 4u * (hc ? n + s.eR + ce0 + u : W1 - 1);
     }
@@ -216,15 +301,15 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     return __builtin_amdgcn_raw_buffer_load_b32(plans, byte_offset, round * rec_bytes, 0);
   };
   struct Plan {
-    int node, r[kDeg], c[kDeg];
+    int node, r[kR], c[kL], hub;
   };
   auto fetch = [&](int round, Plan& P) {
     P.node = word(round, node_pw);
 #pragma unroll
-    for (int u = 0; u < kDeg; ++u) {
-      P.r[u] = word(round, r_pw[u]);
-      P.c[u] = word(round, c_pw[u]);
-    }
+    for (int u = 0; u < kR; ++u) P.r[u] = word(round, r_pw[u]);
+#pragma unroll
+    for (int u = 0; u < kL; ++u) P.c[u] = word(round, c_pw[u]);
+    if (HUB) P.hub = word(round, 4u * (unsigned)blk.hub);
   };
   Plan plan_a, plan_b;  // two register sets that take turns: one in use, one arriving
   fetch(0, plan_a);
@@ -237,7 +322,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     if (momentum) m = ld_group<ANY>(s.mom + off, left);
     // (a version that neither the array of S4 buffers nor the part of the ring on chip holds comes from the ring in memory)
 #pragma unroll
-    for (int u = 0; u < kDeg; ++u)
+    for (int u = 0; u < kL; ++u)
       if (u < dI) {
         where[u] = s.blk_head[kHeadWords * n + ce0 + u];
         outside |= (unsigned)(where[u] >> 1 & 1) << u;
@@ -245,13 +330,13 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
           last[u] = ld_group<ANY>(s.rho_tilde + (size_t)(ce0 + u) * p + k, left);
           prod |= 1u << u;
         } else if (!(where[u] & 4)) {
-          last[u] = ld_group<ANY>(s.sigma_ring + ((size_t)s.c_src[ce0 + u] * M + (where[u] >> 8 & 0xFF)) * p + k, left);
+          last[u] = ld_group<ANY>(s.sigma_ring + ((size_t)(HUB ? i : s.c_src[ce0 + u]) * M + (where[u] >> 8 & 0xFF)) * p + k, left);
         }
       }
   }
   // rings, from the latest version back: kBatch versions of both in flight at a time, then into LDS; a version
   // that nobody can read any more is zeros instead (the multiply-adds with weight zero need finite values)
-  constexpr int kBatch = PER >= 4 ? 5 : PER >= 3 ? 6 : kDeg <= 2 ? 12 : (kDeg <= 4 ? 10 : 8);
+  constexpr int kBatch = PER >= 4 ? 5 : PER >= 3 ? 6 : kR <= 2 ? 12 : (kR <= 4 ? 10 : 8);
   const int64_t back_to_last = (int64_t)(M - 1) * p, to_sums = s.sigma_ring - s.v_ring;
   if (moves) {
     int at_g = head.x, at_l = head.y;
@@ -270,8 +355,8 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)
         if (a0 + u < K) {
-          mv_l[__umul24((unsigned)at_l, (unsigned)lw)] = tv[u];
-          mv_l[ring_f4 + __umul24((unsigned)at_l, (unsigned)lw)] = ts[u];
+          if (mv_has_v) mv_v[__umul24((unsigned)at_l, (unsigned)lw)] = tv[u];
+          if (mv_has_s) mv_s[__umul24((unsigned)at_l, (unsigned)lw)] = ts[u];
           at_l = at_l == 0 ? K - 1 : at_l - 1;
         }
     }
@@ -292,9 +377,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   else wave_sync();
 
   if (mine) {
-    sig = lds_ld(a_cur + sg_off);
+    if (!FEW || dO > 0) sig = lds_ld(a_cur + to_sum);
 #pragma unroll
-    for (int u = 0; u < kDeg; ++u)
+    for (int u = 0; u < kL; ++u)
       if (where[u] & 4) last[u] = lds_ld(c_col[u] + __umul24((unsigned)(where[u] >> 16 & 0xFF), slot_bytes));
   }
 
@@ -302,32 +387,55 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   auto round = [&](int q, const Plan& P, Plan& N) {
     // the plan words of the next round, from global memory, used one round from now
     fetch(min(q + 1, blk.rounds - 1), N);
+    float4 inbox = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (HUB) {
+      const int hub = __builtin_amdgcn_readfirstlane(P.hub);
+      if (hub < 0) {  // the hub is activated: what every sender adds to its sum, formed by the sender's lanes
+        float4 term = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (dI > 0) {
+          float4 sum = lds_ld(c_col[0] + __umul24((unsigned)P.c[0], slot_bytes));
+          if (hub < (int)0xC0000000 && (P.c[0] & 1 << 30) != 0) {
+            sum = ld_group<ANY>(s.sigma_ring + ((size_t)i * M + (P.c[0] >> 24 & 0x3F)) * p + k, left);
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+          }
+          term = mul_s(c_w[0], sub(sum, last[0]));
+          if (hub < (int)0xC0000000 && P.c[0] < 0) {
+            term = sub(mul_s(c_w[0], sum), prod ? last[0] : mul_s(c_w[0], last[0]));
+            prod = 0;
+          }
+          last[0] = sum;
+        }
+        inbox = sum_of_nodes(term, lane, n, i, ln, lw);
+        if (i != blk.hub) inbox = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
     if (P.node < 0) {  // bit 31: node i is activated in this round (never set in the zero word)
-      float4 nb[kDeg], cur[kDeg];
+      float4 nb[kR], cur[kL];
       const unsigned a_new = a_cur + slot_bytes == a_end ? a_own : a_cur + slot_bytes;
       // every ring value of the round in one batch of LDS reads (what a missing edge reads is a valid address; its value
       // is multiplied by zero)
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) nb[u] = lds_ld(r_col[u] + __umul24((unsigned)P.r[u], slot_bytes));
+      for (int u = 0; u < kR; ++u) nb[u] = lds_ld(r_col[u] + __umul24((unsigned)P.r[u], slot_bytes));
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) cur[u] = lds_ld(c_col[u] + __umul24((unsigned)P.c[u], slot_bytes));
+      for (int u = 0; u < kC; ++u) cur[u] = lds_ld(c_col[u] + __umul24((unsigned)P.c[u], slot_bytes));
       const bool rare = P.node < (int)0xC0000000;  // bit 30 clear: one test for whatever is not the usual round
       if (rare) {
         // a version that the chip no longer holds: from the ring in memory, where it has been all along or was put when
         // it lost its place
         const int re0 = s.r_ptr[i];
 #pragma unroll
-        for (int u = 0; u < kDeg; ++u) {
+        for (int u = 0; u < kR; ++u)
           if (P.r[u] & (1 << 30)) nb[u] = ld_group<ANY>(s.v_ring + ((size_t)s.r_src[re0 + u] * M + (P.r[u] >> 24 & 0x3F)) * p + k, left);
+#pragma unroll
+        for (int u = 0; u < kC; ++u)
           if (P.c[u] & (1 << 30)) cur[u] = ld_group<ANY>(s.sigma_ring + ((size_t)s.c_src[ce0 + u] * M + (P.c[u] >> 24 & 0x3F)) * p + k, left);
-        }
         // vmcnt(0), here: with these loads under way on one of two paths, every round waited for the plan words just asked for
         // (20 rounds of 16 nodes, p 11.2 M: 296 -> 263 us per round)
         __builtin_amdgcn_s_waitcnt(0x0F70);
         if (P.node & (1 << 29)) {  // the version whose place this round takes
           float* to = s.v_ring + ((size_t)i * M + (unsigned)(ver_next - K) % (unsigned)M) * p + k;
-          st_group<ANY>(to, left, lds_ld(a_new));
-          if (dO > 0) st_group<ANY>(to + to_sums, left, lds_ld(a_new + sg_off));
+          if (pulled) st_group<ANY>(to, left, lds_ld(a_new));
+          if (dO > 0) st_group<ANY>(to + to_sums, left, lds_ld(a_new + to_sum));
         }
       }
       // S1: local descent; with the optimizer variant along the heavy-ball buffer m <- beta m + z
@@ -337,18 +445,18 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
       float4 x_new = mul_s(r_self, v);
       // (a missing edge has weight zero and reads the node's own ring: it adds zero, without a branch)
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) x_new = fma_s(r_w[u], nb[u], x_new);
+      for (int u = 0; u < kR; ++u) x_new = fma_s(r_w[u], nb[u], x_new);
       const float4 g_new = diag_sample<VEC, MOM>(s, h, c, x_new, i, ver_next, k);
       ++ver_next;
       // S2b: tracker sum over the in-edges of C; S4: keep what was consumed.  An idle edge, whose stamp did not move, reads
       // the sum it holds already and adds zero: no branch.
-      float4 z_half = z;
+      float4 z_half = HUB ? add(z, inbox) : z;
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) z_half = track_edge(z_half, c_w[u], cur[u], last[u], true);
-      if (rare) {  // once more, with what left the sender's ring of M before it was consumed as the product it was kept as
+      for (int u = 0; u < kC; ++u) z_half = track_edge(z_half, c_w[u], cur[u], last[u], true);
+      if (kC > 0 && rare) {  // once more, with what left the sender's ring of M before it was consumed as the product it was kept as
         z_half = z;
 #pragma unroll
-        for (int u = 0; u < kDeg; ++u) {
+        for (int u = 0; u < kC; ++u) {
           if (P.c[u] < 0) {
             z_half = track_edge(z_half, c_w[u], cur[u], prod >> u & 1 ? last[u] : mul_s(c_w[u], last[u]), false);
             prod &= ~(1u << u);
@@ -358,12 +466,12 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
         }
       }
 #pragma unroll
-      for (int u = 0; u < kDeg; ++u) last[u] = cur[u];
+      for (int u = 0; u < kC; ++u) last[u] = cur[u];
       z_half = sub(add(z_half, g_new), g);
       // S3: publish version t+1 (in the place of the oldest one, whose readers of this round are through); S2c: keep a_ii, push
-      lds_st(a_new, v);
+      if (pulled) lds_st(a_new, v);
       sig = add(sig, z_half);
-      if (dO > 0) lds_st(a_new + sg_off, sig);
+      if (dO > 0) lds_st(a_new + to_sum, sig);
       x = x_new;
       z = mul_s(c_self, z_half);
       g = g_new;
@@ -384,7 +492,10 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   auto settle = [](const Plan& P) {
     asm volatile("" ::"v"(P.node));
 #pragma unroll
-    for (int u = 0; u < kDeg; ++u) asm volatile("" ::"v"(P.r[u]), "v"(P.c[u]));
+    for (int u = 0; u < kR; ++u) asm volatile("" ::"v"(P.r[u]));
+#pragma unroll
+    for (int u = 0; u < kL; ++u) asm volatile("" ::"v"(P.c[u]));
+    if (HUB) asm volatile("" ::"v"(P.hub));
   };
   settle(plan_a);
   settle(plan_b);
@@ -399,11 +510,13 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
       if (momentum) st_group<ANY>(s.mom + off, left, m);
     }
 #pragma unroll
-    for (int u = 0; u < kDeg; ++u)
+    for (int u = 0; u < kL; ++u)
       // the buffer lives in the array only if its version is outside the sender's ring now
       if (outside >> u & 1) {
         float4 rt = prod >> u & 1 ? last[u] : mul_s(c_w[u], last[u]);
-        if (blk.rebase) {
+        if (HUB && blk.rebase) {
+          rt = sub(rt, mul_s(c_w[u], sig));
+        } else if (blk.rebase) {
           const int end = s.blk_head[kHeadWords * s.c_src[ce0 + u] + 13];  // of the sender's latest version
           rt = sub(rt, mul_s(c_w[u], lds_ld(c_col[u] + __umul24((unsigned)end, slot_bytes))));
         }
@@ -416,7 +529,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     const unsigned put_v = (unsigned)tail.z, put_s = (unsigned)tail.w;
     float4 base = make_float4(0.f, 0.f, 0.f, 0.f);
     const bool shift = blk.rebase && put_s != 0;  // nobody reads the sums of a node without out-edges
-    if (shift) base = mv_l[ring_f4 + __umul24((unsigned)tail.y, (unsigned)lw)];
+    if (shift) base = mv_s[__umul24((unsigned)tail.y, (unsigned)lw)];
     int at_g = tail.x, at_l = tail.y;
     float* vg = s.v_ring + ((size_t)iT * M + at_g) * p + kT;
     for (int a0 = 0; a0 < K; a0 += kBatch) {
@@ -425,9 +538,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)
         if (a0 + u < K) {
-          if (back_v & (1u << u)) tv[u] = mv_l[__umul24((unsigned)at_l, (unsigned)lw)];
+          if (back_v & (1u << u)) tv[u] = mv_v[__umul24((unsigned)at_l, (unsigned)lw)];
           if (back_s & (1u << u)) {
-            ts[u] = mv_l[ring_f4 + __umul24((unsigned)at_l, (unsigned)lw)];
+            ts[u] = mv_s[__umul24((unsigned)at_l, (unsigned)lw)];
             if (shift) ts[u] = sub(ts[u], base);
           }
           at_l = at_l == 0 ? K - 1 : at_l - 1;
@@ -530,10 +643,10 @@ __global__ void __launch_bounds__(64) rfast_sync_wave_kernel(RfastDev s, float g
 constexpr size_t kCuLds = 160 * 1024, kLdsGrain = 1280;  // LDS of a compute unit, and what it is handed out in
 
 // LDS of one wavefront's tile with `slots` versions per node
-size_t wave_lds_bytes(const RfastDev& d, int slots) { return (size_t)2 * d.n * slots * (64 / d.n) * sizeof(float4); }
+size_t wave_lds_bytes(const rfast_ctx* c, int slots) { return (size_t)(c->v_rows + c->s_rows) * slots * (64 / c->d.n) * sizeof(float4); }
 // Wavefronts of that size that a compute unit holds, `per` to a SIMD at most.
-int wave_resident(const RfastDev& d, int slots, int per) {
-  const size_t one = (wave_lds_bytes(d, slots) + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
+int wave_resident(const rfast_ctx* c, int slots, int per) {
+  const size_t one = (wave_lds_bytes(c, slots) + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
   return (int)std::min<size_t>(kCuLds / one, (size_t)(4 * per));
 }
 
@@ -541,15 +654,19 @@ int wave_resident(const RfastDev& d, int slots, int per) {
 }  // namespace
 
 // The separable objective, at most 64 nodes with at most kWaveMaxDeg edges of a
-// kind each, rings of at most 32 slots (one bit per version in the records of the resolver; the LDS of one
+// kind each or one receiver of all edges of C, rings of at most 32 slots (one bit per version in the records of the resolver; the LDS of one
 // wavefront's tile is 64 KB at most then).
 bool rfast_wave_eligible(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && c->max_degree <= kWaveMaxDeg && d.n <= kWaveMaxNodes && d.M <= 32;
+  return d.prob.kind == RFAST_OBJ_DIAG_QUADRATIC && (c->max_degree <= kWaveMaxDeg || c->hub >= 0) && d.n <= kWaveMaxNodes && d.M <= 32;
 }
 
 int rfast_wave_lanes(const rfast_ctx* c) { return 64 / c->d.n; }
 
+// (Stars and trees with few rings on chip: fewer versions than the longest delay reads where that gives two wavefronts per SIMD, down to two
+// thirds of it.  They have an edge or two per node, so that a read from the ring in memory is rare, and delays count rounds, versions only the
+// sender's active ones.  64 nodes, p 1 M, delays of up to 16, 20 % lost, us per round with 17 / 12 / 10 / 8 versions and 6 / 8 / 10 / 11
+// wavefronts: 124 / 94 / 92 / 110.)
 // Wavefronts per SIMD (the instantiation) and versions of a node on chip.  At least as many versions as the longest delay
 // reads, and one more: with none to spare the reads of versions that have left the chip cost more than the wavefronts bring
 // (16 nodes, p 11.2 M, delays of up to 4, five versions and sixteen wavefronts against six and twelve, us per round of
@@ -560,37 +677,40 @@ struct WaveShape {
 };
 static WaveShape wave_shape(const rfast_ctx* c) {
   const RfastDev& d = c->d;
-  const int least = std::min(d.M - 1, d.d_max + 2);
+  int least = std::min(d.M - 1, d.d_max + 2);
+  if (c->hub >= 0 || c->tree)
+    while (least > d.d_max * 2 / 3 + 2 && wave_resident(c, least, 2) < 8) --least;
   WaveShape w;
-  for (w.per = c->max_degree <= 2 ? 4 : c->max_degree <= 4 ? 3 : 2; w.per > 2 && wave_resident(d, least, w.per) < 4 * w.per;) --w.per;
+  for (w.per = c->max_degree <= 2 ? 4 : c->max_degree <= 4 ? 3 : 2; w.per > 2 && wave_resident(c, least, w.per) < 4 * w.per;) --w.per;
   w.slots = least;
-  while (w.slots < d.M - 1 && wave_resident(d, w.slots + 1, w.per) == wave_resident(d, least, w.per)) ++w.slots;
+  while (w.slots < d.M - 1 && wave_resident(c, w.slots + 1, w.per) == wave_resident(c, least, w.per)) ++w.slots;
   return w;
 }
 int rfast_wave_slots(const rfast_ctx* c) { return wave_shape(c).slots; }
-int rfast_wave_held(const rfast_ctx* c) { return wave_resident(c->d, wave_shape(c).slots, wave_shape(c).per); }
+int rfast_wave_held(const rfast_ctx* c) { return wave_resident(c, wave_shape(c).slots, wave_shape(c).per); }
 
 // Wavefronts per workgroup, as many as LDS holds without losing a resident wavefront.  Short launches, which are
 // mostly tile movement, gain from row segments of whole cache lines; in long ones the barriers of a workgroup weigh as much.
 // Measured with 1 / 2 / 4 wavefronts, us per round: 16 nodes x 11.2 M, 8 rounds 530 / 496 / 486, 20 rounds 260 / 250 /
-// 244, 32 rounds 206 / 202 / 202, 64 and more even; 32 nodes x 1 M, six edge slots, 10 rounds 149 / 138 / 140, 20 rounds 93 / 88 / 87; 8 nodes
+// 244, 32 rounds 206 / 202 / 202, 64 and more even; from 22 nodes on, where the segment of one tile is 16 or 32 bytes, at any length: mesh of 64, p 1 M, 20
+// rounds 6.3 / 5.0 / 4.4 ms, 100 rounds 11.6 / 10.6 / 9.9, 400 rounds 36.4 / 34.4 / 33.0, ring of 64 8.0 / 7.1 / 6.8 of 100, mesh of 32 4.18 / 4.09 / 3.99; 32 nodes x 1 M, six edge slots, 10 rounds 149 / 138 / 140, 20 rounds 93 / 88 / 87; 8 nodes
 // x 3 M, 20 rounds 26.3 / 26.4 / 25.4.
 static int wave_group(const rfast_ctx* c, int rounds, WaveShape shape) {
   const RfastDev& d = c->d;
-  const size_t one = wave_lds_bytes(d, shape.slots);
+  const size_t one = wave_lds_bytes(c, shape.slots);
   if (c->wave_group == 1 || c->wave_group == 2 || c->wave_group == 4) return (size_t)c->wave_group * one <= kCuLds ? c->wave_group : 1;
-  if (rounds > 64) return 1;
-  const size_t most = (size_t)(4 * shape.per), resident = (size_t)wave_resident(d, shape.slots, shape.per);
+  if (rounds > 64 && 64 / d.n > 2) return 1;
+  const size_t most = (size_t)(4 * shape.per), resident = (size_t)wave_resident(c, shape.slots, shape.per);
   int w = 1;
   while (w < 4 && std::min<size_t>(kCuLds / (2 * w * one) * (2 * w), most) >= resident) w *= 2;
   return w;
 }
 
-template <int kDeg, bool MOM, int W, bool ANY, int PER>
+template <class Form, bool MOM, int W, bool ANY, int PER>
 static hipError_t launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   static bool raised = false;
   if (!raised) {  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY, PER>,
+    const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<Form::r, Form::c, Form::few, MOM, W, ANY, PER>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
@@ -601,16 +721,16 @@ static hipError_t launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   const int64_t run = (int64_t)kXcds * (kTileRun / W), per = (int64_t)4 * lw * W;
   const int64_t groups = ((d.p + per - 1) / per + run - 1) / run * run;  // whole runs: a workgroup past the end leaves at once
   if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY, PER>), dim3((unsigned)groups), dim3(64 * W),
-                     (size_t)W * wave_lds_bytes(d, blk.slots), c->stream, c->d, blk, lw, wave_div(lw, W));
+  hipLaunchKernelGGL((rfast_wave_kernel<Form::r, Form::c, Form::few, MOM, W, ANY, PER>), dim3((unsigned)groups), dim3(64 * W),
+                     (size_t)W * wave_lds_bytes(c, blk.slots), c->stream, c->d, blk, lw, wave_div(lw, W));
   return hipGetLastError();
 }
 
 // A launch that does nothing (one workgroup that finds no coordinates and leaves): the first launch of a kernel
 // pays for loading its code, about 0.7 ms, which belongs to setting a context up and not to its first run.
-template <int kDeg, bool MOM, int W, bool ANY, int PER>
+template <class Form, bool MOM, int W, bool ANY, int PER>
 static hipError_t prime_wave(rfast_ctx* c) {
-  const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<kDeg, MOM, W, ANY, PER>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const hipError_t e = hipFuncSetAttribute((const void*)rfast_wave_kernel<Form::r, Form::c, Form::few, MOM, W, ANY, PER>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e != hipSuccess) return e;
   RfastDev none = c->d;
   none.p = 0;
@@ -619,36 +739,48 @@ static hipError_t prime_wave(rfast_ctx* c) {
   blk.rounds = 0;
   blk.rebase = 0;
   blk.slots = 1;
-  hipLaunchKernelGGL((rfast_wave_kernel<kDeg, MOM, W, ANY, PER>), dim3(1), dim3(64 * W), 0, c->stream, none, blk, 64 / c->d.n, wave_div(64 / c->d.n, W));
+  blk.hub = 0;
+  blk.v_rows = blk.s_rows = 0;
+  hipLaunchKernelGGL((rfast_wave_kernel<Form::r, Form::c, Form::few, MOM, W, ANY, PER>), dim3(1), dim3(64 * W), 0, c->stream, none, blk, 64 / c->d.n, wave_div(64 / c->d.n, W));
   return hipGetLastError();
 }
 
 // (the forms of long and of short launches: a third that rfast_set_tile_group may choose cost every context 0.2 ms)
-template <int kDeg, bool MOM, int PER>
+template <class Form, bool MOM, int PER>
 static hipError_t prime_wave_w(rfast_ctx* c, WaveShape shape) {
   const int brief = wave_group(c, 1, shape);
   if (c->d.p % 4 != 0) {
-    const hipError_t e = prime_wave<kDeg, MOM, 1, true, PER>(c);
-    return e == hipSuccess && brief == 4 ? prime_wave<kDeg, MOM, 4, true, PER>(c) : e;
+    const hipError_t e = prime_wave<Form, MOM, 1, true, PER>(c);
+    return e == hipSuccess && brief == 4 ? prime_wave<Form, MOM, 4, true, PER>(c) : e;
   }
-  const hipError_t e = prime_wave<kDeg, MOM, 1, false, PER>(c);
-  if (e == hipSuccess && brief == 2) return prime_wave<kDeg, MOM, 2, false, PER>(c);
-  return e == hipSuccess && brief == 4 ? prime_wave<kDeg, MOM, 4, false, PER>(c) : e;
+  const hipError_t e = prime_wave<Form, MOM, 1, false, PER>(c);
+  if (e == hipSuccess && brief == 2) return prime_wave<Form, MOM, 2, false, PER>(c);
+  return e == hipSuccess && brief == 4 ? prime_wave<Form, MOM, 4, false, PER>(c) : e;
 }
 
-// The instantiation for the edges of this context, its optimizer and a launch of that many rounds: f(degree, optimizer, per SIMD).
+// Edge slots of a node over R and over C (0: the edges of C all lead to one node), and whether only nodes with readers have rings.
+template <int kR, int kC, bool FEW> struct WaveForm {
+  static constexpr int r = kR, c = kC;
+  static constexpr bool few = FEW;
+};
+
+// The instantiation for the edges of this context, its optimizer and a launch of that many rounds: f(form, optimizer, per SIMD).
 template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per, F f) {
   using T = std::true_type;
   using N = std::false_type;
   const int deg = c->max_degree;
+  auto by_per = [&](auto form, auto mom) {
+    if (per == 4) return f(form, mom, std::integral_constant<int, 4>());
+    return per == 3 ? f(form, mom, std::integral_constant<int, 3>()) : f(form, mom, std::integral_constant<int, 2>());
+  };
   auto by_deg = [&](auto mom) {
-    if (deg > 4) return f(std::integral_constant<int, kWaveMaxDeg>(), mom, std::integral_constant<int, 2>());
+    if (c->hub >= 0) return by_per(WaveForm<1, 0, true>(), mom);
+    if (c->tree) return by_per(WaveForm<1, 2, true>(), mom);
+    if (deg > 4) return f(WaveForm<kWaveMaxDeg, kWaveMaxDeg, false>(), mom, std::integral_constant<int, 2>());
     if (deg > 2)
-      return per == 3 ? f(std::integral_constant<int, 4>(), mom, std::integral_constant<int, 3>())
-                      : f(std::integral_constant<int, 4>(), mom, std::integral_constant<int, 2>());
-    if (per == 4) return f(std::integral_constant<int, 2>(), mom, std::integral_constant<int, 4>());
-    return per == 3 ? f(std::integral_constant<int, 2>(), mom, std::integral_constant<int, 3>())
-                    : f(std::integral_constant<int, 2>(), mom, std::integral_constant<int, 2>());
+      return per == 3 ? f(WaveForm<4, 4, false>(), mom, std::integral_constant<int, 3>())
+                      : f(WaveForm<4, 4, false>(), mom, std::integral_constant<int, 2>());
+    return by_per(WaveForm<2, 2, false>(), mom);
   };
   return c->d.mom || c->d.wd != 0.f ? by_deg(T()) : by_deg(N());
 }
@@ -658,20 +790,20 @@ template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per,
 hipError_t rfast_wave_prime(rfast_ctx* c) {
   if (!rfast_wave_eligible(c) || rfast_block_takes(c, kBlockRounds)) return hipSuccess;
   const WaveShape shape = wave_shape(c);
-  return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) { return prime_wave_w<deg.value, mom.value, per.value>(c, shape); });
+  return with_wave_form(c, shape.per, [&](auto form, auto mom, auto per) { return prime_wave_w<decltype(form), mom.value, per.value>(c, shape); });
 }
 
 hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk) {
   const WaveShape shape = wave_shape(c);
   if (shape.slots != blk.slots) return hipErrorInvalidValue;
-  return with_wave_form(c, shape.per, [&](auto deg, auto mom, auto per) {
+  return with_wave_form(c, shape.per, [&](auto form, auto mom, auto per) {
     if (c->d.p % 4 != 0)
-      return c->wave_group == 0 && wave_group(c, blk.rounds, shape) == 4 ? launch_wave<deg.value, mom.value, 4, true, per.value>(c, blk)
-                                                                         : launch_wave<deg.value, mom.value, 1, true, per.value>(c, blk);
+      return c->wave_group == 0 && wave_group(c, blk.rounds, shape) == 4 ? launch_wave<decltype(form), mom.value, 4, true, per.value>(c, blk)
+                                                                         : launch_wave<decltype(form), mom.value, 1, true, per.value>(c, blk);
     switch (wave_group(c, blk.rounds, shape)) {
-      case 4: return launch_wave<deg.value, mom.value, 4, false, per.value>(c, blk);
-      case 2: return launch_wave<deg.value, mom.value, 2, false, per.value>(c, blk);
-      default: return launch_wave<deg.value, mom.value, 1, false, per.value>(c, blk);
+      case 4: return launch_wave<decltype(form), mom.value, 4, false, per.value>(c, blk);
+      case 2: return launch_wave<decltype(form), mom.value, 2, false, per.value>(c, blk);
+      default: return launch_wave<decltype(form), mom.value, 1, false, per.value>(c, blk);
     }
   });
 }

@@ -1,0 +1,80 @@
+"""Several rounds per launch on graphs that only a part of the nodes is read over: all edges of C lead to one node (its sum is
+formed by the senders' lanes), or trees.  Sizes at the edges of the tiling: a lane per node and several, nodes that leave lanes
+over, ragged rows, rings from two slots up, launches across rebases, versions that have left the chip."""
+import numpy as np
+import pytest
+
+from paper_2307_11617_amd import rfast_block_info, rfast_set_rebase_interval, rfast_set_tile_group, rfast_use_blocks
+from rfast_workloads import configs, graphs, problems
+
+import harness
+
+pytestmark = pytest.mark.gpu
+
+
+def _star_at(n, hub):
+    """A directed path as R from node `hub` on, and every other node pushes to it."""
+    r, c = np.zeros((n, n)), np.zeros((n, n))
+    order = [(hub + k) % n for k in range(n)]
+    r[hub, hub] = c[hub, hub] = 1.0
+    for a, b in zip(order, order[1:]):
+        r[b, b], r[b, a] = 0.7, 0.3
+        c[b, b], c[hub, b] = 0.4, 0.6
+    return r, c
+
+
+BUILD = {"tree_star": graphs.tree_pull_star_push, "binary_tree": graphs.binary_tree, "line_tree": graphs.line_tree, "star_at_5": lambda n: _star_at(n, 5),
+         "star_at_last": lambda n: _star_at(n, n - 1)}
+SHAPES = [("tree_star", 64, 1028, 16, 4, 0, 0.0), ("tree_star", 64, 1027, 4, 3, 4, 0.9), ("tree_star", 33, 260, 0, 1, 0, 0.0),
+          ("tree_star", 47, 66, 8, 4, 2, 0.0), ("tree_star", 32, 513, 8, 2, 4, 0.9), ("tree_star", 20, 1028, 3, 8, 0, 0.0),
+          ("tree_star", 9, 4100, 16, 4, 0, 0.0), ("tree_star", 5, 3, 2, 2, 0, 0.0), ("star_at_5", 17, 516, 5, 2, 1, 0.0),
+          ("star_at_5", 50, 129, 3, 3, 0, 0.9), ("star_at_last", 64, 64, 8, 4, 0, 0.0), ("star_at_last", 12, 1, 1, 1, 0, 0.0)]
+
+
+@pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", SHAPES)
+def test_every_push_to_one_node(graph, n, p, d_max, burst, group, momentum, monkeypatch):
+    """Against the oracle: x, z, samples, both rings, buffers, in calls of 2, 3 and 45 rounds; half of the runs with rebases."""
+    r, c = BUILD[graph](n)
+    w = configs._mk("one_receiver", n, p, r, c, d_max, 0.1 / n, 0, "diag_quadratic", problems.diag_quadratic(n, p, 5), 0.7, 0.4, 5, noise_std=0.1,
+                    burst=burst)
+    w.sched.p_active[1::4] = 0.1
+    make = harness.make_gpu
+
+    def launches(w):
+        g = make(w)
+        rfast_use_blocks(g.ctx, 2)
+        rfast_set_rebase_interval(g.ctx, 25 if n % 2 else 0)
+        if group:
+            rfast_set_tile_group(g.ctx, group)
+        if p % 4 == 0:
+            assert rfast_block_info(g.ctx, with_kind=True) == (64 // n, True)
+        return g
+    monkeypatch.setattr(harness, "make_gpu", launches)
+    harness.run_parity(w, 100, every=(2, 3, 45, 50), rebase=n % 2 == 1, momentum=momentum, weight_decay=1e-3 if momentum else 0.0)
+
+
+@pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", [
+    ("binary_tree", 64, 1028, 16, 4, 0, 0.0), ("binary_tree", 63, 1027, 4, 3, 4, 0.9), ("binary_tree", 21, 516, 8, 4, 2, 0.0), ("binary_tree", 7, 130, 3, 2, 0, 0.9),
+    ("line_tree", 40, 260, 8, 4, 0, 0.0), ("line_tree", 6, 2052, 2, 6, 4, 0.0), ("binary_tree", 3, 1, 1, 2, 0, 0.0)])
+def test_trees(graph, n, p, d_max, burst, group, momentum):
+    """The bits of one pass per round."""
+    r, c = BUILD[graph](n)
+    w = configs._mk("trees", n, p, r, c, d_max, 0.01, 0, "diag_quadratic", problems.diag_quadratic(n, p, 5), 0.7, 0.4, 5, noise_std=0.1, burst=burst)
+    w.sched.p_active[1::4] = 0.1
+    pair = [harness.make_gpu(w), harness.make_gpu(w)]
+    x0 = np.random.default_rng(n).standard_normal((n, p)).astype(np.float32)
+    for g, blocks in zip(pair, (2, 0)):
+        rfast_use_blocks(g.ctx, blocks)
+        rfast_set_rebase_interval(g.ctx, 29)
+        if group:
+            rfast_set_tile_group(g.ctx, group)
+        if momentum:
+            g.set_optimizer(momentum, 1e-3)
+        g.init(x0, None)
+    _, dev = harness.upload_chunk(pair[0], w, 0, 90)
+    for lo, hi in ((0, 2), (2, 40), (40, 90)):
+        for g in pair:
+            g.run(hi - lo, *(dev[k][lo:hi] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")), w.gamma)
+            g.check()
+        for f in ("X", "Z", "G", "V_RING", "SIGMA_RING", "RHO_TILDE", "T_NODE", "TAU_R", "TAU_C", "ROUND"):
+            assert np.array_equal(pair[0].read(f), pair[1].read(f)), (hi, f)
