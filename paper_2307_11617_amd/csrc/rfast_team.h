@@ -7,7 +7,8 @@
 namespace {
 
 constexpr int kTeamThreads = 512;
-constexpr int kFlagWords = 16;             // 32-bit words per progress entry (64 bytes): [0] v, [1] sums
+constexpr int kFlagWords = 16;             // 32-bit words per progress entry (64 bytes): the first round of which this is not yet true:
+                                           // [0] v is out, [1] the sums are, [2] others' sums are read, [3] others' v is (softmax: [0] and [3], [1] and [2] in one)
 constexpr size_t kTeamLds = 156 * 1024;
 
 typedef unsigned long long u64;
@@ -173,9 +174,8 @@ __device__ __forceinline__ void wait_progress(const TeamArgs& a, bool sync, int 
   asm volatile("" ::: "memory");
 }
 
-// sampled row b of a round as the caller gave it, clamped into the node's samples and (report) recorded if outside
-__device__ __forceinline__ int team_row(const RfastDev& s, const TeamArgs& a, bool sync, int i, int q, int b, bool report) {
-  int row = a.batch_idx[((size_t)q * s.n + i) * a.B + b];
+// a sampled row of round q as the caller gave it, clamped into the node's samples and (report) recorded if outside
+__device__ __forceinline__ int team_row(const RfastDev& s, const TeamArgs& a, bool sync, int i, int q, int row, bool report) {
   if (row < 0 || row >= s.prob.samples) {
     const TeamKernelArgs& k = team_kernel_args();
     if (report) record_error(k.s.err, RFAST_ERANGE, first_round(k.s, k.a, sync) + q, 2, i);

@@ -9,8 +9,14 @@
 //   rings   v and the running sums are published by stores and read by loads of agent scope (the L2 caches of the
 //           accelerator dies are not coherent with each other; such accesses meet behind them).  The part of a ring
 //           that wavefront y of workgroup (j, w) writes is read by wavefronts y of the workgroups (i, w) only, so the
-//           two progress words of a wavefront, "v of every round before this one is out", "the sums are", are all the
+//           progress words of a wavefront (kFlagWords) are all the
 //           synchronisation there is between nodes: no barrier over the chip, a node waits for the versions it reads.
+//           The longest path through the rounds runs from node to node along these words, each hop 1 to 2 us of travel and
+//           what lies between a wait and the word that it lets its owner set.  So every word is set as soon as what it says
+//           holds (v is out when the dot products are formed, what a round reads of others when it is read), and running
+//           sums that are not out when the dot products are known are waited for behind the gradient.  Us per round with one word per graph,
+//           set behind the dot products and with the sums, and now: 31 nodes in a binary tree, p = 784: 5.6 -> 4.7; full gradients of 5
+//           nodes in a ring, p = 89, 214 rows: 8.4 -> 8.2.
 //   dots    a row's product a_s . x' is the sum of one term per workgroup of the team, exchanged as 8-byte packets of
 //           value and round number: the packet is its own flag, one trip through memory (0.8-1.3 us, measured)
 //           instead of data, acknowledgement, flag, poll and read.
@@ -35,8 +41,8 @@
 // diagnostics and reads see them as rfast_init left them.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
-// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 5.6; 32 nodes, p = 4096,
-// batch 64: 21.2 -> 9.0; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 7.4; one agent of 55 per
+// agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 4.7; 32 nodes, p = 4096,
+// batch 64: 21.2 -> 8.9; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.5; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
 #include <type_traits>
@@ -46,12 +52,31 @@
 namespace {
 
 constexpr int kThreads = kTeamThreads;
+
+// A row of memory in scalar registers, from a pointer of one lane, and a value of it
+typedef const __attribute__((address_space(1))) char* Row;
+__device__ inline Row lane_row(const float* p, int l) {
+  const u64 v = (u64)(uintptr_t)p;
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, l), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), l);
+  return (Row)((u64)hi << 32 | lo);
+}
+__device__ inline float get_row(Row r, unsigned at) {
+  return __hip_atomic_load((const __attribute__((address_space(1))) float*)(r + at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 constexpr int kOwn = 256;                  // lanes that own coordinates
 constexpr int kOwnWaves = kOwn / 64;
 constexpr int kLoad = kThreads - kOwn;     // lanes that fetch rows
 constexpr int kLoadWaves = kLoad / 64;
 constexpr int kTileRows = 64 * kLoadWaves; // most sampled rows of a tile: a fetching wavefront holds their numbers, one per lane
 // packets: [2][n][W][B]; progress entries: [n][W][kOwnWaves]
+
+// A barrier for what is in LDS: accesses to memory may be under way across it.
+__device__ inline void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // value of lane ^ 1, ^ 2 (quad permutes), ^ 4 (half rows reversed, then quads), ^ 8 (rows of 16 rotated by 8)
 template <int CTRL> __device__ inline float dpp(float v) {
@@ -82,7 +107,7 @@ __device__ __forceinline__ void alone(const RfastDev& s, const TeamArgs& a, int*
   auto residuals = [&](int i, int q) {
     const float* x = s.x + (size_t)i * p;
     const float* data = (const float*)s.prob.data0 + (size_t)i * s.prob.samples * p;
-    for (int b = tid; sampled && b < B; b += kTeamThreads) rowi[b] = team_row(s, a, SYNC, i, q, b, true);
+    for (int b = tid; sampled && b < B; b += kTeamThreads) rowi[b] = team_row(s, a, SYNC, i, q, a.batch_idx[((size_t)q * n + i) * B + b], true);
     __syncthreads();  // x and the row numbers
     for (int b = wave; b < B; b += kTeamThreads / 64) {
       const int row = sampled ? rowi[b] : b;
@@ -215,7 +240,22 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   if (SYNC && lane < dI) c_par = s.t[c_src] & 1;
   if (lane < dRo) r_dst = s.r_dst[s.ro_eid[ro0 + lane]];
   if (lane < dCo) c_dst = s.c_dst[s.co_eid[co0 + lane]];
-  auto flag_of = [&](int node, int word) { return a.flags + ((size_t)(node * W + w) * kOwnWaves + wave) * kFlagWords + word; };
+  // What a round touches, formed once: the progress words of the wavefronts of the same number and chunk ([0] .. [2], see
+  // kFlagWords) of the lane's neighbours (nullptr: no such edge), the rings of its senders, and the lane's coordinates as 32-bit
+  // byte offsets, so that a load is an address in scalar registers plus such an offset.  (Formed where they were used they cost up
+  // to 2000 cycles a round in 64-bit products and, with a branch per coordinate, in masks.)
+  auto flag_of = [&](bool there, int node) {
+    return there ? a.flags + ((size_t)(node * W + w) * kOwnWaves + wave) * kFlagWords : nullptr;
+  };
+  unsigned* const f_own = flag_of(true, i);
+  const unsigned* const f_r_src = flag_of(lane < dR, r_src);
+  const unsigned* const f_r_dst = flag_of(lane < dRo, r_dst);
+  const unsigned* const f_c_src = flag_of(lane < dI, c_src);
+  const unsigned* const f_c_dst = flag_of(lane < dCo, c_dst);
+  auto word_of = [](const unsigned* f, int word) { return f ? f + word : nullptr; };
+  const float* const r_ring = s.v_ring + (size_t)r_src * M * p + first;
+  const float* const c_ring = SYNC ? s.g + (size_t)c_src * p + first : s.sigma_ring + (size_t)c_src * M * p + first;
+  const float* const c_save = s.rho_tilde + (size_t)(ce0 + (lane < dI ? lane : 0)) * p + first;
   const bool momentum = s.mom != nullptr;
   const float inv = 1.0f / (float)B;
   const bool logistic = s.prob.kind == RFAST_OBJ_LOGISTIC;
@@ -224,10 +264,12 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const int t0 = SYNC ? s.t[i] : nodew[0] & 0x3FFFFFFF;
   float x[kE], z[kE], g[kE], sc[kE], m[kE];
   bool has[kE];
+  unsigned at[kE];  // byte offset of the coordinate in the chunk (of the first one where the lane has none: a load of it does no harm)
 #pragma unroll
   for (int e = 0; e < kE; ++e) {
     const int k = tid + kOwn * e;
     has[e] = owner && k < Cw;
+    at[e] = has[e] ? 4u * (unsigned)k : 0u;
     x[e] = z[e] = g[e] = sc[e] = m[e] = 0.f;
     if (has[e]) {
       const size_t off = (size_t)i * p + first + k;
@@ -251,9 +293,13 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   };
 
   // ---- rows
-  auto fetch_rows = [&](int q, int* to) {
-    for (int b = tid - kOwn; b < B; b += kLoad) to[b] = team_row(s, a, SYNC, i, q, b, w == 0);
+  // (the lane's first row number as asked for a round ahead)
+  auto ask_row = [&](int q) { return q < a.rounds && tid - kOwn < B ? a.batch_idx[((size_t)q * n + i) * B + (tid - kOwn)] : 0; };
+  auto keep_rows = [&](int q, int first_row, int* to) {
+    for (int b = tid - kOwn; b < B; b += kLoad)
+      to[b] = team_row(s, a, SYNC, i, q, b == tid - kOwn ? first_row : a.batch_idx[((size_t)q * n + i) * B + b], w == 0);
   };
+  int row_ahead = 0;
   // Four coordinates of a row (unaligned where p is no multiple of four).  At the chunk's ragged end the load starts up
   // to three coordinates early, still inside the row, and whole_quad moves them into place and clears the rest.
   const bool ragged = (Cw & 3) != 0;
@@ -306,7 +352,10 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   int parity = 0;  // of the active rounds of this launch: packets and row numbers alternate
   {
     const int qa = next_active(0);
-    if (!owner && sampled && qa < rounds) fetch_rows(qa, rowi);
+    if (!owner && sampled && qa < rounds) {
+      keep_rows(qa, ask_row(qa), rowi);
+      row_ahead = ask_row(next_active(qa + 1));
+    }
     if (sampled) __syncthreads();
     if (TILE && !owner && qa < rounds) load_tile(rowi, tiles);
   }
@@ -339,8 +388,10 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   }
   if (owner) {
     if (!SYNC && lane == 0) {  // rounds before the first event: nothing to wait for
-      put32(flag_of(i, 0), a.base + (unsigned)(q < rounds ? q : rounds));
-      put32(flag_of(i, 1), a.base + (unsigned)(q < rounds ? q : rounds));
+      put32(f_own, a.base + (unsigned)(q < rounds ? q : rounds));
+      put32(f_own + 1, a.base + (unsigned)(q < rounds ? q : rounds));
+      put32(f_own + 2, a.base + (unsigned)(q < rounds ? q : rounds));
+      put32(f_own + 3, a.base + (unsigned)(q < rounds ? q : rounds));
     }
   }
 
@@ -356,8 +407,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     dead = __any(dead);
     if (owner && active) {
       // ---- S1, S2a, S3 (v half)
-      if (!SYNC) wait2(lane < dR ? flag_of(r_src, 0) : nullptr, rneed, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1, seen_r, seen_d);
-      else wait2(lane < dRo ? flag_of(r_dst, 0) : nullptr, q, lane < dCo ? flag_of(c_dst, 0) : nullptr, q, seen_r, seen_d);
+      if (!SYNC) wait2(f_r_src, rneed, word_of(f_r_dst, 3), q_prev + 1, seen_r, seen_d);
+      else wait2(f_r_dst, q, f_c_dst, q, seen_r, seen_d);
       float v[kE], xn[kE];
 #pragma unroll
       for (int e = 0; e < kE; ++e) {
@@ -377,19 +428,18 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
             put_f(own_z + kOwn * e, z[e]);
           }
         drain();
-        if (lane == 0) put32(flag_of(i, 0), a.base + (unsigned)(q + 1));
-        wait2(lane < dR ? flag_of(r_src, 0) : nullptr, q + 1, lane < dI ? flag_of(c_src, 0) : nullptr, q + 1, a.base, a.base);
+        if (lane == 0) put32(f_own, a.base + (unsigned)(q + 1));
+        wait2(f_r_src, q + 1, f_c_src, q + 1, a.base, a.base);
       }
+      const float* const v_from = r_ring + (size_t)(unsigned)(SYNC ? slot_new : rword) * (size_t)p;
       for (int e0 = 0; e0 < dR; e0 += KB) {
         float vb[KB][kE];
 #pragma unroll
         for (int u = 0; u < KB; ++u)
           if (e0 + u < dR) {
-            const int slot = SYNC ? slot_new : lane_value(rword, e0 + u);
-            const float* src = s.v_ring + ((size_t)lane_value(r_src, e0 + u) * M + slot) * p + first + tid;
+            const Row src = lane_row(v_from, e0 + u);
 #pragma unroll
-            for (int e = 0; e < kE; ++e)
-              if (has[e]) vb[u][e] = get_f(src + kOwn * e);
+            for (int e = 0; e < kE; ++e) vb[u][e] = get_row(src, at[e]);
           }
 #pragma unroll
         for (int u = 0; u < KB; ++u)
@@ -414,13 +464,17 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       __syncthreads();  // the mixed x and the sampled rows are in LDS
       unsigned seen_c = a.base, seen_o = a.base;  // the words that the running sums wait for travel during the dot products
       if (owner && !SYNC) {
-        seen_c = peek(a, lane < dI ? flag_of(c_src, 1) : nullptr, cneed);
-        seen_o = peek(a, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+        asm volatile("" ::: "memory");
+        if (lane == 0) put32(f_own + 3, done_word);  // what this round reads of others' v has been used
+        seen_c = peek(a, word_of(f_c_src, 1), cneed);
+        seen_o = peek(a, word_of(f_c_dst, 2), q_prev + 1);
       }
       // ---- gradient, rows: eight (four) rows per wavefront at a time; lane c sums coordinates 4c .. 4c+3 (+ 256 m) of the
       // chunk, and the lanes' sums are added as a butterfly from distance 32 down to 1 whose first steps halve the rows
       const int* rows = rowi + (parity ? B : 0);
       const float target = tid < B ? targets[sampled ? rows[tid] : tid] : 0.f;  // of the lane's first row
+      u64* const packets = a.packets + (size_t)(unsigned)((parity * n + i) * W) * (unsigned)B;  // of the team and the round
+      u64* const out = packets + w * B;
       auto dots = [&](auto rb) {
         constexpr int RB = decltype(rb)::value;
         for (int b0 = wave * RB; b0 < B; b0 += RB * (kThreads / 64)) {
@@ -477,12 +531,15 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
           sum += xor4(sum);
           sum += xor2(sum);
           sum += xor1(sum);
+          if (!SYNC && b0 == wave * RB && owner) {  // v has gone out meanwhile
+            drain();
+            if (lane == 0) put32(f_own, done_word);
+          }
           const int b = b0 + row;
           if ((lane & (64 / RB - 1)) == 0 && b < B) {
             if (W == 1) rs[(b & 3) * Bq + (b >> 2)] = sum;
             else
-              put64(a.packets + (((size_t)parity * n + i) * W + w) * B + b,
-                    (u64)(a.base + (unsigned)q + 1u) << 32 | __float_as_uint(sum));
+              put64(out + b, (u64)(a.base + (unsigned)q + 1u) << 32 | __float_as_uint(sum));
           }
         }
       };
@@ -491,40 +548,33 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       // ---- the owners ask for the ring values of the tracker update; the others look up the rows of the next round
       float sg[KB][kE], rt[KB][kE];
       const int qa = next_active(q + 1);
+      const bool late_sums = !SYNC && __any(lane < dI && (cword & (1 << 18)));
+      // (a batch of in-edges from e0 on; as many loads as there are live edges)
+      const unsigned c_prev = (unsigned)cword >> 8 & 0xFFu;
+      const float* const c_now = c_ring + (size_t)(SYNC ? (unsigned)((c_par + q) & 1) * (unsigned)n : (unsigned)cword & 0xFFu) * (size_t)p;
+      const float* const c_last = c_prev != 0xFFu ? c_ring + (size_t)c_prev * (size_t)p : c_save;
+      auto ask_sums = [&](int e0) {
+#pragma unroll
+        for (int u = 0; u < KB; ++u)
+          if (e0 + u < dI && (SYNC || (lane_value(cword, e0 + u) & (1 << 16)))) {
+            const Row now = lane_row(c_now, e0 + u), last = lane_row(c_last, e0 + u);
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+              sg[u][e] = get_row(now, at[e]);
+              if (!SYNC) rt[u][e] = get_row(last, at[e]);
+            }
+          }
+      };
+      bool early = false;
       if (owner) {
-        if (!SYNC) {
-          wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1, seen_c, seen_o);
-#pragma unroll
-          for (int u = 0; u < KB; ++u)
-            if (u < dI) {
-              const int pl = lane_value(cword, u);
-              if (pl & (1 << 16)) {
-                const float* ring = s.sigma_ring + (size_t)lane_value(c_src, u) * M * p + first + tid;
-                const int prev = (pl >> 8) & 0xFF;
-                const float* saved = s.rho_tilde + (size_t)(ce0 + u) * p + first + tid;
-#pragma unroll
-                for (int e = 0; e < kE; ++e)
-                  if (has[e]) {
-                    sg[u][e] = get_f(ring + (size_t)(pl & 0xFF) * p + kOwn * e);
-                    rt[u][e] = prev != 0xFF ? get_f(ring + (size_t)prev * p + kOwn * e) : saved[kOwn * e];
-                  }
-              }
-            }
-        } else {
-          seen_r = peek(a, lane < dRo ? flag_of(r_dst, 0) : nullptr, q + 1);
-          seen_d = peek(a, lane < dCo ? flag_of(c_dst, 0) : nullptr, q + 1);
-#pragma unroll
-          for (int u = 0; u < KB; ++u)
-            if (u < dI) {
-              const float* src = s.g + ((size_t)((lane_value(c_par, u) + q) & 1) * n + lane_value(c_src, u)) * p + first + tid;
-#pragma unroll
-              for (int e = 0; e < kE; ++e)
-                if (has[e]) sg[u][e] = get_f(src + kOwn * e);
-            }
+        if (SYNC) {
+          seen_r = peek(a, f_r_dst, q + 1);
+          seen_d = peek(a, f_c_dst, q + 1);
+          ask_sums(0);
         }
         fetch_plan(q_next);
       } else if (sampled && qa < rounds) {
-        fetch_rows(qa, rowi + (parity ? 0 : B));
+        keep_rows(qa, row_ahead, rowi + (parity ? 0 : B));
       }
       // ---- residuals: the terms of the team in order
       if (W == 1) __syncthreads();
@@ -534,7 +584,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
           dot = rs[(b & 3) * Bq + (b >> 2)];
         } else {
           dot = 0.f;
-          const u64* src = a.packets + ((size_t)parity * n + i) * W * B + b;
+          const u64* src = packets + b;
           const unsigned tag = a.base + (unsigned)q + 1u;
           for (int w0 = 0; w0 < W; w0 += 8) {
             u64 got[8];
@@ -561,13 +611,17 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         const float y = b == tid ? target : targets[sampled ? rows[b] : b];
         rs[(b & 3) * Bq + (b >> 2)] = logistic ? 1.0f / (1.0f + expf(-dot)) - y : dot - y;
       }
-      // the loads above were issued after the stores of v and have returned: v is out
       if (owner && !SYNC) {
-        drain();
-        if (lane == 0) put32(flag_of(i, 0), done_word);
+        if (wave * (B >= 64 ? 8 : 4) >= B) {  // (a wavefront without rows)
+          drain();
+          if (lane == 0) put32(f_own, done_word);
+        }
+        // The running sums of the in-edges, if the words say that they are out and that the place of this round's own is free.  (Here, where
+        // the words have returned with the packets: waited for before them they cost 1500 cycles more.)
+        early = !__any((lane < dI && cneed > 0 && (int)(seen_c - a.base) < cneed) || (lane < dCo && (int)(seen_o - a.base) <= q_prev));
+        if (early) ask_sums(0);
       }
       __syncthreads();  // residuals, and the row numbers of the next active round
-      if (TILE && !owner && sampled && qa < rounds && a.buffers > 1) load_tile(rowi + (parity ? 0 : B), tile_next);
       // ---- gradient, columns: group rg sums rows rg, rg + 4, ... for four coordinates
       for (int f = tid; f < 4 * Q; f += kThreads) {
         int rg, quad;
@@ -593,67 +647,59 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         for (; b < B; b += 4) row_of_group(b, rq[b >> 2]);
         cp4[f] = acc;
       }
-      __syncthreads();  // column sums; the tile may be overwritten
+      // (loads on their way into LDS would be waited for by a barrier that orders memory, and by reads of LDS behind them: the rows
+      // of the next round are asked for when the column sums are done, their numbers a round ahead of that: 31 nodes, p = 784: 5.6 -> 5.4 us)
+      lds_barrier();  // column sums; the tile may be overwritten
       if (!owner) {
-        if (TILE && sampled && qa < rounds && a.buffers == 1) load_tile(rowi + (parity ? 0 : B), tile_next);
+        if (sampled && qa < rounds) {
+          if (TILE) load_tile(rowi + (parity ? 0 : B), tile_next);
+          row_ahead = ask_row(next_active(qa + 1));
+        }
       } else {
         // ---- S2b, S2c, S3 (rho half), S4; or eq. (2)
         float g_new[kE], z_half[kE];
         const float* cp = reinterpret_cast<const float*>(cp4);
 #pragma unroll
-        for (int e = 0; e < kE; ++e)
-          if (has[e]) {
-            const int k = tid + kOwn * e;
-            const float acc = ((cp[k] + cp[4 * Q + k]) + cp[8 * Q + k]) + cp[12 * Q + k];
-            g_new[e] = fmaf(lam, x[e], acc * inv);
-            z_half[e] = SYNC ? c_self * z[e] : z[e];
-          }
+        for (int e = 0; e < kE; ++e) {
+          const unsigned k = at[e] / 4;
+          const float acc = ((cp[k] + cp[4 * Q + k]) + cp[8 * Q + k]) + cp[12 * Q + k];
+          g_new[e] = fmaf(lam, x[e], acc * inv);
+          z_half[e] = SYNC ? c_self * z[e] : z[e];
+        }
+        // (waited for here where they were not out when the dot products were: nothing before needs them)
+        if (!SYNC && !early) {
+          wait2(word_of(f_c_src, 1), cneed, word_of(f_c_dst, 2), q_prev + 1, a.base, a.base);
+          ask_sums(0);
+        }
         for (int e0 = 0; e0 < dI; e0 += KB) {
-          if (e0 > 0) {  // in-degree above one batch
-#pragma unroll
-            for (int u = 0; u < KB; ++u)
-              if (e0 + u < dI) {
-                const int pl = SYNC ? 0 : lane_value(cword, e0 + u);
-                if (SYNC) {
-                  const float* src = s.g + ((size_t)((lane_value(c_par, e0 + u) + q) & 1) * n + lane_value(c_src, e0 + u)) * p + first + tid;
-#pragma unroll
-                  for (int e = 0; e < kE; ++e)
-                    if (has[e]) sg[u][e] = get_f(src + kOwn * e);
-                } else if (pl & (1 << 16)) {
-                  const float* ring = s.sigma_ring + (size_t)lane_value(c_src, e0 + u) * M * p + first + tid;
-                  const int prev = (pl >> 8) & 0xFF;
-                  const float* saved = s.rho_tilde + (size_t)(ce0 + e0 + u) * p + first + tid;
-#pragma unroll
-                  for (int e = 0; e < kE; ++e)
-                    if (has[e]) {
-                      sg[u][e] = get_f(ring + (size_t)(pl & 0xFF) * p + kOwn * e);
-                      rt[u][e] = prev != 0xFF ? get_f(ring + (size_t)prev * p + kOwn * e) : saved[kOwn * e];
-                    }
-                }
-              }
-          }
+          if (e0 > 0) ask_sums(e0);  // in-degree above one batch
 #pragma unroll
           for (int u = 0; u < KB; ++u)
             if (e0 + u < dI) {
               const float wt = lane_value(c_w, e0 + u);
               if (SYNC) {
 #pragma unroll
-                for (int e = 0; e < kE; ++e)
-                  if (has[e]) z_half[e] = fmaf(wt, sg[u][e], z_half[e]);
+                for (int e = 0; e < kE; ++e) z_half[e] = fmaf(wt, sg[u][e], z_half[e]);
               } else {
                 const int pl = lane_value(cword, e0 + u);
                 if (pl & (1 << 16)) {
                   const bool in_ring = ((pl >> 8) & 0xFF) != 0xFF;
-                  float* saved = s.rho_tilde + (size_t)(ce0 + e0 + u) * p + first + tid;
 #pragma unroll
-                  for (int e = 0; e < kE; ++e)
-                    if (has[e]) {
-                      z_half[e] = track_edge(z_half[e], wt, sg[u][e], rt[u][e], in_ring);
-                      if (pl & (1 << 17)) saved[kOwn * e] = wt * sg[u][e];
-                    }
+                  for (int e = 0; e < kE; ++e) z_half[e] = track_edge(z_half[e], wt, sg[u][e], rt[u][e], in_ring);
+                  if (pl & (1 << 17)) {
+                    float* saved = s.rho_tilde + (size_t)(ce0 + e0 + u) * p + first + tid;
+#pragma unroll
+                    for (int e = 0; e < kE; ++e)
+                      if (has[e]) saved[kOwn * e] = wt * sg[u][e];
+                  }
                 }
               }
             }
+        }
+        // what this round reads of others' sums is read, unless a buffer is still to be saved
+        if (!SYNC && !late_sums) {
+          drain();
+          if (lane == 0) put32(f_own + 2, done_word);
         }
         float* own_s = s.sigma_ring + ((size_t)i * M + slot_new) * p + first + tid;
 #pragma unroll
@@ -682,7 +728,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
     if (owner && !SYNC) {
       // S4 for buffers whose version leaves the sender's ring in this round without being consumed
       u64 leaving = __ballot(lane < dI && (cword & (1 << 18)));
-      if (!active && leaving) wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, nullptr, 0, a.base, a.base);
+      if (!active && leaving) wait2(word_of(f_c_src, 1), cneed, nullptr, 0, a.base, a.base);
       while (leaving) {
         const int u = __ffsll((long long)leaving) - 1;
         leaving &= leaving - 1;
@@ -694,12 +740,14 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
           if (has[e]) saved[kOwn * e] = wt * get_f(ring + kOwn * e);
       }
       // the words that the next mix waits for are read on the trip that the stores take anyway
-      seen_r = peek(a, lane < dR ? flag_of(r_src, 0) : nullptr, q_next - clamped(rd_n));
-      seen_d = peek(a, lane < dRo ? flag_of(r_dst, 0) : nullptr, q_prev + 1);
+      seen_r = peek(a, f_r_src, q_next - clamped(rd_n));
+      seen_d = peek(a, word_of(f_r_dst, 3), q_prev + 1);
       drain();
       if (lane == 0) {
-        if (!active) put32(flag_of(i, 0), done_word);
-        put32(flag_of(i, 1), done_word);
+        if (!active) put32(f_own, done_word);
+        put32(f_own + 1, done_word);
+        put32(f_own + 2, done_word);
+        if (!active) put32(f_own + 3, done_word);
       }
     }
     q = q_next;
@@ -709,7 +757,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const int t_end = SYNC ? t0 + rounds : s.t[i];
   // the half of the samples that the new one goes to held z of the step before the last: its receivers are past that
   // step once they have published the last one
-  if (SYNC && owner && rounds > 1) wait2(nullptr, 0, lane < dCo ? flag_of(c_dst, 0) : nullptr, rounds, a.base, seen_d);
+  if (SYNC && owner && rounds > 1) wait2(nullptr, 0, f_c_dst, rounds, a.base, seen_d);
   if (owner && (SYNC ? rounds > 0 : q_prev >= 0)) {
 #pragma unroll
     for (int e = 0; e < kE; ++e)

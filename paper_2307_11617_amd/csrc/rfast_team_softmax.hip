@@ -58,7 +58,7 @@ __device__ __forceinline__ void alone(const RfastDev& s, const TeamArgs& a, int*
         const u16* pool = (const u16*)s.prob.data0 + (size_t)i * s.prob.samples * d;
         const float* x = s.x + (size_t)i * s.p;
         alone_mix(s, i, (t_old + 1) % s.M, a.gamma, rec + n);
-        for (int b = tid; b < B; b += kTeamThreads) rowi[b] = sampled ? team_row(s, a, false, i, q, b, true) : b;
+        for (int b = tid; b < B; b += kTeamThreads) rowi[b] = sampled ? team_row(s, a, false, i, q, a.batch_idx[((size_t)q * n + i) * B + b], true) : b;
         __syncthreads();  // x and the row numbers
         // logits in the packets' place (as packets of round 0, which nobody waits for)
         for (int f = tid; f < B * K; f += kTeamThreads) {
@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
   auto next_active = [&](int from) { return next_bit(act_mask, from); };
   auto next_event = [&](int from) { return next_bit(ev_mask, from); };
   auto fetch_rows = [&](int q, int* to) {
-    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, false, i, q, b, w == 0);
+    for (int b = kTeamThreads - 1 - tid; b < B; b += kTeamThreads) to[b] = team_row(s, a, false, i, q, a.batch_idx[((size_t)q * n + i) * B + b], w == 0);
   };
   int parity = 0;
   {
