@@ -446,10 +446,12 @@ void leave_team_order(rfast_ctx* c) {
 // share (lazily allocated, given back with the last context; one of its own for small reads, which need not pay for the
 // 16 MB of the other), and, where it is large, several threads move it on:
 // most of their time goes into the page faults of a destination that has never been written.  Measured, a field of
-// 9 KB 30 -> 17 us, 36 MB 3.6 -> 1.4 ms, 128 MB 12.4 -> 4.3 ms.
+// 9 KB 30 -> 17 us, 36 MB 3.6 -> 1.4 ms, 128 MB 12.4 -> 5.0 ms with pieces of 1 MB, one to a thread; 36 MB 0.97 ms, 128 MB 4.6 ms with pieces of up to 4
+// MB that the threads share and the page faults taken before the first arrives (1.78 ms without: several threads then meet in a large page).
 constexpr size_t kStageSlot = (size_t)1 << 20;
 constexpr size_t kStageSmall = (size_t)64 << 10;
-constexpr int kStageThreads = 8, kStageSlots = 2 * kStageThreads;
+constexpr size_t kStageMost = (size_t)4 << 20;
+constexpr int kStageThreads = 8, kStageSlots = 16;
 std::mutex g_stage_mutex;   // whoever holds it owns the buffers; others copy without them
 char* g_stage = nullptr;
 char* g_stage_small = nullptr;
@@ -463,31 +465,75 @@ hipError_t stage_ready(char** stage, size_t bytes) {
   return e;
 }
 
-// Thread t of `threads` copies pieces t, t + threads, ... through its two slots.
-hipError_t copy_pieces(rfast_ctx* c, char* dst, const char* src, size_t bytes, int t, int threads) {
+// A large read: the calling thread has pieces copied into the slots in turn, and all threads move each piece on together, a part
+// each, so that little is left to move when the last one arrives.
+struct Relay {
+  char* dst;
+  const char* src;
+  size_t bytes, piece;
+  int slots, planned, threads = 0;        // threads: those that could be started (set before `arrived` is) of the planned ones
+  std::atomic<size_t> arrived{0};         // pieces that are in their slots (all ones: give up)
+  std::atomic<int> done[kStageSlots] = {};  // threads through with the piece in a slot, counted over all pieces
+  size_t pieces() const { return (bytes + piece - 1) / piece; }
+  size_t size(size_t k) const { return std::min(piece, bytes - k * piece); }
+  // Takes the page faults of a destination that has never been written while the first pieces are on their way: blocks of the size of
+  // a large page in turn, as two threads that meet a new large page both clear one.
+  void touch(int t) {
+    constexpr uintptr_t kBlock = (uintptr_t)2 << 20, kPage = 4096;
+    const uintptr_t from = (uintptr_t)dst, to = from + bytes;
+    for (uintptr_t b = from / kBlock + t; b * kBlock < to; b += planned)
+      for (uintptr_t p = std::max(b * kBlock, from); p < std::min((b + 1) * kBlock, to); p += kPage) *(volatile char*)p = 0;
+  }
+  void part(size_t k, int t) {
+    const size_t len = size(k), each = (len / threads + 4095) / 4096 * 4096, from = std::min(len, each * t);
+    memcpy(dst + k * piece + from, g_stage + (k % slots) * piece + from, t == threads - 1 ? len - from : std::min(each, len - from));
+    done[k % slots].fetch_add(1, std::memory_order_release);
+  }
+};
+constexpr size_t kRelayStop = ~(size_t)0;
+
+void relay_worker(Relay* r, int t) {
+  r->touch(t);
+  for (size_t k = 0;; ++k) {
+    size_t in;
+    for (int spin = 0; (in = r->arrived.load(std::memory_order_acquire)) <= k; ++spin)
+      if (spin > 64) std::this_thread::yield();
+    if (in == kRelayStop || k >= r->pieces() || t >= r->threads) return;
+    r->part(k, t);
+    if (k + 1 == r->pieces()) return;
+  }
+}
+
+hipError_t relay_pieces(rfast_ctx* c, Relay* r) {
   hipError_t e = hipSuccess;
-  hipEvent_t ev[2] = {nullptr, nullptr};
-  for (int q = 0; q < 2 && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
-  const size_t pieces = (bytes + kStageSlot - 1) / kStageSlot;
-  auto size = [&](size_t k) { return std::min(kStageSlot, bytes - k * kStageSlot); };
-  char* slot[2] = {g_stage + (size_t)(2 * t) * kStageSlot, g_stage + (size_t)(2 * t + 1) * kStageSlot};
-  auto issue = [&](size_t k, int q) {
+  hipEvent_t ev[kStageSlots] = {};
+  const size_t pieces = r->pieces();
+  for (int q = 0; q < r->slots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
+  auto issue = [&](size_t k) {
     if (e != hipSuccess || k >= pieces) return;
-    e = hipMemcpyAsync(slot[q], src + k * kStageSlot, size(k), hipMemcpyDeviceToHost, c->stream);
+    const size_t q = k % r->slots;
+    e = hipMemcpyAsync(g_stage + q * r->piece, r->src + k * r->piece, r->size(k), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipEventRecord(ev[q], c->stream);
   };
-  issue((size_t)t, 0);
-  issue((size_t)t + threads, 1);
-  int q = 0;
-  for (size_t k = (size_t)t; k < pieces && e == hipSuccess; k += threads, q ^= 1) {
+  for (size_t k = 0; k < (size_t)r->slots; ++k) issue(k);
+  if (e == hipSuccess) r->touch(0);
+  for (size_t k = 0; k < pieces && e == hipSuccess; ++k) {
+    const size_t q = k % r->slots;
     e = hipEventSynchronize(ev[q]);
     if (e != hipSuccess) break;
-    memcpy(dst + k * kStageSlot, slot[q], size(k));
-    issue(k + 2 * (size_t)threads, q);
+    r->arrived.store(k + 1, std::memory_order_release);
+    r->part(k, 0);
+    const int through = (int)(k / r->slots + 1) * r->threads;
+    for (int spin = 0; r->done[q].load(std::memory_order_acquire) < through; ++spin)
+      if (spin > 64) std::this_thread::yield();
+    issue(k + r->slots);
   }
-  if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);  // nothing is under way into the buffer afterwards
-  for (int r = 0; r < 2; ++r)
-    if (ev[r]) (void)hipEventDestroy(ev[r]);
+  if (e != hipSuccess) {
+    r->arrived.store(kRelayStop, std::memory_order_release);
+    (void)hipStreamSynchronize(c->stream);  // nothing is under way into the buffer afterwards
+  }
+  for (hipEvent_t x : ev)
+    if (x) (void)hipEventDestroy(x);
   return e;
 }
 
@@ -507,27 +553,27 @@ hipError_t to_host(rfast_ctx* c, void* dst, const void* src, size_t bytes) {
     if (e == hipSuccess) memcpy(dst, stage, bytes);
     return e;
   }
-  const size_t pieces = (bytes + kStageSlot - 1) / kStageSlot;
   const int cores = (int)std::thread::hardware_concurrency();
-  // a thread is worth starting for two pieces and more
-  const int threads = (int)std::max<size_t>(1, std::min({(size_t)kStageThreads, pieces / 2, (size_t)std::max(cores, 1)}));
+  Relay r;
+  r.dst = (char*)dst;
+  r.src = (const char*)src;
+  r.bytes = bytes;
+  // a copy into pinned memory costs some 8 us of its own: pieces of 1, 2 and 4 MB reach 37, 45 and 50 GB/s
+  r.piece = std::min<size_t>(kStageMost, std::max(kStageSlot, (bytes / 8 + kStageSlot - 1) / kStageSlot * kStageSlot));
+  r.slots = (int)(kStageSlots * kStageSlot / r.piece);
+  // a thread is worth starting (15 us) for 2 MB and more
+  const int threads = (int)std::max<size_t>(1, std::min({(size_t)kStageThreads, bytes / (2 * kStageSlot), (size_t)std::max(cores, 1)}));
+  r.planned = threads;
   std::vector<std::thread> pool;
-  std::vector<hipError_t> got(threads, hipSuccess);
   int started = 1;
   try {
-    for (; started < threads; ++started)
-      pool.emplace_back([&, t = started] {
-        got[t] = hipSetDevice(c->device);
-        if (got[t] == hipSuccess) got[t] = copy_pieces(c, (char*)dst, (const char*)src, bytes, t, threads);
-      });
-  } catch (...) {  // no more threads to be had: their pieces are done here
+    for (; started < threads; ++started) pool.emplace_back(relay_worker, &r, started);
+  } catch (...) {  // no more threads to be had: those there are do it
   }
-  got[0] = copy_pieces(c, (char*)dst, (const char*)src, bytes, 0, threads);
-  for (int t = started; t < threads; ++t) got[t] = copy_pieces(c, (char*)dst, (const char*)src, bytes, t, threads);
+  r.threads = started;
+  const hipError_t e = relay_pieces(c, &r);
   for (std::thread& t : pool) t.join();
-  for (hipError_t e : got)
-    if (e != hipSuccess) return e;
-  return hipSuccess;
+  return e;
 }
 
 void context_made() { g_contexts++; }
