@@ -471,22 +471,33 @@ struct Relay {
   char* dst;
   const char* src;
   size_t bytes, piece;
-  int slots, planned, threads = 0;        // threads: those that could be started (set before `arrived` is) of the planned ones
+  size_t unit;                            // bytes touched at a time, a part of a piece
+  int slots, threads = 1;
+  std::vector<std::atomic<bool>> touched;    // [units]
   std::atomic<size_t> arrived{0};         // pieces that are in their slots (all ones: give up)
   std::atomic<int> done[kStageSlots] = {};  // threads through with the piece in a slot, counted over all pieces
   size_t pieces() const { return (bytes + piece - 1) / piece; }
   size_t size(size_t k) const { return std::min(piece, bytes - k * piece); }
-  // Takes the page faults of a destination that has never been written while the first pieces are on their way: blocks of the size of
-  // a large page in turn, as two threads that meet a new large page both clear one.
+  // Takes the page faults of a destination that has never been written while the first pieces are on their way: in units of a
+  // large page, as two threads that meet a new large page both clear one.  What it writes is overwritten: a unit is copied into only
+  // when it has been touched.
   void touch(int t) {
-    constexpr uintptr_t kBlock = (uintptr_t)2 << 20, kPage = 4096;
-    const uintptr_t from = (uintptr_t)dst, to = from + bytes;
-    for (uintptr_t b = from / kBlock + t; b * kBlock < to; b += planned)
-      for (uintptr_t p = std::max(b * kBlock, from); p < std::min((b + 1) * kBlock, to); p += kPage) *(volatile char*)p = 0;
+    for (size_t u = t; u * unit < bytes; u += threads) {
+      for (size_t at = u * unit; at < std::min(bytes, (u + 1) * unit); at += 4096) *(volatile char*)(dst + at) = 0;
+      touched[u].store(true, std::memory_order_release);
+    }
   }
   void part(size_t k, int t) {
     const size_t len = size(k), each = (len / threads + 4095) / 4096 * 4096, from = std::min(len, each * t);
-    memcpy(dst + k * piece + from, g_stage + (k % slots) * piece + from, t == threads - 1 ? len - from : std::min(each, len - from));
+    const size_t end = t == threads - 1 ? len : std::min(len, from + each);
+    if (from >= end) {
+      done[k % slots].fetch_add(1, std::memory_order_release);
+      return;
+    }
+    for (size_t u = (k * piece + from) / unit; u * unit < k * piece + end; ++u)
+      for (int spin = 0; !touched[u].load(std::memory_order_acquire); ++spin)
+        if (spin > 64) std::this_thread::yield();
+    memcpy(dst + k * piece + from, g_stage + (k % slots) * piece + from, end - from);
     done[k % slots].fetch_add(1, std::memory_order_release);
   }
 };
@@ -498,7 +509,7 @@ void relay_worker(Relay* r, int t) {
     size_t in;
     for (int spin = 0; (in = r->arrived.load(std::memory_order_acquire)) <= k; ++spin)
       if (spin > 64) std::this_thread::yield();
-    if (in == kRelayStop || k >= r->pieces() || t >= r->threads) return;
+    if (in == kRelayStop) return;
     r->part(k, t);
     if (k + 1 == r->pieces()) return;
   }
@@ -559,18 +570,30 @@ hipError_t to_host(rfast_ctx* c, void* dst, const void* src, size_t bytes) {
   r.src = (const char*)src;
   r.bytes = bytes;
   // a copy into pinned memory costs some 8 us of its own: pieces of 1, 2 and 4 MB reach 37, 45 and 50 GB/s
-  r.piece = std::min<size_t>(kStageMost, std::max(kStageSlot, (bytes / 8 + kStageSlot - 1) / kStageSlot * kStageSlot));
+  r.piece = bytes >= 32 * kStageSlot ? kStageMost : bytes >= 16 * kStageSlot ? kStageMost / 2 : kStageSlot;
+  r.unit = std::min(r.piece, 2 * kStageSlot);
+  try {
+    r.touched = std::vector<std::atomic<bool>>((bytes + r.unit - 1) / r.unit);
+  } catch (...) {
+    return hipErrorOutOfMemory;
+  }
   r.slots = (int)(kStageSlots * kStageSlot / r.piece);
   // a thread is worth starting (15 us) for 2 MB and more
   const int threads = (int)std::max<size_t>(1, std::min({(size_t)kStageThreads, bytes / (2 * kStageSlot), (size_t)std::max(cores, 1)}));
-  r.planned = threads;
   std::vector<std::thread> pool;
+  std::atomic<int> go{0};  // how many there are is known
   int started = 1;
   try {
-    for (; started < threads; ++started) pool.emplace_back(relay_worker, &r, started);
+    for (; started < threads; ++started)
+      pool.emplace_back([&go, &r, t = started] {
+        for (int spin = 0; go.load(std::memory_order_acquire) == 0; ++spin)
+          if (spin > 64) std::this_thread::yield();
+        relay_worker(&r, t);
+      });
   } catch (...) {  // no more threads to be had: those there are do it
   }
   r.threads = started;
+  go.store(1, std::memory_order_release);
   const hipError_t e = relay_pieces(c, &r);
   for (std::thread& t : pool) t.join();
   return e;

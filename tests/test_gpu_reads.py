@@ -27,3 +27,5 @@ def test_read(n, p, offset):
         got = rfast_read_state(g.ctx, "X", out[offset:offset + n * p].reshape(n, p))
         assert np.array_equal(got, x0)
         assert (out[:offset] == -7.0).all() and (out[offset + n * p:] == -7.0).all()
+    for _ in range(20 if n * p < 4_000_000 else 3):   # new memory each time: its page faults are taken beside the copies
+        assert np.array_equal(g.read("X"), x0)
