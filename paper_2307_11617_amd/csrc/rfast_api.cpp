@@ -40,7 +40,7 @@ struct Offsets {
   size_t n_active, active_plan, plan_t, slot_r, slot_c, plan_c, node_spill, plan_set_bytes, blk_plan, blk_spill, blk_far, blk_head, t_next, hist_next, ticket;
   size_t gen_active, gen_delay_r, gen_delay_c, gen_drop_r, gen_drop_c, gen_batch, gen_cdf;
   int32_t gen_depth;
-  size_t xbar, resid, gscratch, diag, team_packets, team_gate, team_flags;  // (flags right behind the gate)
+  size_t xbar, resid, gscratch, diag, team_packets, team_sync, team_gate, team_flags;  // (flags right behind the gate)
   size_t total;
 };
 
@@ -144,6 +144,7 @@ Offsets layout(int32_t n, int64_t p, int32_t nnzR, int32_t nnzC, int32_t D, cons
     o.team_gate = L.take(2 * kGateBytes + rfast_team_flag_bytes(most, n));
   }
   o.team_flags = o.team_gate + 2 * kGateBytes;
+  o.team_sync = L.take(rfast_team_sync_bytes(n, p, prob));
   o.total = L.total;
   return o;
 }
@@ -846,6 +847,7 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   d.xbar = (float*)(b + o.xbar);
   c->team_packets = (void*)(b + o.team_packets); c->team_flags = (unsigned*)(b + o.team_flags);
   c->team_gate = (unsigned*)(b + o.team_gate);
+  c->team_sync = (void*)(b + o.team_sync);
   d.mom = nullptr; d.beta = 0.f; d.wd = 0.f;
   d.resid = (float*)(b + o.resid); d.gscratch = (void*)(b + o.gscratch);
   c->d_diag = (double*)(b + o.diag);
@@ -891,6 +893,7 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
     const bool softmax = prob->kind == RFAST_OBJ_SOFTMAX_BF16;
     chk(hipMemsetAsync(c->team_packets, 0, softmax ? rfast_team_softmax_packet_bytes(c->team, n, prob) : rfast_team_packet_bytes(c->team, n, prob), c->stream));
     chk(hipMemsetAsync(c->team_gate, 0, 2 * kGateBytes + (softmax ? rfast_team_softmax_flag_bytes(c->team, n, prob) : rfast_team_flag_bytes(c->team, n)), c->stream));
+    if (const size_t sync = rfast_team_sync_bytes(n, p, prob)) chk(hipMemsetAsync(c->team_sync, 0, sync, c->stream));
     chk(take_told(c));
   }
   chk(rfast_wave_prime(c));

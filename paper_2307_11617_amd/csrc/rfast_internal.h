@@ -182,6 +182,7 @@ struct rfast_ctx {
   RfastTeam team;
   unsigned team_base = 0;       // rounds handed to the team kernel so far (its progress words and packet tags never repeat)
   void* team_packets = nullptr;
+  void* team_sync = nullptr;
   unsigned* team_flags = nullptr;
   unsigned* team_gate = nullptr;    // two sets of words on which the workgroups of a launch report, used in turn
   unsigned team_turn = 0;           // launches so far
@@ -245,6 +246,7 @@ hipError_t rfast_launch_cols_track_mix(rfast_ctx* c, const int32_t* d_batch_idx,
 RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree_r, int compute_units);
 size_t rfast_team_packet_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob);
 size_t rfast_team_flag_bytes(const RfastTeam& t, int32_t n);
+size_t rfast_team_sync_bytes(int32_t n, int64_t p, const rfast_problem* prob);  // packets of its synchronous steps
 hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, const int32_t* d_batch_idx,
                              const int32_t* d_delay_R, const int32_t* d_delay_C);
 // the same for rounds of softmax regression (RfastTeam::C: tiles of 32 features per workgroup, tiles: copies of a round's rows in LDS)

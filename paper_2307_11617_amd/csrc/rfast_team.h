@@ -38,6 +38,7 @@ struct TeamArgs {
   const int32_t* delay_R;     // [rounds][eR] (not the synchronous steps)
   const int32_t* delay_C;     // [rounds][eC]
   u64* packets;
+  u64* sync;                  // the packets of the synchronous steps
   unsigned* flags;            // [n][owning wavefronts of a node][kFlagWords]
   unsigned* gate;             // kGateWords words: workgroups of this launch that have started (kGone in one of them: the
                               // launch goes on with one workgroup); behind them the word by which one gets to decide that

@@ -35,14 +35,15 @@
 //
 // The arithmetic is, operation for operation, that of rfast_state_kernel<MIX>, rfast_rows_kernel, rfast_cols_kernel and
 // rfast_state_kernel<TRACK> (same bits); rfast_rows_kernel adds a row's terms by the chunks of RfastDev::row_chunk, the
-// chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step; v goes
-// through slots 0 and 1 of the v ring (slot 0 keeps the last one, as with a kernel per step), z through the two halves of
-// the stored samples, which are in registers during the launch.  The rings of the running sums are not touched: the
-// diagnostics and reads see them as rfast_init left them.
+// chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step; v and z
+// go from node to node as packets of value and step, like the dot products, in memory of their own (slot 0 of the v ring keeps the last v, as
+// with a kernel per step): one trip through memory, where values, acknowledgement, word, poll and read were four.  16 nodes, p = 1001, 96
+// rows: 6.5 -> 6.4 us per step.  The rings of the running sums are not touched: the diagnostics and reads see them as
+// rfast_init left them.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
 // agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 4.7; 32 nodes, p = 4096,
-// batch 64: 21.2 -> 8.9; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.5; one agent of 55 per
+// batch 64: 21.2 -> 8.9; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.25; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
 #include <type_traits>
@@ -62,6 +63,9 @@ __device__ inline Row lane_row(const float* p, int l) {
 }
 __device__ inline float get_row(Row r, unsigned at) {
   return __hip_atomic_load((const __attribute__((address_space(1))) float*)(r + at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline u64 get_pair(Row r, unsigned at) {
+  return __hip_atomic_load((const __attribute__((address_space(1))) u64*)(r + at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 constexpr int kOwn = 256;                  // lanes that own coordinates
 constexpr int kOwnWaves = kOwn / 64;
@@ -233,11 +237,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const int ro0 = s.ro_ptr[i], dRo = s.ro_ptr[i + 1] - ro0, co0 = s.co_ptr[i], dCo = s.co_ptr[i + 1] - co0;
   const float r_self = s.r_self[i], c_self = s.c_self[i];
   int r_src = 0, c_src = 0, r_dst = 0, c_dst = 0;
-  int c_par = 0;  // SYNC: of the sender's counter before the launch
   float r_w = 0.f, c_w = 0.f;
   if (lane < dR) { r_src = s.r_src[re0 + lane]; r_w = s.r_w[re0 + lane]; }
   if (lane < dI) { c_src = s.c_src[ce0 + lane]; c_w = s.c_w[ce0 + lane]; }
-  if (SYNC && lane < dI) c_par = s.t[c_src] & 1;
   if (lane < dRo) r_dst = s.r_dst[s.ro_eid[ro0 + lane]];
   if (lane < dCo) c_dst = s.c_dst[s.co_eid[co0 + lane]];
   // What a round touches, formed once: the progress words of the wavefronts of the same number and chunk ([0] .. [2], see
@@ -254,7 +256,12 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const unsigned* const f_c_dst = flag_of(lane < dCo, c_dst);
   auto word_of = [](const unsigned* f, int word) { return f ? f + word : nullptr; };
   const float* const r_ring = s.v_ring + (size_t)r_src * M * p + first;
-  const float* const c_ring = SYNC ? s.g + (size_t)c_src * p + first : s.sigma_ring + (size_t)c_src * M * p + first;
+  const float* const c_ring = s.sigma_ring + (size_t)c_src * M * p + first;
+  // SYNC: [2][n][p] pairs of packets, v and z of a coordinate; the senders' and the node's own in the half of the even steps
+  const size_t sync_half = (size_t)n * p * 2;
+  const u64* const r_pair = a.sync + ((size_t)r_src * p + first) * 2;
+  const u64* const c_pair = a.sync + ((size_t)c_src * p + first) * 2;
+  u64* const own_pair = a.sync + ((size_t)i * p + first) * 2;
   const float* const c_save = s.rho_tilde + (size_t)(ce0 + (lane < dI ? lane : 0)) * p + first;
   const bool momentum = s.mom != nullptr;
   const float inv = 1.0f / (float)B;
@@ -396,14 +403,50 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   }
 
   unsigned seen_r = a.base, seen_d = a.base;  // the words that the next mix waits for, as read ahead
+  // SYNC: asks for the packets of up to KB in-edges from e0 on (which: 0 v, 1 z), an edge's senders in the lanes of `from`; whether
+  // all of them are those of the step; and both until they are
+  u64 step_tag = 0;
+  auto ask_pairs = [&](const u64* from, int which, int e0, int edges, u64 (&got)[KB][kE]) {
+#pragma unroll
+    for (int u = 0; u < KB; ++u)
+      if (e0 + u < edges) {
+        const Row row = lane_row(reinterpret_cast<const float*>(from + which), e0 + u);
+#pragma unroll
+        for (int e = 0; e < kE; ++e) got[u][e] = get_pair(row, 4 * at[e]);
+      }
+  };
+  auto all_there = [&](int e0, int edges, const u64 (&got)[KB][kE]) {
+    bool ok = true;
+#pragma unroll
+    for (int u = 0; u < KB; ++u)
+      if (e0 + u < edges) {
+#pragma unroll
+        for (int e = 0; e < kE; ++e) ok = ok && got[u][e] >> 32 == step_tag >> 32;
+      }
+    return __all(ok);
+  };
+  auto until_there = [&](const u64* from, int which, int e0, int edges, u64 (&got)[KB][kE]) {
+    for (int spin = 0; !dead && !all_there(e0, edges, got); ++spin) {
+      if (spin >= a.wait_polls) {
+        dead = true;
+        report_wait(SYNC, i);
+      }
+      ask_pairs(from, which, e0, edges, got);
+    }
+  };
+  auto poll_pairs = [&](const u64* from, int which, int e0, int edges, u64 (&got)[KB][kE]) {
+    ask_pairs(from, which, e0, edges, got);
+    until_there(from, which, e0, edges, got);
+  };
   while (q < rounds) {
+    step_tag = (u64)(a.base + (unsigned)q + 1u) << 32;
     const int q_next = next_event(q + 1);
     const unsigned done_word = a.base + (unsigned)(q_next < rounds ? q_next : rounds);
     const int word = SYNC ? (int)0x80000000 : nodew[q];
     const bool active = word < 0;
     const int t_old = SYNC ? t0 + q : word & 0x3FFFFFFF;
     const int rword = rw_n, cword = cw_n, rneed = q - clamped(rd_n), cneed = q - clamped(cd_n);
-    const int slot_new = SYNC ? (rounds - 1 - q) & 1 : (t_old + 1) % M;
+    const int slot_new = SYNC ? 0 : (t_old + 1) % M;
     dead = __any(dead);
     if (owner && active) {
       // ---- S1, S2a, S3 (v half)
@@ -418,21 +461,32 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         xn[e] = r_self * v[e];
       }
       float* own_v = s.v_ring + ((size_t)i * M + slot_new) * p + first + tid;
-      if (SYNC) {  // everybody's v and z of this step go out before anybody's are read
-        // step q takes half (t0 + q) mod 2: the last step's is not the one that the new sample goes to
-        float* own_z = s.g + ((size_t)(t_old & 1) * n + i) * p + first + tid;
+      if (SYNC) {
+        // Everybody's v and z of this step, as packets: each is its own flag, so that a step has no other word to wait for than the
+        // one that says that the readers of the packets overwritten here are through (whoever publishes step q has read all of step q - 1).
+        u64* own = own_pair + (q & 1 ? sync_half : 0);
 #pragma unroll
         for (int e = 0; e < kE; ++e)
           if (has[e]) {
-            put_f(own_v + kOwn * e, v[e]);
-            put_f(own_z + kOwn * e, z[e]);
+            put64(own + 2 * (tid + kOwn * e), step_tag | __float_as_uint(v[e]));
+            put64(own + 2 * (tid + kOwn * e) + 1, step_tag | __float_as_uint(z[e]));
+            if (q == rounds - 1) own_v[kOwn * e] = v[e];
           }
-        drain();
         if (lane == 0) put32(f_own, a.base + (unsigned)(q + 1));
-        wait2(f_r_src, q + 1, f_c_src, q + 1, a.base, a.base);
+        for (int e0 = 0; e0 < dR; e0 += KB) {
+          u64 got[KB][kE];
+          poll_pairs(r_pair + (q & 1 ? sync_half : 0), 0, e0, dR, got);
+#pragma unroll
+          for (int u = 0; u < KB; ++u)
+            if (e0 + u < dR) {
+              const float wt = lane_value(r_w, e0 + u);
+#pragma unroll
+              for (int e = 0; e < kE; ++e) xn[e] = fmaf(wt, __uint_as_float((unsigned)got[u][e]), xn[e]);
+            }
+        }
       }
-      const float* const v_from = r_ring + (size_t)(unsigned)(SYNC ? slot_new : rword) * (size_t)p;
-      for (int e0 = 0; e0 < dR; e0 += KB) {
+      const float* const v_from = r_ring + (size_t)(unsigned)rword * (size_t)p;
+      for (int e0 = 0; !SYNC && e0 < dR; e0 += KB) {
         float vb[KB][kE];
 #pragma unroll
         for (int u = 0; u < KB; ++u)
@@ -547,21 +601,22 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       else dots(std::integral_constant<int, 4>());
       // ---- the owners ask for the ring values of the tracker update; the others look up the rows of the next round
       float sg[KB][kE], rt[KB][kE];
+      u64 zp[KB][kE];  // SYNC
       const int qa = next_active(q + 1);
       const bool late_sums = !SYNC && __any(lane < dI && (cword & (1 << 18)));
       // (a batch of in-edges from e0 on; as many loads as there are live edges)
       const unsigned c_prev = (unsigned)cword >> 8 & 0xFFu;
-      const float* const c_now = c_ring + (size_t)(SYNC ? (unsigned)((c_par + q) & 1) * (unsigned)n : (unsigned)cword & 0xFFu) * (size_t)p;
+      const float* const c_now = c_ring + (size_t)((unsigned)cword & 0xFFu) * (size_t)p;
       const float* const c_last = c_prev != 0xFFu ? c_ring + (size_t)c_prev * (size_t)p : c_save;
       auto ask_sums = [&](int e0) {
 #pragma unroll
         for (int u = 0; u < KB; ++u)
-          if (e0 + u < dI && (SYNC || (lane_value(cword, e0 + u) & (1 << 16)))) {
+          if (e0 + u < dI && (lane_value(cword, e0 + u) & (1 << 16))) {
             const Row now = lane_row(c_now, e0 + u), last = lane_row(c_last, e0 + u);
 #pragma unroll
             for (int e = 0; e < kE; ++e) {
               sg[u][e] = get_row(now, at[e]);
-              if (!SYNC) rt[u][e] = get_row(last, at[e]);
+              rt[u][e] = get_row(last, at[e]);
             }
           }
       };
@@ -570,7 +625,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         if (SYNC) {
           seen_r = peek(a, f_r_dst, q + 1);
           seen_d = peek(a, f_c_dst, q + 1);
-          ask_sums(0);
+          ask_pairs(c_pair + (q & 1 ? sync_half : 0), 1, 0, dI, zp);
         }
         fetch_plan(q_next);
       } else if (sampled && qa < rounds) {
@@ -622,8 +677,34 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         if (early) ask_sums(0);
       }
       __syncthreads();  // residuals, and the row numbers of the next active round
-      // ---- gradient, columns: group rg sums rows rg, rg + 4, ... for four coordinates
-      for (int f = tid; f < 4 * Q; f += kThreads) {
+      // ---- gradient, columns: group rg sums rows rg, rg + 4, ... for four coordinates; for two where four would leave half of
+      // the wavefronts without any (a SIMD issues for one wavefront every other time only: 16 nodes, p = 1001, 96 rows, synchronous, 6.4 -> 6.25 us per step)
+      if (TILE && 8 * Q <= kThreads) {
+        if (tid < 8 * Q) {
+          int rg, quad;
+          split(tid >> 1, &rg, &quad);
+          float2 acc = make_float2(0.f, 0.f);
+          const float* rq = rs + rg * Bq;
+          const float2* half = reinterpret_cast<const float2*>(tile + quad) + (tid & 1);
+          auto row_of_group = [&](int b, float r) {
+            const float2 av = half[2 * b * Q];
+            acc.x = fmaf(r, av.x, acc.x);
+            acc.y = fmaf(r, av.y, acc.y);
+          };
+          int b = rg;
+#pragma unroll 2
+          for (; b + 12 < B; b += 16) {
+            const float4 r4 = *reinterpret_cast<const float4*>(rq + (b >> 2));
+            row_of_group(b, r4.x);
+            row_of_group(b + 4, r4.y);
+            row_of_group(b + 8, r4.z);
+            row_of_group(b + 12, r4.w);
+          }
+          for (; b < B; b += 4) row_of_group(b, rq[b >> 2]);
+          reinterpret_cast<float2*>(cp4)[tid] = acc;
+        }
+      }
+      for (int f = TILE && 8 * Q <= kThreads ? 4 * Q : tid; f < 4 * Q; f += kThreads) {
         int rg, quad;
         split(f, &rg, &quad);
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -672,14 +753,20 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
           ask_sums(0);
         }
         for (int e0 = 0; e0 < dI; e0 += KB) {
-          if (e0 > 0) ask_sums(e0);  // in-degree above one batch
+          if (SYNC) {
+            const u64* from = c_pair + (q & 1 ? sync_half : 0);
+            if (e0 > 0) ask_pairs(from, 1, e0, dI, zp);
+            until_there(from, 1, e0, dI, zp);
+          } else if (e0 > 0) {
+            ask_sums(e0);  // in-degree above one batch
+          }
 #pragma unroll
           for (int u = 0; u < KB; ++u)
             if (e0 + u < dI) {
               const float wt = lane_value(c_w, e0 + u);
               if (SYNC) {
 #pragma unroll
-                for (int e = 0; e < kE; ++e) z_half[e] = fmaf(wt, sg[u][e], z_half[e]);
+                for (int e = 0; e < kE; ++e) z_half[e] = fmaf(wt, __uint_as_float((unsigned)zp[u][e]), z_half[e]);
               } else {
                 const int pl = lane_value(cword, e0 + u);
                 if (pl & (1 << 16)) {
@@ -755,9 +842,6 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
 
   // ---- write-back
   const int t_end = SYNC ? t0 + rounds : s.t[i];
-  // the half of the samples that the new one goes to held z of the step before the last: its receivers are past that
-  // step once they have published the last one
-  if (SYNC && owner && rounds > 1) wait2(nullptr, 0, f_c_dst, rounds, a.base, seen_d);
   if (owner && (SYNC ? rounds > 0 : q_prev >= 0)) {
 #pragma unroll
     for (int e = 0; e < kE; ++e)
@@ -847,6 +931,11 @@ RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree
 size_t rfast_team_packet_bytes(const RfastTeam& t, int32_t n, const rfast_problem* prob) {
   return t.W > 0 ? (size_t)2 * n * t.W * rows_per_gradient(prob) * sizeof(u64) : 0;
 }
+// (a team holds kTeamMost chunks of 8 kOwn coordinates at most)
+size_t rfast_team_sync_bytes(int32_t n, int64_t p, const rfast_problem* prob) {
+  const bool any = (prob->kind == RFAST_OBJ_LEAST_SQUARES || prob->kind == RFAST_OBJ_LOGISTIC) && n * p <= (int64_t)kTeamMost * 8 * kOwn;
+  return any ? (size_t)2 * n * p * 2 * sizeof(u64) : 0;
+}
 size_t rfast_team_flag_bytes(const RfastTeam& t, int32_t n) { return (size_t)n * t.W * kOwnWaves * kFlagWords * 4; }
 
 // rounds: at most kBlockRounds with sync = false (their plan records are in c->d.blk_plan)
@@ -866,6 +955,7 @@ hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, c
   a.delay_R = d_delay_R;
   a.delay_C = d_delay_C;
   a.packets = (u64*)c->team_packets;
+  a.sync = (u64*)c->team_sync;
   a.flags = c->team_flags;
   team_begin(c, &a);
   return team_end(c, rounds, sync ? launch_team<true>(c, a) : launch_team<false>(c, a));
