@@ -8,7 +8,7 @@ namespace {
 
 constexpr int kTeamThreads = 512;
 constexpr int kFlagWords = 16;             // 32-bit words per progress entry (64 bytes): the first round of which this is not yet true:
-                                           // [0] v is out, [1] the sums are, [2] others' sums are read, [3] others' v is (softmax: [0] and [3], [1] and [2] in one)
+                                           // [0] v is out, [1] the sums are, [2] others' sums are read, [3] others' v is (softmax: [0] and [3] in one)
 constexpr size_t kTeamLds = 156 * 1024;
 
 typedef unsigned long long u64;

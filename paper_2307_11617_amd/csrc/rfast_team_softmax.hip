@@ -16,7 +16,7 @@
 //
 // The partial logits are rounded to fp32 per chunk where the one-kernel form keeps one accumulator over all features;
 // nothing else differs from rfast_softmax.hip.  Measured, us per round, before (four kernels) and now: 16 nodes, d 512,
-// K 32, batch 64, heavy-ball buffer: 33.6 -> 13.6; one agent of 16 per iteration, d 192: 20.6 -> 5.0.
+// K 32, batch 64, heavy-ball buffer: 33.6 -> 12.9 (13.5 with one word for the sums that are out and those that are read); one agent of 16 per iteration, d 192: 20.6 -> 5.0.
 //
 // With 256 registers per lane the five arrays of a tile (x, z, sample, running sum, heavy-ball buffer: 64 or 80 registers)
 // and the ring values in flight beside them do not all fit: 69 to 120 registers are spilled over the eight instantiations
@@ -247,6 +247,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
     if (lane == 0) {
       put32(flag_of(i, 0), a.base + (unsigned)(q < rounds ? q : rounds));
       put32(flag_of(i, 1), a.base + (unsigned)(q < rounds ? q : rounds));
+      put32(flag_of(i, 2), a.base + (unsigned)(q < rounds ? q : rounds));
     }
   }
   unsigned seen_r = a.base, seen_d = a.base;  // the words that the next mix waits for, as read ahead
@@ -318,7 +319,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
       if (owner) {
         // v is out; the words that the running sums wait for are read on the same trip
         seen_c = peek(a, lane < dI ? flag_of(c_src, 1) : nullptr, cneed);
-        seen_o = peek(a, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1);
+        seen_o = peek(a, lane < dCo ? flag_of(c_dst, 2) : nullptr, q_prev + 1);
         drain();
         if (lane == 0) put32(flag_of(i, 0), done_word);
       }
@@ -349,7 +350,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
       }
       // ---- S2b without the gradient, S4: z + sum over the in-edges of C, two live edges at a time
       if (owner) {
-        wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 1) : nullptr, q_prev + 1, seen_c, seen_o);
+        wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 2) : nullptr, q_prev + 1, seen_c, seen_o);
 #pragma unroll
         for (int v = 0; v < 16; ++v) z_half[v] = z[v];
         u64 live = __ballot(lane < dI && (cword & (1 << 16)));
@@ -388,6 +389,11 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
                 for (int v = 0; v < 16; ++v) put_f(saved + step(v) + at, ce * sg[u][v]);
               }
             }
+        }
+        // what this round reads of others' sums is read, unless a buffer is still to be saved
+        if (!__any(lane < dI && (cword & (1 << 18)))) {
+          drain();
+          if (lane == 0) put32(flag_of(i, 2), done_word);
         }
         fetch_plan(q_next);
       }
@@ -555,6 +561,7 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
       if (lane == 0) {
         if (!active) put32(flag_of(i, 0), done_word);
         put32(flag_of(i, 1), done_word);
+        put32(flag_of(i, 2), done_word);
       }
     }
     q = q_next;
