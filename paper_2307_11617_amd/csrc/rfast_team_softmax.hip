@@ -8,7 +8,8 @@
 //   mix          x' in registers; its bf16 rounding to LDS, class-major (8 consecutive features per operand)
 //   forward      partial logits of all B sampled rows over the chunk's features, 32 x 32 tiles shared out over the
 //                wavefronts; to the workgroup that looks after the row, as packets
-//   sums         while they travel: the running sums of the in-neighbours, z + sum of a (sigma - sigma~)
+//   sums         while they travel, or behind the backward product where they are not out yet: the running sums of the
+//                in-neighbours, z + sum of a (sigma - sigma~)
 //   softmax      workgroup w' adds the partial logits of its B / W rows (in the order of the chunks), forms
 //                E = bf16((softmax - onehot) / B) and sends it to all of the team, two classes per packet
 //   backward     G = X^T E from the rows in LDS (8 rows of one feature gathered per operand), then the tracker update
@@ -16,7 +17,7 @@
 //
 // The partial logits are rounded to fp32 per chunk where the one-kernel form keeps one accumulator over all features;
 // nothing else differs from rfast_softmax.hip.  Measured, us per round, before (four kernels) and now: 16 nodes, d 512,
-// K 32, batch 64, heavy-ball buffer: 33.6 -> 12.9 (13.5 with one word for the sums that are out and those that are read); one agent of 16 per iteration, d 192: 20.6 -> 5.0.
+// K 32, batch 64, heavy-ball buffer: 33.6 -> 12.2 (13.5 with one word for the sums that are out and those that are read, 12.9 with the sums waited for before the softmax); one agent of 16 per iteration, d 192: 20.6 -> 5.0.
 //
 // With 256 registers per lane the five arrays of a tile (x, z, sample, running sum, heavy-ball buffer: 64 or 80 registers)
 // and the ring values in flight beside them do not all fit: 69 to 120 registers are spilled over the eight instantiations
@@ -348,9 +349,9 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           put64(base + ((size_t)dest * W * R + (bb - dest * R)) * K, (u64)tag << 32 | __float_as_uint(acc[v]));
         }
       }
-      // ---- S2b without the gradient, S4: z + sum over the in-edges of C, two live edges at a time
-      if (owner) {
-        wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 2) : nullptr, q_prev + 1, seen_c, seen_o);
+      // ---- S2b without the gradient, S4: z + sum over the in-edges of C, two live edges at a time; where the words say that they are
+      // not out yet, behind the gradient
+      auto sums = [&] {
 #pragma unroll
         for (int v = 0; v < 16; ++v) z_half[v] = z[v];
         u64 live = __ballot(lane < dI && (cword & (1 << 16)));
@@ -395,6 +396,11 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           drain();
           if (lane == 0) put32(flag_of(i, 2), done_word);
         }
+      };
+      bool early = false;
+      if (owner) {
+        early = !__any((lane < dI && cneed > 0 && (int)(seen_c - a.base) < cneed) || (lane < dCo && (int)(seen_o - a.base) <= q_prev));
+        if (early) sums();
         fetch_plan(q_next);
       }
       // ---- softmax of the workgroup's rows: K lanes (two classes per lane above 64) per row
@@ -514,6 +520,10 @@ __global__ void __launch_bounds__(kTeamThreads) rfast_team_softmax_kernel(RfastD
           }
           const bf16x8 bf = *reinterpret_cast<const bf16x8*>(er + b0);
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, col), bf, acc, 0, 0, 0);
+        }
+        if (!early) {
+          wait2(lane < dI ? flag_of(c_src, 1) : nullptr, cneed, lane < dCo ? flag_of(c_dst, 2) : nullptr, q_prev + 1, a.base, a.base);
+          sums();
         }
         // ---- S2b, S2c, S3 (rho half)
         float* own_s = s.sigma_ring + ((size_t)i * M + slot_new) * p + tile0;
