@@ -875,7 +875,10 @@ int rfast_create(rfast_ctx** out, int32_t n, int64_t p, const int32_t* R_rowptr,
   c->v_rows = c->s_rows = n;
   if (v_rows > 0 && s_rows > 0 && max_in_r <= 1) {
     if (one_receiver && max_in_c > 2) c->hub = gc.dst[0];
-    else c->tree = max_in_c <= 2 && c->max_degree <= 2 && v_rows + s_rows < 2 * n;
+    // (rings of nodes without readers left out: only where all of them would leave fewer than eight wavefronts to a compute unit.  What
+    // finding the rings costs a launch, half a microsecond, weighs more elsewhere: binary tree of 12, p 1664, delays of up to 4, calls of four
+    // 0.93, of 40 0.98; of 64, delays of up to 16, p 1 M, 1.8 times as fast.)
+    else if (n <= 64) c->tree = max_in_c <= 2 && c->max_degree <= 2 && v_rows + s_rows < 2 * n && n * (64 / n) * std::min(d.M - 1, d.d_max + 2) > 640;
     if (c->hub >= 0 || c->tree) {
       c->v_rows = v_rows;
       c->s_rows = s_rows;

@@ -230,7 +230,7 @@ hipError_t rfast_launch_rebase(rfast_ctx* c);
 bool rfast_wave_eligible(const rfast_ctx* c);   // the multi-round kernel with one tile per wavefront
 int rfast_wave_lanes(const rfast_ctx* c);       // its lanes per node
 int rfast_wave_slots(const rfast_ctx* c);       // versions of a node it keeps on chip
-int rfast_wave_held(const rfast_ctx* c);        // wavefronts of it that a compute unit holds
+int rfast_wave_held(const rfast_ctx* c);        // wavefronts that a compute unit would hold with every version that the longest delay reads
 hipError_t rfast_launch_wave(rfast_ctx* c, const RfastBlock& blk);
 hipError_t rfast_wave_prime(rfast_ctx* c);      // loads the kernels this context can launch, with launches that do nothing
 bool rfast_block_eligible(const rfast_ctx* c);  // the multi-round kernel with one tile per workgroup (where it is, the other one is too)

@@ -640,15 +640,18 @@ __global__ void __launch_bounds__(64) rfast_sync_wave_kernel(RfastDev s, float g
   st_group<ANY>(s.v_ring + (size_t)i * s.M * p + k, left, v);
 }
 
+constexpr int kUnits = 256;
 constexpr size_t kCuLds = 160 * 1024, kLdsGrain = 1280;  // LDS of a compute unit, and what it is handed out in
 
 // LDS of one wavefront's tile with `slots` versions per node
-size_t wave_lds_bytes(const rfast_ctx* c, int slots) { return (size_t)(c->v_rows + c->s_rows) * slots * (64 / c->d.n) * sizeof(float4); }
+size_t wave_lds_bytes(const rfast_ctx* c, int slots, int rings) { return (size_t)rings * slots * (64 / c->d.n) * sizeof(float4); }
+size_t wave_lds_bytes(const rfast_ctx* c, int slots) { return wave_lds_bytes(c, slots, c->v_rows + c->s_rows); }
 // Wavefronts of that size that a compute unit holds, `per` to a SIMD at most.
-int wave_resident(const rfast_ctx* c, int slots, int per) {
-  const size_t one = (wave_lds_bytes(c, slots) + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
+int wave_resident(const rfast_ctx* c, int slots, int per, int rings) {
+  const size_t one = (wave_lds_bytes(c, slots, rings) + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
   return (int)std::min<size_t>(kCuLds / one, (size_t)(4 * per));
 }
+int wave_resident(const rfast_ctx* c, int slots, int per) { return wave_resident(c, slots, per, c->v_rows + c->s_rows); }
 
 
 }  // namespace
@@ -663,10 +666,14 @@ bool rfast_wave_eligible(const rfast_ctx* c) {
 
 int rfast_wave_lanes(const rfast_ctx* c) { return 64 / c->d.n; }
 
-// (Stars and trees with few rings on chip: fewer versions than the longest delay reads where that gives two wavefronts per SIMD, down to two
-// thirds of it.  They have an edge or two per node, so that a read from the ring in memory is rare, and delays count rounds, versions only the
-// sender's active ones.  64 nodes, p 1 M, delays of up to 16, 20 % lost, us per round with 17 / 12 / 10 / 8 versions and 6 / 8 / 10 / 11
-// wavefronts: 124 / 94 / 92 / 110.)
+// (Stars and graphs with at most two edges of a kind: fewer versions than the longest delay reads where that gives more wavefronts, until there
+// are two per SIMD, down to three quarters of it.  A wavefront has few edges to read over then, so that a read from the ring in memory is
+// rare, and delays count rounds, versions only the sender's active ones.  Star of 64 nodes, p 1 M, delays of up to 16, 20 % lost, us per
+// round with 17 / 12 / 10 / 8 versions and 6 / 8 / 10 / 11 wavefronts: 124 / 94 / 92 / 110.  Delays of up to 16, ms for 132 rounds with 18 / 14 /
+// 12 / 10 versions, half of the nodes active and all: bidirectional ring of 16, p 1 M, 4.64 / 3.78 / 3.27 / 2.80 and 4.68 / 3.83 / 4.56 / 5.07; ring of
+// 32, p 524288, 4.54 / 3.95 / 3.35 / 2.76 and 4.64 / 4.08 / 4.70 / 4.74.  Not where the chip holds every tile as it is: fewer versions only
+// cost then (ring of 32, p 8192, all active: 0.86).  With more edges all nodes active lose what half of them
+// gain: mesh of 64, 5.61 / 5.21 / 4.46 / 4.97 and 5.73 / 8.91 / 8.19 / 11.5.)
 // Wavefronts per SIMD (the instantiation) and versions of a node on chip.  At least as many versions as the longest delay
 // reads, and one more: with none to spare the reads of versions that have left the chip cost more than the wavefronts bring
 // (16 nodes, p 11.2 M, delays of up to 4, five versions and sixteen wavefronts against six and twelve, us per round of
@@ -675,19 +682,26 @@ int rfast_wave_lanes(const rfast_ctx* c) { return 64 / c->d.n; }
 struct WaveShape {
   int per, slots;
 };
+static int wave_most(const rfast_ctx* c) { return c->hub >= 0 || c->max_degree <= 2 ? 4 : c->max_degree <= 4 ? 3 : 2; }
 static WaveShape wave_shape(const rfast_ctx* c) {
   const RfastDev& d = c->d;
   int least = std::min(d.M - 1, d.d_max + 2);
-  if (c->hub >= 0 || c->tree)
-    while (least > d.d_max * 2 / 3 + 2 && wave_resident(c, least, 2) < 8) --least;
+  const int64_t tiles = (d.p + 4 * (64 / d.n) - 1) / (4 * (64 / d.n));
+  if (c->hub >= 0 || c->max_degree <= 2)
+    while (least > (3 * d.d_max + 3) / 4 && wave_resident(c, least, 2) < 8 && tiles > (int64_t)kUnits * wave_resident(c, least, 2)) --least;
   WaveShape w;
-  for (w.per = c->max_degree <= 2 ? 4 : c->max_degree <= 4 ? 3 : 2; w.per > 2 && wave_resident(c, least, w.per) < 4 * w.per;) --w.per;
+  for (w.per = wave_most(c); w.per > 2 && wave_resident(c, least, w.per) < 4 * w.per;) --w.per;
   w.slots = least;
   while (w.slots < d.M - 1 && wave_resident(c, w.slots + 1, w.per) == wave_resident(c, least, w.per)) ++w.slots;
   return w;
 }
 int rfast_wave_slots(const rfast_ctx* c) { return wave_shape(c).slots; }
-int rfast_wave_held(const rfast_ctx* c) { return wave_resident(c, wave_shape(c).slots, wave_shape(c).per); }
+int rfast_wave_held(const rfast_ctx* c) {
+  const int reach = std::min(c->d.M - 1, c->d.d_max + 2), rings = 2 * c->d.n;
+  int per = wave_most(c);
+  while (per > 2 && wave_resident(c, reach, per, rings) < 4 * per) --per;
+  return wave_resident(c, reach, per, rings);
+}
 
 // Wavefronts per workgroup, as many as LDS holds without losing a resident wavefront.  Short launches, which are
 // mostly tile movement, gain from row segments of whole cache lines; in long ones the barriers of a workgroup weigh as much.
@@ -702,7 +716,10 @@ static int wave_group(const rfast_ctx* c, int rounds, WaveShape shape) {
   if (rounds > 64 && 64 / d.n > 2) return 1;
   const size_t most = (size_t)(4 * shape.per), resident = (size_t)wave_resident(c, shape.slots, shape.per);
   int w = 1;
-  while (w < 4 && std::min<size_t>(kCuLds / (2 * w * one) * (2 * w), most) >= resident) w *= 2;
+  // (a resident wavefront fewer is no loss where the chip holds all tiles even so: binary tree of 64, p 4096, delays of up to 16, calls of 8: 26 -> 23 us)
+  const size_t tiles = (size_t)((d.p + 4 * (64 / d.n) - 1) / (4 * (64 / d.n)));
+  auto enough = [&](size_t held) { return held >= resident || (held > 0 && tiles <= (size_t)kUnits * held); };
+  while (w < 4 && enough(std::min<size_t>(kCuLds / (2 * w * one) * (2 * w), most))) w *= 2;
   return w;
 }
 
