@@ -24,7 +24,7 @@
 // five; a SIMD is busy with its vector ALU only from three wavefronts on).
 //
 // The arithmetic is, operation for operation, that of rfast_state_kernel<FUSED> and of
-// rfast_block_kernel: the three paths give the same bits.  (One liberty: where those skip a missing
+// rfast_block_kernel: the three paths give the same bits (but for kC = 0, below).  (One liberty: where those skip a missing
 // or idle edge, this kernel runs it through the multiply-add with weight zero or a difference of zero, which spares the round
 // loop most of its branches.  Adding zero changes nothing but the sign of a sum that is exactly zero,
 // as long as the ring values are finite; an infinity of a node with fewer edges than the kernel has slots can turn to NaN here
@@ -104,8 +104,9 @@ __device__ inline float4 sum_of_nodes(float4 t, int lane, int n, int i, int ln, 
 // would need a slot per sender.  Instead the lanes of every sender, which have its sums in their own column, form its term
 // a (sigma - what was consumed last) and keep what belongs to the edge (S4), and the terms are added up across the wavefront.  That is
 // another order of a sum of up to 63 terms than that of one pass per round (the depth of the tree, not the number of terms, bounds its
-// error), so these launches agree with it to the rounding of that sum and not bit for bit.  Tree and star of 64 nodes, p 1 M, delays of up
-// to 16, 100 rounds: 25.0 ms one pass per round (6.0 TB/s), 11.4 this way, 94 us per round and 2 ms of tile movement.
+// error: against 64 bits, stars of 12 to 64 nodes after 200 to 600 rounds, x 1.4 to 3 times closer, z 1.0 to 1.8), so these launches agree with
+// it to the rounding of that sum and not bit for bit.  Tree and star of 64 nodes, p 1 M, delays of up to 16, 100 rounds: 25.2 ms one pass per
+// round (6.0 TB/s), 10.2 this way, 80 to 94 us per round and 2 ms of tile movement.
 // FEW: only nodes with readers have rings on chip: a tree is read over half of its nodes, the others publish no v.
 // PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 to 128 registers), 3 at four (164 to 168), 2 at six (three
 // would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).  At four edge slots
