@@ -233,7 +233,10 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   static_assert(kThreads == kBlockRounds, "one lane per round above");
 
   // ---- graph of the node, one edge per lane; state of the owned coordinates
-  const int re0 = s.r_ptr[i], dR = s.r_ptr[i + 1] - re0, ce0 = s.c_ptr[i], dI = s.c_ptr[i + 1] - ce0;
+  // (SYNC: a wavefront without coordinates reads nobody's packets)
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const bool wave_has = wave_s < kOwnWaves && 64 * wave_s < Cw, reads = !SYNC || wave_has;
+  const int re0 = s.r_ptr[i], dR = reads ? s.r_ptr[i + 1] - re0 : 0, ce0 = s.c_ptr[i], dI = reads ? s.c_ptr[i + 1] - ce0 : 0;
   const int ro0 = s.ro_ptr[i], dRo = s.ro_ptr[i + 1] - ro0, co0 = s.co_ptr[i], dCo = s.co_ptr[i + 1] - co0;
   const float r_self = s.r_self[i], c_self = s.c_self[i];
   int r_src = 0, c_src = 0, r_dst = 0, c_dst = 0;
@@ -242,7 +245,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   if (lane < dI) { c_src = s.c_src[ce0 + lane]; c_w = s.c_w[ce0 + lane]; }
   if (lane < dRo) r_dst = s.r_dst[s.ro_eid[ro0 + lane]];
   if (lane < dCo) c_dst = s.c_dst[s.co_eid[co0 + lane]];
-  // What a round touches, formed once: the progress words of the wavefronts of the same number and chunk ([0] .. [2], see
+  // What a round touches, formed once: the progress words of the wavefronts of the same number and chunk ([0] .. [3], see
   // kFlagWords) of the lane's neighbours (nullptr: no such edge), the rings of its senders, and the lane's coordinates as 32-bit
   // byte offsets, so that a load is an address in scalar registers plus such an offset.  (Formed where they were used they cost up
   // to 2000 cycles a round in 64-bit products and, with a branch per coordinate, in masks.)
@@ -271,12 +274,17 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const int t0 = SYNC ? s.t[i] : nodew[0] & 0x3FFFFFFF;
   float x[kE], z[kE], g[kE], sc[kE], m[kE];
   bool has[kE];
-  unsigned at[kE];  // byte offset of the coordinate in the chunk (of the first one where the lane has none: a load of it does no harm)
+  // Byte offset of the coordinate in the chunk.  A lane that has none loads the first one of its wavefront, and nobody looks at the value.  SYNC: the
+  // tags of all lanes are looked at, so it must not be another wavefront's: what keeps a sender's wavefront from overwriting a packet
+  // is the word of the wavefront of its number here, which may be a step ahead of the others behind the last barrier of a
+  // step, and the tag that they wait for would never come.  (A test of the tags that leaves such lanes out costs 16 nodes, p = 1001, 96
+  // rows 3 %.)
+  unsigned at[kE];
 #pragma unroll
   for (int e = 0; e < kE; ++e) {
     const int k = tid + kOwn * e;
     has[e] = owner && k < Cw;
-    at[e] = has[e] ? 4u * (unsigned)k : 0u;
+    at[e] = has[e] ? 4u * (unsigned)k : wave_has ? 4u * (unsigned)(tid - lane) : 0u;
     x[e] = z[e] = g[e] = sc[e] = m[e] = 0.f;
     if (has[e]) {
       const size_t off = (size_t)i * p + first + k;
@@ -463,7 +471,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       float* own_v = s.v_ring + ((size_t)i * M + slot_new) * p + first + tid;
       if (SYNC) {
         // Everybody's v and z of this step, as packets: each is its own flag, so that a step has no other word to wait for than the
-        // one that says that the readers of the packets overwritten here are through (whoever publishes step q has read all of step q - 1).
+        // one that says that the readers of the packets overwritten here are through (a wavefront that publishes step q has read all that it
+        // reads of step q - 1, which is what the sender's wavefronts of its number have written).
         u64* own = own_pair + (q & 1 ? sync_half : 0);
 #pragma unroll
         for (int e = 0; e < kE; ++e)

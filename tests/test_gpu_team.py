@@ -103,6 +103,32 @@ def test_synchronous_steps(case):
             assert abs(da[k] - db[k]) <= 1e-9 * (abs(db[k]) + db["gsum_sq"] + db["z_sq"]), (case, hi, k, da[k], db[k])
 
 
+@pytest.mark.parametrize("graph,n,p,samples,batch", [
+    # chunks that leave whole wavefronts, lanes of one and second coordinates of a lane over; eight batches of in-edges at one node,
+    # whose senders read nothing of it and run ahead
+    ("tree_star", 40, 300, 30, 0), ("tree_star", 64, 257, 16, 5), ("tree_star", 60, 5, 24, 0), ("tree_star", 31, 1283, 40, 8),
+    ("directed_ring", 16, 1001, 96, 0), ("binary_tree", 20, 65, 20, 4)])
+def test_synchronous_steps_of_chunks_that_leave_lanes_over(graph, n, p, samples, batch):
+    """A wavefront waits for packets of the same wavefront of its senders only, whichever lanes have a coordinate: long stretches of steps, none of
+    whose waits runs out, give the bits of one chain of kernels per step."""
+    r, c = BUILD[graph](n)
+    w = configs._mk("sync_lanes", n, p, r, c, 3, 0.05 / p, 0, "least_squares", problems.least_squares(n, p, samples, 5), 1.0, 0.0, 5, batch=batch,
+                    samples=samples, burst=3)
+    a, b = harness.make_gpu(w), harness.make_gpu(w)
+    rfast_use_blocks(a.ctx, 2)
+    rfast_use_blocks(b.ctx, False)
+    x0 = (0.1 * np.random.default_rng(3).standard_normal((n, p))).astype(np.float32)
+    for g in (a, b):
+        g.init(x0, w.sched.initial_batch())
+    st, dev = harness.upload_chunk(a, w, 0, 120)
+    for lo, hi in ((0, 100), (100, 102), (102, 120)):
+        for g in (a, b):
+            g.sync_run(hi - lo, w.gamma, None if dev["batch_idx"] is None else dev["batch_idx"][lo:hi].contiguous())
+            g.check()
+        _same(a, b, hi, ("X", "Z", "G", "T_NODE", "ROUND"))
+    assert np.abs(a.read("X") - x0).max() > 1e-5 and np.isfinite(a.read("Z")).all()
+
+
 def test_two_streams():
     """Contexts on two streams whose launches overlap: the workgroups of a team wait for each other, so the library
     orders the launches of different streams."""
