@@ -234,7 +234,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
   float r_self = 0.f, c_self = 0.f;
   // the node's edges, in registers for the whole launch: LDS column of the sender's ring, weight,
   // position of the edge's plan word in a record; a missing edge has weight zero, the node's own
-  // column and the zero word of the record
+  // column and the zero word of the record.  (FEW: in a ring that the node has, as zero times another node's infinity would be NaN wherever
+  // it is in the graph.  A node without in-edges of R is the root of R, which is read; one without a ring of sums is the root of C,
+  // which is that of R and has a ring of v.)
   unsigned r_col[kR], c_col[kL];
   // positions of plan words as unsigned byte offsets: a 32-bit offset from a uniform base, no 64-bit address arithmetic
   unsigned r_pw[kR], c_pw[kL];
@@ -273,8 +275,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
 #pragma unroll
     for (int u = 0; u < kR; ++u) {
       const bool hr = u < dR;
-      // (a missing edge reads the first ring there is)
-      r_col[u] = tile + (unsigned)((hr ? row(has_v, s.r_src[re0 + u]) : FEW ? 0 : i) * K * lw + ln) * sizeof(float4);
+      r_col[u] = tile + (unsigned)(row(has_v, hr ? s.r_src[re0 + u] : i) * K * lw + ln) * sizeof(float4);
       r_w[u] = hr ? s.r_w[re0 + u] : 0.f;
       r_pw[u] = 4u * (hr ? n + re0 + u : W1 - 1);
     }
@@ -286,7 +287,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
 #pragma unroll
     for (int u = 0; u < kC; ++u) {
       const bool hc = u < dI;
-      c_col[u] = tile + sg_off + (unsigned)((hc ? row(has_s, s.c_src[ce0 + u]) : FEW ? 0 : i) * K * lw + ln) * sizeof(float4);
+      c_col[u] = FEW && !hc && dO == 0 ? a_own : tile + sg_off + (unsigned)(row(has_s, hc ? s.c_src[ce0 + u] : i) * K * lw + ln) * sizeof(float4);
       c_w[u] = hc ? s.c_w[ce0 + u] : 0.f;
       c_pw[u] = 4u * (hc ? n + s.eR + ce0 + u : W1 - 1);
     }

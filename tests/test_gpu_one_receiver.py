@@ -80,3 +80,37 @@ def test_trees(graph, n, p, d_max, burst, group, momentum):
             g.check()
         for f in ("X", "Z", "G", "V_RING", "SIGMA_RING", "RHO_TILDE", "T_NODE", "TAU_R", "TAU_C", "ROUND"):
             assert np.array_equal(pair[0].read(f), pair[1].read(f)), (hi, f)
+
+
+@pytest.mark.parametrize("graph,n,d_max", [("binary_tree", 64, 16), ("binary_tree", 21, 16), ("line_tree", 40, 16), ("tree_star", 64, 4), ("star_at_5", 17, 5),
+                                           ("bidirectional_ring", 30, 4)])
+@pytest.mark.parametrize("backwards", [False, True])
+def test_infinities_stay_where_edges_lead(graph, n, d_max, backwards):
+    """The first node that is read over C or over R has diverged, for longer than the chip keeps its versions and with nobody else active.  An
+    infinity takes a round per edge, so two rounds later nobody further away than that has anything but finite values, whatever
+    the launch does with the edges that a node has not got."""
+    r, c = BUILD[graph](n)
+    if backwards:
+        r, c = r[::-1, ::-1].copy(), c[::-1, ::-1].copy()
+    p = 64
+    off = 1 - np.eye(n)
+    for m in (c, r):
+        bad = int(np.flatnonzero((m * off).any(axis=0))[0])
+        w = configs._mk("infinities", n, p, r, c, d_max, 1e-3, 0, "diag_quadratic", problems.diag_quadratic(n, p, 5), 1.0, 0.0, 5, burst=2)
+        g = harness.make_gpu(w)
+        rfast_use_blocks(g.ctx, 2)
+        x0 = np.random.default_rng(n).standard_normal((n, p)).astype(np.float32)
+        x0[bad] = np.inf
+        g.init(x0, None)
+        _, dev = harness.upload_chunk(g, w, 0, 42)
+        dev["active"][:40] = 0
+        dev["active"][:40, bad] = 1
+        for lo, hi in ((0, 40), (40, 42)):
+            g.run(hi - lo, *(dev[k][lo:hi] for k in ("active", "delay_R", "delay_C", "drop_R", "drop_C")), w.gamma)
+            g.check()
+        assert int(g.read("T_NODE")[bad]) == 42 and not np.isfinite(g.read("X")[bad]).any()
+        hop = ((r != 0) | (c != 0)).astype(int)      # [to, from]
+        far = np.linalg.matrix_power(hop, 2)[:, bad] == 0
+        for f in ("X", "Z"):
+            ok = np.isfinite(g.read(f)).all(axis=1)
+            assert ok[far].all(), (bad, f, np.flatnonzero(far & ~ok))
