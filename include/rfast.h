@@ -240,8 +240,8 @@ int rfast_use_graphs(rfast_ctx* ctx, int32_t on);
  * each.  Every step of a round is elementwise in the coordinate, so a tile of coordinates can stay
  * in LDS over several rounds; the results are the same bits as round-by-round execution (finite values: in a run that has
  * diverged to infinity, NaN may come an activation earlier).  Where every edge of C leads to one node (a star; at most one
- * in-edge of R per node) any number of them may: that node's sum is formed across the lanes of its senders, in
- * another order than round by round, so that the results agree to the rounding of a sum and not bit for bit.
+ * in-edge of R per node) any number of them may.  Of more than 7 nodes, that node's sum is then formed across the lanes of
+ * its senders, in another order than round by round, so that the results agree to the rounding of a sum and not bit for bit.
  * Least squares and logistic regression (whose gradient couples the coordinates of a node, so that
  * there are no tiles) take the same stretches of rounds with one launch of a single workgroup when the
  * whole problem fits the LDS of one CU: p a multiple of 4, no heavy-ball buffer, (3 + 2 (D+2)) n p +

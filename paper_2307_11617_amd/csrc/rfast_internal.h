@@ -202,6 +202,7 @@ struct rfast_ctx {
 enum { RFAST_MODE_FUSED = 0, RFAST_MODE_MIX = 1, RFAST_MODE_TRACK = 2 };
 
 constexpr int kHeadWords = 16;  // words per node in RfastDev::blk_head
+constexpr int kStarInOrder = 7;    // most nodes of a star (rfast_ctx::hub) whose sum the wavefront-tile kernel forms in the order of the senders
 constexpr int kBlockRounds = 512;  // rounds that one launch of a multi-round kernel can advance
 constexpr int kFarWords = 1024;    // words per node in RfastDev::blk_far: more than a launch's rounds and a ring's slots together
 constexpr int kGateWords = 8;      // words on which the workgroups of a team launch report, 64 bytes apart ...

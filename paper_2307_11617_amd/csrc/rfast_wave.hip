@@ -105,8 +105,12 @@ __device__ inline float4 sum_of_nodes(float4 t, int lane, int n, int i, int ln, 
 // a (sigma - what was consumed last) and keep what belongs to the edge (S4), and the terms are added up across the wavefront.  That is
 // another order of a sum of up to 63 terms than that of one pass per round (the depth of the tree, not the number of terms, bounds its
 // error: against 64 bits, stars of 12 to 64 nodes after 200 to 600 rounds, x 1.4 to 3 times closer, z 1.0 to 1.8), so these launches agree with
-// it to the rounding of that sum and not bit for bit.  Tree and star of 64 nodes, p 1 M, delays of up to 16, 100 rounds: 25.2 ms one pass per
+// it to the rounding of that sum and not bit for bit.  kC = -1: the same with at most kStarInOrder nodes, whose few terms the lanes of
+// the hub read one after the other, in the order of one pass per round, so that the bits are the same.  (Six edge slots would hold these stars
+// as well, with two wavefronts per SIMD and every ring: star of 7, p 600000, 100 rounds, delays of up to 4 / 16: 762 / 1385 us with slots,
+// 490 / 750 this way, 1700 / 1750 one pass per round.)  Tree and star of 64 nodes, p 1 M, delays of up to 16, 100 rounds: 25.2 ms one pass per
 // round (6.0 TB/s), 10.2 this way, 80 to 94 us per round and 2 ms of tile movement.
+// kC = -1 is there for four wavefronts per SIMD only: it takes no more registers than that leaves with fewer of them.
 // FEW: only nodes with readers have rings on chip: a tree is read over half of its nodes, the others publish no v.
 // PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 to 128 registers), 3 at four (164 to 168), 2 at six (three
 // would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).  At four edge slots
@@ -140,7 +144,7 @@ static WaveDiv wave_div(int lw, int W) {
 template <int kR, int kC, bool FEW, bool MOM, int W, bool ANY, int PER>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER, PER))) rfast_wave_kernel(RfastDev s, RfastBlock blk, int lw, WaveDiv dv) {
   constexpr int VEC = 4;
-  constexpr bool HUB = kC == 0;
+  constexpr bool HUB = kC <= 0, ORDERED = kC < 0;
   extern __shared__ float4 lds4[];
   const int n = s.n, M = s.M, K = blk.slots;
   const int64_t p = s.p;
@@ -193,8 +197,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
     *(LdsVec4*)(uintptr_t)a = t;
   };
   const unsigned sg_off = (unsigned)v_rows * K * slot_bytes;  // from the rings of v to those of sums
-  const unsigned tile_f4 = (unsigned)(v_rows + s_rows) * K * lw;
+  const unsigned tile_f4 = (unsigned)(v_rows + s_rows) * K * lw + (ORDERED ? (unsigned)(n * lw) : 0u);  // ORDERED: a term per lane behind the rings
   const unsigned tile = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds4 + (unsigned)wave * tile_f4 * (unsigned)sizeof(float4);
+  const unsigned terms = tile + (unsigned)(v_rows + s_rows) * K * slot_bytes;
   // Moving the rings: lane T of the workgroup moves column cT (of the lw W columns of a row segment) of
   // node iT, i.e. column lT of the tile of wavefront wT.  With W = 1 that is the lane's own column.
   const int seg = lw * W;
@@ -394,21 +399,37 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
       const int hub = __builtin_amdgcn_readfirstlane(P.hub);
       if (hub < 0) {  // the hub is activated: what every sender adds to its sum, formed by the sender's lanes
         float4 term = make_float4(0.f, 0.f, 0.f, 0.f);
+        float weight = c_w[0];  // ORDERED: that of the term
         if (dI > 0) {
           float4 sum = lds_ld(c_col[0] + __umul24((unsigned)P.c[0], slot_bytes));
           if (hub < (int)0xC0000000 && (P.c[0] & 1 << 30) != 0) {
             sum = ld_group<ANY>(s.sigma_ring + ((size_t)i * M + (P.c[0] >> 24 & 0x3F)) * p + k, left);
             __builtin_amdgcn_s_waitcnt(0x0F70);
           }
-          term = mul_s(c_w[0], sub(sum, last[0]));
+          term = ORDERED ? sub(sum, last[0]) : mul_s(c_w[0], sub(sum, last[0]));
           if (hub < (int)0xC0000000 && P.c[0] < 0) {
             term = sub(mul_s(c_w[0], sum), prod ? last[0] : mul_s(c_w[0], last[0]));
+            weight = 1.f;
             prod = 0;
           }
           last[0] = sum;
         }
-        inbox = sum_of_nodes(term, lane, n, i, ln, lw);
-        if (i != blk.hub) inbox = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ORDERED) {
+          // z + a (sigma - sigma~) + ..., by the lanes of the hub (what the others form is of no use); the terms travel through LDS
+          if (i < n) lds_st(terms + (unsigned)lane * (unsigned)sizeof(float4), term);
+          wave_sync();
+          inbox = z;
+          float4 t[kStarInOrder - 1];
+#pragma unroll
+          for (int u = 0; u < kStarInOrder - 1; ++u)
+            if (u < n - 1) t[u] = lds_ld(terms + (unsigned)((u + (u >= blk.hub ? 1 : 0)) * lw + ln) * (unsigned)sizeof(float4));
+#pragma unroll
+          for (int u = 0; u < kStarInOrder - 1; ++u)
+            if (u < n - 1) inbox = fma_s(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(weight), (u + (u >= blk.hub ? 1 : 0)) * lw)), t[u], inbox);
+        } else {
+          inbox = sum_of_nodes(term, lane, n, i, ln, lw);
+          if (i != blk.hub) inbox = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
       }
     }
     if (P.node < 0) {  // bit 31: node i is activated in this round (never set in the zero word)
@@ -452,7 +473,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PER
       ++ver_next;
       // S2b: tracker sum over the in-edges of C; S4: keep what was consumed.  An idle edge, whose stamp did not move, reads
       // the sum it holds already and adds zero: no branch.
-      float4 z_half = HUB ? add(z, inbox) : z;
+      float4 z_half = ORDERED ? (i == blk.hub ? inbox : z) : HUB ? add(z, inbox) : z;
 #pragma unroll
       for (int u = 0; u < kC; ++u) z_half = track_edge(z_half, c_w[u], cur[u], last[u], true);
       if (kC > 0 && rare) {  // once more, with what left the sender's ring of M before it was consumed as the product it was kept as
@@ -647,7 +668,10 @@ constexpr size_t kCuLds = 160 * 1024, kLdsGrain = 1280;  // LDS of a compute uni
 
 // LDS of one wavefront's tile with `slots` versions per node
 size_t wave_lds_bytes(const rfast_ctx* c, int slots, int rings) { return (size_t)rings * slots * (64 / c->d.n) * sizeof(float4); }
-size_t wave_lds_bytes(const rfast_ctx* c, int slots) { return wave_lds_bytes(c, slots, c->v_rows + c->s_rows); }
+size_t wave_lds_bytes(const rfast_ctx* c, int slots) {
+  const bool in_order = c->hub >= 0 && c->d.n <= kStarInOrder;  // (and a term per lane)
+  return wave_lds_bytes(c, slots, c->v_rows + c->s_rows) + (in_order ? (size_t)c->d.n * (64 / c->d.n) * sizeof(float4) : 0);
+}
 // Wavefronts of that size that a compute unit holds, `per` to a SIMD at most.
 int wave_resident(const rfast_ctx* c, int slots, int per, int rings) {
   const size_t one = (wave_lds_bytes(c, slots, rings) + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
@@ -688,11 +712,12 @@ static int wave_most(const rfast_ctx* c) { return c->hub >= 0 || c->max_degree <
 static WaveShape wave_shape(const rfast_ctx* c) {
   const RfastDev& d = c->d;
   int least = std::min(d.M - 1, d.d_max + 2);
+  const bool in_order = c->hub >= 0 && d.n <= kStarInOrder;  // (has one form, for four wavefronts per SIMD)
   const int64_t tiles = (d.p + 4 * (64 / d.n) - 1) / (4 * (64 / d.n));
   if (c->hub >= 0 || c->max_degree <= 2)
     while (least > (3 * d.d_max + 3) / 4 && wave_resident(c, least, 2) < 8 && tiles > (int64_t)kUnits * wave_resident(c, least, 2)) --least;
   WaveShape w;
-  for (w.per = wave_most(c); w.per > 2 && wave_resident(c, least, w.per) < 4 * w.per;) --w.per;
+  for (w.per = wave_most(c); !in_order && w.per > 2 && wave_resident(c, least, w.per) < 4 * w.per;) --w.per;
   w.slots = least;
   while (w.slots < d.M - 1 && wave_resident(c, w.slots + 1, w.per) == wave_resident(c, least, w.per)) ++w.slots;
   return w;
@@ -777,7 +802,7 @@ static hipError_t prime_wave_w(rfast_ctx* c, WaveShape shape) {
   return e == hipSuccess && brief == 4 ? prime_wave<Form, MOM, 4, false, PER>(c) : e;
 }
 
-// Edge slots of a node over R and over C (0: the edges of C all lead to one node), and whether only nodes with readers have rings.
+// Edge slots of a node over R and over C (0, -1: the edges of C all lead to one node), and whether only nodes with readers have rings.
 template <int kR, int kC, bool FEW> struct WaveForm {
   static constexpr int r = kR, c = kC;
   static constexpr bool few = FEW;
@@ -793,6 +818,7 @@ template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per,
     return per == 3 ? f(form, mom, std::integral_constant<int, 3>()) : f(form, mom, std::integral_constant<int, 2>());
   };
   auto by_deg = [&](auto mom) {
+    if (c->hub >= 0 && c->d.n <= kStarInOrder) return f(WaveForm<1, -1, true>(), mom, std::integral_constant<int, 4>());
     if (c->hub >= 0) return by_per(WaveForm<1, 0, true>(), mom);
     if (c->tree) return by_per(WaveForm<1, 2, true>(), mom);
     if (deg > 4) return f(WaveForm<kWaveMaxDeg, kWaveMaxDeg, false>(), mom, std::integral_constant<int, 2>());

@@ -19,11 +19,12 @@ def _star_at(n, hub):
     r[hub, hub] = c[hub, hub] = 1.0
     for a, b in zip(order, order[1:]):
         r[b, b], r[b, a] = 0.7, 0.3
-        c[b, b], c[hub, b] = 0.4, 0.6
+        c[hub, b] = 0.3 + 0.5 * b / n
+        c[b, b] = 1.0 - c[hub, b]
     return r, c
 
 
-BUILD = {"directed_ring": graphs.directed_ring, "bidirectional_ring": graphs.bidirectional_ring, "tree_star": graphs.tree_pull_star_push, "binary_tree": graphs.binary_tree, "line_tree": graphs.line_tree, "star_at_5": lambda n: _star_at(n, 5),
+BUILD = {"directed_ring": graphs.directed_ring, "bidirectional_ring": graphs.bidirectional_ring, "tree_star": graphs.tree_pull_star_push, "binary_tree": graphs.binary_tree, "line_tree": graphs.line_tree, "star_at_2": lambda n: _star_at(n, 2), "star_at_5": lambda n: _star_at(n, 5),
          "star_at_last": lambda n: _star_at(n, n - 1)}
 SHAPES = [("tree_star", 64, 1028, 16, 4, 0, 0.0), ("tree_star", 64, 1027, 4, 3, 4, 0.9), ("tree_star", 33, 260, 0, 1, 0, 0.0),
           ("tree_star", 47, 66, 8, 4, 2, 0.0), ("tree_star", 32, 513, 8, 2, 4, 0.9), ("tree_star", 20, 1028, 3, 8, 0, 0.0),
@@ -56,9 +57,12 @@ def test_every_push_to_one_node(graph, n, p, d_max, burst, group, momentum, monk
 @pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", [
     ("binary_tree", 64, 1028, 16, 4, 0, 0.0), ("binary_tree", 63, 1027, 4, 3, 4, 0.9), ("binary_tree", 21, 516, 8, 4, 2, 0.0), ("binary_tree", 7, 130, 3, 2, 0, 0.9),
     ("line_tree", 40, 260, 8, 4, 0, 0.0), ("line_tree", 6, 2052, 2, 6, 4, 0.0), ("binary_tree", 3, 1, 1, 2, 0, 0.0),
+    # stars of few senders (of four and five nodes on edge slots while the chip holds every tile)
+    ("tree_star", 4, 1028, 16, 4, 0, 0.0), ("tree_star", 4, 70_000, 16, 4, 0, 0.0), ("star_at_2", 5, 50_003, 16, 2, 0, 0.9), ("star_at_last", 5, 60_000, 16, 4, 2, 0.0), ("tree_star", 7, 2051, 4, 3, 4, 0.9), ("star_at_2", 5, 516, 3, 8, 2, 0.0), ("star_at_5", 6, 1, 1, 1, 0, 0.0),
+    ("star_at_2", 7, 20_000, 8, 4, 1, 0.0), ("star_at_last", 4, 130, 0, 2, 0, 0.9),
     # fewer versions on chip than the longest delay reads
     ("bidirectional_ring", 16, 1028, 16, 4, 0, 0.0), ("directed_ring", 30, 519, 20, 3, 0, 0.9), ("bidirectional_ring", 50, 130, 13, 8, 4, 0.0)])
-def test_trees(graph, n, p, d_max, burst, group, momentum):
+def test_trees_and_small_stars(graph, n, p, d_max, burst, group, momentum):
     """The bits of one pass per round."""
     r, c = BUILD[graph](n)
     w = configs._mk("trees", n, p, r, c, d_max, 0.01, 0, "diag_quadratic", problems.diag_quadratic(n, p, 5), 0.7, 0.4, 5, noise_std=0.1, burst=burst)
