@@ -353,7 +353,8 @@ int rfast_set_gamma_schedule(rfast_ctx* ctx, int32_t step_rounds, float factor);
 int rfast_check(rfast_ctx* ctx);
 
 /* Waits for the stream and copies one field to HOST memory.  `bytes` must be
- * exactly the field's size (RFAST_EINVAL otherwise). */
+ * exactly the field's size (RFAST_EINVAL otherwise).  A copy that fails (RFAST_EHIP) may
+ * have written a part of the field by then, and nothing else. */
 int rfast_read_state(rfast_ctx* ctx, int32_t field, void* host_dst, size_t bytes);
 
 /* Waits for the stream and overwrites one field from HOST memory: the inverse

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "rfast_internal.h"
+#include "rfast_relay.h"
 
 size_t rfast_gemv_scratch_floats(int32_t n, const rfast_problem* prob);
 size_t rfast_softmax_scratch_bytes(int32_t n, const rfast_problem* prob);
@@ -447,12 +448,12 @@ void leave_team_order(rfast_ctx* c) {
 // share (lazily allocated, given back with the last context; one of its own for small reads, which need not pay for the
 // 16 MB of the other), and, where it is large, several threads move it on:
 // most of their time goes into the page faults of a destination that has never been written.  Measured, a field of
-// 9 KB 30 -> 17 us, 36 MB 3.6 -> 1.4 ms, 128 MB 12.4 -> 5.0 ms with pieces of 1 MB, one to a thread; 36 MB 0.97 ms, 128 MB 4.6 ms with pieces of up to 4
+// 9 KB 30 -> 17 us, 36 MB 3.6 -> 1.4 ms, 128 MB 12.4 -> 5.0 ms with pieces of 1 MB, one to a thread; 36 MB 1.05 ms, 128 MB 4.3 ms with pieces of up to 4
 // MB that the threads share and the page faults taken before the first arrives (1.78 ms without: several threads then meet in a large page).
 constexpr size_t kStageSlot = (size_t)1 << 20;
 constexpr size_t kStageSmall = (size_t)64 << 10;
 constexpr size_t kStageMost = (size_t)4 << 20;
-constexpr int kStageThreads = 8, kStageSlots = 16;
+constexpr int kStageThreads = 8;
 std::mutex g_stage_mutex;   // whoever holds it owns the buffers; others copy without them
 char* g_stage = nullptr;
 char* g_stage_small = nullptr;
@@ -466,94 +467,11 @@ hipError_t stage_ready(char** stage, size_t bytes) {
   return e;
 }
 
-// A large read: the calling thread has pieces copied into the slots in turn, and all threads move each piece on together, a part
-// each, so that little is left to move when the last one arrives.
-struct Relay {
-  char* dst;
-  const char* src;
-  size_t bytes, piece;
-  size_t unit;                            // bytes touched at a time, a part of a piece
-  int slots, threads = 1;
-  std::vector<std::atomic<bool>> touched;    // [units]
-  std::atomic<size_t> arrived{0};         // pieces that are in their slots (all ones: give up)
-  std::atomic<int> done[kStageSlots] = {};  // threads through with the piece in a slot, counted over all pieces
-  size_t pieces() const { return (bytes + piece - 1) / piece; }
-  size_t size(size_t k) const { return std::min(piece, bytes - k * piece); }
-  // Takes the page faults of a destination that has never been written while the first pieces are on their way: in units of a
-  // large page, as two threads that meet a new large page both clear one.  What it writes is overwritten: a unit is copied into only
-  // when it has been touched.
-  void touch(int t) {
-    for (size_t u = t; u * unit < bytes; u += threads) {
-      for (size_t at = u * unit; at < std::min(bytes, (u + 1) * unit); at += 4096) *(volatile char*)(dst + at) = 0;
-      touched[u].store(true, std::memory_order_release);
-    }
-  }
-  void part(size_t k, int t) {
-    const size_t len = size(k), each = (len / threads + 4095) / 4096 * 4096, from = std::min(len, each * t);
-    const size_t end = t == threads - 1 ? len : std::min(len, from + each);
-    if (from >= end) {
-      done[k % slots].fetch_add(1, std::memory_order_release);
-      return;
-    }
-    for (size_t u = (k * piece + from) / unit; u * unit < k * piece + end; ++u)
-      for (int spin = 0; !touched[u].load(std::memory_order_acquire); ++spin)
-        if (spin > 64) std::this_thread::yield();
-    memcpy(dst + k * piece + from, g_stage + (k % slots) * piece + from, end - from);
-    done[k % slots].fetch_add(1, std::memory_order_release);
-  }
-};
-constexpr size_t kRelayStop = ~(size_t)0;
-
-void relay_worker(Relay* r, int t) {
-  r->touch(t);
-  for (size_t k = 0;; ++k) {
-    size_t in;
-    for (int spin = 0; (in = r->arrived.load(std::memory_order_acquire)) <= k; ++spin)
-      if (spin > 64) std::this_thread::yield();
-    if (in == kRelayStop) return;
-    r->part(k, t);
-    if (k + 1 == r->pieces()) return;
-  }
-}
-
-hipError_t relay_pieces(rfast_ctx* c, Relay* r) {
-  hipError_t e = hipSuccess;
-  hipEvent_t ev[kStageSlots] = {};
-  const size_t pieces = r->pieces();
-  for (int q = 0; q < r->slots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
-  auto issue = [&](size_t k) {
-    if (e != hipSuccess || k >= pieces) return;
-    const size_t q = k % r->slots;
-    e = hipMemcpyAsync(g_stage + q * r->piece, r->src + k * r->piece, r->size(k), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[q], c->stream);
-  };
-  for (size_t k = 0; k < (size_t)r->slots; ++k) issue(k);
-  if (e == hipSuccess) r->touch(0);
-  for (size_t k = 0; k < pieces && e == hipSuccess; ++k) {
-    const size_t q = k % r->slots;
-    e = hipEventSynchronize(ev[q]);
-    if (e != hipSuccess) break;
-    r->arrived.store(k + 1, std::memory_order_release);
-    r->part(k, 0);
-    const int through = (int)(k / r->slots + 1) * r->threads;
-    for (int spin = 0; r->done[q].load(std::memory_order_acquire) < through; ++spin)
-      if (spin > 64) std::this_thread::yield();
-    issue(k + r->slots);
-  }
-  if (e != hipSuccess) {
-    r->arrived.store(kRelayStop, std::memory_order_release);
-    (void)hipStreamSynchronize(c->stream);  // nothing is under way into the buffer afterwards
-  }
-  for (hipEvent_t x : ev)
-    if (x) (void)hipEventDestroy(x);
-  return e;
-}
-
 // Copies to host memory behind everything on the context's stream and waits for it.
 hipError_t to_host(rfast_ctx* c, void* dst, const void* src, size_t bytes) {
   std::unique_lock<std::mutex> own(g_stage_mutex, std::try_to_lock);
   const bool small = bytes <= kStageSmall;
-  if (!own.owns_lock() || (small ? stage_ready(&g_stage_small, kStageSmall) : stage_ready(&g_stage, kStageSlots * kStageSlot)) != hipSuccess) {
+  if (!own.owns_lock() || (small ? stage_ready(&g_stage_small, kStageSmall) : stage_ready(&g_stage, kRelaySlots * kStageSlot)) != hipSuccess) {
     (void)hipGetLastError();
     const hipError_t e = hipStreamSynchronize(c->stream);
     return e == hipSuccess ? hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) : e;
@@ -568,35 +486,32 @@ hipError_t to_host(rfast_ctx* c, void* dst, const void* src, size_t bytes) {
   const int cores = (int)std::thread::hardware_concurrency();
   Relay r;
   r.dst = (char*)dst;
-  r.src = (const char*)src;
+  r.stage = g_stage;
   r.bytes = bytes;
   // a copy into pinned memory costs some 8 us of its own: pieces of 1, 2 and 4 MB reach 37, 45 and 50 GB/s
   r.piece = bytes >= 32 * kStageSlot ? kStageMost : bytes >= 16 * kStageSlot ? kStageMost / 2 : kStageSlot;
   r.unit = std::min(r.piece, 2 * kStageSlot);
-  try {
-    r.touched = std::vector<std::atomic<bool>>((bytes + r.unit - 1) / r.unit);
-  } catch (...) {
-    return hipErrorOutOfMemory;
-  }
-  r.slots = (int)(kStageSlots * kStageSlot / r.piece);
+  r.slots = (int)(kRelaySlots * kStageSlot / r.piece);
   // a thread is worth starting (15 us) for 2 MB and more
   const int threads = (int)std::max<size_t>(1, std::min({(size_t)kStageThreads, bytes / (2 * kStageSlot), (size_t)std::max(cores, 1)}));
-  std::vector<std::thread> pool;
-  std::atomic<int> go{0};  // how many there are is known
-  int started = 1;
+  hipError_t e = hipSuccess;
+  hipEvent_t ev[kRelaySlots] = {};
+  for (int q = 0; q < r.slots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
   try {
-    for (; started < threads; ++started)
-      pool.emplace_back([&go, &r, t = started] {
-        for (int spin = 0; go.load(std::memory_order_acquire) == 0; ++spin)
-          if (spin > 64) std::this_thread::yield();
-        relay_worker(&r, t);
-      });
-  } catch (...) {  // no more threads to be had: those there are do it
+    if (e == hipSuccess)
+      relay(&r, threads,
+            [&](size_t k, int q) {
+              e = hipMemcpyAsync(g_stage + (size_t)q * r.piece, (const char*)src + k * r.piece, r.size(k), hipMemcpyDeviceToHost, c->stream);
+              if (e == hipSuccess) e = hipEventRecord(ev[q], c->stream);
+              return e == hipSuccess;
+            },
+            [&](int q) { return (e = hipEventSynchronize(ev[q])) == hipSuccess; });
+  } catch (...) {
+    e = hipErrorOutOfMemory;
   }
-  r.threads = started;
-  go.store(1, std::memory_order_release);
-  const hipError_t e = relay_pieces(c, &r);
-  for (std::thread& t : pool) t.join();
+  if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);  // nothing is under way into the buffer afterwards
+  for (hipEvent_t x : ev)
+    if (x) (void)hipEventDestroy(x);
   return e;
 }
 
