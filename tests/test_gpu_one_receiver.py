@@ -1,10 +1,12 @@
 """Several rounds per launch on graphs that only a part of the nodes is read over: all edges of C lead to one node (its sum is
 formed by the senders' lanes), or trees.  Sizes at the edges of the tiling: a lane per node and several, nodes that leave lanes
 over, ragged rows, rings from two slots up, launches across rebases, versions that have left the chip."""
+import ctypes
+
 import numpy as np
 import pytest
 
-from paper_2307_11617_amd import rfast_block_info, rfast_set_rebase_interval, rfast_set_tile_group, rfast_use_blocks
+from paper_2307_11617_amd import lib, rfast_block_info, rfast_set_rebase_interval, rfast_set_tile_group, rfast_use_blocks
 from rfast_workloads import configs, graphs, problems
 
 import harness
@@ -30,9 +32,10 @@ SHAPES = [("tree_star", 64, 1028, 16, 4, 0, 0.0), ("tree_star", 64, 1027, 4, 3, 
           ("tree_star", 47, 66, 8, 4, 2, 0.0), ("tree_star", 32, 513, 8, 2, 4, 0.9), ("tree_star", 20, 1028, 3, 8, 0, 0.0),
           ("tree_star", 9, 4100, 16, 4, 0, 0.0), ("tree_star", 5, 3, 2, 2, 0, 0.0), ("star_at_5", 17, 516, 5, 2, 1, 0.0),
           ("star_at_5", 50, 129, 3, 3, 0, 0.9), ("star_at_last", 64, 64, 8, 4, 0, 0.0), ("star_at_last", 12, 1, 1, 1, 0, 0.0)]
+FEWER = [("tree_star", 64, 8_196, 16, 4, 0, 0.0), ("star_at_5", 20, 20_002, 16, 2, 0, 0.9)]   # fewer versions on chip than the longest delay reads
 
 
-@pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", SHAPES)
+@pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", SHAPES + FEWER)
 def test_every_push_to_one_node(graph, n, p, d_max, burst, group, momentum, monkeypatch):
     """Against the oracle: x, z, samples, both rings, buffers, in calls of 2, 3 and 45 rounds; half of the runs with rebases."""
     r, c = BUILD[graph](n)
@@ -49,6 +52,7 @@ def test_every_push_to_one_node(graph, n, p, d_max, burst, group, momentum, monk
             rfast_set_tile_group(g.ctx, group)
         if p % 4 == 0:
             assert rfast_block_info(g.ctx, with_kind=True) == (64 // n, True)
+        assert (_versions_on_chip(g) < d_max + min(burst, 2)) == ((graph, n, p, d_max, burst, group, momentum) in FEWER)
         return g
     monkeypatch.setattr(harness, "make_gpu", launches)
     harness.run_parity(w, 100, every=(2, 3, 45, 50), rebase=n % 2 == 1, momentum=momentum, weight_decay=1e-3 if momentum else 0.0)
@@ -57,13 +61,39 @@ def test_every_push_to_one_node(graph, n, p, d_max, burst, group, momentum, monk
 @pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", [
     ("binary_tree", 64, 1028, 16, 4, 0, 0.0), ("binary_tree", 63, 1027, 4, 3, 4, 0.9), ("binary_tree", 21, 516, 8, 4, 2, 0.0), ("binary_tree", 7, 130, 3, 2, 0, 0.9),
     ("line_tree", 40, 260, 8, 4, 0, 0.0), ("line_tree", 6, 2052, 2, 6, 4, 0.0), ("binary_tree", 3, 1, 1, 2, 0, 0.0),
-    # stars of few senders (of four and five nodes on edge slots while the chip holds every tile)
-    ("tree_star", 4, 1028, 16, 4, 0, 0.0), ("tree_star", 4, 70_000, 16, 4, 0, 0.0), ("star_at_2", 5, 50_003, 16, 2, 0, 0.9), ("star_at_last", 5, 60_000, 16, 4, 2, 0.0), ("tree_star", 7, 2051, 4, 3, 4, 0.9), ("star_at_2", 5, 516, 3, 8, 2, 0.0), ("star_at_5", 6, 1, 1, 1, 0, 0.0),
-    ("star_at_2", 7, 20_000, 8, 4, 1, 0.0), ("star_at_last", 4, 130, 0, 2, 0, 0.9),
-    # fewer versions on chip than the longest delay reads
     ("bidirectional_ring", 16, 1028, 16, 4, 0, 0.0), ("directed_ring", 30, 519, 20, 3, 0, 0.9), ("bidirectional_ring", 50, 130, 13, 8, 4, 0.0)])
-def test_trees_and_small_stars(graph, n, p, d_max, burst, group, momentum):
+def test_trees(graph, n, p, d_max, burst, group, momentum):
     """The bits of one pass per round."""
+    _bits_of_one_pass(graph, n, p, d_max, burst, group, momentum)
+
+
+# of four and five nodes on edge slots while the chip holds every tile
+@pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", [
+    ("tree_star", 4, 1028, 16, 4, 0, 0.0), ("tree_star", 4, 70_000, 16, 4, 0, 0.0), ("star_at_2", 5, 50_003, 16, 2, 0, 0.9), ("star_at_last", 5, 60_000, 16, 4, 2, 0.0),
+    ("tree_star", 7, 2051, 4, 3, 4, 0.9), ("star_at_2", 5, 516, 3, 8, 2, 0.0), ("star_at_5", 6, 1, 1, 1, 0, 0.0), ("star_at_2", 7, 20_000, 8, 4, 1, 0.0),
+    ("star_at_last", 4, 130, 0, 2, 0, 0.9)])
+def test_stars_of_few_senders(graph, n, p, d_max, burst, group, momentum):
+    """The bits of one pass per round."""
+    _bits_of_one_pass(graph, n, p, d_max, burst, group, momentum)
+
+
+@pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", [
+    ("bidirectional_ring", 16, 20_004, 16, 4, 0, 0.0), ("bidirectional_ring", 16, 17_003, 16, 2, 0, 0.0), ("directed_ring", 30, 7_001, 20, 3, 0, 0.9),
+    ("bidirectional_ring", 50, 6_404, 13, 8, 4, 0.0), ("bidirectional_ring", 9, 40_002, 14, 4, 2, 0.0), ("binary_tree", 64, 8_196, 16, 4, 0, 0.0),
+    ("line_tree", 40, 9_001, 16, 2, 1, 0.9), ("star_at_2", 5, 80_003, 20, 4, 0, 0.0)])
+def test_fewer_versions_on_chip_than_the_longest_delay_reads(graph, n, p, d_max, burst, group, momentum):
+    """More tiles than the chip holds with every version: reads of versions that have left it are ordinary then.  The bits of one pass per round."""
+    g = _bits_of_one_pass(graph, n, p, d_max, burst, group, momentum)
+    assert _versions_on_chip(g) < d_max + min(burst, 2)
+
+
+def _versions_on_chip(gpu):
+    f = lib()._Z16rfast_wave_slotsPK9rfast_ctx   # what a launch takes
+    f.argtypes, f.restype = [ctypes.c_void_p], ctypes.c_int
+    return f(gpu.ctx)
+
+
+def _bits_of_one_pass(graph, n, p, d_max, burst, group, momentum):
     r, c = BUILD[graph](n)
     w = configs._mk("trees", n, p, r, c, d_max, 0.01, 0, "diag_quadratic", problems.diag_quadratic(n, p, 5), 0.7, 0.4, 5, noise_std=0.1, burst=burst)
     w.sched.p_active[1::4] = 0.1
@@ -84,6 +114,7 @@ def test_trees_and_small_stars(graph, n, p, d_max, burst, group, momentum):
             g.check()
         for f in ("X", "Z", "G", "V_RING", "SIGMA_RING", "RHO_TILDE", "T_NODE", "TAU_R", "TAU_C", "ROUND"):
             assert np.array_equal(pair[0].read(f), pair[1].read(f)), (hi, f)
+    return pair[0]
 
 
 @pytest.mark.parametrize("graph,n,d_max", [("binary_tree", 64, 16), ("binary_tree", 21, 16), ("line_tree", 40, 16), ("tree_star", 64, 4), ("star_at_5", 17, 5),
