@@ -142,7 +142,7 @@ struct RfastDev {
 };
 
 // Workgroups per node of the team kernel (rfast_team.hip), their chunk of the coordinates (a multiple of 256 if there
-// are several), coordinates per owning lane, tiles of sampled rows in LDS (0: the rows are read from memory twice).  W = 0: not for this problem.
+// are several), coordinates per owning lane, tiles of sampled rows in LDS (0: the rows are read from memory twice; two with softmax only).  W = 0: not for this problem.
 struct RfastTeam {
   int W = 0, C = 0, per_lane = 0, tiles = 0;
 };

@@ -31,7 +31,7 @@ __device__ inline int lane_value(int v, int l) { return __builtin_amdgcn_readlan
 __device__ inline float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
 
 struct TeamArgs {
-  int rounds, W, C, B, buffers;  // buffers: tiles of rows in LDS (two: the next round's rows arrive during this one)
+  int rounds, W, C, B, buffers;  // buffers: tiles of rows in LDS (softmax; two: the next round's rows arrive during this one)
   float gamma;
   unsigned base;              // progress words and packet tags count rounds from here on (they never repeat)
   const int32_t* batch_idx;   // [rounds][n][B], NULL: all rows, in order

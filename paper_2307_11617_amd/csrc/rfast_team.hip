@@ -201,8 +201,8 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   const bool owner = tid < kOwn;
   const bool sampled = a.batch_idx != nullptr;
   // ---- LDS
-  float4* const tiles = lds4;                                       // TILE: [a.buffers][B][Q]
-  float4* xs4 = tiles + (TILE ? (size_t)a.buffers * B * Qm : 0);    // [Q] the mixed x of this round
+  float4* const tile = lds4;                                        // TILE: [B][Q]
+  float4* xs4 = tile + (TILE ? (size_t)B * Qm : 0);                 // [Q] the mixed x of this round
   float4* cp4 = xs4 + Qm;                                           // [4][Q] column sums of the four groups of rows
   float* rs = reinterpret_cast<float*>(cp4 + 4 * Qm);               // [4][Bq] residuals, row b at [b mod 4][b / 4]
   const int Bq = (B + 15) / 16 * 4;
@@ -297,9 +297,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   }
   if (tid < 4 * Q - Cw) xs[Cw + tid] = 0.f;  // the unused end of the last group of four stays zero
   if (TILE)
-    for (int f = tid; f < a.buffers * B * (4 * Q - Cw); f += kThreads) {
+    for (int f = tid; f < B * (4 * Q - Cw); f += kThreads) {
       const int r = f / (4 * Q - Cw);
-      reinterpret_cast<float*>(tiles + (size_t)r * Q)[Cw + (f - r * (4 * Q - Cw))] = 0.f;
+      reinterpret_cast<float*>(tile + (size_t)r * Q)[Cw + (f - r * (4 * Q - Cw))] = 0.f;
     }
 
   bool dead = false;  // a wait has run out
@@ -343,13 +343,13 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   // Rows into LDS, straight from memory: no registers, so that everything is in flight at once.  A wavefront takes every
   // kLoadWaves-th row; the destination of such a load is contiguous over the lanes.
   const bool wide = (p & 3) == 0;  // 16-byte pieces need 16-byte addresses
-  auto load_tile = [&](const int* rows, float4* dst) {
+  auto load_tile = [&](const int* rows) {
     const int lw = wave - kOwnWaves;
     const int mine = sampled && lw + kLoadWaves * lane < B ? rows[lw + kLoadWaves * lane] : 0;
     int r = 0;
     for (int b = lw; b < B; b += kLoadWaves, ++r) {
       const float* src = rows_g + (size_t)(sampled ? lane_value(mine, r) : b) * p;
-      float4* to = dst + b * Q;
+      float4* to = tile + b * Q;
       if (wide) {
         for (int quad = lane; quad < Q; quad += 64)
           __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + 4 * quad),
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       row_ahead = ask_row(next_active(qa + 1));
     }
     if (sampled) __syncthreads();
-    if (TILE && !owner && qa < rounds) load_tile(rowi, tiles);
+    if (TILE && !owner && qa < rounds) load_tile(rowi);
   }
 
   int q = next_event(0), q_prev = -1;  // this event, and the last round in which the node was active
@@ -521,8 +521,6 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         }
     }
     if (active) {
-      float4* const tile = tiles + (a.buffers > 1 && parity ? B * Q : 0);        // TILE: the rows of this round
-      float4* const tile_next = tiles + (a.buffers > 1 && !parity ? B * Q : 0);  // ... and of the next active one
       if (TILE && !owner) drain();  // the rows on their way into LDS have arrived
       __syncthreads();  // the mixed x and the sampled rows are in LDS
       unsigned seen_c = a.base, seen_o = a.base;  // the words that the running sums wait for travel during the dot products
@@ -738,11 +736,12 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         cp4[f] = acc;
       }
       // (loads on their way into LDS would be waited for by a barrier that orders memory, and by reads of LDS behind them: the rows
-      // of the next round are asked for when the column sums are done, their numbers a round ahead of that: 31 nodes, p = 784: 5.6 -> 5.4 us)
+      // of the next round are asked for when the column sums are done, their numbers a round ahead of that: 31 nodes, p = 784: 5.6 -> 5.4 us.  A second tile would have nothing to
+      // hold: without it 8 nodes of a mesh, p = 8192, batch 128, 9.6 -> 9.3; 16 nodes, p = 2048, batch 128, 8.8 -> 8.6)
       lds_barrier();  // column sums; the tile may be overwritten
       if (!owner) {
         if (sampled && qa < rounds) {
-          if (TILE) load_tile(rowi + (parity ? 0 : B), tile_next);
+          if (TILE) load_tile(rowi + (parity ? 0 : B));
           row_ahead = ask_row(next_active(qa + 1));
         }
       } else {
@@ -864,9 +863,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   }
 }
 
-size_t team_lds(const RfastDev& d, int C, int B, int tiles) {
+size_t team_lds(const RfastDev& d, int C, int B, bool tile) {
   const size_t Qm = (size_t)(C + 3) / 4;
-  return ((size_t)tiles * B * Qm + 5 * Qm) * 16 + ((size_t)B + 15) / 16 * 64 + (d.prob.batch > 0 ? 2 * (size_t)B * 4 : 0) + kBlockRounds * 4;
+  return ((tile ? (size_t)B : 0) * Qm + 5 * Qm) * 16 + ((size_t)B + 15) / 16 * 64 + (d.prob.batch > 0 ? 2 * (size_t)B * 4 : 0) + kBlockRounds * 4;
 }
 
 template <int kE, bool TILE, bool SYNC>
@@ -877,7 +876,7 @@ hipError_t launch_team(rfast_ctx* c, const TeamArgs& a) {
     if (e != hipSuccess) return e;
     raised = true;
   }
-  hipLaunchKernelGGL((rfast_team_kernel<kE, TILE, SYNC>), dim3((unsigned)(c->d.n * a.W)), dim3(kThreads), team_lds(c->d, a.C, a.B, TILE ? a.buffers : 0),
+  hipLaunchKernelGGL((rfast_team_kernel<kE, TILE, SYNC>), dim3((unsigned)(c->d.n * a.W)), dim3(kThreads), team_lds(c->d, a.C, a.B, TILE),
                      c->stream, c->d, a);
   return hipGetLastError();
 }
@@ -919,17 +918,17 @@ RfastTeam rfast_team_shape(const RfastDev& d, int max_degree, int max_out_degree
     if ((p + C - 1) / C != W || C > 8 * kOwn) continue;
     const int64_t quads = (int64_t)B * ((C + 3) / 4);
     const bool fits = d.prob.batch == 0 || B <= kTileRows;
-    const int tiles = !fits || team_lds(d, C, B, 1) > kTeamLds ? 0 : d.prob.batch > 0 && team_lds(d, C, B, 2) <= kTeamLds ? 2 : 1;
-    if (!tiles && (quads * 16 > 512 * 1024 || team_lds(d, C, B, 0) > kTeamLds)) continue;
+    const bool tile = fits && team_lds(d, C, B, true) <= kTeamLds;
+    if (!tile && (quads * 16 > 512 * 1024 || team_lds(d, C, B, false) > kTeamLds)) continue;
     const double kb = quads * 16 / 1024.0;
     double us = 3.0 + (W > 1 ? 1.0 + 0.05 * W : 0.0) + 0.15 * C / kOwn;
-    if (!tiles) us += kb / 20.0;  // read twice, through the L2
-    else us += kb / 120.0 + (d.prob.batch > 0 && tiles == 1 && kb > 64 ? (kb - 64) / 40.0 : 0.0);  // the next rows arrive beside the update
+    if (!tile) us += kb / 20.0;  // read twice, through the L2
+    else us += kb / 120.0 + (d.prob.batch > 0 && kb > 64 ? (kb - 64) / 40.0 : 0.0);  // the next rows arrive beside the update and the mix
     if (us < best_us) {
       best_us = us;
       best.W = W;
       best.C = C;
-      best.tiles = tiles;
+      best.tiles = tile ? 1 : 0;
       const int per = (C + kOwn - 1) / kOwn;
       best.per_lane = per <= 1 ? 1 : per <= 2 ? 2 : per <= 4 ? 4 : 8;
     }
@@ -957,7 +956,7 @@ hipError_t rfast_launch_team(rfast_ctx* c, bool sync, int rounds, float gamma, c
   a.W = t.W;
   a.C = t.C;
   a.B = rows_per_gradient(&c->d.prob);
-  a.buffers = t.tiles;
+  a.buffers = 1;
   a.gamma = gamma;
   a.base = c->team_base;
   a.batch_idx = c->d.prob.batch > 0 ? d_batch_idx : nullptr;
