@@ -694,10 +694,12 @@ int rfast_wave_lanes(const rfast_ctx* c) { return 64 / c->d.n; }
 
 // (Stars and graphs with at most two edges of a kind: fewer versions than the longest delay reads where that gives more wavefronts, until there
 // are two per SIMD, down to three quarters of it.  A wavefront has few edges to read over then, so that a read from the ring in memory is
-// rare, and delays count rounds, versions only the sender's active ones.  Star of 64 nodes, p 1 M, delays of up to 16, 20 % lost, us per
-// round with 17 / 12 / 10 / 8 versions and 6 / 8 / 10 / 11 wavefronts: 124 / 94 / 92 / 110.  Delays of up to 16, ms for 132 rounds with 18 / 14 /
-// 12 / 10 versions, half of the nodes active and all: bidirectional ring of 16, p 1 M, 4.64 / 3.78 / 3.27 / 2.80 and 4.68 / 3.83 / 4.56 / 5.07; ring of
-// 32, p 524288, 4.54 / 3.95 / 3.35 / 2.76 and 4.64 / 4.08 / 4.70 / 4.74.  Not where the chip holds every tile as it is: fewer versions only
+// rare, and delays count rounds, versions only the sender's active ones.  Delays of up to 16, 20 % lost, 132 rounds, ms with 18 / 14 / 13 / 12 / 10
+// versions, half of the nodes active and all (13 is what this takes: as many as fit beside the wavefronts that 12 allow): bidirectional ring
+// of 16, p 1 M, 4.30 / 3.50 / 3.00 / 3.00 / 2.62 and 4.27 / 3.51 / 3.11 / 3.57 / 5.05; of 32, p 524288, 4.52 / 4.02 / 3.36 / 3.42 / 3.08 and 4.59 / 4.29 /
+// 3.63 / 4.16 / 6.16; binary tree of 64, p 262144, 3.84 / 2.93 / 2.44 / 2.48 / 2.97 and 4.00 / 3.30 / 2.81 / 3.21 / 5.86; star of 64, p 524288, 9.26 / 7.43 /
+// 5.86 / 5.80 / 6.48 and 10.5 / 8.53 / 6.97 / 7.46 / 11.2.  With 2 % lost 13 take up to 6 % less, with half lost up to
+// 16 % more, and are the best of them there with all active.  Not where the chip holds every tile as it is: fewer versions only
 // cost then (ring of 32, p 8192, all active: 0.86).  With more edges all nodes active lose what half of them
 // gain: mesh of 64, 5.61 / 5.21 / 4.46 / 4.97 and 5.73 / 8.91 / 8.19 / 11.5.)
 // Wavefronts per SIMD (the instantiation) and versions of a node on chip.  At least as many versions as the longest delay
@@ -820,7 +822,9 @@ template <class F> static hipError_t with_wave_form(const rfast_ctx* c, int per,
   auto by_deg = [&](auto mom) {
     if (c->hub >= 0 && c->d.n <= kStarInOrder) return f(WaveForm<1, -1, true>(), mom, std::integral_constant<int, 4>());
     if (c->hub >= 0) return by_per(WaveForm<1, 0, true>(), mom);
-    if (c->tree) return by_per(WaveForm<1, 2, true>(), mom);
+    // (a tree takes this form only where its rings leave no room for sixteen wavefronts: more than 640 slots of 16 bytes each)
+    if (c->tree)
+      return per >= 3 ? f(WaveForm<1, 2, true>(), mom, std::integral_constant<int, 3>()) : f(WaveForm<1, 2, true>(), mom, std::integral_constant<int, 2>());
     if (deg > 4) return f(WaveForm<kWaveMaxDeg, kWaveMaxDeg, false>(), mom, std::integral_constant<int, 2>());
     if (deg > 2)
       return per == 3 ? f(WaveForm<4, 4, false>(), mom, std::integral_constant<int, 3>())

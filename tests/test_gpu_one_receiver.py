@@ -26,7 +26,15 @@ def _star_at(n, hub):
     return r, c
 
 
-BUILD = {"directed_ring": graphs.directed_ring, "bidirectional_ring": graphs.bidirectional_ring, "tree_star": graphs.tree_pull_star_push, "binary_tree": graphs.binary_tree, "line_tree": graphs.line_tree, "star_at_2": lambda n: _star_at(n, 2), "star_at_5": lambda n: _star_at(n, 5),
+def _star_and_tree(n):
+    """Every node pulls from node 0, and pushes to its parent in a binary tree."""
+    r, c = graphs.tree_pull_star_push(n)[0] * 0.0, graphs.binary_tree(n)[1]
+    r[0, 0] = 1.0
+    r[np.arange(1, n), np.arange(1, n)], r[1:, 0] = 0.5, 0.5
+    return r, c
+
+
+BUILD = {"star_and_tree": _star_and_tree, "directed_ring": graphs.directed_ring, "bidirectional_ring": graphs.bidirectional_ring, "tree_star": graphs.tree_pull_star_push, "binary_tree": graphs.binary_tree, "line_tree": graphs.line_tree, "star_at_2": lambda n: _star_at(n, 2), "star_at_5": lambda n: _star_at(n, 5),
          "star_at_last": lambda n: _star_at(n, n - 1)}
 SHAPES = [("tree_star", 64, 1028, 16, 4, 0, 0.0), ("tree_star", 64, 1027, 4, 3, 4, 0.9), ("tree_star", 33, 260, 0, 1, 0, 0.0),
           ("tree_star", 47, 66, 8, 4, 2, 0.0), ("tree_star", 32, 513, 8, 2, 4, 0.9), ("tree_star", 20, 1028, 3, 8, 0, 0.0),
@@ -60,6 +68,7 @@ def test_every_push_to_one_node(graph, n, p, d_max, burst, group, momentum, monk
 
 @pytest.mark.parametrize("graph,n,p,d_max,burst,group,momentum", [
     ("binary_tree", 64, 1028, 16, 4, 0, 0.0), ("binary_tree", 63, 1027, 4, 3, 4, 0.9), ("binary_tree", 21, 516, 8, 4, 2, 0.0), ("binary_tree", 7, 130, 3, 2, 0, 0.9),
+    ("star_and_tree", 64, 1028, 9, 4, 0, 0.0), ("star_and_tree", 20, 1027, 12, 2, 4, 0.9),
     ("line_tree", 40, 260, 8, 4, 0, 0.0), ("line_tree", 6, 2052, 2, 6, 4, 0.0), ("binary_tree", 3, 1, 1, 2, 0, 0.0),
     ("bidirectional_ring", 16, 1028, 16, 4, 0, 0.0), ("directed_ring", 30, 519, 20, 3, 0, 0.9), ("bidirectional_ring", 50, 130, 13, 8, 4, 0.0)])
 def test_trees(graph, n, p, d_max, burst, group, momentum):
