@@ -38,12 +38,14 @@
 // chunks of the workgroups here.  SYNC: the synchronous step of eq. (2) instead of a round, every node in every step; v and z
 // go from node to node as packets of value and step, like the dot products, in memory of their own (slot 0 of the v ring keeps the last v, as
 // with a kernel per step): one trip through memory, where values, acknowledgement, word, poll and read were four.  16 nodes, p = 1001, 96
-// rows: 6.5 -> 6.4 us per step.  The rings of the running sums are not touched: the diagnostics and reads see them as
+// rows: 6.5 -> 6.4 us per step.  (v and z apart, so that whoever reads one does not fetch the other, too: interleaved, the lines of the rings took
+// twice as long to read where a lane has several coordinates or a node several in-edges: 32 nodes, p = 4096, 64 rows 8.7 -> 7.4 us per step, 7.3 by
+// words; 90 nodes of an exponential graph, p = 1600, 64 rows 18.4 -> 16.0, 15.3; binary tree of 100, p = 2000, 6.7 -> 5.4, 6.8.)  The rings of the running sums are not touched: the diagnostics and reads see them as
 // rfast_init left them.
 //
 // Measured, us per round, before (two kernels per round; five for the synchronous step, the heavy-ball buffer and one
 // agent per iteration) and now: logistic, 31 nodes in a binary tree, p = 784, batch 32: 12.0 -> 4.7; 32 nodes, p = 4096,
-// batch 64: 21.2 -> 8.9; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.25; one agent of 55 per
+// batch 64: 21.2 -> 8.9; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.1; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
 #include <type_traits>
@@ -64,7 +66,7 @@ __device__ inline Row lane_row(const float* p, int l) {
 __device__ inline float get_row(Row r, unsigned at) {
   return __hip_atomic_load((const __attribute__((address_space(1))) float*)(r + at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline u64 get_pair(Row r, unsigned at) {
+__device__ inline u64 get_packet(Row r, unsigned at) {
   return __hip_atomic_load((const __attribute__((address_space(1))) u64*)(r + at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 constexpr int kOwn = 256;                  // lanes that own coordinates
@@ -260,11 +262,11 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   auto word_of = [](const unsigned* f, int word) { return f ? f + word : nullptr; };
   const float* const r_ring = s.v_ring + (size_t)r_src * M * p + first;
   const float* const c_ring = s.sigma_ring + (size_t)c_src * M * p + first;
-  // SYNC: [2][n][p] pairs of packets, v and z of a coordinate; the senders' and the node's own in the half of the even steps
-  const size_t sync_half = (size_t)n * p * 2;
-  const u64* const r_pair = a.sync + ((size_t)r_src * p + first) * 2;
-  const u64* const c_pair = a.sync + ((size_t)c_src * p + first) * 2;
-  u64* const own_pair = a.sync + ((size_t)i * p + first) * 2;
+  // SYNC: [2][2][n][p] packets, v and z in the even steps, then in the odd ones; the senders' and the node's own of the even steps
+  const size_t sync_z = (size_t)n * p, sync_half = 2 * sync_z;
+  const u64* const r_sync = a.sync + (size_t)r_src * p + first;
+  const u64* const c_sync = a.sync + sync_z + (size_t)c_src * p + first;
+  u64* const own_sync = a.sync + (size_t)i * p + first;
   const float* const c_save = s.rho_tilde + (size_t)(ce0 + (lane < dI ? lane : 0)) * p + first;
   const bool momentum = s.mom != nullptr;
   const float inv = 1.0f / (float)B;
@@ -411,16 +413,16 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   }
 
   unsigned seen_r = a.base, seen_d = a.base;  // the words that the next mix waits for, as read ahead
-  // SYNC: asks for the packets of up to KB in-edges from e0 on (which: 0 v, 1 z), an edge's senders in the lanes of `from`; whether
+  // SYNC: asks for the packets of up to KB in-edges from e0 on, an edge's senders in the lanes of `from`; whether
   // all of them are those of the step; and both until they are
   u64 step_tag = 0;
-  auto ask_pairs = [&](const u64* from, int which, int e0, int edges, u64 (&got)[KB][kE]) {
+  auto ask_packets = [&](const u64* from, int e0, int edges, u64 (&got)[KB][kE]) {
 #pragma unroll
     for (int u = 0; u < KB; ++u)
       if (e0 + u < edges) {
-        const Row row = lane_row(reinterpret_cast<const float*>(from + which), e0 + u);
+        const Row row = lane_row(reinterpret_cast<const float*>(from), e0 + u);
 #pragma unroll
-        for (int e = 0; e < kE; ++e) got[u][e] = get_pair(row, 4 * at[e]);
+        for (int e = 0; e < kE; ++e) got[u][e] = get_packet(row, 2 * at[e]);
       }
   };
   auto all_there = [&](int e0, int edges, const u64 (&got)[KB][kE]) {
@@ -433,18 +435,14 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
       }
     return __all(ok);
   };
-  auto until_there = [&](const u64* from, int which, int e0, int edges, u64 (&got)[KB][kE]) {
+  auto until_there = [&](const u64* from, int e0, int edges, u64 (&got)[KB][kE]) {
     for (int spin = 0; !dead && !all_there(e0, edges, got); ++spin) {
       if (spin >= a.wait_polls) {
         dead = true;
         report_wait(SYNC, i);
       }
-      ask_pairs(from, which, e0, edges, got);
+      ask_packets(from, e0, edges, got);
     }
-  };
-  auto poll_pairs = [&](const u64* from, int which, int e0, int edges, u64 (&got)[KB][kE]) {
-    ask_pairs(from, which, e0, edges, got);
-    until_there(from, which, e0, edges, got);
   };
   while (q < rounds) {
     step_tag = (u64)(a.base + (unsigned)q + 1u) << 32;
@@ -473,18 +471,20 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         // Everybody's v and z of this step, as packets: each is its own flag, so that a step has no other word to wait for than the
         // one that says that the readers of the packets overwritten here are through (a wavefront that publishes step q has read all that it
         // reads of step q - 1, which is what the sender's wavefronts of its number have written).
-        u64* own = own_pair + (q & 1 ? sync_half : 0);
+        u64* own = own_sync + (q & 1 ? sync_half : 0) + tid;
 #pragma unroll
         for (int e = 0; e < kE; ++e)
           if (has[e]) {
-            put64(own + 2 * (tid + kOwn * e), step_tag | __float_as_uint(v[e]));
-            put64(own + 2 * (tid + kOwn * e) + 1, step_tag | __float_as_uint(z[e]));
+            put64(own + kOwn * e, step_tag | __float_as_uint(v[e]));
+            put64(own + sync_z + kOwn * e, step_tag | __float_as_uint(z[e]));
             if (q == rounds - 1) own_v[kOwn * e] = v[e];
           }
         if (lane == 0) put32(f_own, a.base + (unsigned)(q + 1));
         for (int e0 = 0; e0 < dR; e0 += KB) {
           u64 got[KB][kE];
-          poll_pairs(r_pair + (q & 1 ? sync_half : 0), 0, e0, dR, got);
+          const u64* from = r_sync + (q & 1 ? sync_half : 0);
+          ask_packets(from, e0, dR, got);
+          until_there(from, e0, dR, got);
 #pragma unroll
           for (int u = 0; u < KB; ++u)
             if (e0 + u < dR) {
@@ -632,7 +632,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         if (SYNC) {
           seen_r = peek(a, f_r_dst, q + 1);
           seen_d = peek(a, f_c_dst, q + 1);
-          ask_pairs(c_pair + (q & 1 ? sync_half : 0), 1, 0, dI, zp);
+          ask_packets(c_sync + (q & 1 ? sync_half : 0), 0, dI, zp);
         }
         fetch_plan(q_next);
       } else if (sampled && qa < rounds) {
@@ -763,9 +763,9 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         }
         for (int e0 = 0; e0 < dI; e0 += KB) {
           if (SYNC) {
-            const u64* from = c_pair + (q & 1 ? sync_half : 0);
-            if (e0 > 0) ask_pairs(from, 1, e0, dI, zp);
-            until_there(from, 1, e0, dI, zp);
+            const u64* from = c_sync + (q & 1 ? sync_half : 0);
+            if (e0 > 0) ask_packets(from, e0, dI, zp);
+            until_there(from, e0, dI, zp);
           } else if (e0 > 0) {
             ask_sums(e0);  // in-degree above one batch
           }
