@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
   for (int e = 0; e < kE; ++e) {
     const int k = tid + kOwn * e;
     has[e] = owner && k < Cw;
-    at[e] = has[e] ? 4u * (unsigned)k : wave_has ? 4u * (unsigned)(tid - lane) : 0u;
+    at[e] = has[e] ? 4u * (unsigned)k : SYNC && wave_has ? 4u * (unsigned)(tid - lane) : 0u;
     x[e] = z[e] = g[e] = sc[e] = m[e] = 0.f;
     if (has[e]) {
       const size_t off = (size_t)i * p + first + k;
@@ -684,6 +684,12 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         if (early) ask_sums(0);
       }
       __syncthreads();  // residuals, and the row numbers of the next active round
+      // The words of the sums again, which travel during the column sums: read behind them only, the wait was a trip of its own wherever all nodes
+      // are active and their words come a little late (us per 100 rounds: 16 nodes, p = 1000, 200 rows 884 -> 853; 31 nodes, p = 784, 200 rounds 957 -> 940).
+      if (owner && !SYNC && !early) {
+        seen_c = peek(a, word_of(f_c_src, 1), cneed);
+        seen_o = peek(a, word_of(f_c_dst, 2), q_prev + 1);
+      }
       // ---- gradient, columns: group rg sums rows rg, rg + 4, ... for four coordinates; for two where four would leave half of
       // the wavefronts without any (a SIMD issues for one wavefront every other time only: 16 nodes, p = 1001, 96 rows, synchronous, 6.4 -> 6.25 us per step)
       if (TILE && 8 * Q <= kThreads) {
@@ -758,7 +764,7 @@ __global__ void __launch_bounds__(kThreads) rfast_team_kernel(RfastDev s, TeamAr
         }
         // (waited for here where they were not out when the dot products were: nothing before needs them)
         if (!SYNC && !early) {
-          wait2(word_of(f_c_src, 1), cneed, word_of(f_c_dst, 2), q_prev + 1, a.base, a.base);
+          wait2(word_of(f_c_src, 1), cneed, word_of(f_c_dst, 2), q_prev + 1, seen_c, seen_o);
           ask_sums(0);
         }
         for (int e0 = 0; e0 < dI; e0 += KB) {
