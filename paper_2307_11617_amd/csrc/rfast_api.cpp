@@ -1010,14 +1010,14 @@ static int chained_rounds(rfast_ctx* c, int32_t count, float gamma, const uint8_
 // and with five and six edges of a kind (exponential graph of 40) 0.93 / 1.07 of 4 to 2 MB, 0.88 to 1.0 / 1.3 of 6 and 7 to 8 MB, 0.9 to 1.04 /
 // 1.4 of 9 and 10 beyond.
 // One receiver of all edges of C, half of the nodes active (one pass has a node with up to 63 in-edges to wait for, so a launch pays earlier
-// where the state is small), delays of up to 4 / 16, even at: 4 to 7 nodes, to 0.5 MB 2 / 3 rounds, 2 MB 2 / 5, 5 MB 3.5 / 8, 12 MB 4 / 10, 30 MB 5 / 12
+// where the state is small), delays of up to 4 / 16, even at: 4 to 7 nodes, to 0.5 MB 2 / 3.5 rounds, 2 MB 2 / 5, 5 MB 3.5 / 8, 12 MB 4 / 10, 30 MB 5 / 12
 // (7 nodes, 17 MB: 75 us in 4 passes, 68 in a launch of 4; 99 and 76 of 6); 12 and 24 nodes, 0.2 MB 2 / 3 rounds, 2 MB 3 / 5, 16 MB 7.5 / 11.5, 48 MB 11 / 19;
 // 48 and 64 nodes, to 2 MB 2 / 2, 16 MB 3.5 / 6, 48 MB 7 / 10, 268 MB 10 / 14; 64 nodes, 2 MB, 20 rounds 6.2 / 5.2 times as fast.
 static int32_t wave_least_rounds(const rfast_ctx* c) {
   const RfastDev& d = c->d;
   const double mb = (double)d.n * (double)d.p * 4.0e-6;
   if (c->hub >= 0) {
-    static const float star[3][5][2] = {{{2, 3}, {3, 5}, {4, 8}, {5, 10}, {5, 12}}, {{2, 3}, {3, 5}, {5, 8}, {8, 12}, {12, 19}}, {{2, 2}, {2, 2}, {3, 4}, {4, 6}, {8, 10}}};
+    static const float star[3][5][2] = {{{2, 4}, {3, 5}, {4, 8}, {5, 10}, {5, 12}}, {{2, 3}, {3, 5}, {5, 8}, {8, 12}, {12, 19}}, {{2, 2}, {2, 2}, {3, 4}, {4, 6}, {8, 10}}};
     const int size = mb > 20.0 ? 4 : mb > 8.0 ? 3 : mb > 2.5 ? 2 : mb > 0.5 ? 1 : 0;
     const float* v = star[d.n <= kStarInOrder ? 0 : d.n <= 32 ? 1 : 2][size];
     const int reach = std::min(d.M - 1, d.d_max + 2);
