@@ -48,6 +48,10 @@
 // batch 64: 21.2 -> 8.9; synchronous least squares, 16 nodes, p = 1001, 96 rows: 25.4 -> 6.1; one agent of 55 per
 // iteration, p = 208: 18.2 -> 1.6.  What bounds it is the chain of trips through memory of a round (versions in, dot
 // products out and in, sums out).
+// Registers spilled outside the synchronous steps with a tile of rows: none with one coordinate per lane, 5 and 6 with four and two, 47 with eight (184 B; 22
+// without a tile).  That is more than with every wait ahead of the gradient and addresses formed where they are used, and still faster: us per
+// 100 rounds then and now, eight per lane: 32 nodes, p = 16384, batch 12 1260 -> 1091 (all active 1486 -> 1353), batch 48 (no tile) 2735 -> 2378; mesh
+// of 60, p = 8191, batch 16 1639 -> 1310; tree of 120, p = 4000 1259 -> 1031; four per lane: ring of 100, p = 1900, batch 32 679 -> 627.
 #include <type_traits>
 
 #include "rfast_team.h"

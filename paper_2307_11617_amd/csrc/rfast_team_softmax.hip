@@ -20,8 +20,8 @@
 // K 32, batch 64, heavy-ball buffer: 33.6 -> 12.2 (13.5 with one word for the sums that are out and those that are read, 12.9 with the sums waited for before the softmax); one agent of 16 per iteration, d 192: 20.6 -> 5.0.
 //
 // With 256 registers per lane the five arrays of a tile (x, z, sample, running sum, heavy-ball buffer: 64 or 80 registers)
-// and the ring values in flight beside them do not all fit: 69 to 120 registers are spilled over the eight instantiations
-// (192 to 320 B of scratch per lane), some of them reloaded between the parts of a round.
+// and the ring values in flight beside them do not all fit: 60 to 119 registers are spilled over the eight instantiations
+// (184 to 328 B of scratch per lane), some of them reloaded between the parts of a round.
 //
 // What bounds it is the chain of trips through memory in the wavefronts that own tiles, so everything else is kept out of
 // them as long as there are others (15.7 -> 13.6 us per round in the first case): the forward product, the softmax, row

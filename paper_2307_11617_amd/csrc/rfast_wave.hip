@@ -114,7 +114,7 @@ __device__ inline float4 sum_of_nodes(float4 t, int lane, int n, int i, int ln, 
 // FEW: only nodes with readers have rings on chip: a tree is read over half of its nodes, the others publish no v.
 // PER: wavefronts per SIMD, to which the registers are cut: 4 at two edge slots (120 to 128 registers), 3 at four (164 to 168), 2 at six (three
 // would spill 45 registers in the round loop: 75 -> 239 us per round on 32 nodes of an exponential graph, p 1 M).  At four edge slots
-// the heavy-ball buffer and several wavefronts per workgroup spill up to 5 registers, and three still win: us per round in
+// the heavy-ball buffer and several wavefronts per workgroup spill up to 6 registers, and three still win: us per round in
 // calls of 20 / 60 / 200 at two and three wavefronts, heavy-ball buffer in use: mesh of 16, p 1 M, 34.8 / 27.7 / 22.1 and 29.0 / 19.7 / 17.6; mesh of
 // 40, p 300000, 45.2 / 36.2 / 28.7 and 38.1 / 26.2 / 23.3.  The forms for three and four at two edge slots take the same registers, but order
 // their loads and rounds differently: three wavefronts of the form for four are 1 to 4 % slower (500 rounds of 16 nodes, p 11.2 M: 69.8 -> 72.3 ms).
